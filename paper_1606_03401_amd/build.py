@@ -1,19 +1,25 @@
 """Builds the C-ABI library ``libmebptt.so`` in-tree with hipcc for gfx950.
 
 Run as ``python -m paper_1606_03401_amd.build``; ``__graft_entry__.build()`` calls ``build()``.
+Every source is compiled to an object of its own, several at a time, then linked.
 """
 from __future__ import annotations
 
+import concurrent.futures
 import os
 import shutil
 import subprocess
 import sys
+import tempfile
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG_DIR)
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libmebptt.so")
-SOURCES = ["planner.cpp", "chain_planner.cpp", "kernels.hip", "run.hip", "chain_run.hip", "measure_sync.hip"]
+SOURCES = ["planner.cpp", "chain_planner.cpp", "kernels.hip", "resident.hip", "run.hip", "chain_run.hip",
+           "measure_sync.hip"]
+FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
+         "-packed-fp32-ops", "-Wall", "-Wno-unused-command-line-argument", "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
 
 def hipcc() -> str:
@@ -23,14 +29,7 @@ def hipcc() -> str:
     return exe
 
 
-def build(verbose: bool = True) -> str:
-    cmd = [hipcc(), "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
-           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           "-Wall", "-Wno-unused-command-line-argument",
-           "-I", os.path.join(ROOT, "include"), "-I", CSRC]
-    cmd += [os.path.join(CSRC, s) for s in SOURCES]
-    tmp = LIB_PATH + ".tmp"
-    cmd += ["-o", tmp]
+def _run(cmd, verbose: bool) -> None:
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
@@ -39,7 +38,19 @@ def build(verbose: bool = True) -> str:
         raise RuntimeError("hipcc failed:\n" + out)
     if verbose and out.strip():
         print(out)
-    os.replace(tmp, LIB_PATH)
+
+
+def build(verbose: bool = True) -> str:
+    exe = hipcc()
+    with tempfile.TemporaryDirectory() as tmp:
+        objs = [os.path.join(tmp, os.path.splitext(s)[0] + ".o") for s in SOURCES]
+        jobs = min(len(SOURCES), int(os.environ.get("MAX_JOBS", "8")), 8)
+        with concurrent.futures.ThreadPoolExecutor(jobs) as pool:
+            for f in [pool.submit(_run, [exe, *FLAGS, "-c", os.path.join(CSRC, s), "-o", o], verbose)
+                      for s, o in zip(SOURCES, objs)]:
+                f.result()
+        _run([exe, "--offload-arch=gfx950", "-fPIC", "-shared", *objs, "-o", LIB_PATH + ".tmp"], verbose)
+    os.replace(LIB_PATH + ".tmp", LIB_PATH)
     return LIB_PATH
 
 

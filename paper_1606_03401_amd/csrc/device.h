@@ -1,0 +1,269 @@
+// Device-side building blocks shared by the kernel files: MFMA operand traits, the fragment-tiled
+// layout, the h plane of a state unit, the pointwise steps, and the shape rules that fix how a
+// shape's sums are split.  Not part of the ABI.
+#pragma once
+
+#include <type_traits>
+
+#include "kernels.h"
+
+namespace mebptt {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+// ---- operand traits ------------------------------------------------------------------------
+
+template <class T>
+struct Mma;
+
+template <>
+struct Mma<__bf16> {
+  static constexpr int VEC = 8;
+  using Frag = bf16x8;
+  __device__ static Frag load(const __bf16* p) { return *reinterpret_cast<const Frag*>(p); }
+  __device__ static Frag from_f32(const float (&v)[8]) {
+    Frag f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) f[e] = (__bf16)v[e];
+    return f;
+  }
+  __device__ static f32x4 mma(Frag a, Frag b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+  }
+};
+
+template <>
+struct Mma<float> {
+  static constexpr int VEC = 4;
+  using Frag = f32x4;
+  __device__ static Frag load(const float* p) { return *reinterpret_cast<const Frag*>(p); }
+  __device__ static Frag from_f32(const float (&v)[4]) { return Frag{v[0], v[1], v[2], v[3]}; }
+  __device__ static f32x4 mma(Frag a, Frag b, f32x4 c) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], c, 0, 0, 0);
+    return c;
+  }
+};
+
+// Pointwise activations on the hardware exp2 / reciprocal units (a few ulp; the absolute error of
+// tanh stays below 1e-7, far inside the fp32 gradient tolerance).
+__device__ inline float sigmoidf_(float z) { return __frcp_rn(1.0f + __expf(-z)); }
+__device__ inline float tanhf_(float z) {
+  const float e = __expf(-2.0f * fabsf(z));            // in (0, 1]: no overflow
+  return copysignf((1.0f - e) * __frcp_rn(1.0f + e), z);
+}
+
+// ---- the h plane of a hidden-state unit ----------------------------------------------------------
+// (layout described in kernels.h).  HPlane<T>::store/load hide whether h is a plain fp32 plane or
+// the split, fragment-tiled pair of 16-bit planes.
+template <class T>
+struct HPlane;
+
+template <>
+struct HPlane<float> {
+  static constexpr bool SPLIT = false;
+  __device__ static void store(float* plane, int b, int u, float v, int, int H, size_t) { plane[(size_t)b * H + u] = v; }
+  __device__ static float load(const float* plane, int b, int u, int, int H, size_t) { return plane[(size_t)b * H + u]; }
+  __device__ static float as_operand(const float* plane, int b, int u, int, int H, size_t) {
+    return plane[(size_t)b * H + u];
+  }
+};
+
+template <class T>
+__device__ inline size_t ft_offset(int row, int k, int nsteps);
+
+template <>
+struct HPlane<__bf16> {
+  static constexpr bool SPLIT = true;
+  // nsh = KH / 32 macro steps per batch tile; half = BP * KH elements per 16-bit plane
+  __device__ static void store(float* plane, int b, int u, float v, int nsh, int, size_t half) {
+    unsigned short* hi = reinterpret_cast<unsigned short*>(plane);
+    const unsigned bits = __float_as_uint(v);
+    const size_t o = ft_offset<__bf16>(b, u, nsh);
+    hi[o] = (unsigned short)((bits + 0x8000u) >> 16);
+    hi[half + o] = (unsigned short)(bits & 0xffffu);
+  }
+  __device__ static float load(const float* plane, int b, int u, int nsh, int, size_t half) {
+    const unsigned short* hi = reinterpret_cast<const unsigned short*>(plane);
+    const size_t o = ft_offset<__bf16>(b, u, nsh);
+    const unsigned lo = hi[half + o];
+    return __uint_as_float((((unsigned)hi[o] - (lo >> 15)) << 16) | lo);
+  }
+  __device__ static __bf16 as_operand(const float* plane, int b, int u, int nsh, int, size_t) {
+    const __bf16* hi = reinterpret_cast<const __bf16*>(plane);
+    return hi[ft_offset<__bf16>(b, u, nsh)];
+  }
+};
+
+// Operand arrays the library builds itself are stored "fragment-tiled": for a logical matrix
+// M[rows][K] the element (row, k) lives at
+//     (((row/16) * (K/KSTEP) + k/KSTEP) * 64 + ((k%KSTEP)/VEC)*16 + row%16) * VEC + k%VEC
+// so that the 64 lanes of a wave fetch the fragment of one 16-row tile and one macro step as one
+// contiguous, fully coalesced block of 64*VEC elements (1 KiB).
+template <class T>
+__device__ inline void ft_decode(size_t idx, int nsteps, int& row, int& k) {
+  constexpr int VEC = Mma<T>::VEC, KSTEP = 4 * VEC;
+  const int e = (int)(idx % VEC);
+  const int lane = (int)((idx / VEC) % 64);
+  const size_t blk = idx / (VEC * 64);
+  const int kstep = (int)(blk % nsteps);
+  const int tile = (int)(blk / nsteps);
+  row = tile * 16 + (lane & 15);
+  k = kstep * KSTEP + (lane >> 4) * VEC + e;
+}
+
+template <class T>
+__device__ inline size_t ft_offset(int row, int k, int nsteps) {
+  constexpr int VEC = Mma<T>::VEC, KSTEP = 4 * VEC;
+  return ((((size_t)(row >> 4) * nsteps + k / KSTEP) * 64 + ((k % KSTEP) / VEC) * 16 + (row & 15)) * VEC) + k % VEC;
+}
+
+// The four packed rows 4u .. 4u+3 of hidden unit u, and which gate block of the caller's W_ih / W_hh
+// feeds each of them (-1: that half of the row is zero).
+//   LSTM: rows i, f, g, o, both halves from the same gate block.
+//   GRU:  rows r, z, n_x, n_h.  The candidate's input part and recurrent part are kept as two rows
+//         (n = tanh(n_x + r * n_h)), so one GEMM with the same 4-rows-per-unit shape serves both cells.
+__host__ __device__ inline int packed_gate_x(int cell, int row) { return cell == 0 ? row : (row < 3 ? row : -1); }
+__host__ __device__ inline int packed_gate_h(int cell, int row) { return cell == 0 ? row : (row == 2 ? -1 : (row == 3 ? 2 : row)); }
+
+// ---- pointwise forward step of one (sequence, hidden unit) -------------------------------------
+// G: the four gate-GEMM results of the unit (packed rows), bias: their biases, state_prev: c_{s-1}
+// (LSTM) or h_{s-1} in full precision (GRU).  Returns h_s; `second` is what the second plane of
+// the state unit keeps (LSTM: c_s; GRU: the recurrent part n_h of the candidate), `gate` the
+// values the backward step needs (LSTM: i, f, g, o; GRU: r, z, n).  Every kernel that computes a
+// forward step calls this one function, with the multiply-adds spelled out, so that a step gives
+// the same bits whichever kernel ran it.
+template <int CELL>
+__device__ inline float cell_forward(const float (&G)[4], const float4& bias, float state_prev, float& second,
+                                     float (&gate)[4]) {
+  if (CELL == 0) {
+    const float gi = sigmoidf_(G[0] + bias.x);
+    const float gf = sigmoidf_(G[1] + bias.y);
+    const float gg = tanhf_(G[2] + bias.z);
+    const float go = sigmoidf_(G[3] + bias.w);
+    const float c = __fmaf_rn(gf, state_prev, __fmul_rn(gi, gg));
+    gate[0] = gi;
+    gate[1] = gf;
+    gate[2] = gg;
+    gate[3] = go;
+    second = c;
+    return __fmul_rn(go, tanhf_(c));
+  } else {
+    // rows r, z, n_x, n_h: n = tanh(n_x + r * n_h), h = (1 - z) n + z h_prev
+    const float r = sigmoidf_(G[0] + bias.x);
+    const float z = sigmoidf_(G[1] + bias.y);
+    const float nh = G[3] + bias.w;
+    const float n = tanhf_(__fmaf_rn(r, nh, G[2] + bias.z));
+    gate[0] = r;
+    gate[1] = z;
+    gate[2] = n;
+    gate[3] = 0.0f;
+    second = nh;
+    return __fmaf_rn(1.0f - z, n, __fmul_rn(z, state_prev));
+  }
+}
+
+// Pointwise backward step of one (sequence, hidden unit) of the LSTM: from dh_s (recurrent part
+// plus injected loss gradient), the running dc, the internal state (i, f, g, o, c_s) and c_{s-1}
+// to the four gate pre-activation gradients and dc_{s-1}.  One function, multiply-adds spelled
+// out, for every kernel that runs a backward step: the same bits whichever kernel ran it.
+__device__ inline void lstm_backward_point(float dh, float dc_in, float gi, float gf, float gg, float go, float c_s,
+                                           float c_prev, float (&dG)[4], float& dc_out) {
+  const float tc = tanhf_(c_s);
+  const float d_o = __fmul_rn(dh, tc);
+  const float dct = __fmaf_rn(__fmul_rn(dh, go), __fmaf_rn(-tc, tc, 1.0f), dc_in);
+  dG[0] = __fmul_rn(__fmul_rn(__fmul_rn(dct, gg), gi), __fsub_rn(1.0f, gi));
+  dG[1] = __fmul_rn(__fmul_rn(__fmul_rn(dct, c_prev), gf), __fsub_rn(1.0f, gf));
+  dG[2] = __fmul_rn(__fmul_rn(dct, gi), __fmaf_rn(-gg, gg, 1.0f));
+  dG[3] = __fmul_rn(__fmul_rn(d_o, go), __fsub_rn(1.0f, go));
+  dc_out = __fmul_rn(dct, gf);
+}
+
+// The same for the GRU: r, z, n the gates, nh the recurrent part of the candidate (n = tanh(n_x + r * nh)),
+// h_prev = h_{s-1} in full precision.  dh is the whole dL/dh_s: the GEMM part, the injected loss
+// gradient and the part that bypasses the GEMM (dh_{s+1} * z_{s+1}, carried in the running plane).
+// dG: gradients of the packed rows r, z, n_x, n_h; carry: what step s - 1 adds to its dh.
+__device__ inline void gru_backward_point(float dh, float r, float z, float n, float nh, float h_prev, float (&dG)[4],
+                                          float& carry) {
+  const float da_n = __fmul_rn(__fmul_rn(dh, __fsub_rn(1.0f, z)), __fmaf_rn(-n, n, 1.0f));
+  dG[0] = __fmul_rn(__fmul_rn(__fmul_rn(da_n, nh), r), __fsub_rn(1.0f, r));
+  dG[1] = __fmul_rn(__fmul_rn(__fmul_rn(dh, __fsub_rn(h_prev, n)), z), __fsub_rn(1.0f, z));
+  dG[2] = da_n;
+  dG[3] = __fmul_rn(da_n, r);
+  carry = __fmul_rn(dh, z);
+}
+
+// Raw (unconverted) activation fragment: VEC fp32 values, zero beyond `limit`.
+template <int VEC>
+struct RawAct {
+  float v[VEC];
+};
+template <int VEC>
+__device__ inline RawAct<VEC> load_raw(const float* __restrict__ row, int k, int limit, bool vec_ok) {
+  RawAct<VEC> r;
+  if (vec_ok && k + VEC <= limit) {
+#pragma unroll
+    for (int e = 0; e < VEC; e += 4) {
+      float4 q = *reinterpret_cast<const float4*>(row + k + e);
+      r.v[e] = q.x;
+      r.v[e + 1] = q.y;
+      r.v[e + 2] = q.z;
+      r.v[e + 3] = q.w;
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) r.v[e] = (k + e < limit) ? row[k + e] : 0.0f;
+  }
+  return r;
+}
+
+// As load_raw for rows whose length is a multiple of VEC (k is one too): a fragment lies wholly
+// inside the row or wholly outside, so one address clamp and one select replace the branches.
+// (Branches that load into the same registers make the compiler wait for every outstanding memory
+// operation between them.)
+template <int VEC>
+__device__ inline RawAct<VEC> load_raw_whole(const float* __restrict__ row, int k, int limit) {
+  RawAct<VEC> r;
+  const bool inside = k < limit;
+  const float* src = row + (inside ? k : 0);
+#pragma unroll
+  for (int e = 0; e < VEC; e += 4) {
+    const float4 q = *reinterpret_cast<const float4*>(src + e);
+    r.v[e] = inside ? q.x : 0.0f;
+    r.v[e + 1] = inside ? q.y : 0.0f;
+    r.v[e + 2] = inside ? q.z : 0.0f;
+    r.v[e + 3] = inside ? q.w : 0.0f;
+  }
+  return r;
+}
+
+// Kernel configurations by shape.  Tiles per workgroup grow with the problem so that the grid
+// stays near one workgroup per compute unit while every operand byte is reused as often as
+// possible; the choice depends on the shape only, never on the schedule.
+enum FwdConfig { FWD_TINY, FWD_SMALLK, FWD_B1, FWD_42, FWD_82 };
+enum BwdConfig { BWD_SMALLK, BWD_11, BWD_12, BWD_22 };
+constexpr int TARGET_WGS = 256;
+
+template <class T>
+inline FwdConfig forward_config(const Dims& d) {
+  const int nsteps = d.KP / (4 * Mma<T>::VEC);
+  if (nsteps <= 8) return FWD_TINY;
+  if (nsteps <= 20) return FWD_SMALLK;
+  const int ngroups = d.HP / 4, bt = d.BP / 16;
+  if (bt >= 2 && ((ngroups + 7) / 8) * ((bt + 1) / 2) >= TARGET_WGS) return FWD_82;
+  if (bt >= 2 && ((ngroups + 3) / 4) * ((bt + 1) / 2) >= TARGET_WGS) return FWD_42;
+  return FWD_B1;
+}
+
+template <class T>
+inline BwdConfig backward_config(const Dims& d) {
+  const int nsteps = d.G4 / (4 * Mma<T>::VEC);
+  if (nsteps <= 16) return BWD_SMALLK;
+  const int nt = d.HP / 16, bt = d.BP / 16;
+  if (nt >= 2 && bt >= 2 && ((nt + 1) / 2) * ((bt + 1) / 2) >= TARGET_WGS) return BWD_22;
+  if (bt >= 2 && nt * ((bt + 1) / 2) >= TARGET_WGS) return BWD_12;
+  return BWD_11;
+}
+
+}  // namespace mebptt

@@ -15,14 +15,11 @@
 // pointwise forward fused).  In the backward step the four rows are four consecutive hidden
 // units of dh, and loss-gradient injection and the pointwise backward again run on the GEMM
 // result (the dh = dG W_hh product of step s+1 fused with the pointwise backward of step s).
-#include <type_traits>
+#include <algorithm>
 
-#include "kernels.h"
+#include "device.h"
 
 namespace mebptt {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 Dims make_dims(int B, int I, int H, int dtype, int cell) {
   Dims d{};
@@ -54,90 +51,6 @@ Dims make_dims(int B, int I, int H, int dtype, int cell) {
   return d;
 }
 
-// ---- operand traits ------------------------------------------------------------------------
-
-template <class T>
-struct Mma;
-
-template <>
-struct Mma<__bf16> {
-  static constexpr int VEC = 8;
-  using Frag = bf16x8;
-  __device__ static Frag load(const __bf16* p) { return *reinterpret_cast<const Frag*>(p); }
-  __device__ static Frag from_f32(const float (&v)[8]) {
-    Frag f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) f[e] = (__bf16)v[e];
-    return f;
-  }
-  __device__ static f32x4 mma(Frag a, Frag b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-  }
-};
-
-template <>
-struct Mma<float> {
-  static constexpr int VEC = 4;
-  using Frag = f32x4;
-  __device__ static Frag load(const float* p) { return *reinterpret_cast<const Frag*>(p); }
-  __device__ static Frag from_f32(const float (&v)[4]) { return Frag{v[0], v[1], v[2], v[3]}; }
-  __device__ static f32x4 mma(Frag a, Frag b, f32x4 c) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], c, 0, 0, 0);
-    return c;
-  }
-};
-
-// Pointwise activations on the hardware exp2 / reciprocal units (a few ulp; the absolute error of
-// tanh stays below 1e-7, far inside the fp32 gradient tolerance).
-__device__ inline float sigmoidf_(float z) { return __frcp_rn(1.0f + __expf(-z)); }
-__device__ inline float tanhf_(float z) {
-  const float e = __expf(-2.0f * fabsf(z));            // in (0, 1]: no overflow
-  return copysignf((1.0f - e) * __frcp_rn(1.0f + e), z);
-}
-
-// ---- the h plane of a hidden-state unit ----------------------------------------------------------
-// (layout described in kernels.h).  HPlane<T>::store/load hide whether h is a plain fp32 plane or
-// the split, fragment-tiled pair of 16-bit planes.
-template <class T>
-struct HPlane;
-
-template <>
-struct HPlane<float> {
-  static constexpr bool SPLIT = false;
-  __device__ static void store(float* plane, int b, int u, float v, int, int H, size_t) { plane[(size_t)b * H + u] = v; }
-  __device__ static float load(const float* plane, int b, int u, int, int H, size_t) { return plane[(size_t)b * H + u]; }
-  __device__ static float as_operand(const float* plane, int b, int u, int, int H, size_t) {
-    return plane[(size_t)b * H + u];
-  }
-};
-
-template <class T>
-__device__ inline size_t ft_offset(int row, int k, int nsteps);
-
-template <>
-struct HPlane<__bf16> {
-  static constexpr bool SPLIT = true;
-  // nsh = KH / 32 macro steps per batch tile; half = BP * KH elements per 16-bit plane
-  __device__ static void store(float* plane, int b, int u, float v, int nsh, int, size_t half) {
-    unsigned short* hi = reinterpret_cast<unsigned short*>(plane);
-    const unsigned bits = __float_as_uint(v);
-    const size_t o = ft_offset<__bf16>(b, u, nsh);
-    hi[o] = (unsigned short)((bits + 0x8000u) >> 16);
-    hi[half + o] = (unsigned short)(bits & 0xffffu);
-  }
-  __device__ static float load(const float* plane, int b, int u, int nsh, int, size_t half) {
-    const unsigned short* hi = reinterpret_cast<const unsigned short*>(plane);
-    const size_t o = ft_offset<__bf16>(b, u, nsh);
-    const unsigned lo = hi[half + o];
-    return __uint_as_float((((unsigned)hi[o] - (lo >> 15)) << 16) | lo);
-  }
-  __device__ static __bf16 as_operand(const float* plane, int b, int u, int nsh, int, size_t) {
-    const __bf16* hi = reinterpret_cast<const __bf16*>(plane);
-    return hi[ft_offset<__bf16>(b, u, nsh)];
-  }
-};
-
 // ---- small utility kernels -------------------------------------------------------------------
 
 __global__ void fill_zero_kernel(uint4* p, size_t n16) {
@@ -154,37 +67,6 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st) {
   fill_zero_kernel<<<dim3((unsigned)blocks), dim3(256), 0, st>>>(reinterpret_cast<uint4*>(p), n16);
   return hipGetLastError();
 }
-
-// Operand arrays the library builds itself are stored "fragment-tiled": for a logical matrix
-// M[rows][K] the element (row, k) lives at
-//     (((row/16) * (K/KSTEP) + k/KSTEP) * 64 + ((k%KSTEP)/VEC)*16 + row%16) * VEC + k%VEC
-// so that the 64 lanes of a wave fetch the fragment of one 16-row tile and one macro step as one
-// contiguous, fully coalesced block of 64*VEC elements (1 KiB).
-template <class T>
-__device__ inline void ft_decode(size_t idx, int nsteps, int& row, int& k) {
-  constexpr int VEC = Mma<T>::VEC, KSTEP = 4 * VEC;
-  const int e = (int)(idx % VEC);
-  const int lane = (int)((idx / VEC) % 64);
-  const size_t blk = idx / (VEC * 64);
-  const int kstep = (int)(blk % nsteps);
-  const int tile = (int)(blk / nsteps);
-  row = tile * 16 + (lane & 15);
-  k = kstep * KSTEP + (lane >> 4) * VEC + e;
-}
-
-template <class T>
-__device__ inline size_t ft_offset(int row, int k, int nsteps) {
-  constexpr int VEC = Mma<T>::VEC, KSTEP = 4 * VEC;
-  return ((((size_t)(row >> 4) * nsteps + k / KSTEP) * 64 + ((k % KSTEP) / VEC) * 16 + (row & 15)) * VEC) + k % VEC;
-}
-
-// The four packed rows 4u .. 4u+3 of hidden unit u, and which gate block of the caller's W_ih / W_hh
-// feeds each of them (-1: that half of the row is zero).
-//   LSTM: rows i, f, g, o, both halves from the same gate block.
-//   GRU:  rows r, z, n_x, n_h.  The candidate's input part and recurrent part are kept as two rows
-//         (n = tanh(n_x + r * n_h)), so one GEMM with the same 4-rows-per-unit shape serves both cells.
-__host__ __device__ inline int packed_gate_x(int cell, int row) { return cell == 0 ? row : (row < 3 ? row : -1); }
-__host__ __device__ inline int packed_gate_h(int cell, int row) { return cell == 0 ? row : (row == 2 ? -1 : (row == 3 ? 2 : row)); }
 
 template <class T>
 __global__ void prep_weights_kernel(Dims d, const float* __restrict__ W_ih, const float* __restrict__ W_hh,
@@ -297,73 +179,6 @@ hipError_t launch_copy_plane(const Dims& d, const float* src, float* dst, int ac
   return hipGetLastError();
 }
 
-// ---- pointwise forward step of one (sequence, hidden unit) -------------------------------------
-// G: the four gate-GEMM results of the unit (packed rows), bias: their biases, state_prev: c_{s-1}
-// (LSTM) or h_{s-1} in full precision (GRU).  Returns h_s; `second` is what the second plane of
-// the state unit keeps (LSTM: c_s; GRU: the recurrent part n_h of the candidate), `gate` the
-// values the backward step needs (LSTM: i, f, g, o; GRU: r, z, n).  Every kernel that computes a
-// forward step calls this one function, with the multiply-adds spelled out, so that a step gives
-// the same bits whichever kernel ran it.
-template <int CELL>
-__device__ inline float cell_forward(const float (&G)[4], const float4& bias, float state_prev, float& second,
-                                     float (&gate)[4]) {
-  if (CELL == 0) {
-    const float gi = sigmoidf_(G[0] + bias.x);
-    const float gf = sigmoidf_(G[1] + bias.y);
-    const float gg = tanhf_(G[2] + bias.z);
-    const float go = sigmoidf_(G[3] + bias.w);
-    const float c = __fmaf_rn(gf, state_prev, __fmul_rn(gi, gg));
-    gate[0] = gi;
-    gate[1] = gf;
-    gate[2] = gg;
-    gate[3] = go;
-    second = c;
-    return __fmul_rn(go, tanhf_(c));
-  } else {
-    // rows r, z, n_x, n_h: n = tanh(n_x + r * n_h), h = (1 - z) n + z h_prev
-    const float r = sigmoidf_(G[0] + bias.x);
-    const float z = sigmoidf_(G[1] + bias.y);
-    const float nh = G[3] + bias.w;
-    const float n = tanhf_(__fmaf_rn(r, nh, G[2] + bias.z));
-    gate[0] = r;
-    gate[1] = z;
-    gate[2] = n;
-    gate[3] = 0.0f;
-    second = nh;
-    return __fmaf_rn(1.0f - z, n, __fmul_rn(z, state_prev));
-  }
-}
-
-// Pointwise backward step of one (sequence, hidden unit) of the LSTM: from dh_s (recurrent part
-// plus injected loss gradient), the running dc, the internal state (i, f, g, o, c_s) and c_{s-1}
-// to the four gate pre-activation gradients and dc_{s-1}.  One function, multiply-adds spelled
-// out, for every kernel that runs a backward step: the same bits whichever kernel ran it.
-__device__ inline void lstm_backward_point(float dh, float dc_in, float gi, float gf, float gg, float go, float c_s,
-                                           float c_prev, float (&dG)[4], float& dc_out) {
-  const float tc = tanhf_(c_s);
-  const float d_o = __fmul_rn(dh, tc);
-  const float dct = __fmaf_rn(__fmul_rn(dh, go), __fmaf_rn(-tc, tc, 1.0f), dc_in);
-  dG[0] = __fmul_rn(__fmul_rn(__fmul_rn(dct, gg), gi), __fsub_rn(1.0f, gi));
-  dG[1] = __fmul_rn(__fmul_rn(__fmul_rn(dct, c_prev), gf), __fsub_rn(1.0f, gf));
-  dG[2] = __fmul_rn(__fmul_rn(dct, gi), __fmaf_rn(-gg, gg, 1.0f));
-  dG[3] = __fmul_rn(__fmul_rn(d_o, go), __fsub_rn(1.0f, go));
-  dc_out = __fmul_rn(dct, gf);
-}
-
-// The same for the GRU: r, z, n the gates, nh the recurrent part of the candidate (n = tanh(n_x + r * nh)),
-// h_prev = h_{s-1} in full precision.  dh is the whole dL/dh_s: the GEMM part, the injected loss
-// gradient and the part that bypasses the GEMM (dh_{s+1} * z_{s+1}, carried in the running plane).
-// dG: gradients of the packed rows r, z, n_x, n_h; carry: what step s - 1 adds to its dh.
-__device__ inline void gru_backward_point(float dh, float r, float z, float n, float nh, float h_prev, float (&dG)[4],
-                                          float& carry) {
-  const float da_n = __fmul_rn(__fmul_rn(dh, __fsub_rn(1.0f, z)), __fmaf_rn(-n, n, 1.0f));
-  dG[0] = __fmul_rn(__fmul_rn(__fmul_rn(da_n, nh), r), __fsub_rn(1.0f, r));
-  dG[1] = __fmul_rn(__fmul_rn(__fmul_rn(dh, __fsub_rn(h_prev, n)), z), __fsub_rn(1.0f, z));
-  dG[2] = da_n;
-  dG[3] = __fmul_rn(da_n, r);
-  carry = __fmul_rn(dh, z);
-}
-
 // ---- forward step: gate GEMM + LSTM pointwise -------------------------------------------------
 
 struct FwdParams {
@@ -380,50 +195,6 @@ struct FwdParams {
   float* g_o;
   int B, I, H, HP, KX, KH, KP, BP;
 };
-
-// Raw (unconverted) activation fragment: VEC fp32 values, zero beyond `limit`.
-template <int VEC>
-struct RawAct {
-  float v[VEC];
-};
-template <int VEC>
-__device__ inline RawAct<VEC> load_raw(const float* __restrict__ row, int k, int limit, bool vec_ok) {
-  RawAct<VEC> r;
-  if (vec_ok && k + VEC <= limit) {
-#pragma unroll
-    for (int e = 0; e < VEC; e += 4) {
-      float4 q = *reinterpret_cast<const float4*>(row + k + e);
-      r.v[e] = q.x;
-      r.v[e + 1] = q.y;
-      r.v[e + 2] = q.z;
-      r.v[e + 3] = q.w;
-    }
-  } else {
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) r.v[e] = (k + e < limit) ? row[k + e] : 0.0f;
-  }
-  return r;
-}
-
-// As load_raw for rows whose length is a multiple of VEC (k is one too): a fragment lies wholly
-// inside the row or wholly outside, so one address clamp and one select replace the branches.
-// (Branches that load into the same registers make the compiler wait for every outstanding memory
-// operation between them.)
-template <int VEC>
-__device__ inline RawAct<VEC> load_raw_whole(const float* __restrict__ row, int k, int limit) {
-  RawAct<VEC> r;
-  const bool inside = k < limit;
-  const float* src = row + (inside ? k : 0);
-#pragma unroll
-  for (int e = 0; e < VEC; e += 4) {
-    const float4 q = *reinterpret_cast<const float4*>(src + e);
-    r.v[e] = inside ? q.x : 0.0f;
-    r.v[e + 1] = inside ? q.y : 0.0f;
-    r.v[e + 2] = inside ? q.z : 0.0f;
-    r.v[e + 3] = inside ? q.w : 0.0f;
-  }
-  return r;
-}
 
 // One workgroup of 64*KS threads = BT batch tiles (16 sequences each) x NG unit groups (4 hidden
 // units = 16 gate rows each).  Its KS waves split the K axis; every wave covers all NG x BT output
@@ -854,34 +625,6 @@ __global__ __launch_bounds__(64 * (FKS > BKS ? FKS : BKS), 4) void pair_kernel(F
     backward_body<T, BNT, BBT, BKS, BU>(b, (id - nf) % nbx, (id - nf) / nbx, red);
 }
 
-// Kernel configurations by shape.  Tiles per workgroup grow with the problem so that the grid
-// stays near one workgroup per compute unit while every operand byte is reused as often as
-// possible; the choice depends on the shape only, never on the schedule.
-enum FwdConfig { FWD_TINY, FWD_SMALLK, FWD_B1, FWD_42, FWD_82 };
-enum BwdConfig { BWD_SMALLK, BWD_11, BWD_12, BWD_22 };
-constexpr int TARGET_WGS = 256;
-
-template <class T>
-static FwdConfig forward_config(const Dims& d) {
-  const int nsteps = d.KP / (4 * Mma<T>::VEC);
-  if (nsteps <= 8) return FWD_TINY;
-  if (nsteps <= 20) return FWD_SMALLK;
-  const int ngroups = d.HP / 4, bt = d.BP / 16;
-  if (bt >= 2 && ((ngroups + 7) / 8) * ((bt + 1) / 2) >= TARGET_WGS) return FWD_82;
-  if (bt >= 2 && ((ngroups + 3) / 4) * ((bt + 1) / 2) >= TARGET_WGS) return FWD_42;
-  return FWD_B1;
-}
-
-template <class T>
-static BwdConfig backward_config(const Dims& d) {
-  const int nsteps = d.G4 / (4 * Mma<T>::VEC);
-  if (nsteps <= 16) return BWD_SMALLK;
-  const int nt = d.HP / 16, bt = d.BP / 16;
-  if (nt >= 2 && bt >= 2 && ((nt + 1) / 2) * ((bt + 1) / 2) >= TARGET_WGS) return BWD_22;
-  if (bt >= 2 && nt * ((bt + 1) / 2) >= TARGET_WGS) return BWD_12;
-  return BWD_11;
-}
-
 template <class T, int NG, int BT, int KS, int U>
 static hipError_t launch_forward_cfg(const Dims& d, const FwdParams& p, hipStream_t st) {
   dim3 grid((d.HP / 4 + NG - 1) / NG, (d.BP / 16 + BT - 1) / BT), block(64 * KS);
@@ -1150,972 +893,6 @@ hipError_t launch_backward_forward_pair(const Dims& d, const BackwardArgs& a, co
   else
     d.cell ? launch_pair_t<float, 1>(d, f, b, st) : launch_pair_t<float, 0>(d, f, b, st);
   return hipGetLastError();
-}
-
-// ---- forward chain with resident weights -----------------------------------------------------
-// Consecutive forward operations (Algorithm 2's forward loop; also the single-step pushes that
-// follow each other when memory is plentiful) depend on each other only through h, so a chain of
-// them can run inside ONE launch if the gate weights stay on the chip and only h travels.  The
-// chip is split along the batch: XCD g (one of 8, each with its own L2) takes the sequences
-// [g*nb, (g+1)*nb) and never needs anything from another XCD, so no step synchronises across
-// XCDs.  Inside an XCD the 32 workgroups (one per compute unit) split the hidden units: workgroup
-// `rank` owns units [rank*H/32, (rank+1)*H/32), keeps the 4*H/32 packed weight rows of those units
-// in registers (and a part in LDS) for the whole launch, and per step
-//   1. waits until all 32 workgroups of its XCD have published their slice of h_{s-1}
-//      (a counter in the XCD's L2, bumped with an atomic add and polled with agent-scope loads),
-//   2. fetches the bf16 h_{s-1} of its sequences from the exchange ring with loads that bypass the
-//      compute unit's vector cache (the ring is written through to the L2 the 32 share),
-//   3. runs its slice of the gate GEMM and the pointwise step, keeps c in registers, publishes
-//      its slice of h_s, and stores the full state only where the schedule wants one.
-// Which XCD a workgroup runs on is read from the hardware (register XCC_ID), not inferred from
-// its id: workgroups are dealt round-robin to the XCDs, but where the deal starts depends on the
-// launches before.  A workgroup takes the next free rank of its XCD from a counter; the launch
-// relies on every XCD receiving exactly 32 of the 256 workgroups, checks it (a rank counter that
-// runs past 32 raises the status word; an XCD that gets fewer never completes its first wait,
-// which is bounded by a wall-clock limit like every other) and gives up rather than compute on
-// an assumption that does not hold.
-// Sums are formed exactly as forward_body forms them (KS partial sums over the macro steps
-// w, w+KS, ..., added in the order 0..KS-1), so a step gives the same bits either way.
-constexpr int RES_MAX_STEPS = 192;  // steps of one launch: their destinations travel as kernel arguments (3 KiB of the 4 KiB there are)
-constexpr int RES_RING = 4;         // h slices in flight (two would do: a step ahead at most)
-constexpr int RES_WGS = 256, RES_GROUPS = 8, RES_MEMBERS = RES_WGS / RES_GROUPS;
-constexpr long long RES_WAIT_TICKS = 50000000;   // 0.5 s of the 100 MHz wall clock
-// The bound every wait of a resident launch runs under, in ticks of that clock.  A host-side
-// setting (resident_wait_ticks) so that a test can make the waits give up at once -- every
-// workgroup then leaves through the same path as after a real time-out -- without anything hanging.
-static long long g_wait_ticks = RES_WAIT_TICKS;
-void set_resident_wait_ticks(long long ticks) { g_wait_ticks = ticks < 0 ? RES_WAIT_TICKS : ticks; }
-
-struct ResStep {
-  float* out;     // unit that receives (h, c) of this step, or NULL
-  float* gates;   // two units that receive (i, f), (g, o), or NULL
-};
-struct ResParams {
-  const void* Wp;
-  const float* bp;
-  const float* x0;     // x of the first step of this launch
-  const float* src;    // unit holding the input state of the first step
-  void* ring;          // RES_RING x [BP][KH] bf16, fragment-tiled like the 16-bit h plane
-  unsigned* sync;      // words: arrival counter of XCD g at [g*64], rank counter at [512 + g*64], status at [1024]
-  unsigned base;       // value of every arrival counter when the launch starts
-  unsigned launch;     // chain launches of this run before this one (every rank counter stands at 32 * launch)
-  long long wait_ticks;   // bound of every wait, in ticks of the 100 MHz wall clock
-  int count;
-  int B, I, H, KX, KH, BP, nb;
-  size_t unit;         // floats per unit
-  ResStep step[RES_MAX_STEPS];
-};
-
-__device__ inline unsigned xcc_id() {
-  unsigned v;
-  asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(v));
-  return v & 0xf;
-}
-
-// One operand fragment (16 bytes per lane) fetched with agent scope: the load skips this compute
-// unit's vector cache and is served by the XCD's L2, where the other compute units of the XCD have
-// just written it.  A buffer load with the scope bit, not an atomic load: the compiler may keep as
-// many of them in flight as it has registers for (atomic loads it issues two at a time).
-// `base` is wave-uniform; byte_off < 2^31.
-__device__ inline bf16x8 load_frag_l2(const void* base, unsigned byte_off) {
-  typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
-  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0x7fffffff, 0x00020000);
-  union { u32x4 u; bf16x8 f; } cv;
-  cv.u = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)byte_off, 0, 16 /* sc1: agent scope */);
-  return cv.f;
-}
-
-template <int NRT, int NSW, int NSL, int KS, int NBT, int NSXW, int CELL>
-__global__ __launch_bounds__(64 * KS) void forward_chain_kernel(ResParams p) {
-  using T = __bf16;
-  using M = Mma<T>;
-  constexpr int VEC = 8, KSTEP = 32, FRAG = 64 * VEC;
-  constexpr int NT = NRT * NBT, NSR = NSW - NSL;
-  constexpr int UW = NRT * 4, ITEMS = NBT * 16 * UW, NTHR = 64 * KS, IPT = (ITEMS + NTHR - 1) / NTHR;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  float* red = reinterpret_cast<float*>(smem);                               // [KS][NT][4][64]
-  T* wl = reinterpret_cast<T*>(smem + (size_t)KS * NT * 4 * 64 * sizeof(float));   // [KS][NRT][NSL] fragments
-  __shared__ int s_go, s_g, s_rank;
-  // the wave index as a scalar: conditions on it become scalar branches (an MFMA under a lane mask
-  // that is empty would still execute)
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-  const int lrow = lane & 15, lq = lane >> 4;
-  if (threadIdx.x == 0) {
-    const unsigned xcc = xcc_id();
-    int ok = xcc < (unsigned)RES_GROUPS;
-    unsigned ticket = 0;
-    if (ok) {
-      ticket = __hip_atomic_fetch_add(p.sync + 512 + xcc * 64, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      ok = ticket / RES_MEMBERS == p.launch;   // more than 32 workgroups on this XCD: ranks would collide
-    }
-    if (!ok) __hip_atomic_store(p.sync + 1024, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s_go = ok;
-    s_g = ok ? (int)xcc : 0;
-    s_rank = (int)(ticket % RES_MEMBERS);
-  }
-  __syncthreads();
-  if (!s_go) return;
-  const int g = s_g, rank = s_rank;
-  constexpr int nsteps = KS * NSW;
-  const int nsx = p.KX / KSTEP, nsh = p.KH / KSTEP;
-  const size_t hhalf = (size_t)p.BP * p.KH;
-  const int b_lo = g * p.nb, b_hi = min(p.B, b_lo + p.nb);
-  const int nbt_all = p.BP / 16;
-  const int ct0 = min(b_lo / 16, nbt_all - 1);
-  unsigned* ctr = p.sync + g * 64;
-  unsigned* status = p.sync + 1024;
-
-  // This workgroup's packed weight rows: row tiles rank*NRT .. +NRT, this wave's macro steps
-  // wave, wave + KS, ...; the last NSL of them are parked in LDS (read back by this wave only).
-  typename M::Frag wr[NRT][NSR > 0 ? NSR : 1];
-  {
-    const T* wbase = reinterpret_cast<const T*>(p.Wp) + ((size_t)rank * NRT * nsteps * 64 + lane) * VEC;
-#pragma unroll
-    for (int rt = 0; rt < NRT; ++rt)
-#pragma unroll
-      for (int i = 0; i < NSW; ++i) {
-        const typename M::Frag f = M::load(wbase + ((size_t)rt * nsteps + wave + KS * i) * FRAG);
-        if (i < NSR)
-          wr[rt][i] = f;
-        else
-          *reinterpret_cast<typename M::Frag*>(&wl[((size_t)(wave * NRT + rt) * NSL + (i - NSR)) * FRAG + lane * VEC]) = f;
-      }
-  }
-
-  // Pointwise items of this thread: item = (output tile, lane of the MFMA layout), i.e. the
-  // (sequence, unit) whose four gate sums that lane holds, so that the partial sums are read back
-  // from LDS at consecutive addresses by consecutive threads.  c stays in registers.
-  bool mine[IPT];
-  int ib[IPT], iu[IPT], icell[IPT];
-  float4 bias[IPT];
-  float c_state[IPT];
-#pragma unroll
-  for (int q = 0; q < IPT; ++q) {
-    const int item = (int)threadIdx.x + q * NTHR;
-    const int tile = item >> 6, il = item & 63;          // tile = rt * NBT + bt
-    const int rt = tile / NBT, bt = tile % NBT;
-    const int b = (ct0 + bt) * 16 + (il & 15), u = rank * UW + rt * 4 + (il >> 4);
-    mine[q] = item < ITEMS && b >= b_lo && b < b_hi;
-    ib[q] = b;
-    iu[q] = u;
-    icell[q] = tile * 4 * 64 + il;   // where the four gate sums of this item sit inside one wave's block of `red`
-    bias[q] = float4{0.f, 0.f, 0.f, 0.f};
-    c_state[q] = 0.0f;
-    if (mine[q]) {
-      bias[q] = *reinterpret_cast<const float4*>(p.bp + 4 * u);
-      // the state the pointwise step blends with, kept in this register from step to step:
-      // c_{s-1} (LSTM) or h_{s-1} in full precision (GRU)
-      c_state[q] = CELL ? HPlane<T>::load(p.src, b, u, nsh, p.H, hhalf) : p.src[hhalf + (size_t)b * p.H + u];
-    }
-  }
-  const bool x_vec = (p.I & 3) == 0;
-
-  // Raw x values of this wave's x macro steps for the step about to run (NSXW = how many of the
-  // wave's first steps can fall into the x segment at all: KX / 32 / KS rounded up).
-  RawAct<VEC> xraw[NSXW][NBT];
-  auto fetch_x = [&](int j) {
-    const float* x_j = p.x0 + (size_t)j * p.B * p.I;
-#pragma unroll
-    for (int i = 0; i < NSXW; ++i) {
-      const int s = wave + KS * i;
-      if (s < nsx) {
-#pragma unroll
-        for (int bt = 0; bt < NBT; ++bt) {
-          const int b_ld = min(min(ct0 + bt, nbt_all - 1) * 16 + lrow, p.B - 1);
-          xraw[i][bt] = load_raw<VEC>(x_j + (size_t)b_ld * p.I, s * KSTEP + VEC * lq, p.I, x_vec);
-        }
-      }
-    }
-  };
-  fetch_x(0);
-
-  for (int j = 0; j < p.count; ++j) {
-    // x fragments: the raw fp32 values were requested a step ahead (see below) and are converted
-    // now; they do not depend on the other workgroups
-    typename M::Frag bf[NSW][NBT];
-#pragma unroll
-    for (int i = 0; i < NSXW; ++i)
-      if (wave + KS * i < nsx) {
-#pragma unroll
-        for (int bt = 0; bt < NBT; ++bt) bf[i][bt] = M::from_f32(xraw[i][bt].v);
-      }
-    f32x4 acc[NRT][NBT];
-#pragma unroll
-    for (int rt = 0; rt < NRT; ++rt)
-#pragma unroll
-      for (int bt = 0; bt < NBT; ++bt) acc[rt][bt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto weight = [&](int rt, int i) -> typename M::Frag {
-      return (i < NSR) ? wr[rt][i < NSR ? i : 0]
-                       : M::load(&wl[((size_t)(wave * NRT + rt) * NSL + (i - NSR)) * FRAG + lane * VEC]);
-    };
-    // the x part of the sum needs nothing from the other workgroups (a wave's x macro steps precede
-    // its h macro steps, so the order of the additions is that of forward_body)
-#pragma unroll
-    for (int i = 0; i < NSXW; ++i)
-      if (wave + KS * i < nsx) {
-#pragma unroll
-        for (int rt = 0; rt < NRT; ++rt) {
-          const typename M::Frag a = weight(rt, i);
-#pragma unroll
-          for (int bt = 0; bt < NBT; ++bt) acc[rt][bt] = M::mma(a, bf[i][bt], acc[rt][bt]);
-        }
-      }
-    if (j > 0) {
-      // all 32 workgroups of this XCD have published h of the previous step?
-      if (threadIdx.x == 0) {
-        const unsigned target = p.base + (unsigned)j * RES_MEMBERS;
-        int ok = 1, polls = 0;
-        long long t0 = 0;
-        // agent-scope loads see the counter in the L2 (32 pollers do not queue behind each other as
-        // read-modify-writes would: 1.95 -> 1.59 us per exchange round in isolation)
-        while ((int)(__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - target) < 0) {
-          if (p.wait_ticks == 0 || (++polls & 15) == 0) {   // a bound of 0: one look only
-            const long long now = wall_clock64();
-            if (t0 == 0) t0 = now;
-            if (now - t0 >= p.wait_ticks ||
-                __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) {
-              __hip_atomic_store(status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              ok = 0;
-              break;
-            }
-          }
-        }
-        s_go = ok;
-      }
-      __syncthreads();
-      if (!s_go) return;
-    }
-    // h fragments: the stored input state for the first step, then the exchange ring
-    {
-      const T* hsrc = (j == 0) ? reinterpret_cast<const T*>(p.src)
-                               : reinterpret_cast<const T*>(p.ring) + (size_t)((j - 1) % RES_RING) * hhalf;
-#pragma unroll
-      for (int i = 0; i < NSW; ++i) {
-        const int s = wave + KS * i;
-        if (s >= nsx) {
-#pragma unroll
-          for (int bt = 0; bt < NBT; ++bt) {
-            const size_t fo = (((size_t)min(ct0 + bt, nbt_all - 1) * nsh + (s - nsx)) * 64 + lane) * VEC;
-            if (j == 0)
-              bf[i][bt] = M::load(hsrc + fo);
-            else
-              bf[i][bt] = load_frag_l2(hsrc, (unsigned)(fo * sizeof(T)));
-          }
-        }
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);   // every fetch is issued before the first MFMA
-#pragma unroll
-    for (int i = 0; i < NSW; ++i)
-      if (!(i < NSXW && wave + KS * i < nsx)) {
-#pragma unroll
-        for (int rt = 0; rt < NRT; ++rt) {
-          const typename M::Frag a = weight(rt, i);
-#pragma unroll
-          for (int bt = 0; bt < NBT; ++bt) acc[rt][bt] = M::mma(a, bf[i][bt], acc[rt][bt]);
-        }
-      }
-    if (j + 1 < p.count) fetch_x(j + 1);   // in flight while this step finishes and the next wait runs
-#pragma unroll
-    for (int rt = 0; rt < NRT; ++rt)
-#pragma unroll
-      for (int bt = 0; bt < NBT; ++bt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) red[((wave * NT + rt * NBT + bt) * 4 + r) * 64 + lane] = acc[rt][bt][r];
-    __syncthreads();
-    const ResStep dst = p.step[j];
-    T* ring_out = reinterpret_cast<T*>(p.ring) + (size_t)(j % RES_RING) * hhalf;
-    const bool publish = j + 1 < p.count;
-    float keep_h[IPT], keep_second[IPT], keep_gate[IPT][4];
-#pragma unroll
-    for (int q = 0; q < IPT; ++q) {
-      if (!mine[q]) continue;
-      float G[4] = {0.f, 0.f, 0.f, 0.f};
-      for (int w = 0; w < KS; ++w)   // fixed order, as in forward_body
-#pragma unroll
-        for (int r = 0; r < 4; ++r) G[r] += red[w * NT * 4 * 64 + icell[q] + r * 64];
-      const float h = cell_forward<CELL>(G, bias[q], c_state[q], keep_second[q], keep_gate[q]);
-      keep_h[q] = h;
-      c_state[q] = CELL ? h : keep_second[q];
-      const int b = ib[q], u = iu[q];
-      if (publish) {
-        // Units u and u + 1 of one sequence sit 16 lanes apart in this layout and next to each other
-        // in the ring: the lane of the even unit stores both as one dword (the rows of a tile belong
-        // to one XCD or, split in halves, to two -- a lane and its partner are always on the same side).
-        const unsigned hi16 = (__float_as_uint(h) + 0x8000u) >> 16;
-        const unsigned other = __shfl_xor(hi16, 16);
-        if (((threadIdx.x >> 4) & 1) == 0)
-          reinterpret_cast<unsigned*>(ring_out)[ft_offset<T>(b, u, nsh) >> 1] = hi16 | (other << 16);
-      }
-    }
-    if (publish) {
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's slice of h has reached the L2
-      __syncthreads();
-      if (threadIdx.x == 0) __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    // What only later launches read goes out after the arrival: the other workgroups do not wait
-    // for these stores to be acknowledged.
-    if (dst.out || dst.gates) {
-#pragma unroll
-      for (int q = 0; q < IPT; ++q) {
-        if (!mine[q]) continue;
-        const int b = ib[q], u = iu[q];
-        if (dst.out) {
-          HPlane<T>::store(dst.out, b, u, keep_h[q], nsh, p.H, hhalf);
-          dst.out[hhalf + (size_t)b * p.H + u] = keep_second[q];
-        }
-        if (dst.gates) {
-          const size_t e = (size_t)b * p.H + u, plane = (size_t)p.B * p.H;
-          dst.gates[e] = keep_gate[q][0];
-          dst.gates[plane + e] = keep_gate[q][1];
-          dst.gates[p.unit + e] = keep_gate[q][2];
-          if (CELL == 0) dst.gates[p.unit + plane + e] = keep_gate[q][3];
-        }
-      }
-    }
-  }
-}
-
-// Shape classes with an instantiation: {NRT = H/128, NSW = macro steps per wave, NSL, KS, NBT}.
-struct ResConfig {
-  int nrt, nsw, nsl, ks, nbt, nsxw;
-};
-static const ResConfig RES_CONFIGS[] = {
-    {8, 5, 1, 8, 1, 1},   // H = 1024, I <= 256
-    {4, 5, 0, 4, 1, 1}, {4, 5, 0, 4, 2, 1},   // H = 512, I <= 128
-    {2, 4, 0, 4, 1, 2}, {2, 4, 0, 4, 2, 2},   // H = 256, 128 < I <= 256
-    {1, 2, 0, 4, 1, 1}, {1, 2, 0, 4, 2, 1},   // H = 128, I <= 128
-};
-
-// The batch is dealt to the XCDs in groups of nb consecutive sequences.  An even share,
-// nb = ceil(B / 8), keeps every XCD busy but may make a group straddle more 16-sequence MFMA tiles
-// than a kernel is instantiated for; the share rounded up to whole tiles never straddles (some XCDs
-// then get no sequences and only keep the meeting going).  group_tiles: batch tiles the widest group
-// touches; the configuration look-ups try the even share first.
-static int group_tiles(const Dims& d, int nb) {
-  int nbt = 1;
-  for (int g = 0; g < RES_GROUPS; ++g) {
-    const int lo = g * nb, hi = (lo + nb < d.B ? lo + nb : d.B);
-    if (lo >= d.B) break;
-    const int span = (hi - 1) / 16 - lo / 16 + 1;
-    nbt = span > nbt ? span : nbt;
-  }
-  return nbt;
-}
-static int group_share(const Dims& d, int candidate) {
-  const int even = (d.B + RES_GROUPS - 1) / RES_GROUPS;
-  return candidate == 0 ? even : round_up(even, 16);
-}
-
-// Index into RES_CONFIGS for this shape, or -1 when the chain kernel does not apply; *nb_out = the
-// sequences per XCD to launch it with.
-static int resident_config(const Dims& d, int* nb_out = nullptr) {
-  if (!d.dtype || d.H % 128 != 0 || d.KH != d.H) return -1;   // either cell: the GRU's rows r, z, n_x, n_h fill the same four packed rows
-  const int nsteps = d.KP / 32;
-  const FwdConfig fc = forward_config<__bf16>(d);
-  const int ks = (fc == FWD_TINY || fc == FWD_SMALLK) ? 4 : 8;   // the K split of the per-step kernels
-  if (nsteps % ks != 0) return -1;
-  for (int cand = 0; cand < 2; ++cand) {
-    const int nb = group_share(d, cand), nbt = group_tiles(d, nb);
-    for (size_t i = 0; i < sizeof RES_CONFIGS / sizeof RES_CONFIGS[0]; ++i) {
-      const ResConfig& c = RES_CONFIGS[i];
-      if (c.nrt == d.H / 128 && c.ks == ks && c.nsw == nsteps / ks && c.nbt == nbt && c.nsxw == (d.KX / 32 + ks - 1) / ks) {
-        if (nb_out) *nb_out = nb;
-        return (int)i;
-      }
-    }
-  }
-  return -1;
-}
-
-bool can_run_forward_chain(const Dims& d) { return resident_config(d) >= 0; }
-int forward_chain_max_steps() { return RES_MAX_STEPS; }
-size_t forward_chain_ring_bytes(const Dims& d) { return (size_t)RES_RING * d.BP * d.KH * sizeof(__bf16); }
-size_t forward_chain_sync_bytes() { return (1024 + 64) * sizeof(unsigned); }
-size_t forward_chain_status_offset() { return 1024 * sizeof(unsigned); }
-unsigned forward_chain_arrivals(int steps) { return steps > 1 ? (unsigned)(steps - 1) * RES_MEMBERS : 0u; }
-
-template <int NRT, int NSW, int NSL, int KS, int NBT, int NSXW, int CELL>
-static hipError_t launch_chain_cell(const ResParams& p, hipStream_t st) {
-  const size_t lds = (size_t)KS * NRT * NBT * 4 * 64 * sizeof(float) + (size_t)KS * NRT * NSL * 64 * 8 * sizeof(__bf16);
-  static bool configured = false;   // per instantiation; the attribute only has to be set once
-  if (!configured) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(forward_chain_kernel<NRT, NSW, NSL, KS, NBT, NSXW, CELL>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    configured = true;
-  }
-  forward_chain_kernel<NRT, NSW, NSL, KS, NBT, NSXW, CELL><<<dim3(RES_WGS), dim3(64 * KS), lds, st>>>(p);
-  return hipGetLastError();
-}
-template <int NRT, int NSW, int NSL, int KS, int NBT, int NSXW>
-static hipError_t launch_chain_cfg(const ResParams& p, int cell, hipStream_t st) {
-  return cell ? launch_chain_cell<NRT, NSW, NSL, KS, NBT, NSXW, 1>(p, st) : launch_chain_cell<NRT, NSW, NSL, KS, NBT, NSXW, 0>(p, st);
-}
-
-hipError_t launch_forward_chain(const Dims& d, const void* Wp, const float* bp, const float* x_first, const float* src_unit,
-                                const ChainStep* steps, int count, void* ring, unsigned* sync, unsigned base,
-                                unsigned launch, hipStream_t st) {
-  int nb = 0;
-  const int cfg = resident_config(d, &nb);
-  if (cfg < 0 || count < 1 || count > RES_MAX_STEPS) return hipErrorInvalidValue;
-  ResParams p{};
-  p.Wp = Wp;
-  p.bp = bp;
-  p.x0 = x_first;
-  p.src = src_unit;
-  p.ring = ring;
-  p.sync = sync;
-  p.base = base;
-  p.launch = launch;
-  p.wait_ticks = g_wait_ticks;
-  p.count = count;
-  p.B = d.B;
-  p.I = d.I;
-  p.H = d.H;
-  p.KX = d.KX;
-  p.KH = d.KH;
-  p.BP = d.BP;
-  p.nb = nb;
-  p.unit = d.unit;
-  for (int j = 0; j < count; ++j) p.step[j] = ResStep{steps[j].out, steps[j].gates};
-  switch (cfg) {
-    case 0: return launch_chain_cfg<8, 5, 1, 8, 1, 1>(p, d.cell, st);
-    case 1: return launch_chain_cfg<4, 5, 0, 4, 1, 1>(p, d.cell, st);
-    case 2: return launch_chain_cfg<4, 5, 0, 4, 2, 1>(p, d.cell, st);
-    case 3: return launch_chain_cfg<2, 4, 0, 4, 1, 2>(p, d.cell, st);
-    case 4: return launch_chain_cfg<2, 4, 0, 4, 2, 2>(p, d.cell, st);
-    case 5: return launch_chain_cfg<1, 2, 0, 4, 1, 1>(p, d.cell, st);
-    default: return launch_chain_cfg<1, 2, 0, 4, 2, 1>(p, d.cell, st);
-  }
-}
-
-// ---- backward sweep with resident weights ------------------------------------------------------
-// Where a sub-sequence fits into memory the schedule alternates "forward operation of step s from
-// the memorised h_{s-1}, keeping the internal state" and "backward operation of step s", s going
-// down.  On shapes whose gate weights AND their transpose fit on the chip such a run of pairs goes
-// out as one launch per chunk of steps, organised like the forward chain (batch split over the
-// XCDs, hidden units over the 32 compute units of an XCD, weights in registers):
-//   * the forward operation of a step needs nothing from other compute units (its input state was
-//     memorised by an earlier launch), and its internal state never leaves the registers of the
-//     thread that owns the (sequence, unit);
-//   * the backward operation needs dG of the step after, all 4H columns of it, for the XCD's
-//     sequences: the compute units publish their columns in the chunk's dG staging buffer (which
-//     is already laid out as that GEMM's operand) and meet at the XCD's arrival counter;
-//   * while the counter fills, every compute unit already runs the forward operation of the next
-//     lower step, so the wait is mostly hidden.
-// K splits and summation orders are those of forward_body and backward_body for the shape, the
-// pointwise steps are the shared functions: bit-identical to the launch-per-step path.
-constexpr int SWEEP_MAX_STEPS = 32;
-struct SweepParams {
-  const void* Wp;
-  const void* WTh;
-  const float* bp;
-  const float* x;        // x of step 1 (step s reads x + (s-1)*B*I)
-  const float* dy;       // upstream gradients, first plane = step dy_first; NULL with dy_is_h
-  int dy_first, dy_is_h;
-  float* dc;             // running cell-state gradient plane
-  float* y_out;          // outputs, plane of step 1 first, or NULL
-  const void* dG_next;   // dG block of step s_hi + 1, or NULL when s_hi is the last step of the sequence
-  void* dG_chunk[2];     // the two chunk buffers: step s lives in buffer ((s-1) / CH) & 1, its block at slot (s-1) % CH
-  void* dGT[2];
-  void* aT[2];
-  unsigned* sync;
-  unsigned base, launch;
-  long long wait_ticks;  // bound of every wait, in ticks of the 100 MHz wall clock
-  int s_hi, count;       // steps s_hi, s_hi - 1, ..., s_hi - count + 1 (in at most two consecutive chunks)
-  int B, I, H, KX, KH, BP, nb, G4, NX, KC, CH;
-  size_t unit;
-  const float* src[SWEEP_MAX_STEPS];   // src[j]: unit holding the state before step s_hi - j
-  const float* state[SWEEP_MAX_STEPS]; // FWD = false: unit holding the stored internal state of step s_hi - j
-};
-
-// FWD = false: the internal states are not recomputed but read from where an earlier launch
-// stored them (internal-state slots): a run of backward operations only, W_hh^T alone resident.
-template <bool FWD, int NRT, int NSWF, int KSF, int NSWB, int KSB, int NBT, int NSXW, int CELL = 0>
-__global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
-  static_assert(!(FWD && CELL), "the launches that recompute internal states are built for the LSTM only");
-  using T = __bf16;
-  using M = Mma<T>;
-  constexpr int VEC = 8, KSTEP = 32;
-  constexpr int FT = 8 / KSF;                       // groups of waves that split the forward row tiles
-  constexpr int NRTW = (NRT + FT - 1) / FT;         // forward row tiles per wave
-  constexpr int UW = NRT * 4;                       // hidden units per workgroup
-  constexpr int NTB = (UW + 15) / 16;               // 16-unit tiles of the dh GEMM that cover them
-  constexpr int NTF = NRT * NBT, NTBT = NTB * NBT;
-  constexpr int ITEMS = NRT * NBT * 64, IPT = (ITEMS + 511) / 512;
-  constexpr int nstepsF = KSF * NSWF, nstepsB = KSB * NSWB;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  float* redF = reinterpret_cast<float*>(smem);                       // [KSF][NTF][4][64]
-  float* redB = redF + (size_t)KSF * NTF * 4 * 64;                    // [KSB][NTBT][4][64]
-  __shared__ int s_go, s_g, s_rank;
-  // the wave index as a scalar: conditions on it become scalar branches (an MFMA under a lane mask
-  // that is empty would still execute)
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-  const int lrow = lane & 15, lq = lane >> 4;
-  if (threadIdx.x == 0) {
-    const unsigned xcc = xcc_id();
-    int ok = xcc < (unsigned)RES_GROUPS;
-    unsigned ticket = 0;
-    if (ok) {
-      ticket = __hip_atomic_fetch_add(p.sync + 512 + xcc * 64, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      ok = ticket / RES_MEMBERS == p.launch;
-    }
-    if (!ok) __hip_atomic_store(p.sync + 1024, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s_go = ok;
-    s_g = ok ? (int)xcc : 0;
-    s_rank = (int)(ticket % RES_MEMBERS);
-  }
-  __syncthreads();
-  if (!s_go) return;
-  const int g = s_g, rank = s_rank;
-  const int nsx = p.KX / KSTEP, nsh = p.KH / KSTEP;
-  const size_t hhalf = (size_t)p.BP * p.KH, plane = (size_t)p.B * p.H;
-  const int b_lo = g * p.nb, b_hi = min(p.B, b_lo + p.nb);
-  const int nbt_all = p.BP / 16;
-  const int ct0 = min(b_lo / 16, nbt_all - 1);
-  unsigned* ctr = p.sync + g * 64;
-  unsigned* status = p.sync + 1024;
-  const int fk = wave % KSF, fg = wave / KSF;       // forward: K part and row-tile group of this wave
-  const bool bwd_wave = wave < KSB;
-  const int nt0 = (rank * UW) / 16;                 // first 16-unit tile of the dh GEMM
-
-  // resident weights: forward rows of this workgroup's units, and the rows of W_hh^T for the same units
-  typename M::Frag wf[FWD ? NRTW : 1][FWD ? NSWF : 1], wb[NTB][NSWB];
-  if (FWD) {
-#pragma unroll
-    for (int i = 0; i < NRTW; ++i) {
-      const int rt = min(fg * NRTW + i, NRT - 1);
-#pragma unroll
-      for (int k = 0; k < NSWF; ++k)
-        wf[FWD ? i : 0][FWD ? k : 0] = M::load(reinterpret_cast<const T*>(p.Wp) +
-                                               (((size_t)(rank * NRT + rt) * nstepsF + fk + KSF * k) * 64 + lane) * VEC);
-    }
-  }
-#pragma unroll
-  for (int tb = 0; tb < NTB; ++tb)
-#pragma unroll
-    for (int k = 0; k < NSWB; ++k)
-      wb[tb][k] = M::load(reinterpret_cast<const T*>(p.WTh) +
-                          (((size_t)(nt0 + tb) * nstepsB + min(wave, KSB - 1) + KSB * k) * 64 + lane) * VEC);
-
-  // items: (output tile, lane of the forward MFMA layout) = (sequence, unit)
-  bool mine[IPT];
-  int ib[IPT], iu[IPT], icellF[IPT], icellB[IPT];
-  float4 bias[IPT];
-  float dc_run[IPT];
-  // internal state of the step whose backward operation comes next, and its input state
-  float st_gate[IPT][4], st_c[IPT], st_h[IPT], st_cprev[IPT], st_hprev[IPT];
-#pragma unroll
-  for (int q = 0; q < IPT; ++q) {
-    const int item = (int)threadIdx.x + q * 512;
-    const int tile = item >> 6, il = item & 63;
-    const int rt = tile / NBT, bt = tile % NBT;
-    const int b = (ct0 + bt) * 16 + (il & 15), u = rank * UW + rt * 4 + (il >> 4);
-    mine[q] = item < ITEMS && b >= b_lo && b < b_hi;
-    ib[q] = b;
-    iu[q] = u;
-    icellF[q] = tile * 4 * 64 + il;
-    // dh of unit u: row u % 16 of tile u / 16 of the dh GEMM, i.e. lane (u%16/4)*16 + b%16, register u%4
-    icellB[q] = (((u / 16 - nt0) * NBT + bt) * 4 + (u & 3)) * 64 + ((u & 15) >> 2) * 16 + (il & 15);
-    bias[q] = float4{0.f, 0.f, 0.f, 0.f};
-    dc_run[q] = 0.0f;
-    if (mine[q]) {
-      bias[q] = *reinterpret_cast<const float4*>(p.bp + 4 * u);
-      dc_run[q] = p.dc[(size_t)b * p.H + u];
-    }
-  }
-  // operands of a forward operation, requested a step ahead: raw x values, h fragments, c_{s-1}, h_{s-1}
-  RawAct<VEC> xraw[FWD ? NSXW : 1][NBT];
-  typename M::Frag hfr[FWD ? NSWF : 1][NBT];
-  float pf_cprev[IPT], pf_hprev[IPT];
-  float pf_gate[FWD ? 1 : IPT][4], pf_c[FWD ? 1 : IPT], pf_h[FWD ? 1 : IPT];   // FWD = false: the stored state, a step ahead
-  const bool want_h = p.dy_is_h || p.y_out != nullptr;
-  auto fetch_fwd = [&](int j) {
-    if (!FWD) {
-      const float* stp = p.state[j];
-      const float* src = p.src[j];
-#pragma unroll
-      for (int q = 0; q < IPT; ++q) {
-        pf_cprev[q] = pf_hprev[q] = 0.0f;
-        pf_c[FWD ? 0 : q] = pf_h[FWD ? 0 : q] = 0.0f;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) pf_gate[FWD ? 0 : q][r] = 0.0f;
-        if (mine[q]) {
-          const size_t e = (size_t)ib[q] * p.H + iu[q];
-          pf_gate[FWD ? 0 : q][0] = stp[p.unit + e];
-          pf_gate[FWD ? 0 : q][1] = stp[p.unit + plane + e];
-          pf_gate[FWD ? 0 : q][2] = stp[2 * p.unit + e];
-          if (CELL == 0) pf_gate[FWD ? 0 : q][3] = stp[2 * p.unit + plane + e];   // the GRU has three gates
-          pf_c[FWD ? 0 : q] = stp[hhalf + e];                                     // c_s, or the GRU's n_h
-          if (want_h) pf_h[FWD ? 0 : q] = HPlane<T>::load(stp, ib[q], iu[q], nsh, p.H, hhalf);
-          // what the pointwise step blends with: c_{s-1}, or the GRU's h_{s-1} in full precision
-          pf_cprev[q] = CELL ? HPlane<T>::load(src, ib[q], iu[q], nsh, p.H, hhalf) : src[hhalf + e];
-          pf_hprev[q] = (float)HPlane<T>::as_operand(src, ib[q], iu[q], nsh, p.H, hhalf);
-        }
-      }
-      return;
-    }
-    const int s = p.s_hi - j;
-    const float* x_s = p.x + (size_t)(s - 1) * p.B * p.I;
-    const float* src = p.src[j];
-#pragma unroll
-    for (int k = 0; k < NSWF; ++k) {
-      const int ms = fk + KSF * k;
-#pragma unroll
-      for (int bt = 0; bt < NBT; ++bt) {
-        const int tile = min(ct0 + bt, nbt_all - 1);
-        if (ms < nsx) {
-          if (k < NSXW) xraw[(FWD && k < NSXW) ? k : 0][bt] = load_raw_whole<VEC>(x_s + (size_t)min(tile * 16 + lrow, p.B - 1) * p.I,
-                                                                                  ms * KSTEP + VEC * lq, p.I);
-        } else {
-          hfr[FWD ? k : 0][bt] = M::load(reinterpret_cast<const T*>(src) + (((size_t)tile * nsh + (ms - nsx)) * 64 + lane) * VEC);
-        }
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < IPT; ++q) {
-      pf_cprev[q] = pf_hprev[q] = 0.0f;
-      if (mine[q]) {
-        pf_cprev[q] = src[hhalf + (size_t)ib[q] * p.H + iu[q]];
-        pf_hprev[q] = (float)HPlane<T>::as_operand(src, ib[q], iu[q], nsh, p.H, hhalf);
-      }
-    }
-  };
-  // The forward operation of step s_hi - j comes in two parts, so that the memory operations
-  // between them overlap with neither's waits.  (Loads and stores share one in-order counter: once
-  // both kinds are in flight, a wait for any load is a wait for everything, store acknowledgements
-  // included.)  Part one runs right after an arrival, when nothing is outstanding: the GEMM slice
-  // from the fetched operands, then the request for the operands of the step after.  Part two, after
-  // the stores that only later launches read have been issued, reduces the slices and applies the
-  // gate functions; it leaves the internal state in st_*.
-  auto forward_gemm = [&](int j) {
-#pragma unroll
-    for (int q = 0; q < IPT; ++q) {
-      st_cprev[q] = pf_cprev[q];
-      st_hprev[q] = pf_hprev[q];
-      if (!FWD) {   // nothing to compute: the fetched state becomes the current one
-#pragma unroll
-        for (int r = 0; r < 4; ++r) st_gate[q][r] = pf_gate[FWD ? 0 : q][r];
-        st_c[q] = pf_c[FWD ? 0 : q];
-        st_h[q] = pf_h[FWD ? 0 : q];
-      }
-    }
-    if (FWD) {
-      f32x4 acc[NRTW][NBT];
-#pragma unroll
-      for (int i = 0; i < NRTW; ++i)
-#pragma unroll
-        for (int bt = 0; bt < NBT; ++bt) acc[i][bt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int k = 0; k < NSWF; ++k) {
-        const int ms = fk + KSF * k;
-#pragma unroll
-        for (int bt = 0; bt < NBT; ++bt) {
-          const typename M::Frag bfr = (k < NSXW && ms < nsx) ? M::from_f32(xraw[(FWD && k < NSXW) ? k : 0][bt].v) : hfr[FWD ? k : 0][bt];
-#pragma unroll
-          for (int i = 0; i < NRTW; ++i) acc[i][bt] = M::mma(wf[FWD ? i : 0][FWD ? k : 0], bfr, acc[i][bt]);
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < NRTW; ++i) {
-        const int rt = fg * NRTW + i;
-        if (rt < NRT) {
-#pragma unroll
-          for (int bt = 0; bt < NBT; ++bt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) redF[((fk * NTF + rt * NBT + bt) * 4 + r) * 64 + lane] = acc[i][bt][r];
-        }
-      }
-    }
-    if (j + 1 < p.count) fetch_fwd(j + 1);
-  };
-  auto forward_point = [&]() {
-    if (!FWD) return;
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < IPT; ++q) {
-      if (!mine[q]) continue;
-      float G[4] = {0.f, 0.f, 0.f, 0.f};
-      for (int w = 0; w < KSF; ++w)   // fixed order, as in forward_body
-#pragma unroll
-        for (int r = 0; r < 4; ++r) G[r] += redF[w * NTF * 4 * 64 + icellF[q] + r * 64];
-      float second;
-      st_h[q] = cell_forward<0>(G, bias[q], st_cprev[q], second, st_gate[q]);
-      st_c[q] = second;
-    }
-  };
-
-  fetch_fwd(0);
-  forward_gemm(0);   // also requests the operands of the step after
-  forward_point();
-
-  for (int j = 0; j < p.count; ++j) {
-    const int s = p.s_hi - j;                       // the step back-propagated now
-    const int slot = (s - 1) % p.CH, buf = ((s - 1) / p.CH) & 1;   // where step s lives in the chunk buffers
-    const size_t dG_step = (size_t)p.BP * p.G4;     // elements of one step's dG block
-    const T* dG_next = (j == 0) ? reinterpret_cast<const T*>(p.dG_next)   // step s + 1: maybe in the other buffer
-                                : reinterpret_cast<const T*>(p.dG_chunk[(s / p.CH) & 1]) + (size_t)(s % p.CH) * dG_step;
-    if (j > 0) {
-      // all 32 workgroups of this XCD have published their columns of dG of step s + 1?
-      if (threadIdx.x == 0) {
-        const unsigned target = p.base + (unsigned)j * RES_MEMBERS;
-        int ok = 1, polls = 0;
-        long long t0 = 0;
-        while ((int)(__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - target) < 0) {
-          if (p.wait_ticks == 0 || (++polls & 15) == 0) {   // a bound of 0: one look only
-            const long long now = wall_clock64();
-            if (t0 == 0) t0 = now;
-            if (now - t0 >= p.wait_ticks ||
-                __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) {
-              __hip_atomic_store(status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              ok = 0;
-              break;
-            }
-          }
-        }
-        s_go = ok;
-      }
-      __syncthreads();
-      if (!s_go) return;
-    }
-    // dh = dG_{s+1} W_hh for this workgroup's units
-    if (dG_next != nullptr) {
-      if (bwd_wave) {
-        f32x4 acc[NTB][NBT];
-#pragma unroll
-        for (int tb = 0; tb < NTB; ++tb)
-#pragma unroll
-          for (int bt = 0; bt < NBT; ++bt) acc[tb][bt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        // The dG fragments come in rounds of GK macro steps: all fetches of a round go out before its
-        // first MFMA (left to itself the scheduler pairs each fetch with the MFMA that needs it, one
-        // L2 round trip after the other).  Two batch tiles beside resident forward weights leave
-        // registers for half the fragments at a time only.
-        constexpr int GK = (FWD && NBT > 1) ? NSWB / 2 : NSWB;
-#pragma unroll
-        for (int k0 = 0; k0 < NSWB; k0 += GK) {
-          typename M::Frag gfr[GK][NBT];
-#pragma unroll
-          for (int k = 0; k < GK; ++k)
-#pragma unroll
-            for (int bt = 0; bt < NBT; ++bt) {
-              const size_t fo = (((size_t)min(ct0 + bt, nbt_all - 1) * nstepsB + wave + KSB * (k0 + k)) * 64 + lane) * VEC;
-              gfr[k][bt] = load_frag_l2(dG_next, (unsigned)(fo * sizeof(T)));
-            }
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int k = 0; k < GK; ++k)
-#pragma unroll
-            for (int tb = 0; tb < NTB; ++tb)
-#pragma unroll
-              for (int bt = 0; bt < NBT; ++bt) acc[tb][bt] = M::mma(wb[tb][k0 + k], gfr[k][bt], acc[tb][bt]);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int tb = 0; tb < NTB; ++tb)
-#pragma unroll
-          for (int bt = 0; bt < NBT; ++bt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) redB[((wave * NTBT + tb * NBT + bt) * 4 + r) * 64 + lane] = acc[tb][bt][r];
-      }
-      __syncthreads();
-    }
-    // pointwise backward of step s on the internal state held in registers
-    const bool publish = j + 1 < p.count;
-    T* dG_cur = reinterpret_cast<T*>(p.dG_chunk[buf]) + (size_t)slot * dG_step;
-    const int ncs = p.KC / KSTEP, col0 = slot * p.B;
-    T gq[IPT][4];
-    float keep_h[IPT], keep_hprev[IPT];
-#pragma unroll
-    for (int q = 0; q < IPT; ++q) {
-      if (!mine[q]) continue;
-      const int b = ib[q], n = iu[q];
-      const size_t e = (size_t)b * p.H + n;
-      float dh = 0.0f;
-      if (dG_next != nullptr)
-        for (int w = 0; w < KSB; ++w) dh += redB[w * NTBT * 4 * 64 + icellB[q]];   // fixed order, as in backward_body
-      float dyv = 0.0f;
-      if (p.dy_is_h)
-        dyv = st_h[q];
-      else if (p.dy != nullptr && s >= p.dy_first)
-        dyv = p.dy[(size_t)(s - p.dy_first) * plane + e];
-      dh += dyv;
-      float dG[4], dc_out;
-      if (CELL == 0)
-        lstm_backward_point(dh, dc_run[q], st_gate[q][0], st_gate[q][1], st_gate[q][2], st_gate[q][3], st_c[q], st_cprev[q],
-                            dG, dc_out);
-      else   // the running plane carries dh_{s+1} * z_{s+1}, as in backward_body
-        gru_backward_point(__fadd_rn(dh, dc_run[q]), st_gate[q][0], st_gate[q][1], st_gate[q][2], st_c[q], st_cprev[q], dG, dc_out);
-      dc_run[q] = dc_out;
-      // the four gates of a unit are consecutive in dG: one 8-byte store (what other compute units
-      // fetch next must not be written in pieces smaller than a dword)
-      union { T t[4]; unsigned long long v; } pk;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) pk.t[r] = gq[q][r] = (T)dG[r];
-      *reinterpret_cast<unsigned long long*>(dG_cur + ft_offset<T>(b, 4 * n, nstepsB)) = pk.v;
-      keep_h[q] = st_h[q];
-      keep_hprev[q] = st_hprev[q];
-    }
-    if (publish) {
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's columns of dG have reached the L2
-      __syncthreads();
-      if (threadIdx.x == 0) __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      forward_gemm(j + 1);
-    }
-    // What only later launches read -- the transposed copies for the weight gradient, the output --
-    // is stored after the arrival: nobody in this launch waits for it.
-#pragma unroll
-    for (int q = 0; q < IPT; ++q) {
-      if (!mine[q]) continue;
-      const int b = ib[q], n = iu[q];
-      const int col = col0 + b;
-      T* dGT = reinterpret_cast<T*>(p.dGT[buf]);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) dGT[ft_offset<T>(4 * n + r, col, ncs)] = gq[q][r];
-      reinterpret_cast<T*>(p.aT[buf])[ft_offset<T>(p.NX + n, col, ncs)] = (T)keep_hprev[q];
-      if (p.y_out) p.y_out[(size_t)(s - 1) * plane + (size_t)b * p.H + n] = keep_h[q];
-    }
-    // the pointwise part of the next lower step's forward operation runs while the others arrive
-    if (publish) forward_point();
-  }
-#pragma unroll
-  for (int q = 0; q < IPT; ++q)
-    if (mine[q]) p.dc[(size_t)ib[q] * p.H + iu[q]] = dc_run[q];
-}
-
-struct SweepConfig {
-  int nrt, nswf, ksf, nswb, ksb, nbt, nsxw;
-};
-static const SweepConfig SWEEP_CONFIGS[] = {
-    {4, 5, 4, 8, 8, 1, 1}, {4, 5, 4, 8, 8, 2, 1},   // H = 512, I <= 128
-    {2, 4, 4, 4, 8, 1, 2}, {2, 4, 4, 4, 8, 2, 2},   // H = 256, 128 < I <= 256
-    {1, 2, 4, 4, 4, 1, 1}, {1, 2, 4, 4, 4, 2, 1},   // H = 128, I <= 128
-    {8, 5, 8, 16, 8, 1, 1},                         // H = 1024, any I: backward operations only (W_hh^T fits, both do not)
-};
-constexpr int SWEEP_BACKWARD_ONLY_FROM = 6;   // configurations from this index on have no forward part
-
-// backward_only: for a launch of backward operations on stored internal states, which never reads x
-// or the gate weights -- only the backward part of a configuration has to fit the shape.
-static int sweep_config(const Dims& d, int* nb_out = nullptr, bool backward_only = false) {
-  if (!d.dtype || d.H % 128 != 0 || d.KH != d.H || d.HP != d.H) return -1;   // either cell; can_run_sweep() narrows
-  const int nstepsF = d.KP / 32, nstepsB = d.G4 / 32;
-  const FwdConfig fc = forward_config<__bf16>(d);
-  const int ksf = (fc == FWD_TINY || fc == FWD_SMALLK) ? 4 : 8;
-  const int ksb = backward_config<__bf16>(d) == BWD_SMALLK ? 4 : 8;
-  if (nstepsB % ksb != 0) return -1;
-  for (int cand = 0; cand < 2; ++cand) {
-    const int nb = group_share(d, cand), nbt = group_tiles(d, nb);
-    for (size_t i = 0; i < sizeof SWEEP_CONFIGS / sizeof SWEEP_CONFIGS[0]; ++i) {
-      const SweepConfig& c = SWEEP_CONFIGS[i];
-      if (c.nrt != d.H / 128 || c.ksb != ksb || c.nswb != nstepsB / ksb || c.nbt != nbt) continue;
-      // the forward part fixes the width of x as well
-      if (backward_only || (int)i >= SWEEP_BACKWARD_ONLY_FROM ||
-          (d.I % 8 == 0 && nstepsF % ksf == 0 && c.ksf == ksf && c.nswf == nstepsF / ksf &&
-           c.nsxw == (d.KX / 32 + ksf - 1) / ksf)) {
-        if (nb_out) *nb_out = nb;
-        return (int)i;
-      }
-    }
-  }
-  return -1;
-}
-
-bool can_run_sweep(const Dims& d) {   // with forward operations: LSTM only
-  const int c = sweep_config(d);
-  return d.cell == 0 && c >= 0 && c < SWEEP_BACKWARD_ONLY_FROM;
-}
-bool can_run_backward_sweep(const Dims& d) { return sweep_config(d, nullptr, true) >= 0; }
-int sweep_max_steps() { return SWEEP_MAX_STEPS; }
-
-template <bool FWD, int NRT, int NSWF, int KSF, int NSWB, int KSB, int NBT, int NSXW, int CELL = 0>
-static hipError_t launch_sweep_cfg(const SweepParams& p, hipStream_t st) {
-  constexpr int NTB = (NRT * 4 + 15) / 16;
-  const size_t lds = ((size_t)KSF * NRT * NBT + (size_t)KSB * NTB * NBT) * 4 * 64 * sizeof(float);
-  static bool configured = false;
-  if (!configured) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(sweep_kernel<FWD, NRT, NSWF, KSF, NSWB, KSB, NBT, NSXW, CELL>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    configured = true;
-  }
-  sweep_kernel<FWD, NRT, NSWF, KSF, NSWB, KSB, NBT, NSXW, CELL><<<dim3(RES_WGS), dim3(512), lds, st>>>(p);
-  return hipGetLastError();
-}
-
-hipError_t launch_sweep(const Dims& d, const SweepArgs& a, hipStream_t st) {
-  int nb = 0;
-  const int cfg = sweep_config(d, &nb, a.state != nullptr);
-  if (cfg < 0 || a.count < 1 || a.count > SWEEP_MAX_STEPS) return hipErrorInvalidValue;
-  if ((a.s_hi - 1) / d.CH - (a.s_hi - a.count) / d.CH > 1) return hipErrorInvalidValue;   // two chunk buffers
-  SweepParams p{};
-  p.Wp = a.Wp;
-  p.WTh = a.WTh;
-  p.bp = a.bp;
-  p.x = a.x;
-  p.dy = a.dy;
-  p.dy_first = a.dy_first;
-  p.dy_is_h = a.dy_is_h;
-  p.dc = a.dc;
-  p.y_out = a.y_out;
-  p.dG_next = a.dG_next;
-  for (int i = 0; i < 2; ++i) {
-    p.dG_chunk[i] = a.dG_chunk[i];
-    p.dGT[i] = a.dGT[i];
-    p.aT[i] = a.aT[i];
-  }
-  p.sync = a.sync;
-  p.base = a.base;
-  p.wait_ticks = g_wait_ticks;
-  p.launch = a.launch;
-  p.s_hi = a.s_hi;
-  p.count = a.count;
-  p.B = d.B;
-  p.I = d.I;
-  p.H = d.H;
-  p.KX = d.KX;
-  p.KH = d.KH;
-  p.BP = d.BP;
-  p.nb = nb;
-  p.G4 = d.G4;
-  p.NX = d.NX;
-  p.KC = d.KC;
-  p.CH = d.CH;
-  p.unit = d.unit;
-  for (int j = 0; j < a.count; ++j) {
-    p.src[j] = a.src[j];
-    p.state[j] = a.state ? a.state[j] : nullptr;
-  }
-  if (a.state) {   // backward operations through stored internal states
-    if (d.cell)
-      switch (cfg) {
-        case 0: return launch_sweep_cfg<false, 4, 5, 4, 8, 8, 1, 1, 1>(p, st);
-        case 1: return launch_sweep_cfg<false, 4, 5, 4, 8, 8, 2, 1, 1>(p, st);
-        case 2: return launch_sweep_cfg<false, 2, 4, 4, 4, 8, 1, 2, 1>(p, st);
-        case 3: return launch_sweep_cfg<false, 2, 4, 4, 4, 8, 2, 2, 1>(p, st);
-        case 4: return launch_sweep_cfg<false, 1, 2, 4, 4, 4, 1, 1, 1>(p, st);
-        case 5: return launch_sweep_cfg<false, 1, 2, 4, 4, 4, 2, 1, 1>(p, st);
-        default: return launch_sweep_cfg<false, 8, 5, 8, 16, 8, 1, 1, 1>(p, st);
-      }
-    switch (cfg) {
-      case 0: return launch_sweep_cfg<false, 4, 5, 4, 8, 8, 1, 1>(p, st);
-      case 1: return launch_sweep_cfg<false, 4, 5, 4, 8, 8, 2, 1>(p, st);
-      case 2: return launch_sweep_cfg<false, 2, 4, 4, 4, 8, 1, 2>(p, st);
-      case 3: return launch_sweep_cfg<false, 2, 4, 4, 4, 8, 2, 2>(p, st);
-      case 4: return launch_sweep_cfg<false, 1, 2, 4, 4, 4, 1, 1>(p, st);
-      case 5: return launch_sweep_cfg<false, 1, 2, 4, 4, 4, 2, 1>(p, st);
-      default: return launch_sweep_cfg<false, 8, 5, 8, 16, 8, 1, 1>(p, st);
-    }
-  }
-  if (d.cell || cfg >= SWEEP_BACKWARD_ONLY_FROM) return hipErrorInvalidValue;
-  switch (cfg) {
-    case 0: return launch_sweep_cfg<true, 4, 5, 4, 8, 8, 1, 1>(p, st);
-    case 1: return launch_sweep_cfg<true, 4, 5, 4, 8, 8, 2, 1>(p, st);
-    case 2: return launch_sweep_cfg<true, 2, 4, 4, 4, 8, 1, 2>(p, st);
-    case 3: return launch_sweep_cfg<true, 2, 4, 4, 4, 8, 2, 2>(p, st);
-    case 4: return launch_sweep_cfg<true, 1, 2, 4, 4, 4, 1, 1>(p, st);
-    case 5: return launch_sweep_cfg<true, 1, 2, 4, 4, 4, 2, 1>(p, st);
-    default: return hipErrorInvalidValue;
-  }
 }
 
 // ---- data-gradient GEMM: out[row][n] = sum_k dG[row][k] * WT[n][k] ---------------------------
