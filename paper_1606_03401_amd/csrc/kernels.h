@@ -53,7 +53,8 @@ inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
 
 Dims make_dims(int B, int I, int H, int dtype, int cell);
 
-hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st);
+// Zeroes p, and fills `empty` with 0xff (what the exchange rings of resident launches start from); sizes multiples of 16.
+hipError_t launch_fill(void* p, size_t bytes, void* empty, size_t empty_bytes, hipStream_t st);
 hipError_t launch_prep_weights(const Dims& d, const float* W_ih, const float* W_hh, const float* b, void* Wp,
                                float* bp, void* WTh, void* WTx, hipStream_t st);
 // dst unit <- (h0, c0), NULL meaning zeros.
@@ -109,9 +110,10 @@ hipError_t launch_backward_forward_pair(const Dims& d, const BackwardArgs& a, co
 // chip (shapes for which can_run_forward_chain() holds).  Step j (0-based) of the chain consumes
 // x_first + j*B*I; its state goes to steps[j].out and its gates to the two units at
 // steps[j].gates where these are not NULL (states nobody asked for never leave the chip).
-// `ring` (forward_chain_ring_bytes) and `sync` (forward_chain_sync_bytes, zero before the first
-// launch of a run) are workspace; `base` is the number of arrivals earlier launches of the run left in
-// the group counters (sum of forward_chain_arrivals over them), `launch` the number of those launches.
+// `ring` (forward_chain_ring_bytes, every byte 0xff before the first chain launch of a run) and `sync`
+// (forward_chain_sync_bytes, zero before the first resident launch of a run) are workspace; `published` is the number
+// of states the run's earlier chain launches exchanged (count each), `launch` the number of its earlier
+// resident launches of any kind.
 // The word at forward_chain_status_offset() inside `sync` is a status word: 0, or non-zero when
 // a launch gave up (an XCD did not receive exactly 32 of the 256 workgroups, or a wait ran into
 // its wall-clock bound); results are then invalid.  Launches that overlap
@@ -130,7 +132,7 @@ size_t forward_chain_sync_bytes();
 size_t forward_chain_status_offset();
 unsigned forward_chain_arrivals(int steps);
 hipError_t launch_forward_chain(const Dims& d, const void* Wp, const float* bp, const float* x_first, const float* src_unit,
-                                const ChainStep* steps, int count, void* ring, unsigned* sync, unsigned base,
+                                const ChainStep* steps, int count, void* ring, unsigned* sync, unsigned published,
                                 unsigned launch, hipStream_t st);
 
 // A run of (forward operation keeping the internal state, backward operation) pairs for steps

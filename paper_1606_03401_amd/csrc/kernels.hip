@@ -53,18 +53,23 @@ Dims make_dims(int B, int I, int H, int dtype, int cell) {
 
 // ---- small utility kernels -------------------------------------------------------------------
 
-__global__ void fill_zero_kernel(uint4* p, size_t n16) {
+__global__ void fill_kernel(uint4* p, size_t n16, uint4* empty, size_t ne16) {
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (; i < n16; i += stride) p[i] = uint4{0, 0, 0, 0};
+  for (; i < n16 + ne16; i += stride) {
+    if (i < n16)
+      p[i] = uint4{0, 0, 0, 0};
+    else
+      empty[i - n16] = uint4{~0u, ~0u, ~0u, ~0u};
+  }
 }
 
-hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st) {
-  if (bytes == 0) return hipSuccess;
-  size_t n16 = bytes / 16;   // callers keep every buffer a multiple of 16 bytes
-  size_t blocks = (n16 + 255) / 256;
+hipError_t launch_fill(void* p, size_t bytes, void* empty, size_t empty_bytes, hipStream_t st) {
+  const size_t n16 = bytes / 16, ne16 = empty_bytes / 16;   // callers keep every buffer a multiple of 16 bytes
+  if (n16 + ne16 == 0) return hipSuccess;
+  size_t blocks = (n16 + ne16 + 255) / 256;
   if (blocks > 4096) blocks = 4096;
-  fill_zero_kernel<<<dim3((unsigned)blocks), dim3(256), 0, st>>>(reinterpret_cast<uint4*>(p), n16);
+  fill_kernel<<<dim3((unsigned)blocks), dim3(256), 0, st>>>(reinterpret_cast<uint4*>(p), n16, reinterpret_cast<uint4*>(empty), ne16);
   return hipGetLastError();
 }
 

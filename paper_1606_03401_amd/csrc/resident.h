@@ -1,0 +1,451 @@
+// Shared parts of the resident launches (forward chains and sweeps): placement of the workgroups, the
+// exchange through an XCD's L2, and the kernel of the forward chain.  Not part of the ABI.
+#pragma once
+
+#include "device.h"
+
+namespace mebptt {
+
+// ---- where a resident workgroup runs ---------------------------------------------------------------
+// The batch is split over the 8 XCDs, each with its own L2: XCD g takes the sequences [g*nb, (g+1)*nb)
+// and never needs anything from another XCD.  Inside an XCD the 32 workgroups (one per compute unit)
+// split the hidden units.  Which XCD a workgroup runs on is read from the hardware (register XCC_ID),
+// not inferred from its id: workgroups are dealt round-robin to the XCDs, but where the deal starts
+// depends on the launches before.  A workgroup takes the next free rank of its XCD from a counter; the
+// launch relies on every XCD receiving exactly 32 of the 256 workgroups, checks it (a rank counter that
+// runs past 32 raises the status word; an XCD that gets fewer never completes its first wait, which is
+// bounded by a wall-clock limit like every other) and gives up rather than compute on an assumption
+// that does not hold.
+constexpr int RES_WGS = 256, RES_GROUPS = 8, RES_MEMBERS = RES_WGS / RES_GROUPS;
+constexpr int RES_RING = 4;   // exchange slots
+// sync words: arrival counter of XCD g at [g * 64], rank counter at [512 + g * 64], status at [1024]
+constexpr int RES_SYNC_RANK = 512, RES_SYNC_STATUS = 1024;
+
+__device__ inline unsigned xcc_id() {
+  unsigned v;
+  asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(v));
+  return v & 0xf;
+}
+
+// One thread of a workgroup: draws the workgroup's rank on its XCD.  False: the workgroups were not
+// dealt 32 per XCD (the status word says so).
+__device__ inline bool draw_rank(unsigned* sync, unsigned launch, int& g, int& rank) {
+  const unsigned xcc = xcc_id();
+  bool ok = xcc < (unsigned)RES_GROUPS;
+  unsigned ticket = 0;
+  if (ok) {
+    ticket = __hip_atomic_fetch_add(sync + RES_SYNC_RANK + xcc * 64, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    ok = ticket / RES_MEMBERS == launch;   // more than 32 workgroups on this XCD: ranks would collide
+  }
+  if (!ok) __hip_atomic_store(sync + RES_SYNC_STATUS, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  g = ok ? (int)xcc : 0;
+  rank = (int)(ticket % RES_MEMBERS);
+  return ok;
+}
+
+// ---- the exchange ------------------------------------------------------------------------------------
+// What a step publishes goes into one of RES_RING slots that hold the consumer's operand layout.  There
+// is no counter: a slot starts out filled with the bit pattern EMPTY, and a wave that needs operand
+// fragments fetches them until none of the dwords it got is EMPTY.  (A bf16 pair or an fp32 value of
+// that pattern is a NaN with all payload bits set; a producer publishes it as the NaN next to it.)  A
+// step thus costs one store and one load through the L2 the XCD's compute units share, where a counter
+// costs the store, its acknowledgement, a barrier, an atomic, a load of the counter, a barrier and the
+// fetch one after the other.  A wave waits for the producers of its own part of K only.
+//
+// Slots are recycled in order: step q goes to slot q mod 4.  Whoever publishes step q has fetched all
+// of step q - 1, whose producers had fetched all of step q - 2: nobody reads q - 2 any more, and the
+// publisher resets its own part of that slot to EMPTY right after publishing q.  The next use of the slot
+// is step q + 2; a reader polls it only after it has seen the publisher's q + 1, which the publisher
+// stores after it waited for loads issued behind the reset (memory operations of a wave complete in
+// order), so the reset is visible before anyone can look.  Step numbers run on from launch to launch
+// of a run, so the slots a launch starts with are the ones the launch before left reset.
+constexpr unsigned RES_EMPTY = 0xffffffffu;
+
+typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
+
+// A wave's 16 bytes per lane of an exchange slot: past the compute unit's vector cache (sc1), from the
+// XCD's L2.  byte_off at or above 2^31 lies outside the buffer: such a lane gets zeros and moves no data.
+constexpr unsigned RES_NO_LANE = 0x80000000u;
+__device__ inline u32x4 load_slot_16(const void* slot, unsigned byte_off, int uniform_off) {
+  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(slot), 0, 0x7fffffff, 0x00020000);
+  return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)byte_off, uniform_off, 16 /* sc1: agent scope */);
+}
+__device__ inline unsigned largest_dword(u32x4 v) { return max(max(v.x, v.y), max(v.z, v.w)); }
+__device__ inline unsigned not_empty(unsigned v) { return min(v, RES_EMPTY - 1u); }   // for a value about to be published
+
+// The bound of a wait: true when it is time to give up (the status word is then non-zero).
+struct WaitBound {
+  long long ticks;      // of the 100 MHz wall clock; 0: give up after one look
+  unsigned* status;
+  int polls = 0;
+  long long t0 = 0;
+  __device__ bool expired() {
+    if (ticks != 0 && (++polls & 15) != 0) return false;
+    const long long now = wall_clock64();
+    if (t0 == 0) t0 = now;
+    if (now - t0 < ticks && __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) return false;
+    __hip_atomic_store(status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return true;
+  }
+};
+
+// A barrier that orders LDS only: stores to memory stay in flight across it.
+__device__ inline void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+template <class F>
+__device__ inline F as_frag(u32x4 v) {
+  union { u32x4 u; F f; } cv;
+  cv.u = v;
+  return cv.f;
+}
+
+// Fragments of fp32 rows of any length.  A lane's VEC values start at k; where they would run over the end
+// of the row (`limit` values, at least VEC) the VEC last values of the row are fetched instead, and
+// shift_tail puts them where they belong when they are used: fetching has no branches (loads under
+// branches make the compiler wait for everything outstanding), and needs only a float's alignment.
+template <int VEC>
+__device__ inline RawAct<VEC> load_window(const float* __restrict__ base, unsigned row, int k, int limit) {
+  typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+  RawAct<VEC> r;
+  const unsigned off = row + (unsigned)min(k, limit - VEC);
+#pragma unroll
+  for (int e = 0; e < VEC; e += 4) {
+    const f4u q = *reinterpret_cast<const f4u*>(base + (size_t)off + e);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r.v[e + i] = q[i];
+  }
+  return r;
+}
+template <int VEC>
+__device__ inline void shift_tail(RawAct<VEC>& r, int k, int limit) {
+  const int d = k + VEC - limit;   // how far the window was moved back: <= 0 not at all, >= VEC all of it lies outside
+#pragma unroll
+  for (int bit = 1; bit < VEC; bit *= 2)
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+      const float from = e + bit < VEC ? r.v[e + bit] : 0.0f;
+      r.v[e] = (d > 0 && (d & bit)) ? from : r.v[e];
+    }
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) r.v[e] = d >= VEC ? 0.0f : r.v[e];
+}
+
+// ---- forward chain -------------------------------------------------------------------------------------
+struct ResStep {
+  float* out;     // unit that receives (h, c) of this step, or NULL
+  float* gates;   // two units that receive (i, f), (g, o), or NULL
+};
+constexpr int RES_MAX_STEPS = 192;  // steps of one launch: their destinations travel as kernel arguments (3 KiB of the 4 KiB there are)
+struct ResParams {
+  const void* Wp;
+  const float* bp;
+  const float* x0;     // x of the first step of this launch
+  const float* src;    // unit holding the input state of the first step
+  void* ring;          // RES_RING slots [BP][KH] of GEMM operands, fragment-tiled
+  unsigned* sync;
+  unsigned published;  // states published by this run's chain launches before this one
+  unsigned launch;     // resident launches of this run before this one (every rank counter stands at 32 * launch)
+  long long wait_ticks;   // bound of every wait, in ticks of the 100 MHz wall clock
+  int count;
+  int B, I, H, HP, KX, KH, BP, nb;
+  size_t unit, hplane; // floats per unit, floats of its h part
+  ResStep step[RES_MAX_STEPS];
+};
+
+// Consecutive forward operations (Algorithm 2's forward loop; also the single-step pushes that
+// follow each other when memory is plentiful) depend on each other only through h, so a chain of
+// them can run inside ONE launch if the gate weights stay on the chip and only h travels.
+// Workgroup `rank` of an XCD owns the NRT * 4 units from rank * NRT * 4 on and keeps their packed weight
+// rows in registers (and a part in LDS) for the whole launch.  Its 8 waves split K KS ways; where
+// KS = 4 the two halves of the workgroup take a batch tile each, or half of the row tiles.  The input
+// state of the first step is published like any other, so all steps are alike:
+//   1. the x part of the gate GEMM (fetched a step ahead), which needs nothing from other workgroups;
+//   2. fetch h_{s-1} of the XCD's sequences from the exchange slot until all of it is there;
+//   3. store what the step before has to keep, and fetch the next x: issued here they complete behind
+//      the MFMAs.  Memory operations complete in order, so anything issued in front of the polls
+//      would hold them up;
+//   4. the h part of the GEMM, partial sums through LDS, the pointwise step (c, or the GRU's h, stays in a
+//      register), publish h_s.
+// What bounds a step is this chain of latencies, not bytes or flops: no weight moves.
+// Sums are formed exactly as forward_body forms them (KS partial sums over the macro steps
+// w, w+KS, ..., added in the order 0..KS-1), so a step gives the same bits either way.  A wave whose part of
+// x or h is shorter than the others' runs its surplus macro steps on zeros.
+// NXW, NHW: macro steps of x and of h per wave; the weights of the last NXL of x are parked in LDS (they are
+// read while the wave would wait anyway); NBT: batch tiles of the XCD's share.
+template <class T, int NRT, int NXW, int NXL, int NHW, int KS, int NBT, int CELL>
+__global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
+  using M = Mma<T>;
+  constexpr int VEC = M::VEC, KSTEP = 4 * VEC, FRAG = 64 * VEC;
+  constexpr int GROUPS = 8 / KS, FTB = (GROUPS == 2 && NBT == 2) ? 2 : 1, FTR = GROUPS / FTB;
+  constexpr int NRTW = (NRT + FTR - 1) / FTR, BTW = NBT / FTB;   // row and batch tiles of one wave
+  constexpr int NT = NRT * NBT, NXR = NXW - NXL;
+  constexpr int UW = NRT * 4, ITEMS = NT * 64, IPT = (ITEMS + 511) / 512;
+  constexpr bool SPLIT = HPlane<T>::SPLIT;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  f32x4* red = reinterpret_cast<f32x4*>(smem);                                     // [KS][NT][64]
+  T* wl = reinterpret_cast<T*>(smem + (size_t)KS * NT * 64 * sizeof(f32x4));       // [8][NRTW][NXL] fragments
+  __shared__ int s_go, s_g, s_rank, s_fail;
+  // the wave index as a scalar: conditions on it become scalar branches (an MFMA under a lane mask
+  // that is empty would still execute)
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  const int lrow = lane & 15, lq = lane >> 4;
+  if (threadIdx.x == 0) {
+    int xg, xr;
+    s_go = draw_rank(p.sync, p.launch, xg, xr);
+    s_g = xg;
+    s_rank = xr;
+    s_fail = 0;
+  }
+  __syncthreads();
+  if (!s_go) return;
+  const int g = __builtin_amdgcn_readfirstlane(s_g), rank = __builtin_amdgcn_readfirstlane(s_rank);
+  const int b_lo = g * p.nb, b_hi = min(p.B, b_lo + p.nb);
+  if (b_lo >= p.B || rank * UW >= p.KH) return;   // no sequences or no units here: nobody waits for this workgroup
+  const int nsx = p.KX / KSTEP, nsh = p.KH / KSTEP, nsteps = nsx + nsh;
+  const size_t hhalf = (size_t)p.BP * p.KH;
+  const int nbt_all = p.BP / 16, ct0 = b_lo / 16;
+  const int ks = wave % KS, grp = wave / KS;
+  const int rt0 = (FTR > 1 ? grp : 0) * NRTW, bt0 = (FTB > 1 ? grp : 0) * BTW;
+  const int ngroups = p.HP / 4;                    // 16-row tiles of the packed weights
+  const int mh0 = (ks + KS - nsx % KS) % KS;       // this wave's h macro steps: mh0, mh0 + KS, ... (below nsh)
+
+  // Pointwise items of this thread: item = (output tile, lane of the MFMA layout), i.e. the
+  // (sequence, unit) whose four gate sums that lane holds, so that the partial sums are read back
+  // from LDS at consecutive addresses by consecutive threads.  c stays in registers.  A unit between
+  // H and the padded KH has no weights: its h is zero, and is published as such.
+  bool mine[IPT], real[IPT];
+  unsigned ie[IPT], io[IPT];   // b * H + u; the element's place in a fragment-tiled plane
+  float4 bias[IPT];
+  float c_state[IPT], keep_h[IPT], keep_second[IPT], keep_gate[IPT][4];
+#pragma unroll
+  for (int q = 0; q < IPT; ++q) {
+    const int item = (int)threadIdx.x + q * 512;
+    const int tile = item >> 6, il = item & 63;          // tile = rt * NBT + bt
+    const int rt = tile / NBT, bt = tile % NBT;
+    const int b = (ct0 + bt) * 16 + (il & 15), u = rank * UW + rt * 4 + (il >> 4);
+    mine[q] = item < ITEMS && b >= b_lo && b < b_hi && u < p.KH;
+    real[q] = u < p.H;
+    ie[q] = (unsigned)(b * p.H + u);
+    io[q] = (unsigned)ft_offset<T>(b, u, nsh);
+    bias[q] = float4{0.f, 0.f, 0.f, 0.f};
+    c_state[q] = keep_h[q] = 0.0f;
+    if (mine[q] && real[q]) {
+      bias[q] = *reinterpret_cast<const float4*>(p.bp + 4 * u);
+      keep_h[q] = HPlane<T>::load(p.src, b, u, p.KH / 32, p.H, hhalf);
+      // the state the pointwise step blends with, kept in this register from step to step:
+      // c_{s-1} (LSTM) or h_{s-1} in full precision (GRU)
+      c_state[q] = CELL ? keep_h[q] : (p.src + p.hplane)[(size_t)ie[q]];
+    }
+  }
+  // publishes keep_h as step number `q_now` and resets this thread's part of the slot two steps back
+  auto publish = [&](unsigned q_now) {
+    unsigned* slot_out = reinterpret_cast<unsigned*>(reinterpret_cast<T*>(p.ring) + (size_t)(q_now % RES_RING) * hhalf);
+    unsigned* slot_old = reinterpret_cast<unsigned*>(reinterpret_cast<T*>(p.ring) + (size_t)((q_now + 2) % RES_RING) * hhalf);
+#pragma unroll
+    for (int q = 0; q < IPT; ++q) {
+      if (!mine[q]) continue;
+      if constexpr (SPLIT) {
+        // Units u and u + 1 of one sequence sit 16 lanes apart in this layout and next to each other
+        // in the slot: the lane of the even unit stores both as one dword.
+        const unsigned hi16 = (__float_as_uint(keep_h[q]) + 0x8000u) >> 16;
+        const unsigned other = __shfl_xor(hi16, 16);
+        if (((threadIdx.x >> 4) & 1) == 0) {
+          slot_out[(size_t)(io[q] >> 1)] = not_empty(hi16 | (other << 16));
+          slot_old[(size_t)(io[q] >> 1)] = RES_EMPTY;
+        }
+      } else {
+        slot_out[(size_t)io[q]] = not_empty(__float_as_uint(keep_h[q]));
+        slot_old[(size_t)io[q]] = RES_EMPTY;
+      }
+    }
+  };
+  publish(p.published);   // travels while the weights are fetched
+
+  // this wave's packed weight rows; the last NXL macro steps of x are parked in LDS (read back by this wave only)
+  typename M::Frag wx[NRTW][NXR > 0 ? NXR : 1], wh[NRTW][NHW];
+#pragma unroll
+  for (int rt = 0; rt < NRTW; ++rt) {
+    const int row_tile = min(rank * NRT + min(rt0 + rt, NRT - 1), ngroups - 1);
+    const T* base = reinterpret_cast<const T*>(p.Wp) + ((size_t)row_tile * nsteps * 64 + lane) * VEC;
+#pragma unroll
+    for (int i = 0; i < NXW; ++i) {
+      const int s = ks + KS * i;
+      typename M::Frag f = M::load(base + (size_t)min(s, nsx - 1) * FRAG);
+      if (s >= nsx) f = typename M::Frag{};
+      if (i < NXR)
+        wx[rt][i < NXR ? i : 0] = f;
+      else
+        *reinterpret_cast<typename M::Frag*>(&wl[((size_t)(wave * NRTW + rt) * NXL + (i - NXR)) * FRAG + lane * VEC]) = f;
+    }
+#pragma unroll
+    for (int i = 0; i < NHW; ++i) {
+      const int m = mh0 + KS * i;
+      wh[rt][i] = M::load(base + (size_t)(nsx + min(m, nsh - 1)) * FRAG);
+      if (m >= nsh) wh[rt][i] = typename M::Frag{};
+    }
+  }
+
+  // where this lane's operands come from: x rows, exchange-slot offsets (fragment 0 of each batch tile).
+  // Columns of a tile that belong to no sequence of this XCD read the first one's x and fetch no h.
+  unsigned xrow[BTW], hoff[BTW];
+#pragma unroll
+  for (int t = 0; t < BTW; ++t) {
+    const int b = (ct0 + bt0 + t) * 16 + lrow;
+    const bool own = b >= b_lo && b < b_hi;
+    xrow[t] = (unsigned)((own ? b : b_lo) * p.I);
+    hoff[t] = own ? (unsigned)((min(ct0 + bt0 + t, nbt_all - 1) * nsh * 64 + lane) * 16) : RES_NO_LANE;
+  }
+  RawAct<VEC> xraw[NXW][BTW];   // x of the step about to run
+  auto fetch_x = [&](int j) {
+    const float* x_j = p.x0 + (size_t)j * p.B * p.I;
+#pragma unroll
+    for (int i = 0; i < NXW; ++i)
+#pragma unroll
+      for (int t = 0; t < BTW; ++t) xraw[i][t] = load_window<VEC>(x_j, xrow[t], (ks + KS * i) * KSTEP + VEC * lq, p.I);
+  };
+  fetch_x(0);
+
+  auto store_kept = [&](int j) {   // what the schedule wants of step j
+    const ResStep dst = p.step[j];
+    if (!dst.out && !dst.gates) return;
+    const unsigned plane = (unsigned)(p.B * p.H);
+#pragma unroll
+    for (int q = 0; q < IPT; ++q) {
+      if (!mine[q]) continue;
+      if (dst.out) {
+        if constexpr (SPLIT) {   // padding columns of a split h plane are part of the operand other launches fetch: zero
+          unsigned short* hi = reinterpret_cast<unsigned short*>(dst.out);
+          const unsigned bits = __float_as_uint(keep_h[q]);
+          hi[(size_t)io[q]] = (unsigned short)((bits + 0x8000u) >> 16);
+          (hi + hhalf)[(size_t)io[q]] = (unsigned short)(bits & 0xffffu);
+        } else if (real[q]) {
+          dst.out[(size_t)ie[q]] = keep_h[q];
+        }
+        if (real[q]) (dst.out + p.hplane)[(size_t)ie[q]] = keep_second[q];
+      }
+      if (dst.gates && real[q]) {
+        dst.gates[(size_t)ie[q]] = keep_gate[q][0];
+        (dst.gates + plane)[(size_t)ie[q]] = keep_gate[q][1];
+        (dst.gates + p.unit)[(size_t)ie[q]] = keep_gate[q][2];
+        if (CELL == 0) (dst.gates + p.unit + plane)[(size_t)ie[q]] = keep_gate[q][3];
+      }
+    }
+  };
+
+  for (int j = 0; j < p.count; ++j) {
+    f32x4 acc[NRTW][BTW];
+#pragma unroll
+    for (int rt = 0; rt < NRTW; ++rt)
+#pragma unroll
+      for (int t = 0; t < BTW; ++t) acc[rt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // the x part (a wave's x macro steps precede its h macro steps, so the order of the additions is
+    // that of forward_body)
+#pragma unroll
+    for (int i = 0; i < NXW; ++i) {
+      const int s = ks + KS * i;
+      if ((s + 1) * KSTEP > p.I) {   // over the end of the row, or a surplus step
+#pragma unroll
+        for (int t = 0; t < BTW; ++t) shift_tail<VEC>(xraw[i][t], s * KSTEP + VEC * lq, p.I);
+      }
+      typename M::Frag xf[BTW];
+#pragma unroll
+      for (int t = 0; t < BTW; ++t) xf[t] = M::from_f32(xraw[i][t].v);
+#pragma unroll
+      for (int rt = 0; rt < NRTW; ++rt) {
+        typename M::Frag a;
+        if (i < NXR)
+          a = wx[rt][i < NXR ? i : 0];
+        else
+          a = M::load(&wl[((size_t)(wave * NRTW + rt) * NXL + (i - NXR)) * FRAG + lane * VEC]);
+#pragma unroll
+        for (int t = 0; t < BTW; ++t) acc[rt][t] = M::mma(a, xf[t], acc[rt][t]);
+      }
+    }
+    // h fragments of the step before
+    typename M::Frag hf[NHW][BTW];
+    {
+      const T* slot = reinterpret_cast<const T*>(p.ring) + (size_t)((p.published + (unsigned)j) % RES_RING) * hhalf;
+      WaitBound bound{p.wait_ticks, p.sync + RES_SYNC_STATUS};
+      while (true) {
+        u32x4 raw[NHW][BTW];
+        unsigned top = 0;
+#pragma unroll
+        for (int i = 0; i < NHW; ++i) {
+          const int m = mh0 + KS * i;
+#pragma unroll
+          for (int t = 0; t < BTW; ++t) raw[i][t] = load_slot_16(slot, m < nsh ? hoff[t] : RES_NO_LANE, m * 1024);
+        }
+#pragma unroll
+        for (int i = 0; i < NHW; ++i)
+#pragma unroll
+          for (int t = 0; t < BTW; ++t) {
+            top = max(top, largest_dword(raw[i][t]));
+            hf[i][t] = as_frag<typename M::Frag>(raw[i][t]);
+          }
+        if (__builtin_amdgcn_ballot_w64(top == RES_EMPTY) == 0) break;
+        if (bound.expired()) {
+          s_fail = 1;
+          break;
+        }
+        asm volatile("" ::: "memory");   // the next look is another load
+      }
+    }
+    if (j > 0) store_kept(j - 1);
+    fetch_x(min(j + 1, p.count - 1));
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < NHW; ++i)
+#pragma unroll
+      for (int rt = 0; rt < NRTW; ++rt)
+#pragma unroll
+        for (int t = 0; t < BTW; ++t) acc[rt][t] = M::mma(wh[rt][i], hf[i][t], acc[rt][t]);
+#pragma unroll
+    for (int rt = 0; rt < NRTW; ++rt)
+      if (rt0 + rt < NRT) {
+#pragma unroll
+        for (int t = 0; t < BTW; ++t) red[(ks * NT + (rt0 + rt) * NBT + bt0 + t) * 64 + lane] = acc[rt][t];
+      }
+    lds_barrier();
+    if (s_fail) return;   // a wave gave up: written before the barrier, so all see it
+#pragma unroll
+    for (int q = 0; q < IPT; ++q) {
+      if (!mine[q]) continue;
+      const int item = (int)threadIdx.x + q * 512;
+      float G[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < KS; ++w) {   // fixed order, as in forward_body
+        const f32x4 v = red[w * NT * 64 + item];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) G[r] += v[r];
+      }
+      const float h = cell_forward<CELL>(G, bias[q], c_state[q], keep_second[q], keep_gate[q]);
+      keep_h[q] = real[q] ? h : 0.0f;
+      c_state[q] = CELL ? keep_h[q] : keep_second[q];
+    }
+    if (j + 1 < p.count) publish(p.published + (unsigned)j + 1);
+    lds_barrier();   // the partial sums have been read: the next step may overwrite them
+  }
+  store_kept(p.count - 1);
+}
+
+template <class T, int NRT, int NXW, int NXL, int NHW, int KS, int NBT, int CELL>
+hipError_t launch_chain_cell(const ResParams& p, hipStream_t st) {
+  constexpr int FTR = (KS == 4 && NBT == 1) ? 2 : 1, NRTW = (NRT + FTR - 1) / FTR;
+  constexpr size_t lds = (size_t)KS * NRT * NBT * 64 * sizeof(f32x4) + (size_t)8 * NRTW * NXL * 1024;
+  static_assert(lds <= 160 * 1024 - 64, "LDS of a compute unit");
+  auto kernel = forward_chain_kernel<T, NRT, NXW, NXL, NHW, KS, NBT, CELL>;
+  static bool configured = false;   // per instantiation; the attribute only has to be set once
+  if (!configured) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    configured = true;
+  }
+  kernel<<<dim3(RES_WGS), dim3(512), lds, st>>>(p);
+  return hipGetLastError();
+}
+
+}  // namespace mebptt

@@ -1,416 +1,60 @@
 // Resident launches: forward chains and sweeps, whose workgroups keep weights on the chip for many
 // time steps (see the comments at each kernel).
-#include "device.h"
+#include "resident.h"
 
 namespace mebptt {
 
-// ---- forward chain with resident weights -----------------------------------------------------
-// Consecutive forward operations (Algorithm 2's forward loop; also the single-step pushes that
-// follow each other when memory is plentiful) depend on each other only through h, so a chain of
-// them can run inside ONE launch if the gate weights stay on the chip and only h travels.  The
-// chip is split along the batch: XCD g (one of 8, each with its own L2) takes the sequences
-// [g*nb, (g+1)*nb) and never needs anything from another XCD, so no step synchronises across
-// XCDs.  Inside an XCD the 32 workgroups (one per compute unit) split the hidden units: workgroup
-// `rank` owns units [rank*H/32, (rank+1)*H/32), keeps the 4*H/32 packed weight rows of those units
-// in registers (and a part in LDS) for the whole launch, and per step
-//   1. waits until all 32 workgroups of its XCD have published their slice of h_{s-1}
-//      (a counter in the XCD's L2, bumped with an atomic add and polled with agent-scope loads),
-//   2. fetches the bf16 h_{s-1} of its sequences from the exchange ring with loads that bypass the
-//      compute unit's vector cache (the ring is written through to the L2 the 32 share),
-//   3. runs its slice of the gate GEMM and the pointwise step, keeps c in registers, publishes
-//      its slice of h_s, and stores the full state only where the schedule wants one.
-// Which XCD a workgroup runs on is read from the hardware (register XCC_ID), not inferred from
-// its id: workgroups are dealt round-robin to the XCDs, but where the deal starts depends on the
-// launches before.  A workgroup takes the next free rank of its XCD from a counter; the launch
-// relies on every XCD receiving exactly 32 of the 256 workgroups, checks it (a rank counter that
-// runs past 32 raises the status word; an XCD that gets fewer never completes its first wait,
-// which is bounded by a wall-clock limit like every other) and gives up rather than compute on
-// an assumption that does not hold.
-// Sums are formed exactly as forward_body forms them (KS partial sums over the macro steps
-// w, w+KS, ..., added in the order 0..KS-1), so a step gives the same bits either way.
-constexpr int RES_MAX_STEPS = 192;  // steps of one launch: their destinations travel as kernel arguments (3 KiB of the 4 KiB there are)
-constexpr int RES_RING = 4;         // h slices in flight (two would do: a step ahead at most)
-constexpr int RES_WGS = 256, RES_GROUPS = 8, RES_MEMBERS = RES_WGS / RES_GROUPS;
-constexpr long long RES_WAIT_TICKS = 50000000;   // 0.5 s of the 100 MHz wall clock
-// The bound every wait of a resident launch runs under, in ticks of that clock.  A host-side
-// setting (resident_wait_ticks) so that a test can make the waits give up at once -- every
-// workgroup then leaves through the same path as after a real time-out -- without anything hanging.
+// The bound every wait of a resident launch runs under, in ticks of the 100 MHz wall clock.  A
+// host-side setting so that a test can make the waits give up at once -- every workgroup then leaves
+// through the same path as after a real time-out -- without anything hanging.
+constexpr long long RES_WAIT_TICKS = 50000000;   // 0.5 s
 static long long g_wait_ticks = RES_WAIT_TICKS;
 void set_resident_wait_ticks(long long ticks) { g_wait_ticks = ticks < 0 ? RES_WAIT_TICKS : ticks; }
 
-struct ResStep {
-  float* out;     // unit that receives (h, c) of this step, or NULL
-  float* gates;   // two units that receive (i, f), (g, o), or NULL
+// ---- which shapes have forward chains -------------------------------------------------------------------
+// Sequences per XCD: as few as keep all of them on the chip at once, in whole halves of an MFMA tile, so
+// that no group straddles tiles (a step takes the same time for 1 and for 8 sequences, so with B < 64
+// fewer XCDs work rather than all of them on less).  Returns 0 for a batch that does not fit.
+static int group_share(const Dims& d) { return d.B <= 64 ? 8 : (d.B <= 128 ? 16 : (d.B <= 256 ? 32 : 0)); }
+
+struct ChainConfig {
+  int nrt, nxw, nhw, ks, nbt;
+  hipError_t (*launch[2])(const ResParams&, hipStream_t);   // by cell
 };
-struct ResParams {
-  const void* Wp;
-  const float* bp;
-  const float* x0;     // x of the first step of this launch
-  const float* src;    // unit holding the input state of the first step
-  void* ring;          // RES_RING x [BP][KH] bf16, fragment-tiled like the 16-bit h plane
-  unsigned* sync;      // words: arrival counter of XCD g at [g*64], rank counter at [512 + g*64], status at [1024]
-  unsigned base;       // value of every arrival counter when the launch starts
-  unsigned launch;     // chain launches of this run before this one (every rank counter stands at 32 * launch)
-  long long wait_ticks;   // bound of every wait, in ticks of the 100 MHz wall clock
-  int count;
-  int B, I, H, KX, KH, BP, nb;
-  size_t unit;         // floats per unit
-  ResStep step[RES_MAX_STEPS];
-};
-
-__device__ inline unsigned xcc_id() {
-  unsigned v;
-  asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(v));
-  return v & 0xf;
-}
-
-// One operand fragment (16 bytes per lane) fetched with agent scope: the load skips this compute
-// unit's vector cache and is served by the XCD's L2, where the other compute units of the XCD have
-// just written it.  A buffer load with the scope bit, not an atomic load: the compiler may keep as
-// many of them in flight as it has registers for (atomic loads it issues two at a time).
-// `base` is wave-uniform; byte_off < 2^31.
-__device__ inline bf16x8 load_frag_l2(const void* base, unsigned byte_off) {
-  typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
-  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0x7fffffff, 0x00020000);
-  union { u32x4 u; bf16x8 f; } cv;
-  cv.u = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)byte_off, 0, 16 /* sc1: agent scope */);
-  return cv.f;
-}
-
-template <int NRT, int NSW, int NSL, int KS, int NBT, int NSXW, int CELL>
-__global__ __launch_bounds__(64 * KS) void forward_chain_kernel(ResParams p) {
-  using T = __bf16;
-  using M = Mma<T>;
-  constexpr int VEC = 8, KSTEP = 32, FRAG = 64 * VEC;
-  constexpr int NT = NRT * NBT, NSR = NSW - NSL;
-  constexpr int UW = NRT * 4, ITEMS = NBT * 16 * UW, NTHR = 64 * KS, IPT = (ITEMS + NTHR - 1) / NTHR;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  float* red = reinterpret_cast<float*>(smem);                               // [KS][NT][4][64]
-  T* wl = reinterpret_cast<T*>(smem + (size_t)KS * NT * 4 * 64 * sizeof(float));   // [KS][NRT][NSL] fragments
-  __shared__ int s_go, s_g, s_rank;
-  // the wave index as a scalar: conditions on it become scalar branches (an MFMA under a lane mask
-  // that is empty would still execute)
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-  const int lrow = lane & 15, lq = lane >> 4;
-  if (threadIdx.x == 0) {
-    const unsigned xcc = xcc_id();
-    int ok = xcc < (unsigned)RES_GROUPS;
-    unsigned ticket = 0;
-    if (ok) {
-      ticket = __hip_atomic_fetch_add(p.sync + 512 + xcc * 64, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      ok = ticket / RES_MEMBERS == p.launch;   // more than 32 workgroups on this XCD: ranks would collide
-    }
-    if (!ok) __hip_atomic_store(p.sync + 1024, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s_go = ok;
-    s_g = ok ? (int)xcc : 0;
-    s_rank = (int)(ticket % RES_MEMBERS);
-  }
-  __syncthreads();
-  if (!s_go) return;
-  const int g = s_g, rank = s_rank;
-  constexpr int nsteps = KS * NSW;
-  const int nsx = p.KX / KSTEP, nsh = p.KH / KSTEP;
-  const size_t hhalf = (size_t)p.BP * p.KH;
-  const int b_lo = g * p.nb, b_hi = min(p.B, b_lo + p.nb);
-  const int nbt_all = p.BP / 16;
-  const int ct0 = min(b_lo / 16, nbt_all - 1);
-  unsigned* ctr = p.sync + g * 64;
-  unsigned* status = p.sync + 1024;
-
-  // This workgroup's packed weight rows: row tiles rank*NRT .. +NRT, this wave's macro steps
-  // wave, wave + KS, ...; the last NSL of them are parked in LDS (read back by this wave only).
-  typename M::Frag wr[NRT][NSR > 0 ? NSR : 1];
-  {
-    const T* wbase = reinterpret_cast<const T*>(p.Wp) + ((size_t)rank * NRT * nsteps * 64 + lane) * VEC;
-#pragma unroll
-    for (int rt = 0; rt < NRT; ++rt)
-#pragma unroll
-      for (int i = 0; i < NSW; ++i) {
-        const typename M::Frag f = M::load(wbase + ((size_t)rt * nsteps + wave + KS * i) * FRAG);
-        if (i < NSR)
-          wr[rt][i] = f;
-        else
-          *reinterpret_cast<typename M::Frag*>(&wl[((size_t)(wave * NRT + rt) * NSL + (i - NSR)) * FRAG + lane * VEC]) = f;
-      }
-  }
-
-  // Pointwise items of this thread: item = (output tile, lane of the MFMA layout), i.e. the
-  // (sequence, unit) whose four gate sums that lane holds, so that the partial sums are read back
-  // from LDS at consecutive addresses by consecutive threads.  c stays in registers.
-  bool mine[IPT];
-  int ib[IPT], iu[IPT], icell[IPT];
-  float4 bias[IPT];
-  float c_state[IPT];
-#pragma unroll
-  for (int q = 0; q < IPT; ++q) {
-    const int item = (int)threadIdx.x + q * NTHR;
-    const int tile = item >> 6, il = item & 63;          // tile = rt * NBT + bt
-    const int rt = tile / NBT, bt = tile % NBT;
-    const int b = (ct0 + bt) * 16 + (il & 15), u = rank * UW + rt * 4 + (il >> 4);
-    mine[q] = item < ITEMS && b >= b_lo && b < b_hi;
-    ib[q] = b;
-    iu[q] = u;
-    icell[q] = tile * 4 * 64 + il;   // where the four gate sums of this item sit inside one wave's block of `red`
-    bias[q] = float4{0.f, 0.f, 0.f, 0.f};
-    c_state[q] = 0.0f;
-    if (mine[q]) {
-      bias[q] = *reinterpret_cast<const float4*>(p.bp + 4 * u);
-      // the state the pointwise step blends with, kept in this register from step to step:
-      // c_{s-1} (LSTM) or h_{s-1} in full precision (GRU)
-      c_state[q] = CELL ? HPlane<T>::load(p.src, b, u, nsh, p.H, hhalf) : p.src[hhalf + (size_t)b * p.H + u];
-    }
-  }
-  const bool x_vec = (p.I & 3) == 0;
-
-  // Raw x values of this wave's x macro steps for the step about to run (NSXW = how many of the
-  // wave's first steps can fall into the x segment at all: KX / 32 / KS rounded up).
-  RawAct<VEC> xraw[NSXW][NBT];
-  auto fetch_x = [&](int j) {
-    const float* x_j = p.x0 + (size_t)j * p.B * p.I;
-#pragma unroll
-    for (int i = 0; i < NSXW; ++i) {
-      const int s = wave + KS * i;
-      if (s < nsx) {
-#pragma unroll
-        for (int bt = 0; bt < NBT; ++bt) {
-          const int b_ld = min(min(ct0 + bt, nbt_all - 1) * 16 + lrow, p.B - 1);
-          xraw[i][bt] = load_raw<VEC>(x_j + (size_t)b_ld * p.I, s * KSTEP + VEC * lq, p.I, x_vec);
-        }
-      }
-    }
-  };
-  fetch_x(0);
-
-  for (int j = 0; j < p.count; ++j) {
-    // x fragments: the raw fp32 values were requested a step ahead (see below) and are converted
-    // now; they do not depend on the other workgroups
-    typename M::Frag bf[NSW][NBT];
-#pragma unroll
-    for (int i = 0; i < NSXW; ++i)
-      if (wave + KS * i < nsx) {
-#pragma unroll
-        for (int bt = 0; bt < NBT; ++bt) bf[i][bt] = M::from_f32(xraw[i][bt].v);
-      }
-    f32x4 acc[NRT][NBT];
-#pragma unroll
-    for (int rt = 0; rt < NRT; ++rt)
-#pragma unroll
-      for (int bt = 0; bt < NBT; ++bt) acc[rt][bt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto weight = [&](int rt, int i) -> typename M::Frag {
-      return (i < NSR) ? wr[rt][i < NSR ? i : 0]
-                       : M::load(&wl[((size_t)(wave * NRT + rt) * NSL + (i - NSR)) * FRAG + lane * VEC]);
-    };
-    // the x part of the sum needs nothing from the other workgroups (a wave's x macro steps precede
-    // its h macro steps, so the order of the additions is that of forward_body)
-#pragma unroll
-    for (int i = 0; i < NSXW; ++i)
-      if (wave + KS * i < nsx) {
-#pragma unroll
-        for (int rt = 0; rt < NRT; ++rt) {
-          const typename M::Frag a = weight(rt, i);
-#pragma unroll
-          for (int bt = 0; bt < NBT; ++bt) acc[rt][bt] = M::mma(a, bf[i][bt], acc[rt][bt]);
-        }
-      }
-    if (j > 0) {
-      // all 32 workgroups of this XCD have published h of the previous step?
-      if (threadIdx.x == 0) {
-        const unsigned target = p.base + (unsigned)j * RES_MEMBERS;
-        int ok = 1, polls = 0;
-        long long t0 = 0;
-        // agent-scope loads see the counter in the L2 (32 pollers do not queue behind each other as
-        // read-modify-writes would: 1.95 -> 1.59 us per exchange round in isolation)
-        while ((int)(__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - target) < 0) {
-          if (p.wait_ticks == 0 || (++polls & 15) == 0) {   // a bound of 0: one look only
-            const long long now = wall_clock64();
-            if (t0 == 0) t0 = now;
-            if (now - t0 >= p.wait_ticks ||
-                __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) {
-              __hip_atomic_store(status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              ok = 0;
-              break;
-            }
-          }
-        }
-        s_go = ok;
-      }
-      __syncthreads();
-      if (!s_go) return;
-    }
-    // h fragments: the stored input state for the first step, then the exchange ring
-    {
-      const T* hsrc = (j == 0) ? reinterpret_cast<const T*>(p.src)
-                               : reinterpret_cast<const T*>(p.ring) + (size_t)((j - 1) % RES_RING) * hhalf;
-#pragma unroll
-      for (int i = 0; i < NSW; ++i) {
-        const int s = wave + KS * i;
-        if (s >= nsx) {
-#pragma unroll
-          for (int bt = 0; bt < NBT; ++bt) {
-            const size_t fo = (((size_t)min(ct0 + bt, nbt_all - 1) * nsh + (s - nsx)) * 64 + lane) * VEC;
-            if (j == 0)
-              bf[i][bt] = M::load(hsrc + fo);
-            else
-              bf[i][bt] = load_frag_l2(hsrc, (unsigned)(fo * sizeof(T)));
-          }
-        }
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);   // every fetch is issued before the first MFMA
-#pragma unroll
-    for (int i = 0; i < NSW; ++i)
-      if (!(i < NSXW && wave + KS * i < nsx)) {
-#pragma unroll
-        for (int rt = 0; rt < NRT; ++rt) {
-          const typename M::Frag a = weight(rt, i);
-#pragma unroll
-          for (int bt = 0; bt < NBT; ++bt) acc[rt][bt] = M::mma(a, bf[i][bt], acc[rt][bt]);
-        }
-      }
-    if (j + 1 < p.count) fetch_x(j + 1);   // in flight while this step finishes and the next wait runs
-#pragma unroll
-    for (int rt = 0; rt < NRT; ++rt)
-#pragma unroll
-      for (int bt = 0; bt < NBT; ++bt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) red[((wave * NT + rt * NBT + bt) * 4 + r) * 64 + lane] = acc[rt][bt][r];
-    __syncthreads();
-    const ResStep dst = p.step[j];
-    T* ring_out = reinterpret_cast<T*>(p.ring) + (size_t)(j % RES_RING) * hhalf;
-    const bool publish = j + 1 < p.count;
-    float keep_h[IPT], keep_second[IPT], keep_gate[IPT][4];
-#pragma unroll
-    for (int q = 0; q < IPT; ++q) {
-      if (!mine[q]) continue;
-      float G[4] = {0.f, 0.f, 0.f, 0.f};
-      for (int w = 0; w < KS; ++w)   // fixed order, as in forward_body
-#pragma unroll
-        for (int r = 0; r < 4; ++r) G[r] += red[w * NT * 4 * 64 + icell[q] + r * 64];
-      const float h = cell_forward<CELL>(G, bias[q], c_state[q], keep_second[q], keep_gate[q]);
-      keep_h[q] = h;
-      c_state[q] = CELL ? h : keep_second[q];
-      const int b = ib[q], u = iu[q];
-      if (publish) {
-        // Units u and u + 1 of one sequence sit 16 lanes apart in this layout and next to each other
-        // in the ring: the lane of the even unit stores both as one dword (the rows of a tile belong
-        // to one XCD or, split in halves, to two -- a lane and its partner are always on the same side).
-        const unsigned hi16 = (__float_as_uint(h) + 0x8000u) >> 16;
-        const unsigned other = __shfl_xor(hi16, 16);
-        if (((threadIdx.x >> 4) & 1) == 0)
-          reinterpret_cast<unsigned*>(ring_out)[ft_offset<T>(b, u, nsh) >> 1] = hi16 | (other << 16);
-      }
-    }
-    if (publish) {
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's slice of h has reached the L2
-      __syncthreads();
-      if (threadIdx.x == 0) __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    // What only later launches read goes out after the arrival: the other workgroups do not wait
-    // for these stores to be acknowledged.
-    if (dst.out || dst.gates) {
-#pragma unroll
-      for (int q = 0; q < IPT; ++q) {
-        if (!mine[q]) continue;
-        const int b = ib[q], u = iu[q];
-        if (dst.out) {
-          HPlane<T>::store(dst.out, b, u, keep_h[q], nsh, p.H, hhalf);
-          dst.out[hhalf + (size_t)b * p.H + u] = keep_second[q];
-        }
-        if (dst.gates) {
-          const size_t e = (size_t)b * p.H + u, plane = (size_t)p.B * p.H;
-          dst.gates[e] = keep_gate[q][0];
-          dst.gates[plane + e] = keep_gate[q][1];
-          dst.gates[p.unit + e] = keep_gate[q][2];
-          if (CELL == 0) dst.gates[p.unit + plane + e] = keep_gate[q][3];
-        }
-      }
-    }
-  }
-}
-
-// Shape classes with an instantiation: {NRT = H/128, NSW = macro steps per wave, NSL, KS, NBT}.
-struct ResConfig {
-  int nrt, nsw, nsl, ks, nbt, nsxw;
-};
-static const ResConfig RES_CONFIGS[] = {
-    {8, 5, 1, 8, 1, 1},   // H = 1024, I <= 256
-    {4, 5, 0, 4, 1, 1}, {4, 5, 0, 4, 2, 1},   // H = 512, I <= 128
-    {2, 4, 0, 4, 1, 2}, {2, 4, 0, 4, 2, 2},   // H = 256, 128 < I <= 256
-    {1, 2, 0, 4, 1, 1}, {1, 2, 0, 4, 2, 1},   // H = 128, I <= 128
+#define CHAIN(T, NRT, NXW, NXL, NHW, KS, NBT) \
+  {NRT, NXW, NHW, KS, NBT, {launch_chain_cell<T, NRT, NXW, NXL, NHW, KS, NBT, 0>, launch_chain_cell<T, NRT, NXW, NXL, NHW, KS, NBT, 1>}}
+static const ChainConfig CHAIN_BF16[] = {
+    CHAIN(__bf16, 8, 1, 1, 4, 8, 1),   // H = 1024, I <= 256
+    CHAIN(__bf16, 4, 1, 0, 4, 4, 1), CHAIN(__bf16, 4, 1, 0, 4, 4, 2),   // H = 512, I <= 128
+    CHAIN(__bf16, 2, 2, 0, 2, 4, 1), CHAIN(__bf16, 2, 2, 0, 2, 4, 2),   // H = 256, I <= 256
+    CHAIN(__bf16, 1, 1, 0, 1, 4, 1), CHAIN(__bf16, 1, 1, 0, 1, 4, 2),   // H = 128, I <= 128
 };
 
-// The batch is dealt to the XCDs in groups of nb consecutive sequences.  An even share,
-// nb = ceil(B / 8), keeps every XCD busy but may make a group straddle more 16-sequence MFMA tiles
-// than a kernel is instantiated for; the share rounded up to whole tiles never straddles (some XCDs
-// then get no sequences and only keep the meeting going).  group_tiles: batch tiles the widest group
-// touches; the configuration look-ups try the even share first.
-static int group_tiles(const Dims& d, int nb) {
-  int nbt = 1;
-  for (int g = 0; g < RES_GROUPS; ++g) {
-    const int lo = g * nb, hi = (lo + nb < d.B ? lo + nb : d.B);
-    if (lo >= d.B) break;
-    const int span = (hi - 1) / 16 - lo / 16 + 1;
-    nbt = span > nbt ? span : nbt;
-  }
-  return nbt;
-}
-static int group_share(const Dims& d, int candidate) {
-  const int even = (d.B + RES_GROUPS - 1) / RES_GROUPS;
-  return candidate == 0 ? even : round_up(even, 16);
-}
-
-// Index into RES_CONFIGS for this shape, or -1 when the chain kernel does not apply; *nb_out = the
-// sequences per XCD to launch it with.
-static int resident_config(const Dims& d, int* nb_out = nullptr) {
-  if (!d.dtype || d.H % 128 != 0 || d.KH != d.H) return -1;   // either cell: the GRU's rows r, z, n_x, n_h fill the same four packed rows
-  const int nsteps = d.KP / 32;
+// The smallest instantiation the shape fits, or NULL.
+static const ChainConfig* chain_config(const Dims& d) {
+  if (!d.dtype || d.I < 8) return nullptr;
+  const int kstep = 32, nsx = d.KX / kstep, nsh = d.KH / kstep, nrt = (d.KH + 127) / 128;
   const FwdConfig fc = forward_config<__bf16>(d);
   const int ks = (fc == FWD_TINY || fc == FWD_SMALLK) ? 4 : 8;   // the K split of the per-step kernels
-  if (nsteps % ks != 0) return -1;
-  for (int cand = 0; cand < 2; ++cand) {
-    const int nb = group_share(d, cand), nbt = group_tiles(d, nb);
-    for (size_t i = 0; i < sizeof RES_CONFIGS / sizeof RES_CONFIGS[0]; ++i) {
-      const ResConfig& c = RES_CONFIGS[i];
-      if (c.nrt == d.H / 128 && c.ks == ks && c.nsw == nsteps / ks && c.nbt == nbt && c.nsxw == (d.KX / 32 + ks - 1) / ks) {
-        if (nb_out) *nb_out = nb;
-        return (int)i;
-      }
-    }
-  }
-  return -1;
+  const int share = group_share(d), nbt = share > 16 ? 2 : 1;
+  if (share == 0) return nullptr;
+  for (const ChainConfig& c : CHAIN_BF16)
+    if (c.nrt == nrt && c.ks == ks && c.nbt == nbt && c.nhw * ks >= nsh && c.nxw * ks >= nsx) return &c;
+  return nullptr;
 }
 
-bool can_run_forward_chain(const Dims& d) { return resident_config(d) >= 0; }
+bool can_run_forward_chain(const Dims& d) { return chain_config(d) != nullptr; }
 int forward_chain_max_steps() { return RES_MAX_STEPS; }
-size_t forward_chain_ring_bytes(const Dims& d) { return (size_t)RES_RING * d.BP * d.KH * sizeof(__bf16); }
-size_t forward_chain_sync_bytes() { return (1024 + 64) * sizeof(unsigned); }
-size_t forward_chain_status_offset() { return 1024 * sizeof(unsigned); }
+size_t forward_chain_ring_bytes(const Dims& d) { return (size_t)RES_RING * d.BP * d.KH * d.op_bytes(); }
+size_t forward_chain_sync_bytes() { return (RES_SYNC_STATUS + 64) * sizeof(unsigned); }
+size_t forward_chain_status_offset() { return RES_SYNC_STATUS * sizeof(unsigned); }
 unsigned forward_chain_arrivals(int steps) { return steps > 1 ? (unsigned)(steps - 1) * RES_MEMBERS : 0u; }
 
-template <int NRT, int NSW, int NSL, int KS, int NBT, int NSXW, int CELL>
-static hipError_t launch_chain_cell(const ResParams& p, hipStream_t st) {
-  const size_t lds = (size_t)KS * NRT * NBT * 4 * 64 * sizeof(float) + (size_t)KS * NRT * NSL * 64 * 8 * sizeof(__bf16);
-  static bool configured = false;   // per instantiation; the attribute only has to be set once
-  if (!configured) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(forward_chain_kernel<NRT, NSW, NSL, KS, NBT, NSXW, CELL>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    configured = true;
-  }
-  forward_chain_kernel<NRT, NSW, NSL, KS, NBT, NSXW, CELL><<<dim3(RES_WGS), dim3(64 * KS), lds, st>>>(p);
-  return hipGetLastError();
-}
-template <int NRT, int NSW, int NSL, int KS, int NBT, int NSXW>
-static hipError_t launch_chain_cfg(const ResParams& p, int cell, hipStream_t st) {
-  return cell ? launch_chain_cell<NRT, NSW, NSL, KS, NBT, NSXW, 1>(p, st) : launch_chain_cell<NRT, NSW, NSL, KS, NBT, NSXW, 0>(p, st);
-}
-
 hipError_t launch_forward_chain(const Dims& d, const void* Wp, const float* bp, const float* x_first, const float* src_unit,
-                                const ChainStep* steps, int count, void* ring, unsigned* sync, unsigned base,
+                                const ChainStep* steps, int count, void* ring, unsigned* sync, unsigned published,
                                 unsigned launch, hipStream_t st) {
-  int nb = 0;
-  const int cfg = resident_config(d, &nb);
-  if (cfg < 0 || count < 1 || count > RES_MAX_STEPS) return hipErrorInvalidValue;
+  const ChainConfig* cfg = chain_config(d);
+  if (!cfg || count < 1 || count > RES_MAX_STEPS) return hipErrorInvalidValue;
   ResParams p{};
   p.Wp = Wp;
   p.bp = bp;
@@ -418,28 +62,22 @@ hipError_t launch_forward_chain(const Dims& d, const void* Wp, const float* bp, 
   p.src = src_unit;
   p.ring = ring;
   p.sync = sync;
-  p.base = base;
+  p.published = published;
   p.launch = launch;
   p.wait_ticks = g_wait_ticks;
   p.count = count;
   p.B = d.B;
   p.I = d.I;
   p.H = d.H;
+  p.HP = d.HP;
   p.KX = d.KX;
   p.KH = d.KH;
   p.BP = d.BP;
-  p.nb = nb;
+  p.nb = group_share(d);
   p.unit = d.unit;
+  p.hplane = d.hplane;
   for (int j = 0; j < count; ++j) p.step[j] = ResStep{steps[j].out, steps[j].gates};
-  switch (cfg) {
-    case 0: return launch_chain_cfg<8, 5, 1, 8, 1, 1>(p, d.cell, st);
-    case 1: return launch_chain_cfg<4, 5, 0, 4, 1, 1>(p, d.cell, st);
-    case 2: return launch_chain_cfg<4, 5, 0, 4, 2, 1>(p, d.cell, st);
-    case 3: return launch_chain_cfg<2, 4, 0, 4, 1, 2>(p, d.cell, st);
-    case 4: return launch_chain_cfg<2, 4, 0, 4, 2, 2>(p, d.cell, st);
-    case 5: return launch_chain_cfg<1, 2, 0, 4, 1, 1>(p, d.cell, st);
-    default: return launch_chain_cfg<1, 2, 0, 4, 2, 1>(p, d.cell, st);
-  }
+  return cfg->launch[d.cell](p, st);
 }
 
 // ---- backward sweep with resident weights ------------------------------------------------------
@@ -458,6 +96,22 @@ hipError_t launch_forward_chain(const Dims& d, const void* Wp, const float* bp, 
 //     lower step, so the wait is mostly hidden.
 // K splits and summation orders are those of forward_body and backward_body for the shape, the
 // pointwise steps are the shared functions: bit-identical to the launch-per-step path.
+static int group_tiles(const Dims& d, int nb) {
+  int nbt = 1;
+  for (int g = 0; g < RES_GROUPS; ++g) {
+    const int lo = g * nb, hi = (lo + nb < d.B ? lo + nb : d.B);
+    if (lo >= d.B) break;
+    const int span = (hi - 1) / 16 - lo / 16 + 1;
+    nbt = span > nbt ? span : nbt;
+  }
+  return nbt;
+}
+static int group_share(const Dims& d, int candidate) {
+  const int even = (d.B + RES_GROUPS - 1) / RES_GROUPS;
+  return candidate == 0 ? even : round_up(even, 16);
+}
+__device__ inline bf16x8 load_frag_l2(const void* base, unsigned byte_off) { return as_frag<bf16x8>(load_slot_16(base, byte_off, 0)); }
+
 constexpr int SWEEP_MAX_STEPS = 32;
 struct SweepParams {
   const void* Wp;

@@ -28,7 +28,7 @@ constexpr size_t ALIGN = 256;
 inline size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
 struct Workspace {
-  size_t Wp, bp, WTh, WTx, state, dWacc, dc, sync, dG[2], dGT[2], aT[2], ring, stage, total;
+  size_t Wp, bp, WTh, WTx, state, dWacc, dc, sync, dG[2], dGT[2], aT[2], ring, ring_bytes, stage, total;
   size_t total_no_stage;   // what a run that issues no batched recomputation needs (the no-allocation path)
   int stage_steps;         // internal states the stage holds
 };
@@ -66,8 +66,9 @@ Workspace layout(const Dims& d) {
   for (int i = 0; i < 2; ++i) w.dG[i] = take((size_t)d.CH * d.BP * d.G4 * op);
   for (int i = 0; i < 2; ++i) w.dGT[i] = take((size_t)d.G4 * d.KC * op);
   for (int i = 0; i < 2; ++i) w.aT[i] = take((size_t)d.NA * d.KC * op);
-  w.ring = take(can_run_forward_chain(d) ? forward_chain_ring_bytes(d) : 0);
   w.total_no_stage = off;
+  w.ring_bytes = can_run_forward_chain(d) ? forward_chain_ring_bytes(d) : 0;
+  w.ring = take(w.ring_bytes);
   w.stage_steps = recompute_stage_steps(d);
   w.stage = take((size_t)w.stage_steps * 3 * unit);   // last: nothing ever clears it
   w.total = off;
@@ -425,7 +426,7 @@ int mebptt_prepare(const mebptt_lstm_desc* desc, const float* W_ih, const float*
   HIP_TRY(timed(MEBPTT_K_SETUP, st, [&] {
     return launch_prep_weights(d, W_ih, W_hh, b, ws + w.Wp, reinterpret_cast<float*>(ws + w.bp), ws + w.WTh, ws + w.WTx, st);
   }));
-  HIP_TRY(timed(MEBPTT_K_SETUP, st, [&] { return launch_fill_zero(ws + w.dc, w.total_no_stage - w.dc, st); }));
+  HIP_TRY(timed(MEBPTT_K_SETUP, st, [&] { return launch_fill(ws + w.dc, w.ring - w.dc, nullptr, 0, st); }));
   remember_prepared(workspace, d);
   return MEBPTT_OK;
 }
@@ -757,16 +758,19 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
     g_prof.open.cls = -1;
   }
 
+  const bool resident_ok = mode != RUN_STATIC && g_chain_enabled && device_fits_resident_launches();
+  const size_t ring_fill = resident_ok ? w.ring_bytes : 0;   // the no-allocation path's workspace ends before the ring
+
   // Set-up: operand copies of the weights, zeroed staging (the padding must stay zero), start state.
   if (mode != RUN_PREPARED) {
     HIP_TRY(tm(MEBPTT_K_SETUP, st, [&] { return launch_prep_weights(d, W_ih, W_hh, b, Wp, bp, WTh, WTx, st); }));
-    HIP_TRY(tm(MEBPTT_K_SETUP, st, [&] { return launch_fill_zero(ws + w.dc, w.total_no_stage - w.dc, st); }));
+    HIP_TRY(tm(MEBPTT_K_SETUP, st, [&] { return launch_fill(ws + w.dc, w.ring - w.dc, ws + w.ring, ring_fill, st); }));
   } else {
     // The staging keeps what the previous run left.  Only the running gradient plane must start
     // at zero, and -- when the last chunk in time is short and its K is padded -- the operand
     // columns between its last step and the padded K, which a full chunk of the previous run
     // filled.
-    HIP_TRY(tm(MEBPTT_K_SETUP, st, [&] { return launch_fill_zero(ws + w.dc, w.dG[0] - w.dc, st); }));
+    HIP_TRY(tm(MEBPTT_K_SETUP, st, [&] { return launch_fill(ws + w.dc, w.dG[0] - w.dc, ws + w.ring, ring_fill, st); }));
     const int last_chunk = (t - 1) / CH, nslots = t - last_chunk * CH;
     const int cols = nslots * d.B, kstep = d.dtype ? 32 : 16;
     if (cols % kstep != 0)
@@ -785,7 +789,6 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
   // Beside launch-per-step kernels, which fill the device on their own, the two only get in each
   // other's way (H = 2048: 2.8 % slower, H = 4096: 1.4 %), so there -- and in the no-allocation
   // path, which creates no stream and no event -- they stay on the caller's stream in the same order.
-  const bool resident_ok = mode != RUN_STATIC && g_chain_enabled && device_fits_resident_launches();
   SideStream* side = nullptr;
   if (resident_ok && (can_run_forward_chain(d) || can_run_backward_sweep(d))) HIP_TRY(get_side_stream(&side));
   hipStream_t st2 = side ? side->stream : st;
@@ -881,6 +884,7 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
   // from overlapping on the device.
   const bool chain_ok = resident_ok && can_run_forward_chain(d);
   constexpr int CHAIN_MIN_STEPS = 2;     // two steps in one launch already beat two launches (measured on the paper's 256-wide model)
+  unsigned chain_published = 0;   // states exchanged inside this run's earlier chain launches
   unsigned chain_base = 0;        // arrivals left in the group counters by this run's earlier chain launches
   unsigned chain_launches = 0;    // chain launches of this run so far
   bool chain_used = false;
@@ -1143,11 +1147,11 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
           const float* x_first = x_of(fsteps[fi].step);
           rc = whole_launch(MEBPTT_K_CHAIN, n, st, [&] {
             return launch_forward_chain(d, Wp, bp, x_first, cur, cs, n, ws + w.ring, reinterpret_cast<unsigned*>(ws + w.sync),
-                                        chain_base, chain_launches, st);
+                                        chain_published, chain_launches, st);
           });
           if (rc) return rc;
           ++chain_launches;
-          chain_base += forward_chain_arrivals(n);
+          chain_published += (unsigned)n;
           cur = fsteps[fi + n - 1].dst;
           fi += n;
           fwd += n;
