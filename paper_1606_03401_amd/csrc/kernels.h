@@ -111,10 +111,10 @@ hipError_t launch_backward_forward_pair(const Dims& d, const BackwardArgs& a, co
 // x_first + j*B*I; its state goes to steps[j].out and its gates to the two units at
 // steps[j].gates where these are not NULL (states nobody asked for never leave the chip).
 // `ring` (forward_chain_ring_bytes, every byte 0xff before the first chain launch of a run) and `sync`
-// (forward_chain_sync_bytes, zero before the first resident launch of a run) are workspace; `published` is the number
+// (resident_sync_bytes, zero before the first resident launch of a run) are workspace; `published` is the number
 // of states the run's earlier chain launches exchanged (count each), `launch` the number of its earlier
 // resident launches of any kind.
-// The word at forward_chain_status_offset() inside `sync` is a status word: 0, or non-zero when
+// The word at resident_status_offset() inside `sync` is a status word: 0, or non-zero when
 // a launch gave up (an XCD did not receive exactly 32 of the 256 workgroups, or a wait ran into
 // its wall-clock bound); results are then invalid.  Launches that overlap
 // on the device would wait for each other's compute units: the caller orders them.
@@ -128,9 +128,8 @@ void set_resident_wait_ticks(long long ticks);
 bool can_run_forward_chain(const Dims& d);
 int forward_chain_max_steps();
 size_t forward_chain_ring_bytes(const Dims& d);
-size_t forward_chain_sync_bytes();
-size_t forward_chain_status_offset();
-unsigned forward_chain_arrivals(int steps);
+size_t resident_sync_bytes();
+size_t resident_status_offset();
 hipError_t launch_forward_chain(const Dims& d, const void* Wp, const float* bp, const float* x_first, const float* src_unit,
                                 const ChainStep* steps, int count, void* ring, unsigned* sync, unsigned published,
                                 unsigned launch, hipStream_t st);
@@ -140,8 +139,9 @@ hipError_t launch_forward_chain(const Dims& d, const void* Wp, const float* bp, 
 // operands resident on the chip (shapes for which can_run_sweep() holds).  src[j] is the unit
 // holding the state before step s_hi - j; the internal states never reach memory; everything a
 // backward step writes (dG, its transposed copies, y_out, the running dc) is written as by
-// launch_backward.  sync/base/launch as for launch_forward_chain, whose counters it shares: a
-// launch of n steps leaves forward_chain_arrivals(n) arrivals.
+// launch_backward.  sync/launch as for launch_forward_chain; `ring` (sweep_ring_bytes, every byte 0xff before
+// the first sweep launch of a run) holds the exchanged dG, `published` is the number of steps the run's earlier
+// sweep launches carried.
 struct SweepArgs {
   const void* Wp;
   const void* WTh;
@@ -155,8 +155,9 @@ struct SweepArgs {
   void* dG_chunk[2];       // the two chunk buffers of each operand, indexed by chunk parity: a launch may cross
   void* dGT[2];            // from one chunk of steps into the one below
   void* aT[2];
+  void* ring;
   unsigned* sync;
-  unsigned base, launch;
+  unsigned published, launch;
   int s_hi, count;
   const float* const* src;
   const float* const* state;   // NULL, or per step the unit where an earlier launch stored the internal state:
@@ -165,6 +166,7 @@ struct SweepArgs {
 bool can_run_sweep(const Dims& d);
 bool can_run_backward_sweep(const Dims& d);
 int sweep_max_steps();
+size_t sweep_ring_bytes(const Dims& d);
 hipError_t launch_sweep(const Dims& d, const SweepArgs& a, hipStream_t st);
 
 // out[slot*B + b][n] = sum_k dG[slot*BP + b][k] * WT[n][k] for slot < nslots, b < B, n < N;

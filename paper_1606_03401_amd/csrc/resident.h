@@ -18,8 +18,8 @@ namespace mebptt {
 // that does not hold.
 constexpr int RES_WGS = 256, RES_GROUPS = 8, RES_MEMBERS = RES_WGS / RES_GROUPS;
 constexpr int RES_RING = 4;   // exchange slots
-// sync words: arrival counter of XCD g at [g * 64], rank counter at [512 + g * 64], status at [1024]
-constexpr int RES_SYNC_RANK = 512, RES_SYNC_STATUS = 1024;
+// sync words: rank counter of XCD g at [g * 64], status at [512]
+constexpr int RES_SYNC_RANK = 0, RES_SYNC_STATUS = 512;
 
 __device__ inline unsigned xcc_id() {
   unsigned v;
@@ -132,6 +132,26 @@ __device__ inline void shift_tail(RawAct<VEC>& r, int k, int limit) {
     }
 #pragma unroll
   for (int e = 0; e < VEC; ++e) r.v[e] = d >= VEC ? 0.0f : r.v[e];
+}
+
+// h of one element in full precision, and as the GEMM operand: `e` = b * H + u (plain plane), `o` its place
+// in a split plane of `half` elements per 16-bit plane.
+template <class T>
+__device__ inline float load_h(const float* plane, unsigned e, unsigned o, size_t half) {
+  if constexpr (HPlane<T>::SPLIT) {
+    const unsigned short* hi = reinterpret_cast<const unsigned short*>(plane);
+    const unsigned lo = (hi + half)[(size_t)o];
+    return __uint_as_float((((unsigned)hi[(size_t)o] - (lo >> 15)) << 16) | lo);
+  } else {
+    return plane[(size_t)e];
+  }
+}
+template <class T>
+__device__ inline float load_h_operand(const float* plane, unsigned e, unsigned o) {
+  if constexpr (HPlane<T>::SPLIT)
+    return (float)reinterpret_cast<const T*>(plane)[(size_t)o];
+  else
+    return plane[(size_t)e];
 }
 
 // ---- forward chain -------------------------------------------------------------------------------------

@@ -1,0 +1,469 @@
+// The sweep kernel: a run of backward steps in one launch, with or without the forward operations that
+// recompute their internal states.  Not part of the ABI.
+#pragma once
+
+#include "resident.h"
+
+namespace mebptt {
+
+constexpr int SWEEP_MAX_STEPS = 32;
+struct SweepParams {
+  const void* Wp;
+  const void* WTh;
+  const float* bp;
+  const float* x;        // x of step 1 (step s reads x + (s-1)*B*I)
+  const float* dy;       // upstream gradients, first plane = step dy_first; NULL with dy_is_h
+  int dy_first, dy_is_h;
+  float* dc;             // running cell-state gradient plane
+  float* y_out;          // outputs, plane of step 1 first, or NULL
+  const void* dG_next;   // dG block of step s_hi + 1, or NULL when s_hi is the last step of the sequence
+  void* dG_chunk[2];     // the two chunk buffers: step s lives in buffer ((s-1) / CH) & 1, its block at slot (s-1) % CH
+  void* dGT[2];
+  void* aT[2];
+  void* ring;            // RES_RING exchange slots [BP][G4] of dG, fragment-tiled
+  unsigned* sync;
+  unsigned published, launch;   // blocks published by this run's sweep launches before this one; resident launches before it
+  long long wait_ticks;  // bound of every wait, in ticks of the 100 MHz wall clock
+  int s_hi, count;       // steps s_hi, s_hi - 1, ..., s_hi - count + 1 (in at most two consecutive chunks)
+  int B, I, H, HP, KX, KH, BP, nb, G4, NX, KC, CH;
+  size_t unit, hplane;
+  const float* src[SWEEP_MAX_STEPS];   // src[j]: unit holding the state before step s_hi - j
+  const float* state[SWEEP_MAX_STEPS]; // FWD = false: unit holding the stored internal state of step s_hi - j
+};
+
+// Where a sub-sequence fits into memory the schedule alternates "forward operation of step s from
+// the memorised h_{s-1}, keeping the internal state" and "backward operation of step s", s going
+// down.  On shapes whose gate weights AND their transpose fit on the chip such a run of pairs goes
+// out as one launch (FWD), organised like the forward chain (batch split over the XCDs, hidden units over
+// the 32 compute units of an XCD, weights in registers):
+//   * the forward operation of a step needs nothing from other compute units (its input state was
+//     memorised by an earlier launch), and its internal state never leaves the registers of the
+//     thread that owns the (sequence, unit);
+//   * the backward operation needs dG of the step after, all 4H columns of it, for the XCD's sequences:
+//     the compute units exchange their columns the way the forward chain exchanges h; dG of the step
+//     above the launch is published like any other, so all steps are alike;
+//   * while the others' columns travel, every compute unit runs the forward operation of the next
+//     lower step.
+// FWD = false: the internal states are not recomputed but read from where an earlier launch stored them
+// (internal-state slots, or the stage of a forward batch): backward operations only, W_hh^T alone resident.
+// What only later launches read of a step (dG in the chunk buffer, its transposed copies, the outputs)
+// is stored, and what the next step needs is fetched, right after the polls of the following
+// exchange: memory operations complete in order, so in front of the polls they would hold them up.
+// K splits and summation orders are those of forward_body and backward_body for the shape, the
+// pointwise steps are the shared functions: bit-identical to the launch-per-step path.
+// NXW, NHW, KSF: macro steps of x and h per wave and K split of the forward part; NBW, KSB: macro steps of
+// dG per wave (the weights of the last NBL are parked in LDS: registers are what the two largest
+// instantiations are short of) and K split of the backward part; NBT: batch tiles of the XCD's share.
+template <class T, bool FWD, int NRT, int NXW, int NHW, int KSF, int NBW, int NBL, int KSB, int NBT, int CELL>
+__global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
+  using M = Mma<T>;
+  constexpr int VEC = M::VEC, KSTEP = 4 * VEC, FRAG = 64 * VEC;
+  constexpr bool SPLIT = HPlane<T>::SPLIT;
+  constexpr int UW = NRT * 4;                       // hidden units per workgroup
+  constexpr int NTB = (UW + 15) / 16;               // 16-unit tiles of the dh GEMM that cover them
+  constexpr int NTF = NRT * NBT, NTBT = NTB * NBT;
+  constexpr int ITEMS = NTF * 64, IPT = (ITEMS + 511) / 512;
+  constexpr int GF = 8 / KSF, FTB = (GF == 2 && NBT == 2) ? 2 : 1, FTR = GF / FTB;   // forward: groups of waves along batch, rows
+  constexpr int NRTW = (NRT + FTR - 1) / FTR, BTWF = NBT / FTB;
+  constexpr int GB = 8 / KSB, BTB = (GB == 2 && NBT == 2) ? 2 : 1, BTWB = NBT / BTB;   // backward: along the batch, or one group idles
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  f32x4* redB = reinterpret_cast<f32x4*>(smem);                       // [KSB][NTBT][64]
+  f32x4* redF = redB + (size_t)KSB * NTBT * 64;                       // [KSF][NTF][64]
+  T* wl = reinterpret_cast<T*>(redF + (FWD ? (size_t)KSF * NTF * 64 : 0));   // [8][NTB][NBL] fragments
+  __shared__ int s_go, s_g, s_rank, s_fail;
+  // the wave index as a scalar: conditions on it become scalar branches (an MFMA under a lane mask
+  // that is empty would still execute)
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  const int lrow = lane & 15, lq = lane >> 4;
+  if (threadIdx.x == 0) {
+    int xg, xr;
+    s_go = draw_rank(p.sync, p.launch, xg, xr);
+    s_g = xg;
+    s_rank = xr;
+    s_fail = 0;
+  }
+  __syncthreads();
+  if (!s_go) return;
+  const int g = __builtin_amdgcn_readfirstlane(s_g), rank = __builtin_amdgcn_readfirstlane(s_rank);
+  const int b_lo = g * p.nb, b_hi = min(p.B, b_lo + p.nb);
+  if (b_lo >= p.B || rank * UW >= p.HP) return;   // no sequences or no units here: nobody waits for this workgroup
+  const int nsx = p.KX / KSTEP, nsh = p.KH / KSTEP, nstepsF = nsx + nsh, nstepsB = p.G4 / KSTEP;
+  const size_t hhalf = (size_t)p.BP * p.KH, dG_step = (size_t)p.BP * p.G4;
+  const unsigned plane = (unsigned)(p.B * p.H);
+  const int nbt_all = p.BP / 16, ct0 = b_lo / 16;
+  const int fk = wave % KSF, fg = wave / KSF, bk = wave % KSB, bg = wave / KSB;
+  const int rt0 = (FTR > 1 ? fg : 0) * NRTW, btf0 = (FTB > 1 ? fg : 0) * BTWF, btb0 = (BTB > 1 ? bg : 0) * BTWB;
+  const bool bwd_wave = bg < BTB;
+  const int mh0 = (fk + KSF - nsx % KSF) % KSF;     // this wave's h macro steps: mh0, mh0 + KSF, ... (below nsh)
+
+  // items: (output tile, lane of the forward MFMA layout) = (sequence, unit).  A unit between H and the
+  // padded HP publishes zeros.
+  bool mine[IPT], real[IPT];
+  unsigned ie[IPT], io[IPT], ig[IPT];   // b * H + u; places in the fragment-tiled h plane and (of gate 0) in a dG block
+  float4 bias[IPT];
+  float dc_run[IPT];
+  // internal state of the step whose backward operation comes next, its input state, its loss gradient
+  float st_gate[IPT][4], st_c[IPT], st_h[IPT], st_cprev[IPT], st_hprev[IPT], st_dy[IPT];
+  unsigned dg[IPT][sizeof(T)];          // the four gates' dG of the last step, as published (8 or 16 bytes)
+  float kp_h[IPT], kp_hprev[IPT];
+#pragma unroll
+  for (int q = 0; q < IPT; ++q) {
+    const int item = (int)threadIdx.x + q * 512;
+    const int tile = item >> 6, il = item & 63;
+    const int rt = tile / NBT, bt = tile % NBT;
+    const int b = (ct0 + bt) * 16 + (il & 15), u = rank * UW + rt * 4 + (il >> 4);
+    mine[q] = item < ITEMS && b >= b_lo && b < b_hi && u < p.HP;
+    real[q] = mine[q] && u < p.H;
+    ie[q] = real[q] ? (unsigned)(b * p.H + u) : 0u;     // element 0 is there for items without one to fetch
+    io[q] = real[q] ? (unsigned)ft_offset<T>(b, u, nsh) : 0u;
+    ig[q] = mine[q] ? (unsigned)ft_offset<T>(b, 4 * u, nstepsB) : 0u;
+    bias[q] = real[q] ? *reinterpret_cast<const float4*>(p.bp + 4 * u) : float4{0.f, 0.f, 0.f, 0.f};
+    dc_run[q] = real[q] ? p.dc[(size_t)ie[q]] : 0.0f;
+    kp_h[q] = kp_hprev[q] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < (int)sizeof(T); ++i) dg[q][i] = 0u;
+    if (real[q] && p.dG_next) {
+      const unsigned* src = reinterpret_cast<const unsigned*>(reinterpret_cast<const T*>(p.dG_next) + (size_t)ig[q]);
+#pragma unroll
+      for (int i = 0; i < (int)sizeof(T); ++i) dg[q][i] = not_empty(src[i]);
+    }
+  }
+  // the four gates of a unit are consecutive in a dG block: one 8- or 16-byte store
+  auto store_dg = [&](T* block, int q, bool empty) {
+    typedef __attribute__((ext_vector_type(sizeof(T)))) unsigned int vec;
+    vec v;
+#pragma unroll
+    for (int i = 0; i < (int)sizeof(T); ++i) v[i] = empty ? RES_EMPTY : dg[q][i];
+    *reinterpret_cast<vec*>(block + (size_t)ig[q]) = v;
+  };
+  auto publish = [&](unsigned q_now) {
+    T* slot_out = reinterpret_cast<T*>(p.ring) + (size_t)(q_now % RES_RING) * dG_step;
+    T* slot_old = reinterpret_cast<T*>(p.ring) + (size_t)((q_now + 2) % RES_RING) * dG_step;   // two steps back
+#pragma unroll
+    for (int q = 0; q < IPT; ++q)
+      if (mine[q]) {
+        store_dg(slot_out, q, false);
+        store_dg(slot_old, q, true);
+      }
+  };
+  publish(p.published);   // travels while the weights are fetched
+
+  // resident weights: the forward rows of this workgroup's units, and the rows of W_hh^T for the same units
+  typename M::Frag wx[FWD ? NRTW : 1][FWD ? NXW : 1], wh[FWD ? NRTW : 1][FWD ? NHW : 1], wb[NTB][NBW - NBL > 0 ? NBW - NBL : 1];
+  if constexpr (FWD) {
+#pragma unroll
+    for (int rt = 0; rt < NRTW; ++rt) {
+      const int row_tile = min(rank * NRT + min(rt0 + rt, NRT - 1), p.HP / 4 - 1);
+      const T* base = reinterpret_cast<const T*>(p.Wp) + ((size_t)row_tile * nstepsF * 64 + lane) * VEC;
+#pragma unroll
+      for (int i = 0; i < NXW; ++i) {
+        const int s = fk + KSF * i;
+        wx[rt][i] = M::load(base + (size_t)min(s, nsx - 1) * FRAG);
+        if (s >= nsx) wx[rt][i] = typename M::Frag{};
+      }
+#pragma unroll
+      for (int i = 0; i < NHW; ++i) {
+        const int m = mh0 + KSF * i;
+        wh[rt][i] = M::load(base + (size_t)(nsx + min(m, nsh - 1)) * FRAG);
+        if (m >= nsh) wh[rt][i] = typename M::Frag{};
+      }
+    }
+  }
+#pragma unroll
+  for (int tb = 0; tb < NTB; ++tb) {
+    const int n = min(rank * UW + min(tb * 16 + lrow, UW - 1), p.HP - 1);   // this lane's row (a row past the units is never used)
+    const T* base = reinterpret_cast<const T*>(p.WTh) + ((size_t)(n >> 4) * nstepsB * 64 + lq * 16 + (n & 15)) * VEC;
+#pragma unroll
+    for (int k = 0; k < NBW; ++k) {
+      const int m = bk + KSB * k;
+      typename M::Frag f = M::load(base + (size_t)min(m, nstepsB - 1) * FRAG);
+      if (m >= nstepsB) f = typename M::Frag{};
+      if (k < NBW - NBL)
+        wb[tb][k < NBW - NBL ? k : 0] = f;
+      else
+        *reinterpret_cast<typename M::Frag*>(&wl[((size_t)(wave * NTB + tb) * NBL + (k - (NBW - NBL))) * FRAG + lane * VEC]) = f;
+    }
+  }
+
+  // where this lane's operands come from.  Columns of a tile that belong to no sequence of this XCD read
+  // the first one's rows and fetch no dG.
+  unsigned xrow[BTWF], hsrc[BTWF], goff[BTWB];
+#pragma unroll
+  for (int t = 0; t < BTWF; ++t) {
+    const int b = (ct0 + btf0 + t) * 16 + lrow, row = (b >= b_lo && b < b_hi) ? b : b_lo;
+    xrow[t] = (unsigned)(row * p.I);
+    hsrc[t] = SPLIT ? (unsigned)(min(ct0 + btf0 + t, nbt_all - 1) * nsh * FRAG + lane * VEC) : (unsigned)(row * p.H);
+  }
+#pragma unroll
+  for (int t = 0; t < BTWB; ++t) {
+    const int b = (ct0 + btb0 + t) * 16 + lrow;
+    goff[t] = (b >= b_lo && b < b_hi) ? (unsigned)((min(ct0 + btb0 + t, nbt_all - 1) * nstepsB * 64 + lane) * 16) : RES_NO_LANE;
+  }
+
+  // what the next lower step needs, fetched a step ahead: raw x values and h fragments, or the stored
+  // internal state; c_{s-1}, h_{s-1}, the loss gradient
+  RawAct<VEC> xraw[FWD ? NXW : 1][BTWF];
+  typename M::Frag hfr[(FWD && SPLIT) ? NHW : 1][BTWF];
+  RawAct<VEC> hraw[(FWD && !SPLIT) ? NHW : 1][BTWF];
+  float pf_gate[IPT][4], pf_c[IPT], pf_h[IPT], pf_cprev[IPT], pf_hprev[IPT], pf_dy[IPT];
+  const bool want_h = p.dy_is_h || p.y_out != nullptr;
+  auto fetch = [&](int j) {
+    const int s = p.s_hi - j;
+    const float* src = p.src[j];
+    if constexpr (FWD) {
+      const float* x_s = p.x + (size_t)(s - 1) * p.B * p.I;
+#pragma unroll
+      for (int t = 0; t < BTWF; ++t) {
+#pragma unroll
+        for (int i = 0; i < NXW; ++i) xraw[i][t] = load_window<VEC>(x_s, xrow[t], (fk + KSF * i) * KSTEP + VEC * lq, p.I);
+#pragma unroll
+        for (int i = 0; i < NHW; ++i) {
+          const int m = mh0 + KSF * i;
+          if constexpr (SPLIT)
+            hfr[i][t] = M::load(reinterpret_cast<const T*>(src) + (size_t)min(m, nsh - 1) * FRAG + (size_t)hsrc[t]);
+          else
+            hraw[i][t] = load_window<VEC>(src, hsrc[t], m * KSTEP + VEC * lq, p.H);
+        }
+      }
+    }
+    const float* stp = FWD ? src : p.state[j];
+#pragma unroll
+    for (int q = 0; q < IPT; ++q) {
+      if constexpr (!FWD) {
+        pf_gate[q][0] = (stp + p.unit)[(size_t)ie[q]];
+        pf_gate[q][1] = (stp + p.unit + plane)[(size_t)ie[q]];
+        pf_gate[q][2] = (stp + 2 * p.unit)[(size_t)ie[q]];
+        if (CELL == 0) pf_gate[q][3] = (stp + 2 * p.unit + plane)[(size_t)ie[q]];   // the GRU has three gates
+        pf_c[q] = (stp + p.hplane)[(size_t)ie[q]];                                 // c_s, or the GRU's n_h
+        if (want_h) pf_h[q] = load_h<T>(stp, ie[q], io[q], hhalf);
+      }
+      // what the pointwise step blends with: c_{s-1}, or the GRU's h_{s-1} in full precision
+      pf_cprev[q] = CELL ? load_h<T>(src, ie[q], io[q], hhalf) : (src + p.hplane)[(size_t)ie[q]];
+      pf_hprev[q] = load_h_operand<T>(src, ie[q], io[q]);
+      pf_dy[q] = 0.0f;
+    }
+    if (p.dy != nullptr && s >= p.dy_first) {
+      const float* dy_s = p.dy + (size_t)(s - p.dy_first) * plane;
+#pragma unroll
+      for (int q = 0; q < IPT; ++q) pf_dy[q] = dy_s[(size_t)ie[q]];
+    }
+  };
+  // Makes the fetched step the current one: its forward operation (FWD; a barrier inside), or its stored state.
+  auto advance = [&]() {
+    if constexpr (FWD) {
+      f32x4 acc[NRTW][BTWF];
+#pragma unroll
+      for (int rt = 0; rt < NRTW; ++rt)
+#pragma unroll
+        for (int t = 0; t < BTWF; ++t) acc[rt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < NXW; ++i) {
+        const int s = fk + KSF * i;
+        if ((s + 1) * KSTEP > p.I) {
+#pragma unroll
+          for (int t = 0; t < BTWF; ++t) shift_tail<VEC>(xraw[i][t], s * KSTEP + VEC * lq, p.I);
+        }
+#pragma unroll
+        for (int t = 0; t < BTWF; ++t) {
+          const typename M::Frag f = M::from_f32(xraw[i][t].v);
+#pragma unroll
+          for (int rt = 0; rt < NRTW; ++rt) acc[rt][t] = M::mma(wx[rt][i], f, acc[rt][t]);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < NHW; ++i) {
+        const int m = mh0 + KSF * i;
+#pragma unroll
+        for (int t = 0; t < BTWF; ++t) {
+          typename M::Frag f;
+          if constexpr (SPLIT) {
+            f = hfr[i][t];
+            if (m >= nsh) f = typename M::Frag{};
+          } else {
+            if ((m + 1) * KSTEP > p.H) shift_tail<VEC>(hraw[i][t], m * KSTEP + VEC * lq, p.H);
+            f = M::from_f32(hraw[i][t].v);
+          }
+#pragma unroll
+          for (int rt = 0; rt < NRTW; ++rt) acc[rt][t] = M::mma(wh[rt][i], f, acc[rt][t]);
+        }
+      }
+#pragma unroll
+      for (int rt = 0; rt < NRTW; ++rt)
+        if (rt0 + rt < NRT) {
+#pragma unroll
+          for (int t = 0; t < BTWF; ++t) redF[(fk * NTF + (rt0 + rt) * NBT + btf0 + t) * 64 + lane] = acc[rt][t];
+        }
+      lds_barrier();
+    }
+#pragma unroll
+    for (int q = 0; q < IPT; ++q) {
+      st_cprev[q] = pf_cprev[q];
+      st_hprev[q] = pf_hprev[q];
+      st_dy[q] = pf_dy[q];
+      if constexpr (FWD) {
+        if (!mine[q]) continue;
+        const int item = (int)threadIdx.x + q * 512;
+        float G[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < KSF; ++w) {   // fixed order, as in forward_body
+          const f32x4 v = redF[w * NTF * 64 + item];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) G[r] += v[r];
+        }
+        st_h[q] = cell_forward<CELL>(G, bias[q], st_cprev[q], st_c[q], st_gate[q]);
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) st_gate[q][r] = pf_gate[q][r];
+        st_c[q] = pf_c[q];
+        st_h[q] = pf_h[q];
+      }
+    }
+  };
+  // What only later launches read of step s: dG in the chunk buffer, the transposed copies for the weight
+  // gradient, the output.
+  auto store_kept = [&](int s) {
+    const int slot = (s - 1) % p.CH, buf = ((s - 1) / p.CH) & 1;   // where step s lives in the chunk buffers
+    T* dG_cur = reinterpret_cast<T*>(p.dG_chunk[buf]) + (size_t)slot * dG_step;
+    T* dGT = reinterpret_cast<T*>(p.dGT[buf]);
+    T* aT = reinterpret_cast<T*>(p.aT[buf]);
+    float* y_s = p.y_out ? p.y_out + (size_t)(s - 1) * plane : nullptr;
+    const int ncs = p.KC / KSTEP;
+#pragma unroll
+    for (int q = 0; q < IPT; ++q) {
+      if (!real[q]) continue;
+      const int item = (int)threadIdx.x + q * 512, tile = item >> 6, il = item & 63;
+      const int b = (ct0 + tile % NBT) * 16 + (il & 15), n = rank * UW + tile / NBT * 4 + (il >> 4);
+      const int col = slot * p.B + b;
+      store_dg(dG_cur, q, false);
+      union { unsigned u[sizeof(T)]; T t[4]; } pk;
+#pragma unroll
+      for (int i = 0; i < (int)sizeof(T); ++i) pk.u[i] = dg[q][i];
+      // rows 4n .. 4n + 3 of one column lie VEC elements apart (they share a 16-row tile)
+      const unsigned o = (unsigned)ft_offset<T>(4 * n, col, ncs);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) dGT[(size_t)(o + r * VEC)] = pk.t[r];
+      aT[(size_t)ft_offset<T>(p.NX + n, col, ncs)] = (T)kp_hprev[q];
+      if (y_s) y_s[(size_t)ie[q]] = kp_h[q];
+    }
+  };
+
+  fetch(0);
+  advance();
+
+  for (int j = 0; j < p.count; ++j) {
+    const int s = p.s_hi - j;                       // the step back-propagated now
+    // dG of step s + 1, all columns of the XCD's sequences
+    typename M::Frag gfr[NBW][BTWB];
+    if (bwd_wave) {
+      const T* slot = reinterpret_cast<const T*>(p.ring) + (size_t)((p.published + (unsigned)j) % RES_RING) * dG_step;
+      WaitBound bound{p.wait_ticks, p.sync + RES_SYNC_STATUS};
+      while (true) {
+        u32x4 raw[NBW][BTWB];
+        unsigned top = 0;
+#pragma unroll
+        for (int k = 0; k < NBW; ++k) {
+          const int m = bk + KSB * k;
+#pragma unroll
+          for (int t = 0; t < BTWB; ++t) raw[k][t] = load_slot_16(slot, m < nstepsB ? goff[t] : RES_NO_LANE, m * 1024);
+        }
+#pragma unroll
+        for (int k = 0; k < NBW; ++k)
+#pragma unroll
+          for (int t = 0; t < BTWB; ++t) {
+            top = max(top, largest_dword(raw[k][t]));
+            gfr[k][t] = as_frag<typename M::Frag>(raw[k][t]);
+          }
+        if (__builtin_amdgcn_ballot_w64(top == RES_EMPTY) == 0) break;
+        if (bound.expired()) {
+          s_fail = 1;
+          break;
+        }
+        asm volatile("" ::: "memory");   // the next look is another load
+      }
+    }
+    if (j > 0) store_kept(s + 1);
+    fetch(min(j + 1, p.count - 1));
+    __builtin_amdgcn_sched_barrier(0);
+    // dh = dG_{s+1} W_hh for this workgroup's units
+    if (bwd_wave) {
+      f32x4 acc[NTB][BTWB];
+#pragma unroll
+      for (int tb = 0; tb < NTB; ++tb)
+#pragma unroll
+        for (int t = 0; t < BTWB; ++t) acc[tb][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int k = 0; k < NBW; ++k)
+#pragma unroll
+        for (int tb = 0; tb < NTB; ++tb) {
+          typename M::Frag a;
+          if (k < NBW - NBL)
+            a = wb[tb][k < NBW - NBL ? k : 0];
+          else
+            a = M::load(&wl[((size_t)(wave * NTB + tb) * NBL + (k - (NBW - NBL))) * FRAG + lane * VEC]);
+#pragma unroll
+          for (int t = 0; t < BTWB; ++t) acc[tb][t] = M::mma(a, gfr[k][t], acc[tb][t]);
+        }
+#pragma unroll
+      for (int tb = 0; tb < NTB; ++tb)
+#pragma unroll
+        for (int t = 0; t < BTWB; ++t) redB[(bk * NTBT + tb * NBT + btb0 + t) * 64 + lane] = acc[tb][t];
+    }
+    lds_barrier();
+    if (s_fail) return;   // a wave gave up: written before the barrier, so all see it
+    // pointwise backward of step s on the internal state held in registers
+#pragma unroll
+    for (int q = 0; q < IPT; ++q) {
+      if (!mine[q]) continue;
+      const int item = (int)threadIdx.x + q * 512, tile = item >> 6, il = item & 63;
+      const int rt = tile / NBT, bt = tile % NBT;
+      // dh of unit rt*4 + il/16 of the workgroup: register il/16 of lane (rt%4)*16 + il%16 of tile rt/4
+      const float* cell = reinterpret_cast<const float*>(redB + ((rt >> 2) * NBT + bt) * 64 + (rt & 3) * 16 + (il & 15)) + (il >> 4);
+      float dh = 0.0f;
+#pragma unroll
+      for (int w = 0; w < KSB; ++w) dh += cell[w * NTBT * 64 * 4];   // fixed order, as in backward_body
+      dh += p.dy_is_h ? st_h[q] : st_dy[q];
+      float dG[4], dc_out;
+      if (CELL == 0)
+        lstm_backward_point(dh, dc_run[q], st_gate[q][0], st_gate[q][1], st_gate[q][2], st_gate[q][3], st_c[q], st_cprev[q],
+                            dG, dc_out);
+      else   // the running plane carries dh_{s+1} * z_{s+1}, as in backward_body
+        gru_backward_point(__fadd_rn(dh, dc_run[q]), st_gate[q][0], st_gate[q][1], st_gate[q][2], st_c[q], st_cprev[q], dG, dc_out);
+      dc_run[q] = dc_out;
+      union { T t[4]; unsigned u[sizeof(T)]; } pk;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) pk.t[r] = (T)dG[r];
+#pragma unroll
+      for (int i = 0; i < (int)sizeof(T); ++i) dg[q][i] = real[q] ? not_empty(pk.u[i]) : 0u;
+      kp_h[q] = st_h[q];
+      kp_hprev[q] = st_hprev[q];
+    }
+    if (j + 1 < p.count) {
+      publish(p.published + (unsigned)j + 1);
+      if constexpr (!FWD) lds_barrier();   // the partial sums have been read: the next step may overwrite them (FWD: advance() meets)
+      advance();
+    }
+  }
+  store_kept(p.s_hi - p.count + 1);
+#pragma unroll
+  for (int q = 0; q < IPT; ++q)
+    if (real[q]) p.dc[(size_t)ie[q]] = dc_run[q];
+}
+
+template <class T, bool FWD, int NRT, int NXW, int NHW, int KSF, int NBW, int NBL, int KSB, int NBT, int CELL>
+hipError_t launch_sweep_cell(const SweepParams& p, hipStream_t st) {
+  constexpr int NTB = (NRT * 4 + 15) / 16;
+  constexpr size_t lds = ((size_t)KSB * NTB * NBT + (FWD ? (size_t)KSF * NRT * NBT : 0)) * 64 * sizeof(f32x4) +
+                         (size_t)8 * NTB * NBL * 1024;
+  static_assert(lds <= 160 * 1024 - 64, "LDS of a compute unit");
+  auto kernel = sweep_kernel<T, FWD, NRT, NXW, NHW, KSF, NBW, NBL, KSB, NBT, CELL>;
+  static bool configured = false;   // per instantiation; the attribute only has to be set once
+  if (!configured) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    configured = true;
+  }
+  kernel<<<dim3(RES_WGS), dim3(512), lds, st>>>(p);
+  return hipGetLastError();
+}
+
+}  // namespace mebptt

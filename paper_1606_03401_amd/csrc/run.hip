@@ -28,7 +28,7 @@ constexpr size_t ALIGN = 256;
 inline size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
 struct Workspace {
-  size_t Wp, bp, WTh, WTx, state, dWacc, dc, sync, dG[2], dGT[2], aT[2], ring, ring_bytes, stage, total;
+  size_t Wp, bp, WTh, WTx, state, dWacc, dc, sync, dG[2], dGT[2], aT[2], ring, gring, ring_bytes, stage, total;
   size_t total_no_stage;   // what a run that issues no batched recomputation needs (the no-allocation path)
   int stage_steps;         // internal states the stage holds
 };
@@ -62,13 +62,14 @@ Workspace layout(const Dims& d) {
   w.state = take(9 * unit);   // T0 | T1 | core A (3 units) | copy of (h0,c0) | core B (3 units)
   w.dWacc = take(wgrad_accumulator_bytes(d));
   w.dc = take((size_t)d.B * d.H * sizeof(float));
-  w.sync = take(forward_chain_sync_bytes());   // counters and status word of the resident launches: cleared with dc
+  w.sync = take(resident_sync_bytes());   // counters and status word of the resident launches: cleared with dc
   for (int i = 0; i < 2; ++i) w.dG[i] = take((size_t)d.CH * d.BP * d.G4 * op);
   for (int i = 0; i < 2; ++i) w.dGT[i] = take((size_t)d.G4 * d.KC * op);
   for (int i = 0; i < 2; ++i) w.aT[i] = take((size_t)d.NA * d.KC * op);
   w.total_no_stage = off;
-  w.ring_bytes = can_run_forward_chain(d) ? forward_chain_ring_bytes(d) : 0;
-  w.ring = take(w.ring_bytes);
+  w.ring = take(can_run_forward_chain(d) ? forward_chain_ring_bytes(d) : 0);
+  w.gring = take(can_run_backward_sweep(d) || can_run_sweep(d) ? sweep_ring_bytes(d) : 0);
+  w.ring_bytes = off - w.ring;   // both exchange rings
   w.stage_steps = recompute_stage_steps(d);
   w.stage = take((size_t)w.stage_steps * 3 * unit);   // last: nothing ever clears it
   w.total = off;
@@ -451,7 +452,7 @@ int mebptt_run_status(const mebptt_lstm_desc* desc, const void* workspace, size_
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   HIP_TRY(hipStreamSynchronize(st));
   unsigned word = 0;
-  HIP_TRY(hipMemcpy(&word, reinterpret_cast<const char*>(workspace) + w.sync + forward_chain_status_offset(), sizeof word,
+  HIP_TRY(hipMemcpy(&word, reinterpret_cast<const char*>(workspace) + w.sync + resident_status_offset(), sizeof word,
                     hipMemcpyDeviceToHost));
   *status = (int32_t)word;
   return MEBPTT_OK;
@@ -885,8 +886,8 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
   const bool chain_ok = resident_ok && can_run_forward_chain(d);
   constexpr int CHAIN_MIN_STEPS = 2;     // two steps in one launch already beat two launches (measured on the paper's 256-wide model)
   unsigned chain_published = 0;   // states exchanged inside this run's earlier chain launches
-  unsigned chain_base = 0;        // arrivals left in the group counters by this run's earlier chain launches
-  unsigned chain_launches = 0;    // chain launches of this run so far
+  unsigned sweep_published = 0;   // the same for the sweep launches
+  unsigned chain_launches = 0;    // resident launches of this run so far
   bool chain_used = false;
   struct FStep {
     int step;
@@ -960,7 +961,8 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
       a.aT[i] = ws + w.aT[i];
     }
     a.sync = reinterpret_cast<unsigned*>(ws + w.sync);
-    a.base = chain_base;
+    a.ring = ws + w.gring;
+    a.published = sweep_published;
     a.launch = chain_launches;
     a.s_hi = s_hi;
     a.count = n;
@@ -969,7 +971,7 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
     rc = whole_launch(MEBPTT_K_SWEEP, n, st, [&] { return launch_sweep(d, a, st); });
     if (rc) return rc;
     if (use_profiler && g_prof.every_n > 0 && !states) g_prof.sweep_forward_steps += n;
-    chain_base += forward_chain_arrivals(n);
+    sweep_published += (unsigned)n;
     ++chain_launches;
     bwd += n;
     if (!states) fwd += n;
