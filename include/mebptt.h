@@ -271,9 +271,10 @@ size_t mebptt_slot_pool_bytes(const mebptt_lstm_desc* desc, const mebptt_plan_t*
  * that is the working core and the two transient hidden states here.  The rest is what this
  * implementation adds around it: operand copies of the weights in the GEMM type, the running
  * gradients, a dW accumulator, staging of dG / [x; h] for the steps of two chunks of the
- * time-batched weight-gradient GEMM and, on shapes where the way back through a stretch of stored
- * hidden states recomputes the stretch's internal states in one launch (bf16 LSTM, H = 1024), a
- * stage for those internal states (at most 32 of them and at most 48 MiB).  Independent of t and
+ * time-batched weight-gradient GEMM and, on shapes with resident launches (see mebptt_run_status), their
+ * exchange slots and, where the way back through a stretch of stored hidden states recomputes the
+ * stretch's internal states in one launch, a stage for those internal states (at most 32 of them and at
+ * most 48 MiB).  Independent of t and
  * of the budget. */
 size_t mebptt_workspace_bytes(const mebptt_lstm_desc* desc);
 /* Largest budget, in the given kind's unit, whose slot pool fits in budget_bytes (0 if none). */
@@ -338,16 +339,16 @@ int mebptt_run_prepared(const mebptt_lstm_desc* desc, const mebptt_plan_t* plan,
 
 /* Forward operations that follow each other (Algorithm 2's forward loop, and the consecutive
  * single-step pushes of a sub-sequence that fits into memory) are issued as "forward-chain"
- * launches where the shape allows it (bf16 operands, either cell, H a multiple of 128 and gate weights
- * that fit into the registers and LDS of one XCD's compute units): one launch then carries up to
- * 192 steps, keeps the gate weights on the chip, splits the batch over the 8 XCDs and lets the 32
- * compute units of an XCD exchange h through their shared L2.  Where the transposed recurrent
- * weights fit as well (LSTM, H = 128, 256, 512 with I <= H/4 .. H), the runs of "forward operation keeping
- * the internal state, then backward operation" that end every sub-sequence are issued the same way
- * ("sweep" launches, up to 32 pairs, internal states never leaving the registers).  Where only the
- * transposed recurrent weights fit (H = 1024), and for the GRU at every such width, the forward operations of such a run -- they do not
- * depend on each other, every input state being in a slot already -- go out as one "forward-batch"
- * launch that leaves the internal states in the workspace's stage, followed by one sweep launch of
+ * launches where the shape allows it (either operand type and cell, B up to 256, H up to 1024 with bf16 and
+ * 512 with fp32 operands, and gate weights that fit into the registers and LDS of one XCD's compute units; B up to
+ * 128 above H = 512): one launch then carries up to 192 steps, keeps the gate weights on the chip, splits the
+ * batch over the 8 XCDs and lets the 32 compute units of an XCD exchange h through their shared L2.  Where the
+ * transposed recurrent weights fit as well (LSTM; H up to 512 with bf16, 256 with fp32 operands), the runs of
+ * "forward operation keeping the internal state, then backward operation" that end every sub-sequence are issued
+ * the same way ("sweep" launches, up to 32 pairs, internal states never leaving the registers).  Where only the
+ * transposed recurrent weights fit, and for the GRU, the forward operations of such a run -- they do not depend on
+ * each other, every input state being in a slot already -- go out as one "forward-batch" launch that leaves the
+ * internal states in the workspace's stage, followed by one sweep launch of
  * backward operations on them; backward operations on internal states stored in slots go out as
  * such sweep launches as well.  Results are bit-identical to the launch-per-step path.  Such a launch assumes that its 256 workgroups are all resident and dealt
  * round-robin to the XCDs; each workgroup checks this, every wait inside is bounded by a wall
@@ -389,7 +390,7 @@ int mebptt_shutdown(void);
  * The call creates no stream and no event and allocates nothing: every kernel, including the
  * time-batched GEMMs, is enqueued on `stream` in schedule order; the measurement hooks are
  * ignored.  Results are bit-identical to mebptt_run's.  Shapes whose workspace (as
- * mebptt_workspace_bytes() counts it, less the recomputation stage, which this path never uses)
+ * mebptt_workspace_bytes() counts it, less the exchange slots and the recomputation stage, which this path never uses)
  * exceeds the array are refused with EWORKSPACE before anything is enqueued.  All calls on one
  * GPU share the array, which keeps the previous call's contents (the call clears what must start
  * at zero): calls whose device work overlaps on one GPU race -- keep them on one stream or

@@ -16,8 +16,10 @@ PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG_DIR)
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libmebptt.so")
-SOURCES = ["planner.cpp", "chain_planner.cpp", "kernels.hip", "resident.hip", "run.hip", "chain_run.hip",
-           "measure_sync.hip"]
+SOURCES = ["resident_sweep_bf16.hip", "resident_sweep_fp32.hip", "resident_chain_bf16_k4.hip",
+           "resident_chain_bf16_k8.hip", "resident_chain_fp32_k8.hip", "resident_back_bf16.hip",
+           "resident_chain_fp32_k4.hip", "kernels.hip", "run.hip", "resident.hip", "chain_run.hip", "measure_sync.hip",
+           "planner.cpp", "chain_planner.cpp"]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
          "-packed-fp32-ops", "-Wall", "-Wno-unused-command-line-argument", "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 

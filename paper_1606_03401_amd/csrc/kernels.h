@@ -67,9 +67,8 @@ hipError_t launch_forward(const Dims& d, const void* Wp, const float* bp, const 
 
 // n independent forward operations in one launch (n <= forward_batch_max_steps()): operation j reads
 // x[j] and the hidden-state unit src[j] and writes the state and the gates to the three units at
-// dst[j].  Same bits as launch_forward.  bf16 LSTM only (can_run_forward_batch).
+// dst[j].  Same bits as launch_forward.
 int forward_batch_max_steps();
-bool can_run_forward_batch(const Dims& d);
 hipError_t launch_forward_batch(const Dims& d, const void* Wp, const float* bp, int n, const float* const* x,
                                 const float* const* src, float* const* dst, hipStream_t st);
 

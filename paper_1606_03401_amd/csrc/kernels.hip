@@ -716,11 +716,30 @@ __global__ __launch_bounds__(64 * KS) void forward_batch_kernel(FwdParams p, Fwd
 }
 
 int forward_batch_max_steps() { return FWD_BATCH_MAX_STEPS; }
-bool can_run_forward_batch(const Dims& d) { return d.dtype == 1; }
+
+template <class T>
+static void launch_forward_batch_t(const Dims& d, const FwdParams& p, const FwdBatchSteps& steps, int n, hipStream_t st) {
+  // 64 gate rows x 32 sequences per workgroup, two macro steps in flight per wave: two workgroups
+  // fit a compute unit.  Measured on H = 1024, B = 64: 2.7 us per operation; 64 x 64 tiles 3.1 us,
+  // three or four macro steps in flight 4.4 - 5.1 us.
+  constexpr int NG = 4, BT = 2, FU = 2;
+  const dim3 grid((d.HP / 4 + NG - 1) / NG, (d.BP / 16 + BT - 1) / BT, n);
+  const size_t plane = (size_t)d.B * d.H;
+  const FwdConfig cfg = forward_config<T>(d);
+  const bool small_k = cfg == FWD_TINY || cfg == FWD_SMALLK;   // the K split of the shape's stand-alone forward kernel
+  if (small_k && d.cell)
+    forward_batch_kernel<T, NG, BT, 4, FU, 1><<<grid, dim3(64 * 4), 0, st>>>(p, steps, d.hplane, d.unit, plane);
+  else if (small_k)
+    forward_batch_kernel<T, NG, BT, 4, FU, 0><<<grid, dim3(64 * 4), 0, st>>>(p, steps, d.hplane, d.unit, plane);
+  else if (d.cell)
+    forward_batch_kernel<T, NG, BT, 8, FU, 1><<<grid, dim3(64 * 8), 0, st>>>(p, steps, d.hplane, d.unit, plane);
+  else
+    forward_batch_kernel<T, NG, BT, 8, FU, 0><<<grid, dim3(64 * 8), 0, st>>>(p, steps, d.hplane, d.unit, plane);
+}
 
 hipError_t launch_forward_batch(const Dims& d, const void* Wp, const float* bp, int n, const float* const* x,
                                 const float* const* src, float* const* dst, hipStream_t st) {
-  if (!can_run_forward_batch(d) || n < 1 || n > FWD_BATCH_MAX_STEPS) return hipErrorInvalidValue;
+  if (n < 1 || n > FWD_BATCH_MAX_STEPS) return hipErrorInvalidValue;
   FwdParams p = make_fwd_params(d, Wp, bp, x[0], src[0], dst[0], dst[0] + d.unit);
   FwdBatchSteps steps{};
   for (int j = 0; j < n; ++j) {
@@ -728,22 +747,10 @@ hipError_t launch_forward_batch(const Dims& d, const void* Wp, const float* bp, 
     steps.src[j] = src[j];
     steps.dst[j] = dst[j];
   }
-  // 64 gate rows x 32 sequences per workgroup, two macro steps in flight per wave: two workgroups
-  // fit a compute unit.  Measured on H = 1024, B = 64: 2.7 us per operation; 64 x 64 tiles 3.1 us,
-  // three or four macro steps in flight 4.4 - 5.1 us.
-  constexpr int NG = 4, BT = 2, FU = 2;
-  const dim3 grid((d.HP / 4 + NG - 1) / NG, (d.BP / 16 + BT - 1) / BT, n);
-  const size_t plane = (size_t)d.B * d.H;
-  const FwdConfig cfg = forward_config<__bf16>(d);
-  const bool small_k = cfg == FWD_TINY || cfg == FWD_SMALLK;   // the K split of the shape's stand-alone forward kernel
-  if (small_k && d.cell)
-    forward_batch_kernel<__bf16, NG, BT, 4, FU, 1><<<grid, dim3(64 * 4), 0, st>>>(p, steps, d.hplane, d.unit, plane);
-  else if (small_k)
-    forward_batch_kernel<__bf16, NG, BT, 4, FU, 0><<<grid, dim3(64 * 4), 0, st>>>(p, steps, d.hplane, d.unit, plane);
-  else if (d.cell)
-    forward_batch_kernel<__bf16, NG, BT, 8, FU, 1><<<grid, dim3(64 * 8), 0, st>>>(p, steps, d.hplane, d.unit, plane);
+  if (d.dtype)
+    launch_forward_batch_t<__bf16>(d, p, steps, n, st);
   else
-    forward_batch_kernel<__bf16, NG, BT, 8, FU, 0><<<grid, dim3(64 * 8), 0, st>>>(p, steps, d.hplane, d.unit, plane);
+    launch_forward_batch_t<float>(d, p, steps, n, st);
   return hipGetLastError();
 }
 

@@ -468,4 +468,22 @@ hipError_t launch_chain_cell(const ResParams& p, hipStream_t st) {
   return hipGetLastError();
 }
 
+// An instantiation: what it covers (see the kernel) and its launchers by cell.  The tables are split over
+// several sources so that they compile side by side.
+struct ChainConfig {
+  int nrt, nxw, nhw, ks, nbt;
+  hipError_t (*launch[2])(const ResParams&, hipStream_t);
+};
+#define MEBPTT_CHAIN(T, NRT, NXW, NXL, NHW, KS, NBT) \
+  ChainConfig{NRT, NXW, NHW, KS, NBT, {launch_chain_cell<T, NRT, NXW, NXL, NHW, KS, NBT, 0>, launch_chain_cell<T, NRT, NXW, NXL, NHW, KS, NBT, 1>}}
+template <class C>
+struct Table {
+  const C* at;
+  int n;
+};
+Table<ChainConfig> chain_table_bf16_k4();   // K split 4 ways
+Table<ChainConfig> chain_table_bf16_k8();
+Table<ChainConfig> chain_table_fp32_k4();
+Table<ChainConfig> chain_table_fp32_k8();
+
 }  // namespace mebptt

@@ -17,29 +17,40 @@ void set_resident_wait_ticks(long long ticks) { g_wait_ticks = ticks < 0 ? RES_W
 // fewer XCDs work rather than all of them on less).  Returns 0 for a batch that does not fit.
 static int group_share(const Dims& d) { return d.B <= 64 ? 8 : (d.B <= 128 ? 16 : (d.B <= 256 ? 32 : 0)); }
 
-struct ChainConfig {
-  int nrt, nxw, nhw, ks, nbt;
-  hipError_t (*launch[2])(const ResParams&, hipStream_t);   // by cell
+// What a shape asks of an instantiation.
+struct ResidentShape {
+  int nrt, nsx, nsh, ksf, nsb, ksb, nbt;   // units per workgroup / 4; macro steps and K splits; batch tiles per XCD
 };
-#define CHAIN(T, NRT, NXW, NXL, NHW, KS, NBT) \
-  {NRT, NXW, NHW, KS, NBT, {launch_chain_cell<T, NRT, NXW, NXL, NHW, KS, NBT, 0>, launch_chain_cell<T, NRT, NXW, NXL, NHW, KS, NBT, 1>}}
-static const ChainConfig CHAIN_BF16[] = {
-    CHAIN(__bf16, 8, 1, 1, 4, 8, 1),   // H = 1024, I <= 256
-    CHAIN(__bf16, 4, 1, 0, 4, 4, 1), CHAIN(__bf16, 4, 1, 0, 4, 4, 2),   // H = 512, I <= 128
-    CHAIN(__bf16, 2, 2, 0, 2, 4, 1), CHAIN(__bf16, 2, 2, 0, 2, 4, 2),   // H = 256, I <= 256
-    CHAIN(__bf16, 1, 1, 0, 1, 4, 1), CHAIN(__bf16, 1, 1, 0, 1, 4, 2),   // H = 128, I <= 128
-};
+template <class T>
+static bool resident_shape_t(const Dims& d, ResidentShape& s) {
+  const int share = group_share(d), kstep = 4 * Mma<T>::VEC;
+  if (share == 0 || d.H < 8) return false;
+  const FwdConfig fc = forward_config<T>(d);
+  s.nrt = (d.KH + 127) / 128;
+  s.nsx = d.KX / kstep;
+  s.nsh = d.KH / kstep;
+  s.nsb = d.G4 / kstep;
+  s.ksf = (fc == FWD_TINY || fc == FWD_SMALLK) ? 4 : 8;   // the K splits of the per-step kernels
+  s.ksb = backward_config<T>(d) == BWD_SMALLK ? 4 : 8;
+  s.nbt = share > 16 ? 2 : 1;
+  return true;
+}
+static bool resident_shape(const Dims& d, ResidentShape& s) {
+  return d.dtype ? resident_shape_t<__bf16>(d, s) : resident_shape_t<float>(d, s);
+}
+// A row of x is fetched in windows of 16 bytes of operands: it has to be at least that long.
+static bool x_wide_enough(const Dims& d) { return d.I >= (d.dtype ? 8 : 4); }
 
-// The smallest instantiation the shape fits, or NULL.
+// The smallest instantiation the shape fits (a table lists them in rising order of x width), or NULL.
 static const ChainConfig* chain_config(const Dims& d) {
-  if (!d.dtype || d.I < 8) return nullptr;
-  const int kstep = 32, nsx = d.KX / kstep, nsh = d.KH / kstep, nrt = (d.KH + 127) / 128;
-  const FwdConfig fc = forward_config<__bf16>(d);
-  const int ks = (fc == FWD_TINY || fc == FWD_SMALLK) ? 4 : 8;   // the K split of the per-step kernels
-  const int share = group_share(d), nbt = share > 16 ? 2 : 1;
-  if (share == 0) return nullptr;
-  for (const ChainConfig& c : CHAIN_BF16)
-    if (c.nrt == nrt && c.ks == ks && c.nbt == nbt && c.nhw * ks >= nsh && c.nxw * ks >= nsx) return &c;
+  ResidentShape s;
+  if (!x_wide_enough(d) || !resident_shape(d, s)) return nullptr;
+  const Table<ChainConfig> table = d.dtype ? (s.ksf == 4 ? chain_table_bf16_k4() : chain_table_bf16_k8())
+                                           : (s.ksf == 4 ? chain_table_fp32_k4() : chain_table_fp32_k8());
+  for (int i = 0; i < table.n; ++i) {
+    const ChainConfig& c = table.at[i];
+    if (c.nrt == s.nrt && c.ks == s.ksf && c.nbt == s.nbt && c.nhw * s.ksf >= s.nsh && c.nxw * s.ksf >= s.nsx) return &c;
+  }
   return nullptr;
 }
 
@@ -80,64 +91,28 @@ hipError_t launch_forward_chain(const Dims& d, const void* Wp, const float* bp, 
 }
 
 // ---- which shapes have sweeps ------------------------------------------------------------------------------
-struct SweepConfig {
-  int nrt, nxw, nhw, ksf, nbw, ksb, nbt;
-  hipError_t (*launch)(const SweepParams&, hipStream_t);
-};
-#define SWEEP(T, NRT, NXW, NHW, KSF, NBW, NBL, KSB, NBT) \
-  {NRT, NXW, NHW, KSF, NBW, KSB, NBT, launch_sweep_cell<T, true, NRT, NXW, NHW, KSF, NBW, NBL, KSB, NBT, 0>}
-static const SweepConfig SWEEP_BF16[] = {
-    SWEEP(__bf16, 4, 1, 4, 4, 8, 0, 8, 1), SWEEP(__bf16, 4, 1, 4, 4, 8, 8, 8, 2),   // H = 512, I <= 128
-    SWEEP(__bf16, 2, 2, 2, 4, 4, 0, 8, 1), SWEEP(__bf16, 2, 2, 2, 4, 4, 0, 8, 2),   // H = 256, I <= 256
-    SWEEP(__bf16, 1, 1, 1, 4, 4, 0, 4, 1), SWEEP(__bf16, 1, 1, 1, 4, 4, 0, 4, 2),   // H = 128, I <= 128
-};
-struct BackSweepConfig {
-  int nrt, nbw, ksb, nbt;
-  hipError_t (*launch[2])(const SweepParams&, hipStream_t);   // by cell
-};
-#define BACK_SWEEP(T, NRT, NBW, NBL, KSB, NBT)                                           \
-  {NRT, NBW, KSB, NBT, {launch_sweep_cell<T, false, NRT, 1, 1, 8, NBW, NBL, KSB, NBT, 0>, \
-                        launch_sweep_cell<T, false, NRT, 1, 1, 8, NBW, NBL, KSB, NBT, 1>}}
-static const BackSweepConfig BACK_SWEEP_BF16[] = {
-    BACK_SWEEP(__bf16, 8, 16, 4, 8, 1),                                        // H = 1024
-    BACK_SWEEP(__bf16, 4, 8, 0, 8, 1), BACK_SWEEP(__bf16, 4, 8, 0, 8, 2),         // H = 512
-    BACK_SWEEP(__bf16, 2, 4, 0, 8, 1), BACK_SWEEP(__bf16, 2, 4, 0, 8, 2),         // H = 256
-    BACK_SWEEP(__bf16, 1, 4, 0, 4, 1), BACK_SWEEP(__bf16, 1, 4, 0, 4, 2),         // H = 128
-};
-
-struct SweepShape {
-  int nrt, nsx, nsh, ksf, nsb, ksb, nbt;
-};
-static bool sweep_shape(const Dims& d, SweepShape& s) {
-  const int share = group_share(d);
-  if (!d.dtype || share == 0) return false;
-  const int kstep = 32;
-  const FwdConfig fc = forward_config<__bf16>(d);
-  s.nrt = (d.KH + 127) / 128;
-  s.nsx = d.KX / kstep;
-  s.nsh = d.KH / kstep;
-  s.nsb = d.G4 / kstep;
-  s.ksf = (fc == FWD_TINY || fc == FWD_SMALLK) ? 4 : 8;   // the K splits of the per-step kernels
-  s.ksb = backward_config<__bf16>(d) == BWD_SMALLK ? 4 : 8;
-  s.nbt = share > 16 ? 2 : 1;
-  return true;
-}
 static const SweepConfig* sweep_config(const Dims& d) {   // with forward operations: LSTM only
-  SweepShape s;
-  if (d.cell || d.I < 8 || !sweep_shape(d, s)) return nullptr;
-  for (const SweepConfig& c : SWEEP_BF16)
+  ResidentShape s;
+  if (d.cell || !x_wide_enough(d) || !resident_shape(d, s)) return nullptr;
+  const Table<SweepConfig> table = d.dtype ? sweep_table_bf16() : sweep_table_fp32();
+  for (int i = 0; i < table.n; ++i) {
+    const SweepConfig& c = table.at[i];
     if (c.nrt == s.nrt && c.ksf == s.ksf && c.ksb == s.ksb && c.nbt == s.nbt && c.nxw * s.ksf >= s.nsx &&
         c.nhw * s.ksf >= s.nsh && c.nbw * s.ksb >= s.nsb)
       return &c;
+  }
   return nullptr;
 }
 // For launches of backward operations on stored internal states, which read neither x nor the gate weights:
 // any input width.
 static const BackSweepConfig* back_sweep_config(const Dims& d) {
-  SweepShape s;
-  if (!sweep_shape(d, s)) return nullptr;
-  for (const BackSweepConfig& c : BACK_SWEEP_BF16)
+  ResidentShape s;
+  if (!resident_shape(d, s)) return nullptr;
+  const Table<BackSweepConfig> table = d.dtype ? back_sweep_table_bf16() : back_sweep_table_fp32();
+  for (int i = 0; i < table.n; ++i) {
+    const BackSweepConfig& c = table.at[i];
     if (c.nrt == s.nrt && c.ksb == s.ksb && c.nbt == s.nbt && c.nbw * s.ksb >= s.nsb) return &c;
+  }
   return nullptr;
 }
 

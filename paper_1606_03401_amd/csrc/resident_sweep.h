@@ -466,4 +466,22 @@ hipError_t launch_sweep_cell(const SweepParams& p, hipStream_t st) {
   return hipGetLastError();
 }
 
+struct SweepConfig {   // with forward operations: LSTM only
+  int nrt, nxw, nhw, ksf, nbw, ksb, nbt;
+  hipError_t (*launch)(const SweepParams&, hipStream_t);
+};
+#define MEBPTT_SWEEP(T, NRT, NXW, NHW, KSF, NBW, NBL, KSB, NBT) \
+  SweepConfig{NRT, NXW, NHW, KSF, NBW, KSB, NBT, launch_sweep_cell<T, true, NRT, NXW, NHW, KSF, NBW, NBL, KSB, NBT, 0>}
+struct BackSweepConfig {
+  int nrt, nbw, ksb, nbt;
+  hipError_t (*launch[2])(const SweepParams&, hipStream_t);   // by cell
+};
+#define MEBPTT_BACK_SWEEP(T, NRT, NBW, NBL, KSB, NBT)                                                     \
+  BackSweepConfig{NRT, NBW, KSB, NBT, {launch_sweep_cell<T, false, NRT, 1, 1, 8, NBW, NBL, KSB, NBT, 0>, \
+                                       launch_sweep_cell<T, false, NRT, 1, 1, 8, NBW, NBL, KSB, NBT, 1>}}
+Table<SweepConfig> sweep_table_bf16();
+Table<SweepConfig> sweep_table_fp32();
+Table<BackSweepConfig> back_sweep_table_bf16();
+Table<BackSweepConfig> back_sweep_table_fp32();
+
 }  // namespace mebptt

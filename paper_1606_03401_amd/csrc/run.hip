@@ -29,7 +29,7 @@ inline size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
 struct Workspace {
   size_t Wp, bp, WTh, WTx, state, dWacc, dc, sync, dG[2], dGT[2], aT[2], ring, gring, ring_bytes, stage, total;
-  size_t total_no_stage;   // what a run that issues no batched recomputation needs (the no-allocation path)
+  size_t total_no_stage;   // what a run without resident launches needs (the no-allocation path): no rings, no stage
   int stage_steps;         // internal states the stage holds
 };
 
@@ -39,7 +39,7 @@ struct Workspace {
 // against 189 ms per gradient step).
 constexpr size_t STAGE_MAX_BYTES = (size_t)48 << 20;
 int recompute_stage_steps(const Dims& d) {
-  if (!can_run_forward_batch(d) || !can_run_backward_sweep(d) || can_run_sweep(d)) return 0;
+  if (!can_run_backward_sweep(d) || can_run_sweep(d)) return 0;
   const size_t state_bytes = 3 * d.unit * sizeof(float);
   const int n = (int)std::min<size_t>(STAGE_MAX_BYTES / state_bytes, (size_t)std::min(sweep_max_steps(), forward_batch_max_steps()));
   return n >= 4 ? n : 0;
@@ -671,7 +671,7 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
                      mebptt_slot_pool_bytes(desc, plan));
   const Dims d = make_dims(desc->B, desc->I, desc->H, desc->gemm_dtype, desc->cell);
   const Workspace w = layout(d);
-  const size_t ws_need = mode == RUN_STATIC ? w.total_no_stage : w.total;   // the no-allocation path never uses the stage
+  const size_t ws_need = mode == RUN_STATIC ? w.total_no_stage : w.total;   // the no-allocation path has no rings and no stage
   if (workspace_bytes < ws_need)
     return set_error(MEBPTT_EWORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, ws_need);
   if (misaligned(slots, ALIGN) || misaligned(workspace, ALIGN))

@@ -336,3 +336,57 @@ def test_random_shapes_budgets_and_strategies_bit_identical():
         _same(got, base, what)
         for f in FIELDS:
             assert np.all(np.isfinite(getattr(got, f))), (what, f)
+
+
+# (B, I, H, core) around the edges of the resident instantiations: units that do not divide by 32 or by the
+# compute units of an XCD, x rows that end inside a 16-byte window, inputs wider than the state, batches
+# that leave XCDs idle or take two MFMA tiles per XCD.
+EDGE_BF16 = [
+    (4, 16, 32, 0), (5, 8, 9, 0), (64, 600, 100, 0), (70, 1000, 64, 0), (3, 2000, 128, 0), (37, 100, 200, 0), (130, 300, 200, 0),
+    (20, 960, 160, 0), (20, 200, 384, 0), (200, 300, 300, 0), (40, 700, 384, 0), (20, 200, 500, 0), (150, 180, 512, 0),
+    (16, 512, 512, 0), (200, 1000, 500, 0), (24, 90, 600, 0), (24, 512, 576, 0), (20, 650, 650, 0), (128, 300, 700, 0),
+    (33, 1000, 768, 0), (17, 128, 896, 0), (17, 500, 800, 0), (100, 200, 1000, 0), (37, 100, 200, 1), (65, 77, 333, 1), (20, 650, 650, 1),
+]
+EDGE_FP32 = [
+    (4, 16, 32, 0), (9, 100, 50, 0), (64, 256, 60, 0), (130, 4, 64, 0), (30, 64, 100, 0), (20, 500, 128, 0), (20, 900, 70, 0),
+    (32, 64, 256, 0), (32, 128, 256, 0), (150, 300, 200, 0), (20, 700, 256, 0), (8, 32, 288, 0), (16, 200, 384, 0),
+    (32, 200, 500, 0), (16, 1000, 512, 0), (200, 300, 512, 0), (9, 101, 50, 1), (16, 203, 301, 1),
+]
+
+
+@pytest.mark.parametrize("dtype,B,I,H,cell", [(wl.GEMM_BF16, *s) for s in EDGE_BF16] + [(wl.GEMM_FP32, *s) for s in EDGE_FP32])
+def test_resident_launches_at_the_edges_of_their_shapes(dtype, B, I, H, cell):
+    from paper_1606_03401_amd.session import Session
+    t = 37
+    w = wl.Workload("edge", B=B, I=I, H=H, t=t, kind=wl.KIND_HSM, m=5, gemm_dtype=dtype, loss=wl.LOSS_EXTERNAL_DY,
+                    dy_first_step=3, seed=4000 + B + I + H, cell=cell)
+    inp = wl.make_inputs(w, nonzero_state=True, nonzero_bias=True)
+    base = _run(w, inp, wl.KIND_HSM, 5, chain=False)
+    for kind, m in ((wl.KIND_HSM, 5), (wl.KIND_HSM, t), (wl.KIND_ISM, t), (wl.KIND_MSM, 13)):
+        s = Session(w, inp, kind=kind, m=m)
+        mb.mebptt_profile_enable(1)
+        out = s.run_and_fetch()
+        prof = mb.mebptt_profile_collect()
+        mb.mebptt_profile_enable(0)
+        _same(out, base, (kind, m))
+        assert mb.mebptt_run_status(s.desc, s.workspace) == 0
+        assert prof.chain_steps > 0          # the shape really runs as resident launches
+
+
+@pytest.mark.parametrize("dtype,B,I,H", [(wl.GEMM_BF16, 20, 40, 200), (wl.GEMM_FP32, 20, 40, 72), (wl.GEMM_BF16, 64, 64, 1024)])
+def test_resident_launches_pass_on_every_nan(dtype, B, I, H):
+    """The exchange marks what has not arrived by a bit pattern that is a NaN: an input that produces
+    exactly that NaN must neither stall a launch nor reach a sequence it does not belong to."""
+    w = wl.Workload("nan", B=B, I=I, H=H, t=24, kind=wl.KIND_HSM, m=6, gemm_dtype=dtype, loss=wl.LOSS_EXTERNAL_DY, seed=5)
+    inp = wl.make_inputs(w, nonzero_state=True, nonzero_bias=True)
+    clean = _run(w, inp, wl.KIND_HSM, 6, chain=True)
+    bad = 11
+    inp.x[2, bad] = np.uint32(0xFFFFFFFF).view(np.float32)
+    inp.h0[bad + 1] = np.uint32(0xFFFFFFFF).view(np.float32)
+    inp.x[3, bad + 2, 0] = np.inf
+    base = _run(w, inp, wl.KIND_HSM, 6, chain=False)
+    out = _run(w, inp, wl.KIND_HSM, 6, chain=True)        # raises if a launch gave up
+    others = [b for b in range(B) if b not in (bad, bad + 1, bad + 2)]
+    assert np.array_equal(out.y[:, others], clean.y[:, others]) and np.array_equal(out.dx[:, others], clean.dx[:, others])
+    assert np.isnan(out.y[2:, bad]).all()
+    assert np.array_equal(np.isnan(out.y), np.isnan(base.y)) and np.array_equal(out.y[:, bad + 2], base.y[:, bad + 2], equal_nan=True)
