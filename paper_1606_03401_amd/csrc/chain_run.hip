@@ -6,13 +6,14 @@
 // assigned; everything else (the two most recent activations of a forward run, the gradient being
 // passed down, one layer's dz) is working memory in the caller's workspace, outside the budget.
 //
-// All three products of a layer are written as D[i][j] = sum_k A(i,k) B(k,j) with strided
-// operands and executed by one kernel on fp32 MFMA tiles (v_mfma_f32_16x16x4_f32, fp32
-// accumulate):
-//   forward        y   [B, d_i]      = y_{i-1} [B, d_{i-1}] . W_i^T            then + b, tanh
-//   backward data  g'  [B, d_{i-1}]  = dz [B, d_i] . W_i
-//   backward weight dW [d_i, d_{i-1}] = dz^T . y_{i-1}                          (K = B)
-// with dz = g * (1 - y_i^2) and db = column sums of dz.
+// All three products of a layer run in one kernel body on fp32 MFMA tiles (v_mfma_f32_16x16x4_f32, fp32
+// accumulate), operands read in place whichever way they are stored:
+//   forward         y    [B, d_i]       = y_{i-1} [B, d_{i-1}] . W_i^T              then + b, tanh
+//   backward data   dz'  [B, d_{i-1}]   = dz [B, d_i] . W_i                         then * (1 - y_{i-1}^2)
+//   backward weight dW   [d_i, d_{i-1}] = dz^T . y_{i-1}                            (K = B), db = column sums of dz
+// The epilogue of the data product turns the gradient with respect to y_{i-1} into dz of the layer below at
+// once; only the last layer's dz has a launch of its own.  The two backward products of a layer need
+// nothing from each other and share a launch.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -26,40 +27,204 @@ namespace {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-enum { EPI_STORE = 0, EPI_BIAS_TANH = 1 };
+// D[i][j] = sum_k A(i,k) B(j,k).  An operand is stored along k (element (i, k) at i * ld + k) or across it
+// (at k * ld + i); ld in floats, rows need a float's alignment only.
+struct Product {
+  const float *A, *Bm;
+  long lda, ldb;
+  float *C, *C2;          // C2: a second copy of the result, or NULL
+  long ldc;
+  int M, N, K;
+  const float* bias;      // BIAS_TANH: added to column j, or NULL
+  const float* y;         // TIMES_DTANH: [M][ldc] values v of a tanh, the result is multiplied by 1 - v^2; NULL: stored as is
+  float* db;              // A's sums over k, or NULL
+  int gx;                 // workgroups along j
+};
+enum { BIAS_TANH, TIMES_DTANH, STORE_AND_DB };
+constexpr int KS = 8;     // waves of a workgroup, which split K
 
-// One wave per 16 x 16 output tile, four waves (2 x 2 tiles) per workgroup.
-// A(i, k) = A[i * sai + k * sak], B(k, j) = Bm[k * sbk + j * sbj], C[i * ldc + j].
-__global__ __launch_bounds__(256) void chain_gemm_kernel(const float* __restrict__ A, long sai, long sak,
-                                                         const float* __restrict__ Bm, long sbk, long sbj,
-                                                         float* __restrict__ C, long ldc, int M, int N, int K,
-                                                         const float* __restrict__ bias, int epilogue) {
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;   // scalar: conditions on it are scalar branches (an MFMA under an empty lane mask would still execute)
-  const int i0 = (blockIdx.y * 2 + (wave >> 1)) * 16, j0 = (blockIdx.x * 2 + (wave & 1)) * 16;
-  if (i0 >= M || j0 >= N) return;   // whole wave
-  const int li = lane & 15, lk = lane >> 4;
-  const int ia = min(i0 + li, M - 1), jb = min(j0 + li, N - 1);   // clamped rows/columns are never stored
-  const float* ap = A + (long)ia * sai;
-  const float* bp = Bm + (long)jb * sbj;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int k = 0; k < K; k += 4) {
-    const int kk = k + lk;
-    const float a = kk < K ? ap[(long)kk * sak] : 0.0f;
-    const float b = kk < K ? bp[(long)kk * sbk] : 0.0f;
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0);
-  }
-  // lane holds D[4 * (lane / 16) + r][lane % 16]
-  const int j = j0 + li;
-  if (j >= N) return;
-  const float bj = (epilogue == EPI_BIAS_TANH && bias) ? bias[j] : 0.0f;
+// 4 values of k (4*lq .. +3 of the macro step at k0) for T tiles of 16 rows.  Operands stored along k: tile t's
+// row lrow is row r0 + 16 t + lrow, one 16-byte load per tile.  Stored across k: the rows are dealt so that a
+// lane's T rows are neighbours, row r0 + T * lrow + t, one T-wide load per k.  Rows past the end repeat rows
+// before it (moved as a window in the second case): their results are the same values, stored twice or
+// not at all.  TAIL: the macro step runs over K; surplus values are zero.  NARROW: fewer rows (or fewer k)
+// than a vector: value by value.
+template <bool ACROSS, int T, bool TAIL, bool NARROW>
+__device__ inline void fetch_tiles(float (&v)[T][4], const float* __restrict__ base, long ld, int r0, int rows, int k0, int K, int lrow,
+                                   int lq) {
+  typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+  typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));
+  if constexpr (!ACROSS) {
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int i = i0 + 4 * lk + r;
-    if (i >= M) continue;
-    float v = acc[r];
-    if (epilogue == EPI_BIAS_TANH) v = tanhf(v + bj);
-    C[(long)i * ldc + j] = v;
+    for (int t = 0; t < T; ++t) {
+      const float* row = base + (long)min(r0 + 16 * t + lrow, rows - 1) * ld;
+      if constexpr (TAIL || NARROW) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int k = k0 + 4 * lq + e;
+          const float x = row[min(k, K - 1)];
+          v[t][e] = k < K ? x : 0.0f;
+        }
+      } else {
+        const f4u x = *reinterpret_cast<const f4u*>(row + k0 + 4 * lq);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[t][e] = x[e];
+      }
+    }
+  } else {
+    const int c = min(r0 + T * lrow, rows - T);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int k = k0 + 4 * lq + e;
+      const float* p = base + (long)(TAIL ? min(k, K - 1) : k) * ld;
+      if constexpr (NARROW) {
+#pragma unroll
+        for (int t = 0; t < T; ++t) v[t][e] = p[max(min(c + t, rows - 1), 0)];
+      } else if constexpr (T == 4) {
+        const f4u x = *reinterpret_cast<const f4u*>(p + c);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[t][e] = x[t];
+      } else if constexpr (T == 2) {
+        const f2u x = *reinterpret_cast<const f2u*>(p + c);
+        v[0][e] = x[0];
+        v[1][e] = x[1];
+      } else {
+        v[0][e] = p[c];
+      }
+      if constexpr (TAIL) {
+#pragma unroll
+        for (int t = 0; t < T; ++t) v[t][e] = k < K ? v[t][e] : 0.0f;
+      }
+    }
   }
+}
+// The row of an operand that tile t's row x stands for.
+template <bool ACROSS, int T>
+__device__ inline int tile_row(int r0, int rows, int t, int x) {
+  return ACROSS ? max(min(r0 + T * x, rows - T), 0) + t : r0 + 16 * t + x;
+}
+
+// One workgroup of 8 waves = TM x TN tiles of 16 x 16 outputs.  The waves split K in macro steps of 16, every
+// wave covering all outputs (no operand byte is fetched twice by a workgroup, no barrier inside the loop), two
+// macro steps in flight; partial sums meet in LDS and are added in a fixed order.
+template <bool A_ACROSS, bool B_ACROSS, int TM, int TN, int EPI, bool NARROW>
+__device__ inline void product_body(const Product& p, int id, float* red) {
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;   // scalar: conditions on it are scalar branches
+  const int lrow = lane & 15, lq = lane >> 4;
+  const int bx = id % p.gx, by = id / p.gx;
+  const int i0 = by * TM * 16, j0 = bx * TN * 16;
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float rowsum[TM];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) rowsum[i] = 0.0f;
+  const bool sums = EPI == STORE_AND_DB && p.db != nullptr && bx == 0;
+  auto use = [&](const float (&a)[TM][4], const float (&b)[TN][4]) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[j][e], acc[i][j], 0, 0, 0);
+    if (sums) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) rowsum[i] += a[i][e];
+    }
+  };
+  const int full = p.K / 16;   // macro steps wholly inside K
+  float a[2][TM][4], b[2][TN][4];
+  auto fetch = [&](int u, int s) {
+    const int k0 = min(s, full - 1) * 16;   // clamped: a surplus fetch is never used
+    fetch_tiles<A_ACROSS, TM, false, NARROW>(a[u], p.A, p.lda, i0, p.M, k0, p.K, lrow, lq);
+    fetch_tiles<B_ACROSS, TN, false, NARROW>(b[u], p.Bm, p.ldb, j0, p.N, k0, p.K, lrow, lq);
+  };
+  if (wave < full) {
+    fetch(0, wave);
+    fetch(1, wave + KS);
+    for (int s = wave; s < full; s += 2 * KS) {
+      use(a[0], b[0]);
+      fetch(0, s + 2 * KS);
+      if (s + KS < full) use(a[1], b[1]);
+      fetch(1, s + 3 * KS);
+    }
+  }
+  if (p.K % 16 != 0 && wave == full % KS) {
+    fetch_tiles<A_ACROSS, TM, true, NARROW>(a[0], p.A, p.lda, i0, p.M, full * 16, p.K, lrow, lq);
+    fetch_tiles<B_ACROSS, TN, true, NARROW>(b[0], p.Bm, p.ldb, j0, p.N, full * 16, p.K, lrow, lq);
+    use(a[0], b[0]);
+  }
+  // red[wave][tile][r][lane]
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[((wave * TM * TN + i * TN + j) * 4 + r) * 64 + lane] = acc[i][j][r];
+  __syncthreads();
+  // A thread finishes the TN values of one row that sit in one lane: neighbours in the row where B is stored across k.
+#pragma unroll
+  for (int item = threadIdx.x; item < TM * 4 * 64; item += KS * 64) {
+    const int l = item & 63, r = (item >> 6) & 3, ti = item >> 8;
+    const int i = tile_row<A_ACROSS, TM>(i0, p.M, ti, 4 * (l >> 4) + r);
+    float v[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      v[j] = 0.0f;
+#pragma unroll
+      for (int w = 0; w < KS; ++w) v[j] += red[((w * TM * TN + ti * TN + j) * 4 + r) * 64 + l];   // fixed order
+    }
+    if (i >= p.M) continue;
+    const int c0 = tile_row<B_ACROSS, TN>(j0, p.N, 0, l & 15);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int c = B_ACROSS ? c0 + j : c0 + 16 * j;
+      if (c >= p.N) continue;
+      const long e = (long)i * p.ldc + c;
+      float x = v[j];
+      if constexpr (EPI == BIAS_TANH) {
+        x = tanhf(x + (p.bias ? p.bias[c] : 0.0f));
+        if (p.C2) p.C2[e] = x;
+      } else if constexpr (EPI == TIMES_DTANH) {
+        if (p.y) x = x * (1.0f - p.y[e] * p.y[e]);
+      }
+      p.C[e] = x;
+    }
+  }
+  if constexpr (EPI == STORE_AND_DB) {
+    if (sums) {   // uniform over the workgroup
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < TM; ++i) red[(wave * TM + i) * 64 + lane] = rowsum[i];
+      __syncthreads();
+      if ((int)threadIdx.x < TM * 16) {
+        const int ti = threadIdx.x >> 4, x = threadIdx.x & 15, i = tile_row<A_ACROSS, TM>(i0, p.M, ti, x);
+        float s = 0.0f;
+        for (int w = 0; w < KS; ++w)
+          for (int q = 0; q < 4; ++q) s += red[(w * TM + ti) * 64 + q * 16 + x];   // fixed order
+        if (i < p.M) p.db[i] = s;
+      }
+    }
+  }
+}
+
+template <int TM, int TN, bool NARROW>
+__global__ __launch_bounds__(KS * 64) void chain_forward_kernel(Product p) {
+  extern __shared__ __attribute__((aligned(16))) float chain_smem[];
+  product_body<false, false, TM, TN, BIAS_TANH, NARROW>(p, blockIdx.x, chain_smem);
+}
+// The first nd workgroups compute the data product (none: nd = 0), the others the weight product.
+template <int DTM, int DTN, int WTM, int WTN, bool NARROW>
+__global__ __launch_bounds__(KS * 64) void chain_backward_kernel(Product data, int nd, Product weight) {
+  extern __shared__ __attribute__((aligned(16))) float chain_smem[];
+  if ((int)blockIdx.x < nd)
+    product_body<false, true, DTM, DTN, TIMES_DTANH, NARROW>(data, blockIdx.x, chain_smem);
+  else
+    product_body<true, true, WTM, WTN, STORE_AND_DB, NARROW>(weight, blockIdx.x - nd, chain_smem);
 }
 
 // dz = g * (1 - y^2), elementwise over B * d values.
@@ -68,25 +233,62 @@ __global__ void chain_dz_kernel(const float* __restrict__ g, const float* __rest
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) dz[i] = g[i] * (1.0f - y[i] * y[i]);
 }
 
-// db[j] = sum_b dz[b][j], rows added in order (one thread per column).
-__global__ void chain_colsum_kernel(const float* __restrict__ dz, int B, int d, float* __restrict__ db) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= d) return;
-  float s = 0.0f;
-  for (int b = 0; b < B; ++b) s += dz[(size_t)b * d + j];
-  db[j] = s;
-}
+int blocks_of(int rows, int tiles) { return (rows + 16 * tiles - 1) / (16 * tiles); }
+constexpr int FILL = 256;   // workgroups that give every compute unit one
 
-__global__ void chain_copy_kernel(const float* __restrict__ src, float* __restrict__ dst, size_t n) {
-  const size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) dst[i] = src[i];
-}
-
-hipError_t gemm(const float* A, long sai, long sak, const float* Bm, long sbk, long sbj, float* C, long ldc, int M, int N,
-                int K, const float* bias, int epilogue, hipStream_t st) {
-  dim3 grid((N + 31) / 32, (M + 31) / 32), block(256);
-  chain_gemm_kernel<<<grid, block, 0, st>>>(A, sai, sak, Bm, sbk, sbj, C, ldc, M, N, K, bias, epilogue);
+template <int TM, int TN, bool NARROW>
+hipError_t launch_forward_tiles(Product& p, hipStream_t st) {
+  constexpr size_t lds = (size_t)KS * TM * TN * 256 * sizeof(float);
+  static bool configured = false;
+  if (!configured) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(chain_forward_kernel<TM, TN, NARROW>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    configured = true;
+  }
+  p.gx = blocks_of(p.N, TN);
+  chain_forward_kernel<TM, TN, NARROW><<<dim3(p.gx * blocks_of(p.M, TM)), dim3(KS * 64), lds, st>>>(p);
   return hipGetLastError();
+}
+
+// The largest output block per workgroup that still gives every compute unit one.  Vectors of four along
+// k (or along a row, for operands stored across k) need dimensions of at least four.
+hipError_t launch_chain_forward(Product p, hipStream_t st) {
+  if (p.K < 4) return launch_forward_tiles<1, 1, true>(p, st);
+  if (blocks_of(p.N, 4) * blocks_of(p.M, 4) >= FILL) return launch_forward_tiles<4, 4, false>(p, st);
+  if (blocks_of(p.N, 4) * blocks_of(p.M, 2) >= FILL) return launch_forward_tiles<2, 4, false>(p, st);
+  if (blocks_of(p.N, 2) * blocks_of(p.M, 2) >= FILL) return launch_forward_tiles<2, 2, false>(p, st);
+  if (blocks_of(p.N, 2) * blocks_of(p.M, 1) >= FILL) return launch_forward_tiles<1, 2, false>(p, st);
+  return launch_forward_tiles<1, 1, false>(p, st);
+}
+
+template <int DTM, int DTN, int WTM, int WTN, bool NARROW>
+hipError_t launch_backward_tiles(Product& data, Product& weight, hipStream_t st) {
+  constexpr int tiles = DTM * DTN > WTM * WTN ? DTM * DTN : WTM * WTN;
+  constexpr size_t lds = (size_t)KS * tiles * 256 * sizeof(float);
+  static bool configured = false;
+  if (!configured) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(chain_backward_kernel<DTM, DTN, WTM, WTN, NARROW>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    configured = true;
+  }
+  data.gx = blocks_of(data.N, DTN);
+  weight.gx = blocks_of(weight.N, WTN);
+  const int nd = data.C ? data.gx * blocks_of(data.M, DTM) : 0, nw = weight.gx * blocks_of(weight.M, WTM);
+  chain_backward_kernel<DTM, DTN, WTM, WTN, NARROW><<<dim3(nd + nw), dim3(KS * 64), lds, st>>>(data, nd, weight);
+  return hipGetLastError();
+}
+
+hipError_t launch_chain_backward(Product data, Product weight, hipStream_t st) {
+  const int d_in = weight.N, d_out = weight.M, B = data.M;
+  if (d_in < 4 || d_out < 4) return launch_backward_tiles<1, 1, 1, 1, true>(data, weight, st);
+  if (blocks_of(d_in, 4) * blocks_of(d_out, 4) >= FILL) {
+    if (blocks_of(d_in, 4) * blocks_of(B, 2) >= FILL) return launch_backward_tiles<2, 4, 4, 4, false>(data, weight, st);
+    return launch_backward_tiles<1, 4, 4, 4, false>(data, weight, st);
+  }
+  if (blocks_of(d_in, 2) * blocks_of(d_out, 2) >= FILL) return launch_backward_tiles<1, 2, 2, 2, false>(data, weight, st);
+  return launch_backward_tiles<1, 1, 1, 1, false>(data, weight, st);
 }
 
 unsigned blocks_for(size_t n) { return (unsigned)std::min<size_t>((n + 255) / 256, 2048); }
@@ -214,15 +416,13 @@ int mebptt_chain_run(const mebptt_chain_desc* desc, const mebptt_chain_plan_t* p
   char* ws = reinterpret_cast<char*>(workspace);
   const size_t slab = align_up((size_t)B * max_width(desc) * sizeof(float));
   float* act[2] = {reinterpret_cast<float*>(ws), reinterpret_cast<float*>(ws + slab)};
-  float* grad[2] = {reinterpret_cast<float*>(ws + 2 * slab), reinterpret_cast<float*>(ws + 3 * slab)};
-  float* dz = reinterpret_cast<float*>(ws + 4 * slab);
+  float* dzs[2] = {reinterpret_cast<float*>(ws + 2 * slab), reinterpret_cast<float*>(ws + 3 * slab)};
   auto pool_at = [&](int32_t off) { return reinterpret_cast<float*>(reinterpret_cast<char*>(pool) + (size_t)off * unit); };
 
   // working memory after a forward run: `wk_out` = its last output, `wk_in` = the activation before it
   const float* wk_in = nullptr;
   const float* wk_out = nullptr;
-  int flip = 0, gflip = 0;
-  const float* g = dy;   // gradient with respect to the output of the layer about to be back-propagated
+  int flip = 0, zflip = 0;   // dzs[zflip]: dz of the layer back-propagated next (filled by the layer above)
   int64_t forward_cost = 0, backward_ops = 0;
 
   for (size_t k = 0; k < nops; ++k) {
@@ -236,34 +436,58 @@ int mebptt_chain_run(const mebptt_chain_desc* desc, const mebptt_chain_plan_t* p
         const bool last = i == o.count - 1;
         float* out = (last && o.dst >= 0) ? pool_at(o.dst) : act[flip];
         if (!(last && o.dst >= 0)) flip ^= 1;
-        // y [B, dout] = a [B, din] . W^T : A(i,k) = a[i*din + k], B(k,j) = W[j*din + k]
-        HIP_TRY(gemm(a, din, 1, W[L - 1], 1, din, out, dout, B, dout, din, b[L - 1], EPI_BIAS_TANH, st));
+        Product p{};
+        p.A = a;
+        p.lda = din;
+        p.Bm = W[L - 1];
+        p.ldb = din;
+        p.C = out;
+        p.C2 = L == n ? y_out : nullptr;
+        p.ldc = dout;
+        p.M = B;
+        p.N = dout;
+        p.K = din;
+        p.bias = b[L - 1];
+        HIP_TRY(launch_chain_forward(p, st));
         forward_cost += layers[L - 1].cost;
         before = a;
         a = out;
       }
       wk_in = before;
       wk_out = a;
-      if (o.layer + o.count - 1 == n && y_out)
-        chain_copy_kernel<<<blocks_for((size_t)B * desc->widths[n]), 256, 0, st>>>(a, y_out, (size_t)B * desc->widths[n]);
     } else {
       const int L = o.layer, din = desc->widths[L - 1], dout = desc->widths[L];
       const float* xin = o.src == MEBPTT_CHAIN_INPUT ? x0 : (o.src == MEBPTT_CHAIN_WORKING ? wk_in : pool_at(o.src));
       if (!wk_out || !xin) return set_error(MEBPTT_ESHAPE, "backward operation without a forward operation before it");
-      const size_t ne = (size_t)B * dout;
-      chain_dz_kernel<<<blocks_for(ne), 256, 0, st>>>(g, wk_out, dz, ne);
-      HIP_TRY(hipGetLastError());
-      chain_colsum_kernel<<<(dout + 255) / 256, 256, 0, st>>>(dz, B, dout, db[L - 1]);
-      HIP_TRY(hipGetLastError());
-      // dW [dout, din] = dz^T . x : A(i,k) = dz[k*dout + i], B(k,j) = x[k*din + j]
-      HIP_TRY(gemm(dz, 1, dout, xin, din, 1, dW[L - 1], din, dout, din, B, nullptr, EPI_STORE, st));
-      // g' [B, din] = dz . W : A(i,k) = dz[i*dout + k], B(k,j) = W[k*din + j]
-      float* gout = (L == 1) ? dx0 : grad[gflip];
-      if (gout) HIP_TRY(gemm(dz, dout, 1, W[L - 1], din, 1, gout, din, B, din, dout, nullptr, EPI_STORE, st));
-      if (L > 1) {
-        g = gout;
-        gflip ^= 1;
+      if (L == n) {
+        const size_t ne = (size_t)B * dout;
+        chain_dz_kernel<<<blocks_for(ne), 256, 0, st>>>(dy, wk_out, dzs[zflip], ne);
+        HIP_TRY(hipGetLastError());
       }
+      const float* dz = dzs[zflip];
+      Product data{}, weight{};
+      data.A = dz;
+      data.lda = dout;
+      data.Bm = W[L - 1];
+      data.ldb = din;
+      data.C = L == 1 ? dx0 : dzs[zflip ^ 1];   // NULL: nobody wants dx0
+      data.ldc = din;
+      data.M = B;
+      data.N = din;
+      data.K = dout;
+      data.y = L == 1 ? nullptr : xin;          // y_{L-1}: dz of the layer below at once
+      weight.A = dz;
+      weight.lda = dout;
+      weight.Bm = xin;
+      weight.ldb = din;
+      weight.C = dW[L - 1];
+      weight.ldc = din;
+      weight.M = dout;
+      weight.N = din;
+      weight.K = B;
+      weight.db = db[L - 1];
+      HIP_TRY(launch_chain_backward(data, weight, st));
+      zflip ^= 1;
       ++backward_ops;
       wk_out = nullptr;   // consumed: the next backward operation needs its own forward operation
     }

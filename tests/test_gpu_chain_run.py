@@ -110,3 +110,18 @@ def test_chain_run_rejects_a_plan_for_another_chain():
     with pytest.raises(mb.MebpttError) as e:
         mb.mebptt_chain_run(desc, plan, tW, tb, up(x0), up(dy), pool, ws, dW, db)
     assert e.value.code == mb.ESHAPE
+
+
+@pytest.mark.parametrize("widths,B", [
+    ([3, 5, 2, 4, 1, 9], 7),                     # narrower than a 16-byte vector
+    ([4, 4, 17, 33], 1), ([16, 64, 65, 63], 15), ([64, 128, 64], 16), ([67, 1, 67], 17),
+    ([600, 1030, 514], 129),                     # every output block size of the data and weight products
+    ([1100, 2100, 1025], 70), ([2048, 1024], 512),
+])
+def test_chain_products_at_the_edges_of_their_tiles(widths, B):
+    W, b, x0, dy = _inputs(widths, B, 99 + len(widths) + B)
+    ref = cb.chain_backprop(W, b, x0, dy)
+    out, _, _ = _run(widths, B, 4096, sum(-(-B * d * 4 // 4096) for d in widths[1:]), W, b, x0, dy)
+    for i in range(len(widths) - 1):
+        assert max(_errs(out["dW"][i], ref.dW[i])) <= TOL and max(_errs(out["db"][i], ref.db[i])) <= TOL, i
+    assert max(_errs(out["dx0"], ref.dx0)) <= TOL and max(_errs(out["y"], ref.y)) <= TOL
