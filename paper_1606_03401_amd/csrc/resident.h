@@ -154,6 +154,60 @@ __device__ inline float load_h_operand(const float* plane, unsigned e, unsigned 
     return plane[(size_t)e];
 }
 
+// ---- columns, items, partial sums ----------------------------------------------------------------------
+// Column c of the MFMA tiles is sequence b_lo + c of the XCD's share.  NBT is the number of 16-column tiles of
+// the share; NBT = 0 stands for half a tile, 8 sequences.
+//
+// The pointwise work of a workgroup -- UW units x the XCD's sequences -- is dealt to its threads in blocks
+// of 64.  BLOCK order: WU units x 64/WU sequences (WU = 8, or 4 where UW is no multiple of 8), unit fastest: every
+// array a wave touches falls into runs of at least 32 bytes, and the fragment-tiled ones into whole cache lines.
+// Otherwise the MFMA's own order, sequence fastest: 4 units x 16 sequences (8 x 8 on half a tile).  The difference is in plain planes: 16 rows of
+// 16 bytes per instruction keep a compute unit's address path busy so long that the twenty such
+// loads and stores of a backward step took three times as long as the MFMAs beside them.
+// Either way the blocks of one group of units follow each other (the other order was 4 % slower on H = 512, B = 256).
+template <int UW, int COLUMNS, bool BLOCK>
+struct Items {
+  static constexpr int WU = (BLOCK || COLUMNS == 8) && UW % 8 == 0 ? 8 : 4, WB = 64 / WU;   // units, sequences of a block
+  static constexpr int DOWN = (COLUMNS + WB - 1) / WB, COUNT = UW / WU * DOWN * 64;   // blocks of one group of units; items
+  __device__ static int unit_in(int item) { return BLOCK ? item & (WU - 1) : (item & 63) / WB; }
+  __device__ static int row_in(int item) { return BLOCK ? (item & 63) / WU : item & (WB - 1); }
+  // unit (of the workgroup) and column of an item
+  __device__ static int unit(int item) { return (item >> 6) / DOWN * WU + unit_in(item); }
+  __device__ static int column(int item) { return (item >> 6) % DOWN * WB + row_in(item); }
+};
+
+// Partial sums meet in LDS as the MFMA leaves them: blocks of 64 lanes x 4 consecutive rows.  Writing one costs a
+// compute unit 31 cycles whatever its lanes hold (reading one 17), which at 64 blocks a step was more than
+// the MFMAs; with half a tile of sequences, two row tiles share a block: the second one's sums take the
+// place of the first one's empty columns.
+__device__ inline f32x4 join_halves(f32x4 a, f32x4 b) {
+  f32x4 r;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)   // lanes 8-15 of every 16 take b from lanes 0-7
+    r[i] = __uint_as_float(__builtin_amdgcn_update_dpp(__float_as_uint(a[i]), __float_as_uint(b[i]), 0x128 /* row_ror:8 */, 0xf, 0xc, false));
+  return r;
+}
+// Blocks a wave writes for its NR row tiles x NB batch tiles, and the block and lane of (row tile, row group lq, column).
+template <int NR, int NBT>
+struct Sums {
+  static constexpr bool HALF = NBT == 0;
+  static constexpr int NB = HALF ? 1 : NBT, BLOCKS = HALF ? (NR + 1) / 2 : NR * NB;
+  __device__ static int block(int tile, int column) { return HALF ? tile >> 1 : tile * NB + (column >> 4); }
+  __device__ static int lane(int tile, int lq, int column) { return lq * 16 + (HALF ? ((tile & 1) << 3) + column : column & 15); }
+  template <class Acc>
+  __device__ static void write(f32x4* red, int lane, const Acc& acc) {
+    if constexpr (HALF) {
+#pragma unroll
+      for (int t = 0; t < NR; t += 2) red[(t / 2) * 64 + lane] = t + 1 < NR ? join_halves(acc[t][0], acc[t + 1 < NR ? t + 1 : t][0]) : acc[t][0];
+    } else {
+#pragma unroll
+      for (int t = 0; t < NR; ++t)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) red[(t * NB + b) * 64 + lane] = acc[t][b];
+    }
+  }
+};
+
 // ---- forward chain -------------------------------------------------------------------------------------
 struct ResStep {
   float* out;     // unit that receives (h, c) of this step, or NULL
@@ -195,19 +249,22 @@ struct ResParams {
 // w, w+KS, ..., added in the order 0..KS-1), so a step gives the same bits either way.  A wave whose part of
 // x or h is shorter than the others' runs its surplus macro steps on zeros.
 // NXW, NHW: macro steps of x and of h per wave; the weights of the last NXL of x are parked in LDS (they are
-// read while the wave would wait anyway); NBT: batch tiles of the XCD's share.
+// read while the wave would wait anyway); NBT: batch tiles of the XCD's share (0: half a tile).
 template <class T, int NRT, int NXW, int NXL, int NHW, int KS, int NBT, int CELL>
 __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
   using M = Mma<T>;
   constexpr int VEC = M::VEC, KSTEP = 4 * VEC, FRAG = 64 * VEC;
   constexpr int GROUPS = 8 / KS, FTB = (GROUPS == 2 && NBT == 2) ? 2 : 1, FTR = GROUPS / FTB;
-  constexpr int NRTW = (NRT + FTR - 1) / FTR, BTW = NBT / FTB;   // row and batch tiles of one wave
-  constexpr int NT = NRT * NBT, NXR = NXW - NXL;
-  constexpr int UW = NRT * 4, ITEMS = NT * 64, IPT = (ITEMS + 511) / 512;
+  constexpr int NRTW = (NRT + FTR - 1) / FTR, BTW = (NBT ? NBT : 1) / FTB;   // row and batch tiles of one wave
+  constexpr int NXR = NXW - NXL, COLS = NBT ? NBT * 16 : 8;
+  constexpr int UW = NRT * 4;
+  using It = Items<UW, COLS, NBT == 0>;
+  constexpr int ITEMS = It::COUNT, IPT = (ITEMS + 511) / 512;
+  using Sum = Sums<NRTW, NBT == 0 ? 0 : BTW>;
   constexpr bool SPLIT = HPlane<T>::SPLIT;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  f32x4* red = reinterpret_cast<f32x4*>(smem);                                     // [KS][NT][64]
-  T* wl = reinterpret_cast<T*>(smem + (size_t)KS * NT * 64 * sizeof(f32x4));       // [8][NRTW][NXL] fragments
+  f32x4* red = reinterpret_cast<f32x4*>(smem);                                     // [8 waves][Sum::BLOCKS][64]
+  T* wl = reinterpret_cast<T*>(red + 8 * Sum::BLOCKS * 64);                        // [8][NRTW][NXL] fragments
   __shared__ int s_go, s_g, s_rank, s_fail;
   // the wave index as a scalar: conditions on it become scalar branches (an MFMA under a lane mask
   // that is empty would still execute)
@@ -227,27 +284,27 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
   if (b_lo >= p.B || rank * UW >= p.KH) return;   // no sequences or no units here: nobody waits for this workgroup
   const int nsx = p.KX / KSTEP, nsh = p.KH / KSTEP, nsteps = nsx + nsh;
   const size_t hhalf = (size_t)p.BP * p.KH;
-  const int nbt_all = p.BP / 16, ct0 = b_lo / 16;
   const int ks = wave % KS, grp = wave / KS;
-  const int rt0 = (FTR > 1 ? grp : 0) * NRTW, bt0 = (FTB > 1 ? grp : 0) * BTW;
+  const int rt0 = (FTR > 1 ? grp : 0) * NRTW, bt0 = (FTB > 1 ? grp : 0) * BTW;   // wave = group * KS + K part
   const int ngroups = p.HP / 4;                    // 16-row tiles of the packed weights
   const int mh0 = (ks + KS - nsx % KS) % KS;       // this wave's h macro steps: mh0, mh0 + KS, ... (below nsh)
 
-  // Pointwise items of this thread: item = (output tile, lane of the MFMA layout), i.e. the
-  // (sequence, unit) whose four gate sums that lane holds, so that the partial sums are read back
-  // from LDS at consecutive addresses by consecutive threads.  c stays in registers.  A unit between
-  // H and the padded KH has no weights: its h is zero, and is published as such.
+  // Pointwise items of this thread; c stays in registers.  A unit between H and the padded KH has no
+  // weights: its h is zero, and is published as such.
   bool mine[IPT], real[IPT];
   unsigned ie[IPT], io[IPT];   // b * H + u; the element's place in a fragment-tiled plane
+  const f32x4* cell[IPT];      // its gate sums of K part 0
   float4 bias[IPT];
   float c_state[IPT], keep_h[IPT], keep_second[IPT], keep_gate[IPT][4];
 #pragma unroll
   for (int q = 0; q < IPT; ++q) {
     const int item = (int)threadIdx.x + q * 512;
-    const int tile = item >> 6, il = item & 63;          // tile = rt * NBT + bt
-    const int rt = tile / NBT, bt = tile % NBT;
-    const int b = (ct0 + bt) * 16 + (il & 15), u = rank * UW + rt * 4 + (il >> 4);
-    mine[q] = item < ITEMS && b >= b_lo && b < b_hi && u < p.KH;
+    const int ul = It::unit(item), col = It::column(item), b = b_lo + col, u = rank * UW + ul, rt = ul >> 2;
+    // the wave that holds it: row group (or batch group) of the workgroup, then its block
+    const int w0 = FTR > 1 ? rt / NRTW : (FTB > 1 ? (col >> 4) / BTW : 0);
+    cell[q] = red + (size_t)(w0 * KS * Sum::BLOCKS + Sum::block(FTR > 1 ? rt % NRTW : rt, FTB > 1 ? col % (BTW * 16) : col)) * 64 +
+              Sum::lane(FTR > 1 ? rt % NRTW : rt, ul & 3, col);
+    mine[q] = item < ITEMS && b < b_hi && u < p.KH;
     real[q] = u < p.H;
     ie[q] = (unsigned)(b * p.H + u);
     io[q] = (unsigned)ft_offset<T>(b, u, nsh);
@@ -269,12 +326,17 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
     for (int q = 0; q < IPT; ++q) {
       if (!mine[q]) continue;
       if constexpr (SPLIT) {
-        // Units u and u + 1 of one sequence sit 16 lanes apart in this layout and next to each other
-        // in the slot: the lane of the even unit stores both as one dword.
+        // the lane of an even unit stores it and the next one as one dword: its neighbour's, or 16 lanes on
         const unsigned hi16 = (__float_as_uint(keep_h[q]) + 0x8000u) >> 16;
-        const unsigned other = __shfl_xor(hi16, 16);
-        if (((threadIdx.x >> 4) & 1) == 0) {
-          slot_out[(size_t)(io[q] >> 1)] = not_empty(hi16 | (other << 16));
+        unsigned pair;
+        if constexpr (NBT == 0) {
+          pair = hi16 | (__builtin_amdgcn_update_dpp(hi16, hi16, 0xb1 /* quad_perm 1,0,3,2 */, 0xf, 0xf, false) << 16);
+        } else {
+          const auto rows = __builtin_amdgcn_permlane16_swap(hi16, hi16, false, false);   // even rows of 16 lanes, odd rows
+          pair = rows[0] | (rows[1] << 16);
+        }
+        if ((io[q] & 1) == 0) {
+          slot_out[(size_t)(io[q] >> 1)] = not_empty(pair);
           slot_old[(size_t)(io[q] >> 1)] = RES_EMPTY;
         }
       } else {
@@ -314,10 +376,10 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
   unsigned xrow[BTW], hoff[BTW];
 #pragma unroll
   for (int t = 0; t < BTW; ++t) {
-    const int b = (ct0 + bt0 + t) * 16 + lrow;
-    const bool own = b >= b_lo && b < b_hi;
+    const int b = b_lo + (bt0 + t) * 16 + lrow;
+    const bool own = b < b_hi;
     xrow[t] = (unsigned)((own ? b : b_lo) * p.I);
-    hoff[t] = own ? (unsigned)((min(ct0 + bt0 + t, nbt_all - 1) * nsh * 64 + lane) * 16) : RES_NO_LANE;
+    hoff[t] = own ? (unsigned)(((b >> 4) * nsh * 64 + lq * 16 + (b & 15)) * 16) : RES_NO_LANE;
   }
   RawAct<VEC> xraw[NXW][BTW];   // x of the step about to run
   auto fetch_x = [&](int j) {
@@ -423,22 +485,16 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
       for (int rt = 0; rt < NRTW; ++rt)
 #pragma unroll
         for (int t = 0; t < BTW; ++t) acc[rt][t] = M::mma(wh[rt][i], hf[i][t], acc[rt][t]);
-#pragma unroll
-    for (int rt = 0; rt < NRTW; ++rt)
-      if (rt0 + rt < NRT) {
-#pragma unroll
-        for (int t = 0; t < BTW; ++t) red[(ks * NT + (rt0 + rt) * NBT + bt0 + t) * 64 + lane] = acc[rt][t];
-      }
+    Sum::write(red + (size_t)wave * Sum::BLOCKS * 64, lane, acc);
     lds_barrier();
     if (s_fail) return;   // a wave gave up: written before the barrier, so all see it
 #pragma unroll
     for (int q = 0; q < IPT; ++q) {
       if (!mine[q]) continue;
-      const int item = (int)threadIdx.x + q * 512;
       float G[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int w = 0; w < KS; ++w) {   // fixed order, as in forward_body
-        const f32x4 v = red[w * NT * 64 + item];
+        const f32x4 v = cell[q][w * Sum::BLOCKS * 64];
 #pragma unroll
         for (int r = 0; r < 4; ++r) G[r] += v[r];
       }
@@ -454,8 +510,9 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
 
 template <class T, int NRT, int NXW, int NXL, int NHW, int KS, int NBT, int CELL>
 hipError_t launch_chain_cell(const ResParams& p, hipStream_t st) {
-  constexpr int FTR = (KS == 4 && NBT == 1) ? 2 : 1, NRTW = (NRT + FTR - 1) / FTR;
-  constexpr size_t lds = (size_t)KS * NRT * NBT * 64 * sizeof(f32x4) + (size_t)8 * NRTW * NXL * 1024;
+  constexpr int GROUPS = 8 / KS, FTB = (GROUPS == 2 && NBT == 2) ? 2 : 1, FTR = GROUPS / FTB, NRTW = (NRT + FTR - 1) / FTR;
+  constexpr int BLOCKS = Sums<NRTW, NBT == 0 ? 0 : NBT / FTB>::BLOCKS;
+  constexpr size_t lds = (size_t)8 * BLOCKS * 1024 + (size_t)8 * NRTW * NXL * 1024;
   static_assert(lds <= 160 * 1024 - 64, "LDS of a compute unit");
   auto kernel = forward_chain_kernel<T, NRT, NXW, NXL, NHW, KS, NBT, CELL>;
   static bool configured = false;   // per instantiation; the attribute only has to be set once

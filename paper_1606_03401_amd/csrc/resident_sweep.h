@@ -54,6 +54,7 @@ struct SweepParams {
 // NXW, NHW, KSF: macro steps of x and h per wave and K split of the forward part; NBW, KSB: macro steps of
 // dG per wave (the weights of the last NBL are parked in LDS: registers are what the two largest
 // instantiations are short of) and K split of the backward part; NBT: batch tiles of the XCD's share.
+constexpr int SWEEP_KEPT = 320;   // values a wave turns over per step: 64 items' dG and h_{s-1}
 template <class T, bool FWD, int NRT, int NXW, int NHW, int KSF, int NBW, int NBL, int KSB, int NBT, int CELL>
 __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
   using M = Mma<T>;
@@ -61,15 +62,21 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
   constexpr bool SPLIT = HPlane<T>::SPLIT;
   constexpr int UW = NRT * 4;                       // hidden units per workgroup
   constexpr int NTB = (UW + 15) / 16;               // 16-unit tiles of the dh GEMM that cover them
-  constexpr int NTF = NRT * NBT, NTBT = NTB * NBT;
-  constexpr int ITEMS = NTF * 64, IPT = (ITEMS + 511) / 512;
+  constexpr int NB = NBT ? NBT : 1, COLS = NBT ? NBT * 16 : 8;
+  // backward operations on stored states fetch whole planes: BLOCK order; with forward operations most of what
+  // an item moves is fragment-tiled: the MFMA's order
+  using It = Items<UW, COLS, !FWD>;
+  constexpr int ITEMS = It::COUNT, IPT = (ITEMS + 511) / 512;
   constexpr int GF = 8 / KSF, FTB = (GF == 2 && NBT == 2) ? 2 : 1, FTR = GF / FTB;   // forward: groups of waves along batch, rows
-  constexpr int NRTW = (NRT + FTR - 1) / FTR, BTWF = NBT / FTB;
-  constexpr int GB = 8 / KSB, BTB = (GB == 2 && NBT == 2) ? 2 : 1, BTWB = NBT / BTB;   // backward: along the batch, or one group idles
+  constexpr int NRTW = (NRT + FTR - 1) / FTR, BTWF = NB / FTB;
+  constexpr int GB = 8 / KSB, BTB = (GB == 2 && NBT == 2) ? 2 : 1, BTWB = NB / BTB;   // backward: along the batch, or one group idles
+  using SumF = Sums<NRTW, NBT == 0 ? 0 : BTWF>;
+  using SumB = Sums<NTB, NBT == 0 ? 0 : BTWB>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  f32x4* redB = reinterpret_cast<f32x4*>(smem);                       // [KSB][NTBT][64]
-  f32x4* redF = redB + (size_t)KSB * NTBT * 64;                       // [KSF][NTF][64]
-  T* wl = reinterpret_cast<T*>(redF + (FWD ? (size_t)KSF * NTF * 64 : 0));   // [8][NTB][NBL] fragments
+  f32x4* redB = reinterpret_cast<f32x4*>(smem);                       // [8 waves][SumB::BLOCKS][64]: dh of 4 units
+  f32x4* redF = redB + 8 * SumB::BLOCKS * 64;                         // [8 waves][SumF::BLOCKS][64]: the gates of a unit
+  T* wl = reinterpret_cast<T*>(redF + (FWD ? 8 * SumF::BLOCKS * 64 : 0));   // [8][NTB][NBL] fragments
+  T* kept = wl + (size_t)8 * NTB * NBL * FRAG;                        // [8][IPT][SWEEP_KEPT]
   __shared__ int s_go, s_g, s_rank, s_fail;
   // the wave index as a scalar: conditions on it become scalar branches (an MFMA under a lane mask
   // that is empty would still execute)
@@ -90,15 +97,15 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
   const int nsx = p.KX / KSTEP, nsh = p.KH / KSTEP, nstepsF = nsx + nsh, nstepsB = p.G4 / KSTEP;
   const size_t hhalf = (size_t)p.BP * p.KH, dG_step = (size_t)p.BP * p.G4;
   const unsigned plane = (unsigned)(p.B * p.H);
-  const int nbt_all = p.BP / 16, ct0 = b_lo / 16;
   const int fk = wave % KSF, fg = wave / KSF, bk = wave % KSB, bg = wave / KSB;
   const int rt0 = (FTR > 1 ? fg : 0) * NRTW, btf0 = (FTB > 1 ? fg : 0) * BTWF, btb0 = (BTB > 1 ? bg : 0) * BTWB;
   const bool bwd_wave = bg < BTB;
   const int mh0 = (fk + KSF - nsx % KSF) % KSF;     // this wave's h macro steps: mh0, mh0 + KSF, ... (below nsh)
 
-  // items: (output tile, lane of the forward MFMA layout) = (sequence, unit).  A unit between H and the
-  // padded HP publishes zeros.
+  // items: (sequence, unit).  A unit between H and the padded HP publishes zeros.
   bool mine[IPT], real[IPT];
+  const f32x4* cellF[IPT];
+  const float* cellB[IPT];
   unsigned ie[IPT], io[IPT], ig[IPT];   // b * H + u; places in the fragment-tiled h plane and (of gate 0) in a dG block
   float4 bias[IPT];
   float dc_run[IPT];
@@ -109,10 +116,15 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
 #pragma unroll
   for (int q = 0; q < IPT; ++q) {
     const int item = (int)threadIdx.x + q * 512;
-    const int tile = item >> 6, il = item & 63;
-    const int rt = tile / NBT, bt = tile % NBT;
-    const int b = (ct0 + bt) * 16 + (il & 15), u = rank * UW + rt * 4 + (il >> 4);
-    mine[q] = item < ITEMS && b >= b_lo && b < b_hi && u < p.HP;
+    const int ul = It::unit(item), col = It::column(item), b = b_lo + col, u = rank * UW + ul;
+    {   // the wave that holds its sums for K part 0 (row group, or batch group), then its block
+      const int rt = ul >> 2, rw = FTR > 1 ? rt % NRTW : rt, wf = FTR > 1 ? rt / NRTW : (FTB > 1 ? (col >> 4) / BTWF : 0);
+      cellF[q] = redF + (size_t)(wf * KSF * SumF::BLOCKS + SumF::block(rw, FTB > 1 ? col % (BTWF * 16) : col)) * 64 + SumF::lane(rw, ul & 3, col);
+      const int tb = ul >> 4, wB = BTB > 1 ? (col >> 4) / BTWB : 0;
+      cellB[q] = reinterpret_cast<const float*>(redB + (size_t)(wB * KSB * SumB::BLOCKS + SumB::block(tb, BTB > 1 ? col % (BTWB * 16) : col)) * 64 +
+                                                SumB::lane(tb, (ul & 15) >> 2, col)) + (ul & 3);
+    }
+    mine[q] = item < ITEMS && b < b_hi && u < p.HP;
     real[q] = mine[q] && u < p.H;
     ie[q] = real[q] ? (unsigned)(b * p.H + u) : 0u;     // element 0 is there for items without one to fetch
     io[q] = real[q] ? (unsigned)ft_offset<T>(b, u, nsh) : 0u;
@@ -190,14 +202,14 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
   unsigned xrow[BTWF], hsrc[BTWF], goff[BTWB];
 #pragma unroll
   for (int t = 0; t < BTWF; ++t) {
-    const int b = (ct0 + btf0 + t) * 16 + lrow, row = (b >= b_lo && b < b_hi) ? b : b_lo;
+    const int b = b_lo + (btf0 + t) * 16 + lrow, row = b < b_hi ? b : b_lo;
     xrow[t] = (unsigned)(row * p.I);
-    hsrc[t] = SPLIT ? (unsigned)(min(ct0 + btf0 + t, nbt_all - 1) * nsh * FRAG + lane * VEC) : (unsigned)(row * p.H);
+    hsrc[t] = SPLIT ? (unsigned)(((row >> 4) * nsh * 64 + lq * 16 + (row & 15)) * VEC) : (unsigned)(row * p.H);
   }
 #pragma unroll
   for (int t = 0; t < BTWB; ++t) {
-    const int b = (ct0 + btb0 + t) * 16 + lrow;
-    goff[t] = (b >= b_lo && b < b_hi) ? (unsigned)((min(ct0 + btb0 + t, nbt_all - 1) * nstepsB * 64 + lane) * 16) : RES_NO_LANE;
+    const int b = b_lo + (btb0 + t) * 16 + lrow;
+    goff[t] = b < b_hi ? (unsigned)(((b >> 4) * nstepsB * 64 + lq * 16 + (b & 15)) * 16) : RES_NO_LANE;
   }
 
   // what the next lower step needs, fetched a step ahead: raw x values and h fragments, or the stored
@@ -287,12 +299,7 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
           for (int rt = 0; rt < NRTW; ++rt) acc[rt][t] = M::mma(wh[rt][i], f, acc[rt][t]);
         }
       }
-#pragma unroll
-      for (int rt = 0; rt < NRTW; ++rt)
-        if (rt0 + rt < NRT) {
-#pragma unroll
-          for (int t = 0; t < BTWF; ++t) redF[(fk * NTF + (rt0 + rt) * NBT + btf0 + t) * 64 + lane] = acc[rt][t];
-        }
+      SumF::write(redF + (size_t)wave * SumF::BLOCKS * 64, lane, acc);
       lds_barrier();
     }
 #pragma unroll
@@ -302,11 +309,10 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
       st_dy[q] = pf_dy[q];
       if constexpr (FWD) {
         if (!mine[q]) continue;
-        const int item = (int)threadIdx.x + q * 512;
         float G[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int w = 0; w < KSF; ++w) {   // fixed order, as in forward_body
-          const f32x4 v = redF[w * NTF * 64 + item];
+          const f32x4 v = cellF[q][w * SumF::BLOCKS * 64];
 #pragma unroll
           for (int r = 0; r < 4; ++r) G[r] += v[r];
         }
@@ -320,7 +326,27 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
     }
   };
   // What only later launches read of step s: dG in the chunk buffer, the transposed copies for the weight
-  // gradient, the output.
+  // gradient, the output.  A block of items holds whole 16-byte slots of the transposed operands when the
+  // batch is a multiple of the sequences in a slot: the wave then turns its block over in LDS (keep_transposed,
+  // right after the step; each wave its own part, so no barrier) and stores them slot by slot.  Not beside
+  // forward operations, which have no time to spare on LDS where the stored states' loads would have been
+  // (H = 512, B = 256: 79 instead of 70 us a launch).
+  const bool slots_whole = !FWD && p.B % VEC == 0;
+  T* kept_w = kept + (size_t)wave * IPT * SWEEP_KEPT;
+  auto keep_transposed = [&]() {
+    if (!slots_whole) return;
+#pragma unroll
+    for (int q = 0; q < IPT; ++q) {
+      union { unsigned u[sizeof(T)]; T t[4]; } pk;
+#pragma unroll
+      for (int i = 0; i < (int)sizeof(T); ++i) pk.u[i] = dg[q][i];
+      const int ul = It::unit_in(lane), bl = It::row_in(lane);
+      T* k = kept_w + q * SWEEP_KEPT;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) k[(ul * 4 + r) * It::WB + bl] = pk.t[r];   // [row 4u + gate][sequence]
+      k[256 + ul * It::WB + bl] = (T)kp_hprev[q];                            // [unit][sequence]
+    }
+  };
   auto store_kept = [&](int s) {
     const int slot = (s - 1) % p.CH, buf = ((s - 1) / p.CH) & 1;   // where step s lives in the chunk buffers
     T* dG_cur = reinterpret_cast<T*>(p.dG_chunk[buf]) + (size_t)slot * dG_step;
@@ -330,20 +356,38 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
     const int ncs = p.KC / KSTEP;
 #pragma unroll
     for (int q = 0; q < IPT; ++q) {
-      if (!real[q]) continue;
-      const int item = (int)threadIdx.x + q * 512, tile = item >> 6, il = item & 63;
-      const int b = (ct0 + tile % NBT) * 16 + (il & 15), n = rank * UW + tile / NBT * 4 + (il >> 4);
-      const int col = slot * p.B + b;
-      store_dg(dG_cur, q, false);
-      union { unsigned u[sizeof(T)]; T t[4]; } pk;
+      if (real[q]) {
+        store_dg(dG_cur, q, false);
+        if (y_s) y_s[(size_t)ie[q]] = kp_h[q];
+      }
+      const int item = (int)threadIdx.x + q * 512, first = item & ~63;   // the block's first item
+      if (slots_whole) {
+        // chunk c of the block: VEC sequences of one row; rows of dG first, then rows of h_{s-1}
+        constexpr int CR = It::WB / VEC, NDG = 4 * It::WU * CR, NALL = NDG + It::WU * CR;
+        const int u0 = rank * UW + It::unit(first), b0 = b_lo + It::column(first);
 #pragma unroll
-      for (int i = 0; i < (int)sizeof(T); ++i) pk.u[i] = dg[q][i];
-      // rows 4n .. 4n + 3 of one column lie VEC elements apart (they share a 16-row tile)
-      const unsigned o = (unsigned)ft_offset<T>(4 * n, col, ncs);
+        for (int c0 = 0; c0 < NALL; c0 += 64) {
+          const int c = c0 + lane, row = c / CR, b = b0 + c % CR * VEC;
+          const bool is_dg = c < NDG;
+          const int n = u0 + (is_dg ? row >> 2 : row - 4 * It::WU);
+          if (c < NALL && first < ITEMS && b < b_hi && n < p.H) {
+            T* dst = is_dg ? dGT + (size_t)ft_offset<T>(4 * n + (row & 3), slot * p.B + b, ncs)
+                           : aT + (size_t)ft_offset<T>(p.NX + n, slot * p.B + b, ncs);
+            *reinterpret_cast<u32x4*>(dst) = *reinterpret_cast<const u32x4*>(kept_w + q * SWEEP_KEPT + c * VEC);
+          }
+        }
+      } else if (real[q]) {
+        const int b = b_lo + It::column(item), n = rank * UW + It::unit(item);
+        const int col = slot * p.B + b;
+        union { unsigned u[sizeof(T)]; T t[4]; } pk;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) dGT[(size_t)(o + r * VEC)] = pk.t[r];
-      aT[(size_t)ft_offset<T>(p.NX + n, col, ncs)] = (T)kp_hprev[q];
-      if (y_s) y_s[(size_t)ie[q]] = kp_h[q];
+        for (int i = 0; i < (int)sizeof(T); ++i) pk.u[i] = dg[q][i];
+        // rows 4n .. 4n + 3 of one column lie VEC elements apart (they share a 16-row tile)
+        const unsigned o = (unsigned)ft_offset<T>(4 * n, col, ncs);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dGT[(size_t)(o + r * VEC)] = pk.t[r];
+        aT[(size_t)ft_offset<T>(p.NX + n, col, ncs)] = (T)kp_hprev[q];
+      }
     }
   };
 
@@ -403,10 +447,7 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
 #pragma unroll
           for (int t = 0; t < BTWB; ++t) acc[tb][t] = M::mma(a, gfr[k][t], acc[tb][t]);
         }
-#pragma unroll
-      for (int tb = 0; tb < NTB; ++tb)
-#pragma unroll
-        for (int t = 0; t < BTWB; ++t) redB[(bk * NTBT + tb * NBT + btb0 + t) * 64 + lane] = acc[tb][t];
+      SumB::write(redB + (size_t)wave * SumB::BLOCKS * 64, lane, acc);
     }
     lds_barrier();
     if (s_fail) return;   // a wave gave up: written before the barrier, so all see it
@@ -414,13 +455,9 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
 #pragma unroll
     for (int q = 0; q < IPT; ++q) {
       if (!mine[q]) continue;
-      const int item = (int)threadIdx.x + q * 512, tile = item >> 6, il = item & 63;
-      const int rt = tile / NBT, bt = tile % NBT;
-      // dh of unit rt*4 + il/16 of the workgroup: register il/16 of lane (rt%4)*16 + il%16 of tile rt/4
-      const float* cell = reinterpret_cast<const float*>(redB + ((rt >> 2) * NBT + bt) * 64 + (rt & 3) * 16 + (il & 15)) + (il >> 4);
       float dh = 0.0f;
 #pragma unroll
-      for (int w = 0; w < KSB; ++w) dh += cell[w * NTBT * 64 * 4];   // fixed order, as in backward_body
+      for (int w = 0; w < KSB; ++w) dh += cellB[q][w * SumB::BLOCKS * 64 * 4];   // fixed order, as in backward_body
       dh += p.dy_is_h ? st_h[q] : st_dy[q];
       float dG[4], dc_out;
       if (CELL == 0)
@@ -439,10 +476,12 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
     }
     if (j + 1 < p.count) {
       publish(p.published + (unsigned)j + 1);
+      keep_transposed();
       if constexpr (!FWD) lds_barrier();   // the partial sums have been read: the next step may overwrite them (FWD: advance() meets)
       advance();
     }
   }
+  keep_transposed();
   store_kept(p.s_hi - p.count + 1);
 #pragma unroll
   for (int q = 0; q < IPT; ++q)
@@ -451,9 +490,10 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
 
 template <class T, bool FWD, int NRT, int NXW, int NHW, int KSF, int NBW, int NBL, int KSB, int NBT, int CELL>
 hipError_t launch_sweep_cell(const SweepParams& p, hipStream_t st) {
-  constexpr int NTB = (NRT * 4 + 15) / 16;
-  constexpr size_t lds = ((size_t)KSB * NTB * NBT + (FWD ? (size_t)KSF * NRT * NBT : 0)) * 64 * sizeof(f32x4) +
-                         (size_t)8 * NTB * NBL * 1024;
+  constexpr int NTB = (NRT * 4 + 15) / 16, NB = NBT ? NBT : 1, IPT = (Items<NRT * 4, NBT ? NBT * 16 : 8, !FWD>::COUNT + 511) / 512;
+  constexpr int GF = 8 / KSF, FTB = (GF == 2 && NBT == 2) ? 2 : 1, FTR = GF / FTB, BTB = (KSB == 4 && NBT == 2) ? 2 : 1;
+  constexpr int blocksB = Sums<NTB, NBT == 0 ? 0 : NB / BTB>::BLOCKS, blocksF = Sums<(NRT + FTR - 1) / FTR, NBT == 0 ? 0 : NB / FTB>::BLOCKS;
+  constexpr size_t lds = (size_t)8 * (blocksB + (FWD ? blocksF : 0) + NTB * NBL) * 1024 + (size_t)8 * IPT * SWEEP_KEPT * sizeof(T);
   static_assert(lds <= 160 * 1024 - 64, "LDS of a compute unit");
   auto kernel = sweep_kernel<T, FWD, NRT, NXW, NHW, KSF, NBW, NBL, KSB, NBT, CELL>;
   static bool configured = false;   // per instantiation; the attribute only has to be set once
