@@ -1399,12 +1399,11 @@ hipError_t launch_zero_operand_columns(const Dims& d, void* dGT, void* aT, int c
 
 // A workgroup of 2 x 2 waves owns a block of 2*WT x 2*WT MFMA tiles of dW (128 x 128 elements for
 // WT = 4, 64 x 64 for WT = 2, used when the larger block would leave most compute units idle);
-// each wave a WT x WT quarter.  Per macro step the workgroup copies the 2*WT + 2*WT operand
-// fragments of its block (1 KiB each, already in fragment order) from HBM/L2 into LDS with fully
-// coalesced 16-byte loads -- fetched PD macro steps ahead through a ring of registers -- and every
-// wave reads the WT + WT fragments it needs from LDS, so each operand byte crosses the L2 fabric
-// once per workgroup instead of once per wave.  gridDim.z workgroups may share one output block,
-// each with its own part of K and its own partial accumulator.
+// each wave a WT x WT quarter.  Per macro step the workgroup copies the 2*WT fragments of dGT (1 KiB each, already
+// in fragment order) into LDS with fully coalesced 16-byte loads, from which the two waves of a row read
+// them; the fragments of aT every wave fetches straight into its MFMA registers.  Both are fetched PD macro steps
+// ahead.  (Both operands through LDS: 39.6 us per chunk on H = 1024, B = 64, so: 37.0; two macro steps per barrier: 37.8.)  gridDim.z workgroups may share one
+// output block, each with its own part of K and its own partial accumulator.
 template <class T, int WT>
 __global__ __launch_bounds__(256) void wgrad_kernel(const T* __restrict__ dGT, const T* __restrict__ aT, int K, int KC,
                                                     int G4, int NTOT, int accumulate, float* __restrict__ dWacc) {
@@ -1412,7 +1411,8 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const T* __restrict__ dGT, c
   constexpr int VEC = M::VEC, KSTEP = 4 * VEC, PD = 3;
   constexpr int FRAG = 64 * VEC;                  // elements of one fragment block (1 KiB)
   typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
-  __shared__ __attribute__((aligned(16))) T lds[2][4 * WT * FRAG];
+  __shared__ __attribute__((aligned(16))) T lds[2][2 * WT * FRAG];
+  constexpr int SW = WT / 2;                      // fragments of dGT this wave copies per macro step
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;   // scalar: see wave_index note
   const int wm = wave & 1, wn = wave >> 1;
   const int MT = G4 / 16, NT = NTOT / 16;
@@ -1425,26 +1425,24 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const T* __restrict__ dGT, c
   const int nk_all = K / KSTEP;
   const int k_begin = (int)((long long)nk_all * blockIdx.z / gridDim.z);
   const int nk = (int)((long long)nk_all * (blockIdx.z + 1) / gridDim.z) - k_begin;
-  // this thread copies blocks q*4 + wave, q = 0..WT-1: the first 2*WT blocks are dGT row tiles,
-  // the other 2*WT are aT row tiles
-  const T* src[WT];
+  const T* src[SW];   // row tiles q*4 + wave of dGT
+  const T* srcB[WT];  // this wave's row tiles of aT
 #pragma unroll
-  for (int q = 0; q < WT; ++q) {
-    const int blk = q * 4 + wave;
-    if (blk < 2 * WT)
-      src[q] = dGT + (((size_t)min(mt_wg + blk, MT - 1) * ncs + k_begin) * 64 + lane) * VEC;
-    else
-      src[q] = aT + (((size_t)min(nt_wg + blk - 2 * WT, NT - 1) * ncs + k_begin) * 64 + lane) * VEC;
-  }
-  u32x4 ring[PD][WT];
+  for (int q = 0; q < SW; ++q) src[q] = dGT + (((size_t)min(mt_wg + q * 4 + wave, MT - 1) * ncs + k_begin) * 64 + lane) * VEC;
+#pragma unroll
+  for (int i = 0; i < WT; ++i) srcB[i] = aT + (((size_t)min(nt_wg + wn * WT + i, NT - 1) * ncs + k_begin) * 64 + lane) * VEC;
+  u32x4 ring[PD][SW];
+  typename M::Frag ringB[PD][WT];
   auto fetch = [&](int stage, int ks) {
     const size_t off = (size_t)min(ks, nk - 1) * FRAG;
 #pragma unroll
-    for (int q = 0; q < WT; ++q) ring[stage][q] = *reinterpret_cast<const u32x4*>(src[q] + off);
+    for (int q = 0; q < SW; ++q) ring[stage][q] = *reinterpret_cast<const u32x4*>(src[q] + off);
+#pragma unroll
+    for (int i = 0; i < WT; ++i) ringB[stage][i] = M::load(srcB[i] + off);
   };
   auto stash = [&](int stage, int buf) {
 #pragma unroll
-    for (int q = 0; q < WT; ++q)
+    for (int q = 0; q < SW; ++q)
       *reinterpret_cast<u32x4*>(&lds[buf][(q * 4 + wave) * FRAG + lane * VEC]) = ring[stage][q];
   };
   f32x4 acc[WT][WT];
@@ -1463,26 +1461,23 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const T* __restrict__ dGT, c
     for (int j = 0; j < PD; ++j) {
       const int ks = k0 + j;           // macro step computed now (held in lds[ks & 1])
       if (ks < nk) {
-        fetch(j, ks + PD);             // ring slot j was stashed for step ks; refill it PD steps ahead
-        typename M::Frag af[WT], bf[WT];
-#pragma unroll
-        for (int i = 0; i < WT; ++i) bf[i] = M::load(&lds[ks & 1][(2 * WT + wn * WT + i) * FRAG + lane * VEC]);
+        typename M::Frag af[WT];
 #pragma unroll
         for (int i = 0; i < WT; ++i) af[i] = M::load(&lds[ks & 1][(wm * WT + i) * FRAG + lane * VEC]);
 #pragma unroll
         for (int i = 0; i < WT; ++i)
 #pragma unroll
-          for (int jj = 0; jj < WT; ++jj) acc[i][jj] = M::mma(af[i], bf[jj], acc[i][jj]);
-        // order of this block's LDS reads (0x100) and MFMAs (0x008): what the first row of MFMAs
-        // needs (af[0] and every bf) plus af[1], then a row of MFMAs and the next af in turn, so
-        // that only the first reads of a macro step are waited for
-        __builtin_amdgcn_sched_group_barrier(0x100, WT + 2, 0);
+          for (int jj = 0; jj < WT; ++jj) acc[i][jj] = M::mma(af[i], ringB[j][jj], acc[i][jj]);
+        // order of this block's LDS reads (0x100) and MFMAs (0x008): two reads ahead, then a row of MFMAs
+        // and one read in turn, so that only the first reads of a macro step are waited for
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
 #pragma unroll
         for (int i = 0; i < WT - 2; ++i) {
           __builtin_amdgcn_sched_group_barrier(0x008, WT, 0);
           __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
         __builtin_amdgcn_sched_group_barrier(0x008, 2 * WT, 0);
+        fetch(j, ks + PD);             // ring slot j has been used for step ks; refill it PD steps ahead
         if (ks + 1 < nk) stash((j + 1) % PD, (ks + 1) & 1);
       }
       __syncthreads();
