@@ -371,13 +371,13 @@ __device__ inline void forward_body(const FwdParams& p, int bx, int by, float* r
     }
   }
 
-  // partial sums -> red[wave][gate r][row][unit] (row stride padded against bank conflicts)
+  // partial sums -> red[wave][row][unit], four gates each: one 16-byte write and read where four of 4 bytes
+  // took twice the LDS time on the way back (row stride padded against bank conflicts)
+  f32x4* red4 = reinterpret_cast<f32x4*>(red);
 #pragma unroll
   for (int g = 0; g < NG; ++g)
 #pragma unroll
-    for (int t = 0; t < BT; ++t)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) red[((wave * 4 + r) * BT * 16 + t * 16 + lrow) * RS + g * 4 + lq] = acc[g][t][r];
+    for (int t = 0; t < BT; ++t) red4[(wave * BT * 16 + t * 16 + lrow) * RS + g * 4 + lq] = acc[g][t];
   __syncthreads();
 #pragma unroll
   for (int q = 0; q < IPT; ++q) {
@@ -385,9 +385,12 @@ __device__ inline void forward_body(const FwdParams& p, int bx, int by, float* r
     if (item >= ITEMS) break;
     const int cell = ((item / UW) % (BT * 16)) * RS + item % UW;
     float G[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int w = 0; w < KS; ++w)   // fixed order: results do not depend on scheduling
 #pragma unroll
-      for (int r = 0; r < 4; ++r) G[r] += red[(w * 4 + r) * BT * 16 * RS + cell];
+    for (int w = 0; w < KS; ++w) {   // fixed order: results do not depend on scheduling
+      const f32x4 v = red4[w * BT * 16 * RS + cell];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) G[r] += v[r];
+    }
     if (!epi[q]) {
       // split layout: the padding columns H..KH of a valid row are part of the operand other
       // launches fetch, so they are (re)written as zero with every state
@@ -413,7 +416,7 @@ constexpr int forward_red_floats(int NG, int BT, int KS) { return KS * 4 * BT * 
 
 template <class T, int NG, int BT, int KS, int U, int CELL>
 __global__ __launch_bounds__(64 * KS) void forward_kernel(FwdParams p) {
-  __shared__ float red[forward_red_floats(NG, BT, KS)];
+  __shared__ __attribute__((aligned(16))) float red[forward_red_floats(NG, BT, KS)];
   forward_body<T, NG, BT, KS, U, CELL>(p, blockIdx.x, blockIdx.y, red);
 }
 
@@ -622,7 +625,7 @@ template <class T, int CELL, int FNG, int FKS, int FU, int BNT, int BBT, int BKS
 __global__ __launch_bounds__(64 * (FKS > BKS ? FKS : BKS), 4) void pair_kernel(FwdParams f, BwdParams b, int nfx, int nf,
                                                                              int nbx) {
   constexpr int FRED = forward_red_floats(FNG, 1, FKS), BRED = BKS * BNT * BBT * 4 * 64;
-  __shared__ float red[FRED > BRED ? FRED : BRED];
+  __shared__ __attribute__((aligned(16))) float red[FRED > BRED ? FRED : BRED];
   const int id = blockIdx.x;
   if (id < nf)
     forward_body<T, FNG, 1, FKS, FU, CELL>(f, id % nfx, id / nfx, red);
@@ -700,7 +703,7 @@ struct FwdBatchSteps {
 template <class T, int NG, int BT, int KS, int U, int CELL>
 __global__ __launch_bounds__(64 * KS) void forward_batch_kernel(FwdParams p, FwdBatchSteps steps, size_t hplane, size_t unit,
                                                                 size_t plane) {
-  __shared__ float red[forward_red_floats(NG, BT, KS)];
+  __shared__ __attribute__((aligned(16))) float red[forward_red_floats(NG, BT, KS)];
   const int j = blockIdx.z;
   float* dst = steps.dst[j];
   p.x_s = steps.x[j];
