@@ -219,6 +219,12 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
   RawAct<VEC> hraw[(FWD && !SPLIT) ? NHW : 1][BTWF];
   float pf_gate[IPT][4], pf_c[IPT], pf_h[IPT], pf_cprev[IPT], pf_hprev[IPT], pf_dy[IPT];
   const bool want_h = p.dy_is_h || p.y_out != nullptr;
+  // Half tiles leave the upper waves without items: those skip the items' fetches and stores, which
+  // still took their issue slots with every lane masked (sweep of H = 512, B = 64 store all, a whole
+  // run 1.243 -> 1.194 ms; H = 1024 10.92 -> 10.64 ms). With forward operations a branch between the
+  // operands' loads and the items' costs more than it saves (H = 256 2.00 -> 2.18 ms, H = 512 of
+  // 10000 steps 109.6 -> 115.5 ms), so not there.
+  const bool has_items = FWD || wave * 64 < ITEMS;
   auto fetch = [&](int j) {
     const int s = p.s_hi - j;
     const float* src = p.src[j];
@@ -239,6 +245,7 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
       }
     }
     const float* stp = FWD ? src : p.state[j];
+    if (!has_items) return;
 #pragma unroll
     for (int q = 0; q < IPT; ++q) {
       if constexpr (!FWD) {
@@ -334,7 +341,7 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
   const bool slots_whole = !FWD && p.B % VEC == 0;
   T* kept_w = kept + (size_t)wave * IPT * SWEEP_KEPT;
   auto keep_transposed = [&]() {
-    if (!slots_whole) return;
+    if (!slots_whole || !has_items) return;
 #pragma unroll
     for (int q = 0; q < IPT; ++q) {
       union { unsigned u[sizeof(T)]; T t[4]; } pk;
@@ -348,6 +355,7 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
     }
   };
   auto store_kept = [&](int s) {
+    if (!has_items) return;
     const int slot = (s - 1) % p.CH, buf = ((s - 1) / p.CH) & 1;   // where step s lives in the chunk buffers
     T* dG_cur = reinterpret_cast<T*>(p.dG_chunk[buf]) + (size_t)slot * dG_step;
     T* dGT = reinterpret_cast<T*>(p.dGT[buf]);
