@@ -50,7 +50,9 @@ __device__ inline bool draw_rank(unsigned* sync, unsigned launch, int& g, int& r
 // that pattern is a NaN with all payload bits set; a producer publishes it as the NaN next to it.)  A
 // step thus costs one store and one load through the L2 the XCD's compute units share, where a counter
 // costs the store, its acknowledgement, a barrier, an atomic, a load of the counter, a barrier and the
-// fetch one after the other.  A wave waits for the producers of its own part of K only.
+// fetch one after the other.  A wave waits for the producers of its own part of K only.  Measured, this
+// exchange against the counters, whole gradient steps: H = 1024, B = 64 chains 14.8 -> 12.9 ms, sweeps
+// 12.9 -> 12.1 ms; H = 512, B = 256 163.5 -> 126.9 -> 109.5 ms; H = 256, B = 64 3.61 -> 2.86 -> 2.03 ms.
 //
 // Slots are recycled in order: step q goes to slot q mod 4.  Whoever publishes step q has fetched all
 // of step q - 1, whose producers had fetched all of step q - 2: nobody reads q - 2 any more, and the
@@ -164,7 +166,8 @@ __device__ inline float load_h_operand(const float* plane, unsigned e, unsigned 
 // Otherwise the MFMA's own order, sequence fastest: 4 units x 16 sequences (8 x 8 on half a tile).  The difference is in plain planes: 16 rows of
 // 16 bytes per instruction keep a compute unit's address path busy so long that the twenty such
 // loads and stores of a backward step took three times as long as the MFMAs beside them.
-// Either way the blocks of one group of units follow each other (the other order was 4 % slower on H = 512, B = 256).
+// Either way the blocks of one group of units follow each other (columns outermost: a chain launch of H = 1024, B = 64
+// 85.5 -> 90.6 us).  BLOCK order for every plane, split ones too, was 2 % slower on H = 512, B = 256.
 template <int UW, int COLUMNS, bool BLOCK>
 struct Items {
   static constexpr int WU = (BLOCK || COLUMNS == 8) && UW % 8 == 0 ? 8 : 4, WB = 64 / WU;   // units, sequences of a block
@@ -179,7 +182,8 @@ struct Items {
 // Partial sums meet in LDS as the MFMA leaves them: blocks of 64 lanes x 4 consecutive rows.  Writing one costs a
 // compute unit 31 cycles whatever its lanes hold (reading one 17), which at 64 blocks a step was more than
 // the MFMAs; with half a tile of sequences, two row tiles share a block: the second one's sums take the
-// place of the first one's empty columns.
+// place of the first one's empty columns (with the items dense, H = 1024, B = 64 12.14 -> 11.04 ms a gradient
+// step; H = 650, B = 20 2.50 -> 2.13 ms).  Rows permuted against bank conflicts lost 5 % on H = 512, B = 256.
 __device__ inline f32x4 join_halves(f32x4 a, f32x4 b) {
   f32x4 r;
 #pragma unroll
@@ -244,7 +248,10 @@ struct ResParams {
 //      would hold them up;
 //   4. the h part of the GEMM, partial sums through LDS, the pointwise step (c, or the GRU's h, stays in a
 //      register), publish h_s.
-// What bounds a step is this chain of latencies, not bytes or flops: no weight moves.
+// What bounds a step is this chain of latencies, not bytes or flops: no weight moves.  Measured per step,
+// with counters and whole tiles before and so: H = 1024, B = 64 3.3 -> 2.27 us, H = 512, B = 256 3.6 -> 2.03 us.
+// Of the 2.27 us, in cycles of 2.2 GHz: x part 560, polls 620 - 820 (1.0 - 1.4 of them), h part with the
+// stores and the next x 1280, barrier 250 - 520, pointwise step 1050, publishing 170.
 // Sums are formed exactly as forward_body forms them (KS partial sums over the macro steps
 // w, w+KS, ..., added in the order 0..KS-1), so a step gives the same bits either way.  A wave whose part of
 // x or h is shorter than the others' runs its surplus macro steps on zeros.

@@ -49,6 +49,8 @@ struct SweepParams {
 // What only later launches read of a step (dG in the chunk buffer, its transposed copies, the outputs)
 // is stored, and what the next step needs is fetched, right after the polls of the following
 // exchange: memory operations complete in order, so in front of the polls they would hold them up.
+// What bounds a step is that chain of latencies.  Measured per step, with counters and whole tiles before
+// and so: without forward operations H = 1024, B = 64 5.3 -> 3.6 us; with them H = 512, B = 256 6.8 -> 5.0 us.
 // K splits and summation orders are those of forward_body and backward_body for the shape, the
 // pointwise steps are the shared functions: bit-identical to the launch-per-step path.
 // NXW, NHW, KSF: macro steps of x and h per wave and K split of the forward part; NBW, KSB: macro steps of
