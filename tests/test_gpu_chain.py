@@ -390,3 +390,16 @@ def test_resident_launches_pass_on_every_nan(dtype, B, I, H):
     assert np.array_equal(out.y[:, others], clean.y[:, others]) and np.array_equal(out.dx[:, others], clean.dx[:, others])
     assert np.isnan(out.y[2:, bad]).all()
     assert np.array_equal(np.isnan(out.y), np.isnan(base.y)) and np.array_equal(out.y[:, bad + 2], base.y[:, bad + 2], equal_nan=True)
+
+
+@pytest.mark.parametrize("B,I,H", [(32, 128, 512), (33, 300, 512), (128, 130, 384), (129, 130, 384), (40, 64, 256)])
+def test_gemms_beside_or_between_resident_launches(B, I, H):
+    """On both sides of every line of the rule that puts the time-batched GEMMs on a stream of their own:
+    several chunks, with sweep launches that may run on from one chunk into the next."""
+    t = 140
+    w = wl.Workload("chunks", B=B, I=I, H=H, t=t, kind=wl.KIND_HSM, m=9, gemm_dtype=wl.GEMM_BF16, loss=wl.LOSS_EXTERNAL_DY,
+                    dy_first_step=20, seed=77 + B)
+    inp = wl.make_inputs(w, nonzero_state=True, nonzero_bias=True)
+    base = _run(w, inp, wl.KIND_HSM, 9, chain=False)
+    for kind, m in ((wl.KIND_HSM, 9), (wl.KIND_HSM, t), (wl.KIND_ISM, t), (wl.KIND_MSM, 30)):
+        _same(_run(w, inp, kind, m, chain=True), base, (kind, m))
