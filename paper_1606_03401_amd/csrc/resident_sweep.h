@@ -50,7 +50,8 @@ struct SweepParams {
 // is stored, and what the next step needs is fetched, right after the polls of the following
 // exchange: memory operations complete in order, so in front of the polls they would hold them up.
 // What bounds a step is that chain of latencies.  Measured per step, with counters and whole tiles before
-// and so: without forward operations H = 1024, B = 64 5.3 -> 3.6 us; with them H = 512, B = 256 6.8 -> 5.0 us.
+// and so: without forward operations H = 1024, B = 64 5.3 -> 3.6 us; with them H = 512, B = 256 6.8 -> 5.0 us
+// (4.1 - 4.4 with the GEMMs in order).
 // K splits and summation orders are those of forward_body and backward_body for the shape, the
 // pointwise steps are the shared functions: bit-identical to the launch-per-step path.
 // NXW, NHW, KSF: macro steps of x and h per wave and K split of the forward part; NBW, KSB: macro steps of
