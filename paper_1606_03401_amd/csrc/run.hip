@@ -845,7 +845,11 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
       HIP_TRY(tm(MEBPTT_K_DGRAD, st2, [&] {
         // the chunk's dG^T buffer is free from here (its dW GEMM is ahead on the same stream) until the
         // chunk after next fills it: the dx GEMM may keep partial sums there
-        return launch_dx_gemm(d, WTx, ws + w.dG[buf], nslots, dx + x_off, ws + w.dGT[buf], w.dGT[1] - w.dGT[0], st2);
+        hipError_t e = launch_dx_gemm(d, WTx, ws + w.dG[buf], nslots, dx + x_off, ws + w.dGT[buf], w.dGT[1] - w.dGT[0], st2);
+        // ... but the columns that pad the chunk to whole macro steps of K belong to no step and have to stay zero
+        if (e == hipSuccess && dx_gemm_uses_blocks(d, w.dGT[1] - w.dGT[0]))
+          e = launch_zero_operand_columns(d, ws + w.dGT[buf], ws + w.aT[buf], CH * d.B, d.KC, st2);
+        return e;
       }));
     if (side) {
       HIP_TRY(hipEventRecord(side->done[buf], st2));

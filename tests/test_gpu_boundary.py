@@ -179,3 +179,27 @@ def test_measurement_hooks():
     inp = wl.make_inputs(w)
     a = Session(w, inp).run_and_fetch()
     _same(Session(w, inp).run_and_fetch(), a)
+
+
+# (B, I, H, t): chunks whose CH * B columns are no multiple of 32, so that K of the weight-gradient GEMM
+# is padded, on shapes whose dx GEMM lends the chunk's transposed dG buffer as scratch, over three chunks:
+# the third one reuses the first one's buffers.
+@pytest.mark.parametrize("B,I,H,t", [(250, 300, 1056, 65), (129, 512, 2048, 60), (129, 512, 2048, 84)])
+def test_weight_gradient_does_not_depend_on_dx_being_wanted(B, I, H, t):
+    from paper_1606_03401_amd.session import Session
+    w = wl.Workload("dx-scratch", B=B, I=I, H=H, t=t, kind=wl.KIND_HSM, m=8, gemm_dtype=wl.GEMM_BF16,
+                    loss=wl.LOSS_EXTERNAL_DY, seed=B + t)
+    inp = wl.make_inputs(w, nonzero_state=True, nonzero_bias=True)
+    s = Session(w, inp)
+    ch = mb.mebptt_chunk_steps(s.desc)
+    assert (ch * B) % 32 != 0 and t > 2 * ch
+    want = Session(w, inp, want_dx=False).run_and_fetch()
+
+    def check(out):
+        differ = [f for f in FIELDS if f != "dx" and not np.array_equal(getattr(out, f), getattr(want, f))]
+        assert differ == []
+        assert np.isfinite(out.dW_ih).all() and np.isfinite(out.db).all() and np.isfinite(out.dx).all()
+    check(s.run_and_fetch())
+    s.prepare()
+    for _ in range(3):                        # the staging a run leaves behind is the next one's
+        check(s.run_and_fetch())
