@@ -605,6 +605,9 @@ int mebptt_measure_gemms(const mebptt_lstm_desc* desc, void* workspace, size_t w
     if (e == hipSuccess) e = hipEventRecord(ev[2], st);
     if (e == hipSuccess) e = hipEventSynchronize(ev[2]);
   }
+  // a prepared workspace stays prepared: the staging's padding has to be zero
+  if (e == hipSuccess) e = launch_fill(ws + w.dG[0], w.ring - w.dG[0], nullptr, 0, st);
+  if (e == hipSuccess) e = hipStreamSynchronize(st);
   float ms_w = 0.0f, ms_d = 0.0f;
   if (e == hipSuccess) e = hipEventElapsedTime(&ms_w, ev[0], ev[1]);
   if (e == hipSuccess) e = hipEventElapsedTime(&ms_d, ev[1], ev[2]);

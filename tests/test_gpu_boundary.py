@@ -203,3 +203,20 @@ def test_weight_gradient_does_not_depend_on_dx_being_wanted(B, I, H, t):
     s.prepare()
     for _ in range(3):                        # the staging a run leaves behind is the next one's
         check(s.run_and_fetch())
+
+
+@pytest.mark.parametrize("dtype,B,I,H", [(wl.GEMM_BF16, 37, 50, 72), (wl.GEMM_FP32, 37, 50, 72), (wl.GEMM_BF16, 250, 300, 1056)])
+def test_gemm_measurement_leaves_a_prepared_workspace_prepared(dtype, B, I, H):
+    """The GEMMs are measured on the staging buffers of the workspace, dx going into one of them; a
+    prepared run that follows finds the padding of the staging zero all the same."""
+    from paper_1606_03401_amd.session import Session
+    w = wl.Workload("measured", B=B, I=I, H=H, t=70, kind=wl.KIND_HSM, m=8, gemm_dtype=dtype, loss=wl.LOSS_EXTERNAL_DY, seed=B)
+    inp = wl.make_inputs(w, nonzero_state=True, nonzero_bias=True)
+    want = Session(w, inp).run_and_fetch()
+    s = Session(w, inp)
+    s.prepare()
+    _same(s.run_and_fetch(), want)
+    wgrad_us, dgrad_us = mb.mebptt_measure_gemms(s.desc, s.workspace, 3)
+    assert wgrad_us > 0 and dgrad_us > 0
+    out = s.run_and_fetch()
+    assert [f for f in FIELDS if not np.array_equal(getattr(out, f), getattr(want, f))] == []
