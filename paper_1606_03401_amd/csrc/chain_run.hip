@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "common.h"
+#include "dynamic_lds.h"
 
 using namespace mebptt;
 
@@ -243,13 +244,8 @@ constexpr int FILL = 256;   // workgroups that give every compute unit one
 template <int TM, int TN, bool NARROW>
 hipError_t launch_forward_tiles(Product& p, hipStream_t st) {
   constexpr size_t lds = (size_t)KS * TM * TN * 256 * sizeof(float);
-  static bool configured = false;
-  if (!configured) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(chain_forward_kernel<TM, TN, NARROW>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    configured = true;
-  }
+  hipError_t e = allow_dynamic_lds<chain_forward_kernel<TM, TN, NARROW>>(lds);
+  if (e != hipSuccess) return e;
   p.gx = blocks_of(p.N, TN);
   chain_forward_kernel<TM, TN, NARROW><<<dim3(p.gx * blocks_of(p.M, TM)), dim3(KS * 64), lds, st>>>(p);
   return hipGetLastError();
@@ -270,13 +266,8 @@ template <int DTM, int DTN, int WTM, int WTN, bool NARROW>
 hipError_t launch_backward_tiles(Product& data, Product& weight, hipStream_t st) {
   constexpr int tiles = DTM * DTN > WTM * WTN ? DTM * DTN : WTM * WTN;
   constexpr size_t lds = (size_t)KS * tiles * 256 * sizeof(float);
-  static bool configured = false;
-  if (!configured) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(chain_backward_kernel<DTM, DTN, WTM, WTN, NARROW>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    configured = true;
-  }
+  hipError_t e = allow_dynamic_lds<chain_backward_kernel<DTM, DTN, WTM, WTN, NARROW>>(lds);
+  if (e != hipSuccess) return e;
   data.gx = blocks_of(data.N, DTN);
   weight.gx = blocks_of(weight.N, WTN);
   const int nd = data.C ? data.gx * blocks_of(data.M, DTM) : 0, nw = weight.gx * blocks_of(weight.M, WTM);

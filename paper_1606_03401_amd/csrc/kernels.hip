@@ -18,6 +18,7 @@
 #include <algorithm>
 
 #include "device.h"
+#include "dynamic_lds.h"
 
 namespace mebptt {
 
@@ -999,13 +1000,8 @@ template <class T, int NT, int RT, int KS, int U>
 static hipError_t launch_dgrad_cfg(dim3 grid, const T* WT, int N, const T* dG, int nrow_tiles, const Dims& d, float* out,
                                    int ld_out, hipStream_t st) {
   const size_t lds = (size_t)KS * NT * RT * 4 * 64 * sizeof(float);
-  static bool configured = false;   // per instantiation; needed above 64 KiB only, harmless below
-  if (!configured) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(dgrad_kernel<T, NT, RT, KS, U>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    configured = true;
-  }
+  hipError_t e = allow_dynamic_lds<dgrad_kernel<T, NT, RT, KS, U>>(lds);   // needed above 64 KiB only, harmless below
+  if (e != hipSuccess) return e;
   dgrad_kernel<T, NT, RT, KS, U><<<grid, dim3(64 * KS), lds, st>>>(WT, N, dG, nrow_tiles, d.B, d.BP, d.G4, out, ld_out);
   return hipGetLastError();
 }
@@ -1223,13 +1219,8 @@ constexpr int TGEMM_MIN_TILES = 192;   // below this the output does not fill th
 
 template <class T>
 static hipError_t launch_tgemm(const TgemmParams& p, hipStream_t st) {
-  static bool configured = false;
-  if (!configured) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(tgemm_kernel<T>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, TGEMM_LDS_BYTES);
-    if (e != hipSuccess) return e;
-    configured = true;
-  }
+  hipError_t e = allow_dynamic_lds<tgemm_kernel<T>>(TGEMM_LDS_BYTES);
+  if (e != hipSuccess) return e;
   tgemm_kernel<T><<<dim3(p.full + (p.gx * p.gy - p.full) * p.split), dim3(512), TGEMM_LDS_BYTES, st>>>(p);
   return hipGetLastError();
 }

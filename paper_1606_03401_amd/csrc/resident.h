@@ -3,6 +3,7 @@
 #pragma once
 
 #include "device.h"
+#include "dynamic_lds.h"
 
 namespace mebptt {
 
@@ -521,14 +522,9 @@ hipError_t launch_chain_cell(const ResParams& p, hipStream_t st) {
   constexpr int BLOCKS = Sums<NRTW, NBT == 0 ? 0 : NBT / FTB>::BLOCKS;
   constexpr size_t lds = (size_t)8 * BLOCKS * 1024 + (size_t)8 * NRTW * NXL * 1024;
   static_assert(lds <= 160 * 1024 - 64, "LDS of a compute unit");
-  auto kernel = forward_chain_kernel<T, NRT, NXW, NXL, NHW, KS, NBT, CELL>;
-  static bool configured = false;   // per instantiation; the attribute only has to be set once
-  if (!configured) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    configured = true;
-  }
-  kernel<<<dim3(RES_WGS), dim3(512), lds, st>>>(p);
+  hipError_t e = allow_dynamic_lds<forward_chain_kernel<T, NRT, NXW, NXL, NHW, KS, NBT, CELL>>(lds);
+  if (e != hipSuccess) return e;
+  forward_chain_kernel<T, NRT, NXW, NXL, NHW, KS, NBT, CELL><<<dim3(RES_WGS), dim3(512), lds, st>>>(p);
   return hipGetLastError();
 }
 

@@ -506,14 +506,9 @@ hipError_t launch_sweep_cell(const SweepParams& p, hipStream_t st) {
   constexpr int blocksB = Sums<NTB, NBT == 0 ? 0 : NB / BTB>::BLOCKS, blocksF = Sums<(NRT + FTR - 1) / FTR, NBT == 0 ? 0 : NB / FTB>::BLOCKS;
   constexpr size_t lds = (size_t)8 * (blocksB + (FWD ? blocksF : 0) + NTB * NBL) * 1024 + (size_t)8 * IPT * SWEEP_KEPT * sizeof(T);
   static_assert(lds <= 160 * 1024 - 64, "LDS of a compute unit");
-  auto kernel = sweep_kernel<T, FWD, NRT, NXW, NHW, KSF, NBW, NBL, KSB, NBT, CELL>;
-  static bool configured = false;   // per instantiation; the attribute only has to be set once
-  if (!configured) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    configured = true;
-  }
-  kernel<<<dim3(RES_WGS), dim3(512), lds, st>>>(p);
+  hipError_t e = allow_dynamic_lds<sweep_kernel<T, FWD, NRT, NXW, NHW, KSF, NBW, NBL, KSB, NBT, CELL>>(lds);
+  if (e != hipSuccess) return e;
+  sweep_kernel<T, FWD, NRT, NXW, NHW, KSF, NBW, NBL, KSB, NBT, CELL><<<dim3(RES_WGS), dim3(512), lds, st>>>(p);
   return hipGetLastError();
 }
 

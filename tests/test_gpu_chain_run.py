@@ -3,6 +3,8 @@ of dense tanh layers of differing widths under the three-dimensional policy) aga
 oracle, through the C ABI: gradients within the fp32 tolerance at every budget, bit-identical
 across budgets, forward cost equal to the oracle's C(n, m, 0), pool use within the budget (guard
 bytes around the pool and the workspace)."""
+import threading
+
 import numpy as np
 import pytest
 
@@ -125,3 +127,31 @@ def test_chain_products_at_the_edges_of_their_tiles(widths, B):
     for i in range(len(widths) - 1):
         assert max(_errs(out["dW"][i], ref.dW[i])) <= TOL and max(_errs(out["db"][i], ref.db[i])) <= TOL, i
     assert max(_errs(out["dx0"], ref.dx0)) <= TOL and max(_errs(out["y"], ref.y)) <= TOL
+
+
+def test_chain_runs_from_two_host_threads():
+    """The call takes no lock: two threads that make their first calls at the same time each set up the
+    launches they need."""
+    shapes = [([600, 1030, 514], 129), ([1100, 2100, 1025], 70)]
+    args = [(w, B, 4096, sum(-(-B * d * 4 // 4096) for d in w[1:]), *_inputs(w, B, 7 + B)) for w, B in shapes]
+    got, errors = [[], []], []
+
+    def worker(k):
+        try:
+            for _ in range(3):
+                got[k].append(_run(*args[k])[0])
+        except Exception as exc:   # noqa: BLE001 - reported by the main thread
+            errors.append(exc)
+
+    threads = [threading.Thread(target=worker, args=(k,)) for k in range(2)]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join(timeout=100)
+    assert not errors, errors
+    for k in range(2):
+        want = _run(*args[k])[0]
+        assert len(got[k]) == 3
+        for out in got[k]:
+            assert np.array_equal(out["dx0"], want["dx0"]) and np.array_equal(out["y"], want["y"])
+            assert all(np.array_equal(a, b) for f in ("dW", "db") for a, b in zip(out[f], want[f]))
