@@ -13,7 +13,7 @@
 //   backward weight dW   [d_i, d_{i-1}] = dz^T . y_{i-1}                            (K = B), db = column sums of dz
 // The epilogue of the data product turns the gradient with respect to y_{i-1} into dz of the layer below at
 // once; only the last layer's dz has a launch of its own.  The two backward products of a layer need
-// nothing from each other and share a launch.
+// nothing from each other and share a launch, except where dx0 is to be written over x0.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -222,7 +222,7 @@ __global__ __launch_bounds__(KS * 64) void chain_forward_kernel(Product p) {
   extern __shared__ __attribute__((aligned(16))) float chain_smem[];
   product_body<false, false, TM, TN, BIAS_TANH, NARROW>(p, blockIdx.x, chain_smem);
 }
-// The first nd workgroups compute the data product (none: nd = 0), the others the weight product.
+// The first nd workgroups compute the data product (none: nd = 0), the others, if any, the weight product.
 template <int DTM, int DTN, int WTM, int WTN, bool NARROW>
 __global__ __launch_bounds__(KS * 64) void chain_backward_kernel(Product data, int nd, Product weight) {
   extern __shared__ __attribute__((aligned(16))) float chain_smem[];
@@ -270,7 +270,7 @@ hipError_t launch_backward_tiles(Product& data, Product& weight, hipStream_t st)
   if (e != hipSuccess) return e;
   data.gx = blocks_of(data.N, DTN);
   weight.gx = blocks_of(weight.N, WTN);
-  const int nd = data.C ? data.gx * blocks_of(data.M, DTM) : 0, nw = weight.gx * blocks_of(weight.M, WTM);
+  const int nd = data.C ? data.gx * blocks_of(data.M, DTM) : 0, nw = weight.C ? weight.gx * blocks_of(weight.M, WTM) : 0;
   chain_backward_kernel<DTM, DTN, WTM, WTN, NARROW><<<dim3(nd + nw), dim3(KS * 64), lds, st>>>(data, nd, weight);
   return hipGetLastError();
 }
@@ -287,6 +287,8 @@ hipError_t launch_chain_backward(Product data, Product weight, hipStream_t st) {
 }
 
 unsigned blocks_for(size_t n) { return (unsigned)std::min<size_t>((n + 255) / 256, 2048); }
+
+bool overlap(const float* a, const float* b, size_t n) { return a < b + n && b < a + n; }
 
 constexpr size_t ALIGN = 256;
 size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
@@ -481,7 +483,15 @@ int mebptt_chain_run(const mebptt_chain_desc* desc, const mebptt_chain_plan_t* p
       weight.N = din;
       weight.K = B;
       weight.db = db[L - 1];
-      HIP_TRY(launch_chain_backward(data, weight, st));
+      if (L == 1 && dx0 && overlap(dx0, x0, (size_t)B * din)) {   // dx0 takes the place of x0: after its last reader
+        Product no_data = data, no_weight = weight;
+        no_data.C = nullptr;
+        no_weight.C = nullptr;
+        HIP_TRY(launch_chain_backward(no_data, weight, st));
+        HIP_TRY(launch_chain_backward(data, no_weight, st));
+      } else {
+        HIP_TRY(launch_chain_backward(data, weight, st));
+      }
       zflip ^= 1;
       ++backward_ops;
       wk_out = nullptr;   // consumed: the next backward operation needs its own forward operation

@@ -35,7 +35,7 @@ def _errs(got, ref):
     return (np.linalg.norm(d) / max(np.linalg.norm(ref), 1e-300), np.abs(d).max() / max(np.abs(ref).max(), 1e-300))
 
 
-def _run(widths, B, unit_bytes, m, W, b, x0, dy):
+def _run(widths, B, unit_bytes, m, W, b, x0, dy, dx0_over_x0=False):
     import torch
     dev = torch.device("cuda:0")
     desc = mb.make_chain_desc(widths, B, unit_bytes)
@@ -45,7 +45,7 @@ def _run(widths, B, unit_bytes, m, W, b, x0, dy):
     tW, tb, tx, tdy = [up(w) for w in W], [up(v) for v in b], up(x0), up(dy)
     dW = [torch.full_like(w, float("nan")) for w in tW]
     db = [torch.full_like(v, float("nan")) for v in tb]
-    dx0, y = torch.full_like(tx, float("nan")), torch.full_like(tdy, float("nan"))
+    dx0, y = tx if dx0_over_x0 else torch.full_like(tx, float("nan")), torch.full_like(tdy, float("nan"))
     pool_bytes = m * unit_bytes
     pool_outer = torch.full((pool_bytes + 2 * GUARD,), PATTERN, dtype=torch.uint8, device=dev)
     ws_bytes = mb.mebptt_chain_workspace_bytes(desc)
@@ -155,3 +155,12 @@ def test_chain_runs_from_two_host_threads():
         for out in got[k]:
             assert np.array_equal(out["dx0"], want["dx0"]) and np.array_equal(out["y"], want["y"])
             assert all(np.array_equal(a, b) for f in ("dW", "db") for a, b in zip(out[f], want[f]))
+
+
+@pytest.mark.parametrize("widths,B", [([1030, 600, 514], 129), ([3, 5], 7), ([2048, 1024], 512)])
+def test_input_gradient_over_the_input(widths, B):
+    """dx0 may be x0's own buffer: it is written after the last reader of x0."""
+    args = (widths, B, 4096, sum(-(-B * d * 4 // 4096) for d in widths[1:]), *_inputs(widths, B, 31 + B))
+    want, out = _run(*args)[0], _run(*args, dx0_over_x0=True)[0]
+    assert np.array_equal(out["dx0"], want["dx0"]) and np.array_equal(out["y"], want["y"])
+    assert all(np.array_equal(a, b) for f in ("dW", "db") for a, b in zip(out[f], want[f]))
