@@ -205,7 +205,7 @@ const mebptt_layer* mebptt_chain_plan_layers(const mebptt_chain_plan_t* plan, in
  * that differ from layer to layer, fp32 throughout (fp32 MFMA tiles, fp32 accumulate).  Memory is
  * counted in units of unit_bytes: the output of layer i takes ceil(B d_i 4 / unit_bytes) units, its
  * forward cost is d_{i-1} d_i (multiply-adds per sequence), and the working memory of an operation
- * (two activations, the gradient passed down, one dz) is the caller's workspace, outside the
+ * (two activations, the dz of a layer and of the one below) is the caller's workspace, outside the
  * budget (work_units = 0) -- the same accounting as the LSTM path's working core.
  * mebptt_chain_layers fills `out` (host, n entries) with that table for mebptt_chain_plan. */
 typedef struct {

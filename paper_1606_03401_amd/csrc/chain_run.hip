@@ -3,8 +3,8 @@
 //     y_i = tanh(y_{i-1} W_i^T + b_i),   W_i [d_i, d_{i-1}],   i = 1 .. n
 // of differing widths, so that forward cost u_i = d_{i-1} d_i and state size s_i = B d_i differ from
 // layer to layer.  Memorised outputs live in the caller's pool at the unit offsets the plan
-// assigned; everything else (the two most recent activations of a forward run, the gradient being
-// passed down, one layer's dz) is working memory in the caller's workspace, outside the budget.
+// assigned; everything else (the two most recent activations of a forward run, the dz of the layer being
+// back-propagated and of the one below) is working memory in the caller's workspace, outside the budget.
 //
 // All three products of a layer run in one kernel body on fp32 MFMA tiles (v_mfma_f32_16x16x4_f32, fp32
 // accumulate), operands read in place whichever way they are stored:
@@ -334,8 +334,8 @@ int mebptt_chain_layers(const mebptt_chain_desc* desc, mebptt_layer* out) {
 
 size_t mebptt_chain_workspace_bytes(const mebptt_chain_desc* desc) {
   if (check_chain_desc(desc) != MEBPTT_OK) return 0;
-  // two activations, two gradients, one dz, each of the widest layer
-  return 5 * align_up((size_t)desc->B * max_width(desc) * sizeof(float));
+  // two activations, the dz of a layer and of the layer below it, each of the widest layer
+  return 4 * align_up((size_t)desc->B * max_width(desc) * sizeof(float));
 }
 
 int mebptt_chain_run(const mebptt_chain_desc* desc, const mebptt_chain_plan_t* plan, const float* const* W,

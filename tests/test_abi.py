@@ -66,3 +66,9 @@ def test_size_queries():
     assert mb.mebptt_units_for_bytes(d, mb.ISM, 4_000_000_000) == 4_000_000_000 // (4 * unit)
     assert mb.mebptt_units_for_bytes(d, mb.HSM, unit - 1) == 0
     assert mb.mebptt_workspace_bytes(mb.make_desc(0, 256, 1024, 7, 1, 0, 1)) == 0
+
+
+def test_dense_chain_workspace_holds_two_activations_and_two_gradients():
+    desc = mb.make_chain_desc([70, 2047, 65], 510, 4096)
+    slab = (510 * 2047 * 4 + 255) // 256 * 256
+    assert mb.mebptt_chain_workspace_bytes(desc) == 4 * slab
