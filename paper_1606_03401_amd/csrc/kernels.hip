@@ -650,7 +650,10 @@ static hipError_t launch_forward_t(const Dims& d, const FwdParams& p, hipStream_
     case FWD_TINY: return launch_forward_cfg<T, 1, 1, 4, 2>(d, p, st);   // tiny K: one small workgroup per tile
     case FWD_SMALLK: return launch_forward_cfg<T, 4, 1, 4, 5>(d, p, st);
     case FWD_82: return launch_forward_cfg<T, 8, 2, 8, 1>(d, p, st);
-    case FWD_42: return launch_forward_cfg<T, 4, 2, 8, 2>(d, p, st);   // two macro steps in flight: 26.6 us on H = 4096, B = 32; three 27.3, four waves 27.9
+    // bf16: two macro steps in flight, 26.6 us on H = 4096, B = 32; three 27.3, four waves 27.9.  fp32, whose macro
+    // steps are half as long: three; a gradient step of H = 1024, B = 128 (t = 60) takes 5.12 ms so, 5.57 with two, of
+    // H = 4096, B = 32 (t = 20) 6.75 against 8.07
+    case FWD_42: return launch_forward_cfg<T, 4, 2, 8, sizeof(T) == 2 ? 2 : 3>(d, p, st);
     default: return launch_forward_cfg<T, PAIR_NG, 1, PAIR_FKS, 5>(d, p, st);
   }
 }
@@ -726,8 +729,9 @@ static void launch_forward_batch_t(const Dims& d, const FwdParams& p, const FwdB
   // 64 gate rows x 32 sequences per workgroup, two macro steps in flight per wave: two workgroups
   // fit a compute unit.  Measured on H = 1024, B = 64, partial sums as single floats: 2.7 us per operation;
   // 64 x 64 tiles 3.1 us, three or four macro steps in flight 4.4 - 5.1 us.  With the sums as 16-byte
-  // vectors a launch of 17 operations takes 43.8 us instead of 45.4.
-  constexpr int NG = 4, BT = 2, FU = 2;
+  // vectors a launch of 17 operations takes 43.8 us instead of 45.4.  fp32 as the stand-alone kernel: three (whole
+  // gradient steps 1 % faster than with two, which needs scratch memory).
+  constexpr int NG = 4, BT = 2, FU = sizeof(T) == 2 ? 2 : 3;
   const dim3 grid((d.HP / 4 + NG - 1) / NG, (d.BP / 16 + BT - 1) / BT, n);
   const size_t plane = (size_t)d.B * d.H;
   const FwdConfig cfg = forward_config<T>(d);

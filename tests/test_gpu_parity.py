@@ -429,6 +429,14 @@ def test_small_k_fused_launches_bit_identical():
                     assert np.array_equal(getattr(out, name), getattr(first, name)), (cell, kind, m, name)
 
 
+@pytest.mark.parametrize("B,I,H", [(130, 101, 1001), (128, 256, 1024)])
+def test_wide_fp32_tiles(B, I, H):
+    """fp32 operands on the 64 x 32 forward tiles, rows of whole and of broken fragments."""
+    w = wl.Workload("wide-fp32", B=B, I=I, H=H, t=5, kind=wl.KIND_HSM, m=2, gemm_dtype=wl.GEMM_FP32, loss=wl.LOSS_EXTERNAL_DY,
+                    dy_first_step=2, seed=79)
+    run_case(w, nonzero=True)
+
+
 def test_graph_replay_matches_eager():
     """A run captured into a HIP graph: several replays, with eager runs, output clobbering and
     synchronisations in between, must each reproduce the eager result bit for bit."""
