@@ -350,15 +350,18 @@ int mebptt_run_prepared(const mebptt_lstm_desc* desc, const mebptt_plan_t* plan,
  * each other, every input state being in a slot already -- go out as one "forward-batch" launch that leaves the
  * internal states in the workspace's stage, followed by one sweep launch of
  * backward operations on them; backward operations on internal states stored in slots go out as
- * such sweep launches as well.  Results are bit-identical to the launch-per-step path.  Such a launch assumes that its 256 workgroups are all resident and dealt
- * round-robin to the XCDs; each workgroup checks this, every wait inside is bounded by a wall
- * clock, and a launch that cannot proceed gives up and raises a status word in the workspace
+ * such sweep launches as well.  Results are bit-identical to the launch-per-step path.  The workgroups of
+ * such a launch that share an XCD wait for each other and have to be on the chip together.  Where other work (another
+ * stream, the replay of a captured graph, another process, perhaps another such launch) keeps some of them
+ * off it, the launch is given up for that XCD after a while and one workgroup there runs its steps alone: the same
+ * results, slowly.  Runs may therefore overlap in any way; the library orders its own eager runs across streams
+ * with an event, which is faster, and so is ordering what else wants the device.  The launch relies on its 256
+ * workgroups being dealt round-robin to the XCDs; each workgroup checks this, every wait inside is bounded by a wall
+ * clock, and a launch that cannot proceed raises a status word in the workspace
  * instead of hanging.  mebptt_run_status copies that word to *status (host) after waiting for
  * `stream`: 0 = every launch of the last run on this workspace completed; non-zero = a launch
- * gave up and the run's outputs are invalid (1: a wait ran into its bound, 2: a workgroup was
- * not placed on the XCD its id implies).  Two runs that use such launches must not overlap on one
- * device (each would hold a part of the chip and wait for the rest): the library orders its own
- * eager runs across streams with an event; replays of captured graphs are the caller's to order.
+ * gave up and the run's outputs are invalid (1: a wait ran into its bound, 2: more than 32 workgroups were
+ * placed on one XCD).
  * Errors: EINVAL, EWORKSPACE, EHIP. */
 int mebptt_run_status(const mebptt_lstm_desc* desc, const void* workspace, size_t workspace_bytes, void* stream,
                       int32_t* status);
@@ -377,6 +380,11 @@ int mebptt_forward_chain_enable(int32_t on);
  * a real time-out takes, made reachable for tests.  Process-wide; applies to launches enqueued
  * after the call. */
 int mebptt_resident_wait_limit(int64_t ticks);
+/* How long the workgroups of a forward-chain or sweep launch wait for each other before the launch is given up for
+ * their XCD and one of them runs alone, in the same ticks (negative, the default: about as long as that would
+ * take, at least 0.5 ms; never longer than the bound above).  0: one workgroup per XCD runs alone from the start.  For
+ * tests of that path.  Process-wide; applies to launches enqueued after the call. */
+int mebptt_resident_patience(int64_t ticks);
 
 /* Releases what the library created on every device: the side streams and their events, the
  * events of the measurement hooks, the record of prepared workspaces.  Waits for the side

@@ -109,14 +109,15 @@ hipError_t launch_backward_forward_pair(const Dims& d, const BackwardArgs& a, co
 // chip (shapes for which can_run_forward_chain() holds).  Step j (0-based) of the chain consumes
 // x_first + j*B*I; its state goes to steps[j].out and its gates to the two units at
 // steps[j].gates where these are not NULL (states nobody asked for never leave the chip).
-// `ring` (forward_chain_ring_bytes, every byte 0xff before the first chain launch of a run) and `sync`
-// (resident_sync_bytes, zero before the first resident launch of a run) are workspace; `published` is the number
-// of states the run's earlier chain launches exchanged (count each), `launch` the number of its earlier
+// `ring` (forward_chain_ring_bytes, every byte 0xff before the first chain launch of a run), `spare` (B * H floats)
+// and `sync` (resident_sync_bytes, zero before the first resident launch of a run) are workspace; `published` is the
+// number of states the run's earlier chain launches exchanged (count each), `launch` the number of its earlier
 // resident launches of any kind.
 // The word at resident_status_offset() inside `sync` is a status word: 0, or non-zero when
-// a launch gave up (an XCD did not receive exactly 32 of the 256 workgroups, or a wait ran into
-// its wall-clock bound); results are then invalid.  Launches that overlap
-// on the device would wait for each other's compute units: the caller orders them.
+// a launch gave up (an XCD received more than 32 of the 256 workgroups, or a wait ran into
+// its wall-clock bound); results are then invalid.  A launch whose workgroups are not all on the chip after a
+// while -- other work holds compute units, perhaps another such launch that waits for them too -- carries on with
+// one workgroup per XCD: the same results, slowly.  The caller orders what it can order.
 struct ChainStep {
   float* out;
   float* gates;
@@ -124,13 +125,16 @@ struct ChainStep {
 // Bound of every wait inside a resident launch, in ticks of the 100 MHz wall clock (negative: the
 // default of 0.5 s).  0 makes every wait give up at once.
 void set_resident_wait_ticks(long long ticks);
+// Bound of the wait for a launch's first exchange, in the same ticks (negative: the default, by what running alone would
+// take).  0: only one workgroup per XCD runs, alone.
+void set_resident_patience(long long ticks);
 bool can_run_forward_chain(const Dims& d);
 int forward_chain_max_steps();
 size_t forward_chain_ring_bytes(const Dims& d);
 size_t resident_sync_bytes();
 size_t resident_status_offset();
 hipError_t launch_forward_chain(const Dims& d, const void* Wp, const float* bp, const float* x_first, const float* src_unit,
-                                const ChainStep* steps, int count, void* ring, unsigned* sync, unsigned published,
+                                const ChainStep* steps, int count, void* ring, float* spare, unsigned* sync, unsigned published,
                                 unsigned launch, hipStream_t st);
 
 // A run of (forward operation keeping the internal state, backward operation) pairs for steps

@@ -13,14 +13,23 @@ namespace mebptt {
 // split the hidden units.  Which XCD a workgroup runs on is read from the hardware (register XCC_ID),
 // not inferred from its id: workgroups are dealt round-robin to the XCDs, but where the deal starts
 // depends on the launches before.  A workgroup takes the next free rank of its XCD from a counter; the
-// launch relies on every XCD receiving exactly 32 of the 256 workgroups, checks it (a rank counter that
-// runs past 32 raises the status word; an XCD that gets fewer never completes its first wait, which is
-// bounded by a wall-clock limit like every other) and gives up rather than compute on an assumption
-// that does not hold.
+// launch relies on no XCD receiving more than 32 of the 256 workgroups, checks it (a rank counter that
+// runs past 32 raises the status word) and gives up rather than compute on an assumption that does
+// not hold.
+//
+// The workgroups of an XCD wait for each other, so all that have units (`producers`: the first ranks) have to
+// be on the chip at once.  Work of somebody else -- another stream, a replayed graph, another process -- can keep
+// some of them off it, and two resident launches can keep each other off for good.  A workgroup whose first
+// exchange does not come within `patience` therefore gives the launch up for its XCD, in one atomic step on the
+// rank word that only succeeds while producers are missing (then nobody can have got past the first exchange, and
+// nothing a launch leaves behind has been written).  The others see it and leave, late ones leave at once, and
+// the one that gave up runs all steps for the XCD's sequences alone: slow, but it waits for nobody, and its
+// sums are formed in the same order.
 constexpr int RES_WGS = 256, RES_GROUPS = 8, RES_MEMBERS = RES_WGS / RES_GROUPS;
 constexpr int RES_RING = 4;   // exchange slots
-// sync words: rank counter of XCD g at [g * 64], status at [512]
-constexpr int RES_SYNC_RANK = 0, RES_SYNC_STATUS = 512;
+// sync words of XCD g from [g * 64] on: the rank word (the counter in its low half, in its high half the launch given
+// up last, + 1), the workgroups that have left that launch; status at [512]
+constexpr int RES_SYNC_RANK = 0, RES_SYNC_LEFT = 2, RES_SYNC_STATUS = 512;
 
 __device__ inline unsigned xcc_id() {
   unsigned v;
@@ -28,20 +37,24 @@ __device__ inline unsigned xcc_id() {
   return v & 0xf;
 }
 
-// One thread of a workgroup: draws the workgroup's rank on its XCD.  False: the workgroups were not
-// dealt 32 per XCD (the status word says so).
+__device__ inline unsigned long long* rank_word(unsigned* sync, int g) {
+  return reinterpret_cast<unsigned long long*>(sync + RES_SYNC_RANK + g * 64);
+}
+
+// One thread of a workgroup: draws the workgroup's rank on its XCD.  False: nothing to do here; the workgroups
+// were not dealt 32 per XCD (the status word says so), or the XCD has given this launch up.
 __device__ inline bool draw_rank(unsigned* sync, unsigned launch, int& g, int& rank) {
   const unsigned xcc = xcc_id();
   bool ok = xcc < (unsigned)RES_GROUPS;
-  unsigned ticket = 0;
+  unsigned long long word = 0;
   if (ok) {
-    ticket = __hip_atomic_fetch_add(sync + RES_SYNC_RANK + xcc * 64, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    ok = ticket / RES_MEMBERS == launch;   // more than 32 workgroups on this XCD: ranks would collide
+    word = __hip_atomic_fetch_add(rank_word(sync, (int)xcc), 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    ok = (unsigned)word / RES_MEMBERS == launch;   // more than 32 workgroups on this XCD: ranks would collide
   }
   if (!ok) __hip_atomic_store(sync + RES_SYNC_STATUS, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   g = ok ? (int)xcc : 0;
-  rank = (int)(ticket % RES_MEMBERS);
-  return ok;
+  rank = (int)((unsigned)word % RES_MEMBERS);
+  return ok && (unsigned)(word >> 32) != launch + 1;
 }
 
 // ---- the exchange ------------------------------------------------------------------------------------
@@ -76,9 +89,9 @@ __device__ inline u32x4 load_slot_16(const void* slot, unsigned byte_off, int un
 __device__ inline unsigned largest_dword(u32x4 v) { return max(max(v.x, v.y), max(v.z, v.w)); }
 __device__ inline unsigned not_empty(unsigned v) { return min(v, RES_EMPTY - 1u); }   // for a value about to be published
 
-// The bound of a wait: true when it is time to give up (the status word is then non-zero).
+// The bound of a wait: true when it is time to stop waiting, or a launch of the run has failed.
 struct WaitBound {
-  long long ticks;      // of the 100 MHz wall clock; 0: give up after one look
+  long long ticks;      // of the 100 MHz wall clock; 0: stop after one look
   unsigned* status;
   int polls = 0;
   long long t0 = 0;
@@ -86,11 +99,93 @@ struct WaitBound {
     if (ticks != 0 && (++polls & 15) != 0) return false;
     const long long now = wall_clock64();
     if (t0 == 0) t0 = now;
-    if (now - t0 < ticks && __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) return false;
-    __hip_atomic_store(status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return true;
+    return now - t0 >= ticks || __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
   }
 };
+
+// The kernel's arguments (it has one, a struct) once more, by an address the compiler cannot see through: what only
+// a workgroup that has stopped waiting reads is not fetched ahead, and kept in registers, for the others.
+template <class P>
+__device__ __forceinline__ const __attribute__((address_space(4))) P* arguments_again() {
+  auto* p = (const __attribute__((address_space(4))) P*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
+// Where a workgroup's waves go, all of them, when one has stopped waiting (*s_fail: 1 + the step).  There is no way
+// back into the loop over the steps, and none to the kernel's end: an exit that rejoined either had the
+// compiler copy what the loop carries and wait for the step's stores, in every step (H = 512, B = 256
+// 3 - 9 % slower); for the same reason it takes nothing along but LDS.  carry_on: all steps once more, slowly -- for
+// all units of the XCD's sequences where this workgroup has given the launch up, for its own UW where all
+// producers have turned out to be here after all.
+template <class P, int UW, class CarryOn>
+__device__ __forceinline__ void stop_waiting(const int* s_g, const int* s_rank, int* s_fail, CarryOn&& carry_on) {
+  const auto& p = *arguments_again<P>();
+  const int g = __builtin_amdgcn_readfirstlane(*s_g), rank = __builtin_amdgcn_readfirstlane(*s_rank);
+  const int units = units_of(p), producers = (units + UW - 1) / UW;
+  unsigned* sync = p.sync;
+  unsigned* left = sync + RES_SYNC_LEFT + g * 64;
+  __threadfence();   // the workgroup's own stores are done when it says that it leaves
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    enum { LEAVE, ALONE, TOGETHER };
+    int role = LEAVE;
+    bool ok = *s_fail == 1 && p.wait_ticks != 0 && __hip_atomic_load(sync + RES_SYNC_STATUS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u;
+    if (ok && p.alone) {
+      role = ALONE;
+    } else if (ok) {
+      unsigned long long* word = rank_word(sync, g);
+      unsigned long long v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      unsigned here = 0;
+      while (role == LEAVE && (unsigned)(v >> 32) != p.launch + 1) {
+        here = (unsigned)v - p.launch * RES_MEMBERS;
+        if ((int)here >= producers)
+          role = TOGETHER;
+        else if (__hip_atomic_compare_exchange_strong(word, &v, (unsigned long long)(p.launch + 1) << 32 | (unsigned)v, __ATOMIC_RELAXED,
+                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+          role = ALONE;
+      }
+      if (role == LEAVE) __hip_atomic_fetch_add(left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (role == ALONE) {   // those who are here see it, and leave
+        WaitBound bound{p.wait_ticks, sync + RES_SYNC_STATUS};
+        while (ok && __hip_atomic_load(left, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != here - 1) ok = !bound.expired();
+        __hip_atomic_store(left, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+      }
+    }
+    if (!ok) __hip_atomic_store(sync + RES_SYNC_STATUS, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *s_fail = ok ? role : (int)LEAVE;
+  }
+  __threadfence();
+  __syncthreads();
+  const int role = __builtin_amdgcn_readfirstlane(*s_fail);
+  __syncthreads();
+  if (role != 0) {
+    if (threadIdx.x == 0) *s_fail = 0;
+    carry_on(g * p.nb, min(p.B, (g + 1) * p.nb), role == 1 ? 0 : rank * UW, role == 1 ? units : min((rank + 1) * UW, units));
+  }
+  __builtin_amdgcn_endpgm();
+}
+// For carry_on, all threads, before a step: waits until the exchange slot is there, `pieces` fragments of each of the
+// XCD's batch tiles, off: this lane's offset in a tile.  False: it does not come (the status word says so).
+template <class Off>
+__device__ __forceinline__ bool slot_is_there(const void* slot, int pieces, int tiles, Off&& off, long long wait_ticks, unsigned* status,
+                                              int* s_fail) {
+  __threadfence();   // what this workgroup's waves have stored for the step can be fetched
+  __syncthreads();
+  WaitBound bound{wait_ticks, status};
+  for (int m = (int)(threadIdx.x >> 6); m < pieces; m += 8)
+    for (int t = 0; t < tiles; ++t)
+      while (__builtin_amdgcn_ballot_w64(largest_dword(load_slot_16(slot, off(t), m * 1024)) == RES_EMPTY) != 0) {
+        if (bound.expired()) {
+          __hip_atomic_store(status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          *s_fail = 1;
+          break;
+        }
+        asm volatile("" ::: "memory");   // the next look is another load
+      }
+  __syncthreads();
+  return *s_fail == 0;
+}
 
 // A barrier that orders LDS only: stores to memory stay in flight across it.
 __device__ inline void lds_barrier() {
@@ -225,15 +320,162 @@ struct ResParams {
   const float* x0;     // x of the first step of this launch
   const float* src;    // unit holding the input state of the first step
   void* ring;          // RES_RING slots [BP][KH] of GEMM operands, fragment-tiled
+  float* spare;        // [B][H]: the state that stays in registers, where a workgroup carries on slowly
   unsigned* sync;
   unsigned published;  // states published by this run's chain launches before this one
   unsigned launch;     // resident launches of this run before this one (every rank counter stands at 32 * launch)
   long long wait_ticks;   // bound of every wait, in ticks of the 100 MHz wall clock
+  long long patience;     // bound of the first one: then the launch may be given up
+  int alone;              // only rank 0 of each XCD runs, and carries on alone
   int count;
   int B, I, H, HP, KX, KH, BP, nb;
   size_t unit, hplane; // floats per unit, floats of its h part
   ResStep step[RES_MAX_STEPS];
 };
+__device__ inline int units_of(const __attribute__((address_space(4))) ResParams& p) { return p.KH; }   // dealt out among an XCD's workgroups
+
+// Gate sums of 16 packed rows (units 4 * tile .. + 3) and 16 sequences, by one wave on its own, for workgroups
+// that carry on slowly: the KS partial sums of the cooperating waves one beside the other, added in their order.
+// load_h(m): this lane's h fragment of macro step m.  Two loops over K, four macro steps in flight (eight would
+// set the register count of the smaller instantiations, and two launches of those fit the chip together); steps
+// outside a loop's range run on zeros.
+template <class T, int KS, class LoadH>
+__device__ __forceinline__ void gates_slowly(const void* Wp, int tile, const float* x, unsigned xrow, int I, int nsx, int nsh, LoadH&& load_h,
+                                   float (&G)[4]) {
+  using M = Mma<T>;
+  constexpr int VEC = M::VEC, KSTEP = 4 * VEC, FRAG = 64 * VEC;
+  const int lane = threadIdx.x & 63, lq = lane >> 4, nsteps = nsx + nsh;
+  const T* base = reinterpret_cast<const T*>(Wp) + ((size_t)tile * nsteps * 64 + lane) * VEC;
+  f32x4 acc[KS];
+#pragma unroll
+  for (int w = 0; w < KS; ++w) acc[w] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0; s0 < nsx; s0 += KS) {
+#pragma unroll
+    for (int w0 = 0; w0 < KS; w0 += 4) {
+      typename M::Frag a[4];
+      RawAct<VEC> raw[4];
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        a[w] = M::load(base + (size_t)min(s0 + w0 + w, nsx - 1) * FRAG);
+        raw[w] = load_window<VEC>(x, xrow, (s0 + w0 + w) * KSTEP + VEC * lq, I);
+      }
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        if (s0 + w0 + w >= nsx) a[w] = typename M::Frag{};
+        shift_tail<VEC>(raw[w], (s0 + w0 + w) * KSTEP + VEC * lq, I);
+        acc[w0 + w] = M::mma(a[w], M::from_f32(raw[w].v), acc[w0 + w]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  for (int s0 = nsx / KS * KS; s0 < nsteps; s0 += KS) {
+#pragma unroll
+    for (int w0 = 0; w0 < KS; w0 += 4) {
+      typename M::Frag a[4], f[4];
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const int s = min(max(s0 + w0 + w, nsx), nsteps - 1);
+        a[w] = M::load(base + (size_t)s * FRAG);
+        f[w] = load_h(s - nsx);
+      }
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        if (s0 + w0 + w < nsx || s0 + w0 + w >= nsteps) a[w] = f[w] = typename M::Frag{};
+        acc[w0 + w] = M::mma(a[w], f[w], acc[w0 + w]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) G[r] = 0.0f;
+#pragma unroll
+  for (int w = 0; w < KS; ++w)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) G[r] += acc[w][r];
+}
+
+// All steps of a launch for units [u0, u1) of the XCD's sequences, by a workgroup that has stopped waiting.  Its waves
+// deal the units out four at a time; the state that stays in registers in a chain goes through `spare`, and the
+// weights are fetched again in every step.
+template <class T, int KS, int CELL>
+__device__ __forceinline__ void chain_slowly(int b_lo, int b_hi, int u0, int u1, int* s_fail) {
+  const auto& p = *arguments_again<ResParams>();
+  using M = Mma<T>;
+  constexpr int VEC = M::VEC, KSTEP = 4 * VEC;
+  constexpr bool SPLIT = HPlane<T>::SPLIT;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  const int lrow = lane & 15, lq = lane >> 4;
+  const int nsx = p.KX / KSTEP, nsh = p.KH / KSTEP;
+  const size_t hhalf = (size_t)p.BP * p.KH;
+  const unsigned plane = (unsigned)(p.B * p.H);
+  auto slot = [&](unsigned q) { return reinterpret_cast<T*>(p.ring) + (size_t)(q % RES_RING) * hhalf; };
+  auto off = [&](int t) {
+    const int b = b_lo + t * 16 + lrow;
+    return b < b_hi ? (unsigned)(((b >> 4) * nsh * 64 + lq * 16 + (b & 15)) * 16) : RES_NO_LANE;
+  };
+  auto publish = [&](unsigned q, int b, int u, float h) {   // as in a chain; all lanes
+    const size_t o = ft_offset<T>(b, u, nsh);
+    unsigned *to = reinterpret_cast<unsigned*>(slot(q)), *old = reinterpret_cast<unsigned*>(slot(q + 2));
+    if constexpr (SPLIT) {
+      const unsigned hi16 = (__float_as_uint(h) + 0x8000u) >> 16;
+      const auto rows = __builtin_amdgcn_permlane16_swap(hi16, hi16, false, false);
+      if (b < b_hi && (lq & 1) == 0) {
+        to[o >> 1] = not_empty(rows[0] | (rows[1] << 16));
+        old[o >> 1] = RES_EMPTY;
+      }
+    } else if (b < b_hi) {
+      to[o] = not_empty(__float_as_uint(h));
+      old[o] = RES_EMPTY;
+    }
+  };
+  for (int u4 = u0 + 4 * wave; u4 < u1; u4 += 32)
+    for (int c = b_lo; c < b_hi; c += 16) {
+      const int b = c + lrow, u = u4 + lq;
+      float h = 0.0f;
+      if (b < b_hi && u < p.H) {
+        h = HPlane<T>::load(p.src, b, u, p.KH / 32, p.H, hhalf);
+        p.spare[(size_t)b * p.H + u] = CELL ? h : (p.src + p.hplane)[(size_t)b * p.H + u];
+      }
+      publish(p.published, b, u, h);
+    }
+  for (int j = 0; j < p.count; ++j) {
+    const T* in = slot(p.published + (unsigned)j);
+    if (!slot_is_there(in, nsh, (b_hi - b_lo + 15) / 16, off, p.wait_ticks, p.sync + RES_SYNC_STATUS, s_fail)) return;
+    float *dst = p.step[j].out, *gates = p.step[j].gates;
+    for (int u4 = u0 + 4 * wave; u4 < u1; u4 += 32)
+      for (int c = b_lo; c < b_hi; c += 16) {
+        const int b = c + lrow, u = u4 + lq;
+        const bool own = b < b_hi, real = own && u < p.H;
+        const unsigned hoff = off((c - b_lo) / 16);
+        float G[4] = {0.f, 0.f, 0.f, 0.f}, second = 0.0f, gate[4], h = 0.0f;
+        if (u4 < p.HP)
+          gates_slowly<T, KS>(p.Wp, u4 / 4, p.x0 + (size_t)j * p.B * p.I, (unsigned)((own ? b : b_lo) * p.I), p.I, nsx, nsh,
+                              [&](int m) { return as_frag<typename M::Frag>(load_slot_16(in, hoff, m * 1024)); }, G);
+        const size_t e = (size_t)b * p.H + u, o = ft_offset<T>(b, u, nsh);
+        if (real) {
+          h = cell_forward<CELL>(G, *reinterpret_cast<const float4*>(p.bp + 4 * u), p.spare[e], second, gate);
+          p.spare[e] = CELL ? h : second;
+          if (dst) (dst + p.hplane)[e] = second;
+          if (gates) {
+            gates[e] = gate[0];
+            (gates + plane)[e] = gate[1];
+            (gates + p.unit)[e] = gate[2];
+            if (CELL == 0) (gates + p.unit + plane)[e] = gate[3];
+          }
+        }
+        if (j + 1 < p.count) publish(p.published + (unsigned)j + 1, b, u, h);
+        if (dst && own) {
+          if constexpr (SPLIT) {
+            unsigned short* hi = reinterpret_cast<unsigned short*>(dst);
+            hi[o] = (unsigned short)((__float_as_uint(h) + 0x8000u) >> 16);
+            (hi + hhalf)[o] = (unsigned short)(__float_as_uint(h) & 0xffffu);
+          } else if (real) {
+            dst[e] = h;
+          }
+        }
+      }
+  }
+}
 
 // Consecutive forward operations (Algorithm 2's forward loop; also the single-step pushes that
 // follow each other when memory is plentiful) depend on each other only through h, so a chain of
@@ -289,7 +531,8 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
   if (!s_go) return;
   const int g = __builtin_amdgcn_readfirstlane(s_g), rank = __builtin_amdgcn_readfirstlane(s_rank);
   const int b_lo = g * p.nb, b_hi = min(p.B, b_lo + p.nb);
-  if (b_lo >= p.B || rank * UW >= p.KH) return;   // no sequences or no units here: nobody waits for this workgroup
+  // no sequences or no units here: nobody waits for this workgroup
+  if (b_lo >= p.B || rank * UW >= p.KH || (p.alone && rank)) return;
   const int nsx = p.KX / KSTEP, nsh = p.KH / KSTEP, nsteps = nsx + nsh;
   const size_t hhalf = (size_t)p.BP * p.KH;
   const int ks = wave % KS, grp = wave / KS;
@@ -459,7 +702,7 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
     typename M::Frag hf[NHW][BTW];
     {
       const T* slot = reinterpret_cast<const T*>(p.ring) + (size_t)((p.published + (unsigned)j) % RES_RING) * hhalf;
-      WaitBound bound{p.wait_ticks, p.sync + RES_SYNC_STATUS};
+      WaitBound bound{j == 0 ? p.patience : p.wait_ticks, p.sync + RES_SYNC_STATUS};
       while (true) {
         u32x4 raw[NHW][BTW];
         unsigned top = 0;
@@ -478,7 +721,7 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
           }
         if (__builtin_amdgcn_ballot_w64(top == RES_EMPTY) == 0) break;
         if (bound.expired()) {
-          s_fail = 1;
+          s_fail = 1 + j;
           break;
         }
         asm volatile("" ::: "memory");   // the next look is another load
@@ -495,7 +738,8 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
         for (int t = 0; t < BTW; ++t) acc[rt][t] = M::mma(wh[rt][i], hf[i][t], acc[rt][t]);
     Sum::write(red + (size_t)wave * Sum::BLOCKS * 64, lane, acc);
     lds_barrier();
-    if (s_fail) return;   // a wave gave up: written before the barrier, so all see it
+    if (__builtin_amdgcn_readfirstlane(s_fail))   // a wave has stopped waiting: written before the barrier, so all see it
+      stop_waiting<ResParams, UW>(&s_g, &s_rank, &s_fail, [&](int b_lo, int b_hi, int u0, int u1) { chain_slowly<T, KS, CELL>(b_lo, b_hi, u0, u1, &s_fail); });
 #pragma unroll
     for (int q = 0; q < IPT; ++q) {
       if (!mine[q]) continue;

@@ -1,5 +1,7 @@
 // Resident launches: forward chains and sweeps, whose workgroups keep weights on the chip for many
 // time steps (see the comments at each kernel).
+#include <algorithm>
+
 #include "resident_sweep.h"
 
 namespace mebptt {
@@ -10,6 +12,21 @@ namespace mebptt {
 constexpr long long RES_WAIT_TICKS = 50000000;   // 0.5 s
 static long long g_wait_ticks = RES_WAIT_TICKS;
 void set_resident_wait_ticks(long long ticks) { g_wait_ticks = ticks < 0 ? RES_WAIT_TICKS : ticks; }
+
+// How long a workgroup waits for the first exchange before it gives the launch up and runs alone: about as long
+// as that then takes (so giving up costs at most twice what knowing beforehand would have), and no less than
+// another resident launch or a chunk's GEMMs hold the chip.  A workgroup that runs alone streams its weights from
+// its L2, at 50 - 80 GB/s (H = 1024, B = 64: 47 ms a gradient step of 60 steps, 1.4 ms together).
+// (g_patience: what a test asks for; negative: nothing, 0: nobody to wait for.)
+static long long g_patience = -1;
+void set_resident_patience(long long ticks) { g_patience = ticks; }
+constexpr double ALONE_BYTES_PER_TICK = 600.0;   // 60 GB/s
+constexpr long long MIN_PATIENCE = 50000;        // 0.5 ms
+static long long patience(const Dims& d, int steps, size_t weights_per_step) {
+  if (g_patience >= 0) return std::min(g_patience > 0 ? g_patience : 100LL, g_wait_ticks);
+  const double ticks = (double)steps * (double)weights_per_step * d.op_bytes() / ALONE_BYTES_PER_TICK;
+  return std::min(std::max(MIN_PATIENCE, (long long)ticks), g_wait_ticks / 4);
+}
 
 // ---- which shapes have forward chains -------------------------------------------------------------------
 // Sequences per XCD: as few as keep all of them on the chip at once, in whole halves of an MFMA tile, so
@@ -61,7 +78,7 @@ size_t resident_sync_bytes() { return (RES_SYNC_STATUS + 64) * sizeof(unsigned);
 size_t resident_status_offset() { return RES_SYNC_STATUS * sizeof(unsigned); }
 
 hipError_t launch_forward_chain(const Dims& d, const void* Wp, const float* bp, const float* x_first, const float* src_unit,
-                                const ChainStep* steps, int count, void* ring, unsigned* sync, unsigned published,
+                                const ChainStep* steps, int count, void* ring, float* spare, unsigned* sync, unsigned published,
                                 unsigned launch, hipStream_t st) {
   const ChainConfig* cfg = chain_config(d);
   if (!cfg || count < 1 || count > RES_MAX_STEPS) return hipErrorInvalidValue;
@@ -71,10 +88,13 @@ hipError_t launch_forward_chain(const Dims& d, const void* Wp, const float* bp, 
   p.x0 = x_first;
   p.src = src_unit;
   p.ring = ring;
+  p.spare = spare;
   p.sync = sync;
   p.published = published;
   p.launch = launch;
   p.wait_ticks = g_wait_ticks;
+  p.patience = patience(d, count, (size_t)d.G4 * d.KP * (group_share(d) > 16 ? 2 : 1));
+  p.alone = g_patience == 0;
   p.count = count;
   p.B = d.B;
   p.I = d.I;
@@ -150,6 +170,8 @@ hipError_t launch_sweep(const Dims& d, const SweepArgs& a, hipStream_t st) {
   p.published = a.published;
   p.launch = a.launch;
   p.wait_ticks = g_wait_ticks;
+  p.patience = patience(d, a.count, (size_t)d.G4 * (d.HP + (a.state ? 0 : d.KP)) * (group_share(d) > 16 ? 2 : 1));
+  p.alone = g_patience == 0;
   p.s_hi = a.s_hi;
   p.count = a.count;
   p.B = d.B;

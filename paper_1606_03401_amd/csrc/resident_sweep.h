@@ -24,12 +24,161 @@ struct SweepParams {
   unsigned* sync;
   unsigned published, launch;   // blocks published by this run's sweep launches before this one; resident launches before it
   long long wait_ticks;  // bound of every wait, in ticks of the 100 MHz wall clock
+  long long patience;    // bound of the first one: then the launch may be given up
+  int alone;             // only rank 0 of each XCD runs, and carries on alone
   int s_hi, count;       // steps s_hi, s_hi - 1, ..., s_hi - count + 1 (in at most two consecutive chunks)
   int B, I, H, HP, KX, KH, BP, nb, G4, NX, KC, CH;
   size_t unit, hplane;
   const float* src[SWEEP_MAX_STEPS];   // src[j]: unit holding the state before step s_hi - j
   const float* state[SWEEP_MAX_STEPS]; // FWD = false: unit holding the stored internal state of step s_hi - j
 };
+__device__ inline int units_of(const __attribute__((address_space(4))) SweepParams& p) { return p.HP; }
+
+// All steps of a launch for units [u0, u1) of the XCD's sequences, by a workgroup that has stopped waiting (see
+// chain_slowly).  Its waves deal the units out sixteen at a time: dh of a tile passes through LDS from the MFMA's layout (a lane has four
+// consecutive units) to that of the gate sums (a lane has one unit of each four).
+template <class T, bool FWD, int KSF, int KSB, int CELL>
+__device__ __forceinline__ void sweep_slowly(int b_lo, int b_hi, int u0, int u1, float* smem, int* s_fail) {
+  const auto& p = *arguments_again<SweepParams>();
+  using M = Mma<T>;
+  constexpr int VEC = M::VEC, KSTEP = 4 * VEC, FRAG = 64 * VEC;
+  constexpr bool SPLIT = HPlane<T>::SPLIT;
+  typedef __attribute__((ext_vector_type(sizeof(T)))) unsigned int vec;   // the four gates of a unit
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  const int lrow = lane & 15, lq = lane >> 4;
+  const int nsx = p.KX / KSTEP, nsh = p.KH / KSTEP, nsteps = p.G4 / KSTEP, tiles = (u1 - u0 + 15) / 16, ncs = p.KC / KSTEP;
+  const size_t hhalf = (size_t)p.BP * p.KH, dG_step = (size_t)p.BP * p.G4;
+  const unsigned plane = (unsigned)(p.B * p.H);
+  float* dhs = smem + wave * 256;   // [16 units][16 sequences]
+  auto slot = [&](unsigned q) { return reinterpret_cast<T*>(p.ring) + (size_t)(q % RES_RING) * dG_step; };
+  auto off = [&](int t) {
+    const int b = b_lo + t * 16 + lrow;
+    return b < b_hi ? (unsigned)(((b >> 4) * nsteps * 64 + lq * 16 + (b & 15)) * 16) : RES_NO_LANE;
+  };
+  auto publish = [&](unsigned q, size_t o, vec v) {   // as in a sweep
+    vec empty;
+#pragma unroll
+    for (int r = 0; r < (int)sizeof(T); ++r) empty[r] = RES_EMPTY;
+    *reinterpret_cast<vec*>(slot(q) + o) = v;
+    *reinterpret_cast<vec*>(slot(q + 2) + o) = empty;
+  };
+  for (int tile = wave; tile < tiles; tile += 8)
+    for (int c = b_lo; c < b_hi; c += 16) {
+      const int b = c + lrow;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int u = u0 + 16 * tile + 4 * i + lq;
+        if (b >= b_hi || u >= u1) continue;
+        const size_t o = ft_offset<T>(b, 4 * u, nsteps);
+        vec v{};
+        if (u < p.H && p.dG_next) v = *reinterpret_cast<const vec*>(reinterpret_cast<const T*>(p.dG_next) + o);
+#pragma unroll
+        for (int r = 0; r < (int)sizeof(T); ++r) v[r] = not_empty(v[r]);
+        publish(p.published, o, v);
+      }
+    }
+  for (int j = 0; j < p.count; ++j) {
+    const int s = p.s_hi - j, step_slot = (s - 1) % p.CH, buf = ((s - 1) / p.CH) & 1;
+    const T* in = slot(p.published + (unsigned)j);
+    if (!slot_is_there(in, nsteps, (b_hi - b_lo + 15) / 16, off, p.wait_ticks, p.sync + RES_SYNC_STATUS, s_fail)) return;
+    T* dG_cur = reinterpret_cast<T*>(p.dG_chunk[buf]) + (size_t)step_slot * dG_step;
+    T *dGT = reinterpret_cast<T*>(p.dGT[buf]), *aT = reinterpret_cast<T*>(p.aT[buf]);
+    const float *src = p.src[j], *stp = FWD ? src : p.state[j];
+    for (int tile = wave; tile < tiles; tile += 8)
+      for (int c = b_lo; c < b_hi; c += 16) {
+        const int b = c + lrow, row = b < b_hi ? b : b_lo;
+        const bool own = b < b_hi;
+        const unsigned goff = off((c - b_lo) / 16);
+        const int n = min(u0 + 16 * tile + lrow, u1 - 1);   // this lane's row (a row past the units is never used)
+        const T* base = reinterpret_cast<const T*>(p.WTh) + ((size_t)(n >> 4) * nsteps * 64 + lq * 16 + (n & 15)) * VEC;
+        f32x4 acc[KSB], dh4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < KSB; ++w) acc[w] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int s0 = 0; s0 < nsteps; s0 += KSB)
+#pragma unroll
+          for (int w0 = 0; w0 < KSB; w0 += 4) {
+            typename M::Frag a[4], f[4];
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+              const int m = min(s0 + w0 + w, nsteps - 1);
+              a[w] = M::load(base + (size_t)m * FRAG);
+              f[w] = as_frag<typename M::Frag>(load_slot_16(in, goff, m * 1024));
+            }
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+              if (s0 + w0 + w >= nsteps) a[w] = f[w] = typename M::Frag{};
+              acc[w0 + w] = M::mma(a[w], f[w], acc[w0 + w]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+#pragma unroll
+        for (int w = 0; w < KSB; ++w)   // fixed order, as in backward_body
+#pragma unroll
+          for (int r = 0; r < 4; ++r) dh4[r] += acc[w][r];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dhs[(4 * lq + r) * 16 + lrow] = dh4[r];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the wave's own part: no barrier
+        __builtin_amdgcn_wave_barrier();
+        const unsigned hsrc = SPLIT ? (unsigned)(((row >> 4) * nsh * 64 + lq * 16 + (row & 15)) * VEC) : (unsigned)(row * p.H);
+#pragma unroll 1
+        for (int i = 0; i < 4; ++i) {
+          const int u4 = u0 + 16 * tile + 4 * i, u = u4 + lq;
+          if (u4 >= u1) break;
+          const bool real = own && u < p.H;
+          const size_t e = real ? (size_t)b * p.H + u : 0, o = real ? ft_offset<T>(b, u, nsh) : 0;
+          float gate[4], second = 0.0f, h = 0.0f;
+          const float prev = CELL ? load_h<T>(src, (unsigned)e, (unsigned)o, hhalf) : (src + p.hplane)[e];
+          if constexpr (FWD) {
+            float G[4];
+            gates_slowly<T, KSF>(p.Wp, u4 / 4, p.x + (size_t)(s - 1) * p.B * p.I, (unsigned)(row * p.I), p.I, nsx, nsh,
+                                [&](int m) {
+                                  if constexpr (SPLIT) {
+                                    return M::load(reinterpret_cast<const T*>(src) + (size_t)m * FRAG + (size_t)hsrc);
+                                  } else {
+                                    RawAct<VEC> raw = load_window<VEC>(src, hsrc, m * KSTEP + VEC * lq, p.H);
+                                    shift_tail<VEC>(raw, m * KSTEP + VEC * lq, p.H);
+                                    return M::from_f32(raw.v);
+                                  }
+                                },
+                                G);
+            if (real) h = cell_forward<CELL>(G, *reinterpret_cast<const float4*>(p.bp + 4 * u), prev, second, gate);
+          } else {
+            gate[0] = (stp + p.unit)[e];
+            gate[1] = (stp + p.unit + plane)[e];
+            gate[2] = (stp + 2 * p.unit)[e];
+            gate[3] = CELL == 0 ? (stp + 2 * p.unit + plane)[e] : 0.0f;
+            second = (stp + p.hplane)[e];
+            if (p.dy_is_h || p.y_out) h = load_h<T>(stp, (unsigned)e, (unsigned)o, hhalf);
+          }
+          union { T t[4]; unsigned w[sizeof(T)]; vec v; } dg;
+          dg.v = vec{};
+          if (real) {
+            float dh = dhs[(4 * i + lq) * 16 + lrow], dG[4], dc_out;
+            dh += p.dy_is_h ? h : (p.dy != nullptr && s >= p.dy_first ? (p.dy + (size_t)(s - p.dy_first) * plane)[e] : 0.0f);
+            if (CELL == 0)
+              lstm_backward_point(dh, p.dc[e], gate[0], gate[1], gate[2], gate[3], second, prev, dG, dc_out);
+            else
+              gru_backward_point(__fadd_rn(dh, p.dc[e]), gate[0], gate[1], gate[2], second, prev, dG, dc_out);
+            p.dc[e] = dc_out;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) dg.t[r] = (T)dG[r];
+#pragma unroll
+            for (int r = 0; r < (int)sizeof(T); ++r) dg.w[r] = not_empty(dg.w[r]);
+            if (p.y_out) (p.y_out + (size_t)(s - 1) * plane)[e] = h;
+            const int col = step_slot * p.B + b;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) dGT[ft_offset<T>(4 * u + r, col, ncs)] = dg.t[r];
+            aT[ft_offset<T>(p.NX + u, col, ncs)] = (T)load_h_operand<T>(src, (unsigned)e, (unsigned)o);
+          }
+          if (own) {
+            const size_t og = ft_offset<T>(b, 4 * u, nsteps);
+            if (j + 1 < p.count) publish(p.published + (unsigned)j + 1, og, dg.v);
+            if (real) *reinterpret_cast<vec*>(dG_cur + og) = dg.v;
+          }
+        }
+      }
+  }
+}
 
 // Where a sub-sequence fits into memory the schedule alternates "forward operation of step s from
 // the memorised h_{s-1}, keeping the internal state" and "backward operation of step s", s going
@@ -96,7 +245,8 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
   if (!s_go) return;
   const int g = __builtin_amdgcn_readfirstlane(s_g), rank = __builtin_amdgcn_readfirstlane(s_rank);
   const int b_lo = g * p.nb, b_hi = min(p.B, b_lo + p.nb);
-  if (b_lo >= p.B || rank * UW >= p.HP) return;   // no sequences or no units here: nobody waits for this workgroup
+  // no sequences or no units here: nobody waits for this workgroup
+  if (b_lo >= p.B || rank * UW >= p.HP || (p.alone && rank)) return;
   const int nsx = p.KX / KSTEP, nsh = p.KH / KSTEP, nstepsF = nsx + nsh, nstepsB = p.G4 / KSTEP;
   const size_t hhalf = (size_t)p.BP * p.KH, dG_step = (size_t)p.BP * p.G4;
   const unsigned plane = (unsigned)(p.B * p.H);
@@ -411,7 +561,7 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
     typename M::Frag gfr[NBW][BTWB];
     if (bwd_wave) {
       const T* slot = reinterpret_cast<const T*>(p.ring) + (size_t)((p.published + (unsigned)j) % RES_RING) * dG_step;
-      WaitBound bound{p.wait_ticks, p.sync + RES_SYNC_STATUS};
+      WaitBound bound{j == 0 ? p.patience : p.wait_ticks, p.sync + RES_SYNC_STATUS};
       while (true) {
         u32x4 raw[NBW][BTWB];
         unsigned top = 0;
@@ -430,7 +580,7 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
           }
         if (__builtin_amdgcn_ballot_w64(top == RES_EMPTY) == 0) break;
         if (bound.expired()) {
-          s_fail = 1;
+          s_fail = 1 + j;
           break;
         }
         asm volatile("" ::: "memory");   // the next look is another load
@@ -461,7 +611,10 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
       SumB::write(redB + (size_t)wave * SumB::BLOCKS * 64, lane, acc);
     }
     lds_barrier();
-    if (s_fail) return;   // a wave gave up: written before the barrier, so all see it
+    if (__builtin_amdgcn_readfirstlane(s_fail))   // a wave has stopped waiting: written before the barrier, so all see it
+      stop_waiting<SweepParams, UW>(&s_g, &s_rank, &s_fail, [&](int b_lo, int b_hi, int u0, int u1) {
+        sweep_slowly<T, FWD, KSF, KSB, CELL>(b_lo, b_hi, u0, u1, reinterpret_cast<float*>(smem), &s_fail);
+      });
     // pointwise backward of step s on the internal state held in registers
 #pragma unroll
     for (int q = 0; q < IPT; ++q) {
@@ -505,7 +658,7 @@ hipError_t launch_sweep_cell(const SweepParams& p, hipStream_t st) {
   constexpr int GF = 8 / KSF, FTB = (GF == 2 && NBT == 2) ? 2 : 1, FTR = GF / FTB, BTB = (KSB == 4 && NBT == 2) ? 2 : 1;
   constexpr int blocksB = Sums<NTB, NBT == 0 ? 0 : NB / BTB>::BLOCKS, blocksF = Sums<(NRT + FTR - 1) / FTR, NBT == 0 ? 0 : NB / FTB>::BLOCKS;
   constexpr size_t lds = (size_t)8 * (blocksB + (FWD ? blocksF : 0) + NTB * NBL) * 1024 + (size_t)8 * IPT * SWEEP_KEPT * sizeof(T);
-  static_assert(lds <= 160 * 1024 - 64, "LDS of a compute unit");
+  static_assert(lds >= 8 * 1024 && lds <= 160 * 1024 - 64, "8 KiB for a workgroup that carries on slowly; LDS of a compute unit");
   hipError_t e = allow_dynamic_lds<sweep_kernel<T, FWD, NRT, NXW, NHW, KSF, NBW, NBL, KSB, NBT, CELL>>(lds);
   if (e != hipSuccess) return e;
   sweep_kernel<T, FWD, NRT, NXW, NHW, KSF, NBW, NBL, KSB, NBT, CELL><<<dim3(RES_WGS), dim3(512), lds, st>>>(p);

@@ -28,7 +28,7 @@ constexpr size_t ALIGN = 256;
 inline size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
 struct Workspace {
-  size_t Wp, bp, WTh, WTx, state, dWacc, dc, sync, dG[2], dGT[2], aT[2], ring, gring, ring_bytes, stage, total;
+  size_t Wp, bp, WTh, WTx, state, dWacc, dc, sync, dG[2], dGT[2], aT[2], ring, gring, ring_bytes, spare, stage, total;
   size_t total_no_stage;   // what a run without resident launches needs (the no-allocation path): no rings, no stage
   int stage_steps;         // internal states the stage holds
 };
@@ -90,6 +90,7 @@ Workspace layout(const Dims& d) {
   w.ring = take(can_run_forward_chain(d) ? forward_chain_ring_bytes(d) : 0);
   w.gring = take(can_run_backward_sweep(d) || can_run_sweep(d) ? sweep_ring_bytes(d) : 0);
   w.ring_bytes = off - w.ring;   // both exchange rings
+  w.spare = take(can_run_forward_chain(d) ? (size_t)d.B * d.H * sizeof(float) : 0);
   w.stage_steps = recompute_stage_steps(d);
   w.stage = take((size_t)w.stage_steps * 3 * unit);   // last: nothing ever clears it
   w.total = off;
@@ -218,9 +219,6 @@ struct SideStream {
 };
 SideStream g_side[MAX_DEVICES];
 std::mutex g_run_mutex;
-// Forward-chain launches want every compute unit of the device; two of them from different streams
-// would each hold a part of the chip and wait for the rest.  The last run that used them records
-// this event when its work is enqueued and the next such run makes its stream wait for it.
 bool g_chain_enabled = true;
 
 // The resident launches (forward chains, sweeps) are laid out for a device of 8 XCDs with 32 compute
@@ -238,6 +236,9 @@ bool device_fits_resident_launches() {
   }
   return g_device_cus[dev] == 256;
 }
+// Resident launches want every compute unit of the device; two of them at once would each hold a part of the chip
+// until one loses its patience and goes on slowly.  The last run that used them records this event when its work is
+// enqueued and the next such run makes its stream wait for it.  (Captured runs and other processes are not ordered.)
 hipEvent_t g_chain_done[MAX_DEVICES] = {};
 bool g_chain_recorded[MAX_DEVICES] = {};
 
@@ -481,6 +482,12 @@ int mebptt_run_status(const mebptt_lstm_desc* desc, const void* workspace, size_
 int mebptt_resident_wait_limit(int64_t ticks) {
   std::lock_guard<std::mutex> lock(g_run_mutex);
   set_resident_wait_ticks((long long)ticks);
+  return MEBPTT_OK;
+}
+
+int mebptt_resident_patience(int64_t ticks) {
+  std::lock_guard<std::mutex> lock(g_run_mutex);
+  set_resident_patience((long long)ticks);
   return MEBPTT_OK;
 }
 
@@ -1172,8 +1179,8 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
           }
           const float* x_first = x_of(fsteps[fi].step);
           rc = whole_launch(MEBPTT_K_CHAIN, n, st, [&] {
-            return launch_forward_chain(d, Wp, bp, x_first, cur, cs, n, ws + w.ring, reinterpret_cast<unsigned*>(ws + w.sync),
-                                        chain_published, chain_launches, st);
+            return launch_forward_chain(d, Wp, bp, x_first, cur, cs, n, ws + w.ring, reinterpret_cast<float*>(ws + w.spare),
+                                        reinterpret_cast<unsigned*>(ws + w.sync), chain_published, chain_launches, st);
           });
           if (rc) return rc;
           ++chain_launches;

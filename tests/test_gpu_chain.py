@@ -403,3 +403,120 @@ def test_gemms_beside_or_between_resident_launches(B, I, H):
     base = _run(w, inp, wl.KIND_HSM, 9, chain=False)
     for kind, m in ((wl.KIND_HSM, 9), (wl.KIND_HSM, t), (wl.KIND_ISM, t), (wl.KIND_MSM, 30)):
         _same(_run(w, inp, kind, m, chain=True), base, (kind, m))
+
+
+# as EDGE_*: both K splits of either direction, one and two batch tiles per XCD, padded units and x rows
+ALONE = [(wl.GEMM_BF16, 5, 8, 9, 0), (wl.GEMM_BF16, 37, 100, 200, 0), (wl.GEMM_BF16, 70, 1000, 64, 0), (wl.GEMM_BF16, 150, 180, 500, 0),
+         (wl.GEMM_BF16, 33, 300, 500, 1), (wl.GEMM_BF16, 100, 200, 1000, 0), (wl.GEMM_BF16, 65, 77, 333, 1), (wl.GEMM_BF16, 20, 650, 650, 1),
+         (wl.GEMM_FP32, 4, 16, 32, 0), (wl.GEMM_FP32, 70, 100, 50, 0), (wl.GEMM_FP32, 130, 300, 200, 0), (wl.GEMM_FP32, 9, 101, 50, 1),
+         (wl.GEMM_FP32, 32, 200, 500, 0), (wl.GEMM_FP32, 100, 203, 301, 1)]
+
+
+@pytest.fixture(params=[0, 1], ids=["alone", "impatient"])
+def patience(request):
+    import torch   # noqa: F401 - its HIP runtime is the one the library uses
+    mb.mebptt_resident_patience(request.param)
+    yield
+    mb.mebptt_resident_patience(-1)
+
+
+@pytest.mark.parametrize("dtype,B,I,H,cell", ALONE)
+def test_launches_that_are_given_up(patience, dtype, B, I, H, cell):
+    """One workgroup per XCD instead of all of them gives the launch-per-step path's bits, and so does any
+    mixture of those who wait and those who have lost their patience, whoever is there by then."""
+    from paper_1606_03401_amd.session import Session
+    t = 37
+    w = wl.Workload("given-up", B=B, I=I, H=H, t=t, kind=wl.KIND_HSM, m=5, gemm_dtype=dtype, loss=wl.LOSS_EXTERNAL_DY,
+                    dy_first_step=3, seed=5000 + B + I + H, cell=cell)
+    inp = wl.make_inputs(w, nonzero_state=True, nonzero_bias=True)
+    base = _run(w, inp, wl.KIND_HSM, 5, chain=False)
+    for kind, m in ((wl.KIND_HSM, 5), (wl.KIND_HSM, t), (wl.KIND_ISM, t), (wl.KIND_MSM, 13)):
+        s = Session(w, inp, kind=kind, m=m)
+        mb.mebptt_profile_enable(1)
+        out = s.run_and_fetch()
+        prof = mb.mebptt_profile_collect()
+        mb.mebptt_profile_enable(0)
+        _same(out, base, (kind, m))
+        assert prof.chain_steps > 0 and prof.sweep_steps > 0
+    w = w.scaled(loss=wl.LOSS_HALF_SUM_H2)
+    base = _run(w, inp, wl.KIND_HSM, 5, chain=False)
+    for kind, m in ((wl.KIND_HSM, 5), (wl.KIND_ISM, t)):
+        _same(_run(w, inp, kind, m, chain=True), base, ("loss on h", kind, m))
+
+
+def test_launches_given_up_and_not_in_turn():
+    """What a launch leaves behind is the same either way: the exchange of the next one starts from it."""
+    from paper_1606_03401_amd.session import Session
+    for dtype, B, I, H in ((wl.GEMM_BF16, 64, 100, 200), (wl.GEMM_FP32, 20, 40, 72)):
+        w = wl.Workload("turns", B=B, I=I, H=H, t=60, kind=wl.KIND_HSM, m=6, gemm_dtype=dtype, loss=wl.LOSS_EXTERNAL_DY, seed=B)
+        s = Session(w, wl.make_inputs(w, nonzero_state=True, nonzero_bias=True))
+        want = s.run_and_fetch()
+        for ticks in (0, -1, 0, 1, 0, 1, -1):
+            mb.mebptt_resident_patience(ticks)
+            try:
+                _same(s.run_and_fetch(), want, ticks)
+            finally:
+                mb.mebptt_resident_patience(-1)
+
+
+@pytest.mark.parametrize("shapes", [((64, 128, 512), (64, 100, 500)), ((37, 100, 200), (20, 64, 300)), ((64, 256, 1024), (37, 100, 200))])
+def test_replays_of_two_graphs_at_the_same_time(shapes):
+    """Two captured runs replayed on two streams without any order between them: their resident launches
+    meet on the chip and get into each other's way; both give the eager result every time, status 0."""
+    import torch
+    from paper_1606_03401_amd.session import Session
+    sessions, want = [], []
+    for k, (B, I, H) in enumerate(shapes):
+        w = wl.Workload("meet", B=B, I=I, H=H, t=60, kind=wl.KIND_HSM, m=6, gemm_dtype=wl.GEMM_BF16, loss=wl.LOSS_EXTERNAL_DY, seed=40 + k)
+        s = Session(w, wl.make_inputs(w, nonzero_state=True, nonzero_bias=True))
+        want.append(s.run_and_fetch())
+        s.capture()
+        sessions.append(s)
+    streams = [torch.cuda.Stream() for _ in sessions]
+    torch.cuda.synchronize()
+    for rep in range(8):
+        for s in sessions:
+            s.dW_hh.fill_(float("nan"))
+        torch.cuda.synchronize()
+        for _ in range(3):
+            for s, st in zip(sessions, streams):
+                with torch.cuda.stream(st):
+                    s.replay()
+        torch.cuda.synchronize()
+        for k, s in enumerate(sessions):
+            _same(s.fetch(), want[k], (rep, k))      # fetch raises if a launch gave up
+
+
+CHILD = """
+import sys
+import numpy as np
+from paper_1606_03401_amd import binding as mb, workloads as wl
+from paper_1606_03401_amd.session import Session
+B, I, H = (int(v) for v in sys.argv[1:])
+w = wl.Workload("process", B=B, I=I, H=H, t=60, kind=wl.KIND_HSM, m=6, gemm_dtype=wl.GEMM_BF16, loss=wl.LOSS_EXTERNAL_DY, seed=B)
+s = Session(w, wl.make_inputs(w, nonzero_state=True, nonzero_bias=True))
+mb.mebptt_forward_chain_enable(False)
+want = s.run_and_fetch()
+mb.mebptt_forward_chain_enable(True)
+for rep in range(30):
+    for _ in range(10):
+        s.run()
+    out = s.run_and_fetch()          # raises if a launch failed
+    assert all(np.array_equal(getattr(out, f), getattr(want, f)) for f in ("dW_ih", "dW_hh", "db", "dh0", "dc0", "dx", "y")), rep
+"""
+
+
+def test_two_processes_on_one_device():
+    """Nothing orders the resident launches of two processes: they meet on the chip, and both compute the
+    launch-per-step path's gradients every time."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    procs = [subprocess.Popen([sys.executable, "-c", CHILD, *map(str, shape)], cwd=root) for shape in ((64, 128, 512), (64, 100, 500))]
+    try:
+        assert [p.wait(timeout=90) for p in procs] == [0, 0]
+    finally:
+        for p in procs:
+            if p.poll() is None:
+                p.kill()
