@@ -520,3 +520,86 @@ def test_two_processes_on_one_device():
         for p in procs:
             if p.poll() is None:
                 p.kill()
+
+
+# (B, I, H, core): one shape for every instantiation of the resident kernels -- units per compute unit, macro steps of
+# x, h and dG per wave, K splits, batch tiles per XCD, both cores -- that the shapes above do not select.
+INSTANCES_BF16 = [
+    (1, 21, 404, 0), (1, 52, 401, 1), (1, 54, 553, 1), (1, 62, 559, 0), (1, 83, 701, 1), (1, 93, 290, 1), (1, 93, 652, 0),
+    (1, 111, 535, 1), (1, 171, 931, 1), (1, 176, 895, 1), (1, 267, 426, 1), (1, 291, 783, 1), (1, 308, 107, 0),
+    (1, 313, 330, 1), (1, 317, 149, 0), (1, 414, 200, 1), (1, 727, 520, 0), (1, 782, 141, 1), (1, 818, 432, 0),
+    (1, 836, 486, 1), (1, 945, 519, 1), (1, 956, 651, 1), (1, 1826, 24, 1), (2, 128, 28, 1), (2, 136, 59, 1),
+    (2, 157, 461, 1), (2, 159, 20, 0), (2, 180, 424, 0), (2, 657, 11, 1), (16, 278, 9, 1), (65, 18, 281, 0),
+    (65, 58, 783, 1), (65, 133, 401, 0), (65, 280, 14, 0), (65, 283, 790, 0), (65, 826, 653, 0), (66, 8, 403, 1),
+    (66, 17, 129, 1), (66, 18, 523, 1), (66, 53, 773, 0), (66, 139, 400, 1), (66, 297, 769, 1), (66, 358, 282, 0),
+    (66, 426, 9, 1), (66, 477, 170, 1), (66, 568, 400, 1), (66, 923, 671, 1), (67, 19, 680, 1), (67, 51, 141, 0),
+    (67, 165, 453, 0), (67, 398, 286, 1), (68, 15, 900, 1), (68, 121, 515, 1), (68, 148, 514, 0), (68, 191, 9, 0),
+    (68, 273, 133, 1), (68, 287, 147, 0), (69, 29, 531, 0), (69, 204, 426, 1), (70, 531, 674, 1), (70, 637, 535, 1),
+    (71, 517, 534, 0), (71, 718, 394, 0), (72, 531, 137, 0), (72, 722, 16, 1), (73, 18, 17, 1), (77, 561, 647, 0),
+    (84, 145, 11, 1), (85, 1069, 11, 1), (93, 18, 9, 0), (121, 1048, 9, 0), (129, 1214, 10, 0), (130, 57, 532, 0),
+    (130, 257, 135, 1), (130, 483, 153, 1), (130, 1197, 9, 1), (132, 855, 10, 1), (133, 33, 517, 1), (135, 537, 402, 1),
+    (136, 9, 392, 1), (136, 251, 408, 1), (136, 552, 9, 0), (137, 34, 140, 1), (138, 717, 129, 0), (139, 140, 413, 0),
+    (139, 439, 257, 0), (140, 136, 11, 1), (140, 149, 385, 1), (142, 811, 11, 0), (143, 44, 10, 0), (144, 16, 260, 1),
+    (149, 9, 9, 1), (154, 145, 9, 0), (154, 365, 265, 1), (180, 290, 9, 1),
+]
+INSTANCES_FP32 = [
+    (1, 50, 148, 1), (1, 61, 449, 1), (1, 139, 99, 1), (1, 258, 167, 0), (1, 266, 467, 1), (1, 366, 497, 0),
+    (1, 407, 129, 1), (1, 621, 155, 1), (1, 808, 397, 1), (2, 226, 145, 1), (3, 585, 15, 1), (4, 290, 16, 1),
+    (6, 16, 264, 1), (65, 9, 420, 0), (65, 20, 403, 1), (65, 166, 129, 1), (65, 284, 406, 1), (65, 603, 130, 0),
+    (65, 699, 9, 0), (66, 143, 71, 0), (66, 545, 391, 0), (67, 154, 73, 1), (67, 280, 385, 0), (68, 41, 137, 0),
+    (68, 260, 147, 1), (68, 277, 134, 0), (68, 530, 389, 1), (69, 12, 268, 0), (69, 668, 11, 1), (70, 183, 142, 0),
+    (70, 358, 14, 1), (71, 18, 263, 1), (71, 33, 257, 0), (73, 10, 11, 1), (73, 52, 264, 1), (76, 29, 132, 1),
+    (82, 570, 137, 1), (88, 26, 10, 0), (95, 292, 15, 0), (129, 26, 392, 1), (130, 9, 286, 0), (132, 144, 78, 0),
+    (133, 13, 275, 1), (133, 19, 407, 0), (133, 224, 130, 1), (134, 41, 270, 1), (134, 181, 138, 0), (135, 268, 385, 1),
+    (135, 729, 9, 0), (136, 537, 140, 1), (138, 14, 85, 0), (138, 266, 136, 1), (139, 38, 266, 0), (140, 31, 131, 0),
+    (140, 536, 12, 1), (142, 297, 10, 0), (144, 560, 129, 0), (149, 148, 12, 0), (151, 159, 65, 1), (153, 14, 131, 1),
+    (173, 235, 65, 0), (239, 9, 17, 1), (256, 294, 9, 1),
+]
+
+
+@pytest.mark.parametrize("dtype,B,I,H,cell", [(wl.GEMM_BF16, *s) for s in INSTANCES_BF16] + [(wl.GEMM_FP32, *s) for s in INSTANCES_FP32])
+def test_every_instantiation(dtype, B, I, H, cell):
+    """Bit for bit the launch-per-step path, and really by chain and sweep launches: with hidden states stored
+    the sweeps recompute the internal ones or a forward batch does, with internal states stored neither."""
+    from paper_1606_03401_amd.session import Session
+    t = 20
+    w = wl.Workload("instance", B=B, I=I, H=H, t=t, kind=wl.KIND_HSM, m=5, gemm_dtype=dtype, loss=wl.LOSS_EXTERNAL_DY,
+                    dy_first_step=2, seed=B + I + H, cell=cell)
+    inp = wl.make_inputs(w, nonzero_state=True, nonzero_bias=True)
+    base = _run(w, inp, wl.KIND_HSM, 5, chain=False)
+    for kind, m in ((wl.KIND_HSM, 5), (wl.KIND_HSM, t), (wl.KIND_ISM, t)):
+        s = Session(w, inp, kind=kind, m=m)
+        mb.mebptt_profile_enable(1)
+        out = s.run_and_fetch()
+        prof = mb.mebptt_profile_collect()
+        mb.mebptt_profile_enable(0)
+        _same(out, base, (kind, m))
+        assert prof.chain_steps > 0
+        if B > 128 and H > (512 if dtype == wl.GEMM_BF16 else 256):   # two batch tiles per XCD: the way back does not fit
+            assert prof.sweep_steps == 0
+        elif kind == wl.KIND_ISM:
+            assert prof.batch_steps == 0 and prof.sweep_forward_steps == 0 and prof.sweep_steps >= t - 2
+        elif mb.mebptt_stage_steps(s.desc):
+            assert prof.batch_steps > 0 and prof.sweep_forward_steps == 0 and prof.sweep_steps > 0
+        else:
+            assert prof.batch_steps == 0 and prof.sweep_forward_steps > 0
+
+
+def test_random_widths_types_and_budgets_bit_identical():
+    """As the seeded random cases above, over any width, both operand types, batches up to 256 and inputs
+    wider and narrower than the state."""
+    rng = np.random.default_rng(20261)
+    for case in range(80):
+        dtype = wl.GEMM_FP32 if rng.random() < 0.4 else wl.GEMM_BF16
+        H = int(rng.integers(8, 513 if dtype == wl.GEMM_FP32 else 1025))
+        I = int(np.exp(rng.uniform(np.log(4), np.log(1200))))
+        B = int(np.exp(rng.uniform(0, np.log(257))))
+        t = int(rng.integers(2, 60))
+        kind = int(rng.choice([wl.KIND_HSM, wl.KIND_ISM, wl.KIND_MSM]))
+        m = int(rng.integers(1, t + 2)) if kind != wl.KIND_MSM else int(rng.integers(2, 4 * t + 2))
+        w = wl.Workload("random-any", B=B, I=I, H=H, t=t, kind=kind, m=m, gemm_dtype=dtype,
+                        loss=wl.LOSS_HALF_SUM_H2 if rng.random() < 0.2 else wl.LOSS_EXTERNAL_DY,
+                        dy_first_step=int(rng.integers(1, t + 1)), seed=int(rng.integers(1, 10**6)), cell=int(rng.random() < 0.3))
+        inp = wl.make_inputs(w, nonzero_state=True, nonzero_bias=True)
+        what = (case, dtype, B, I, H, t, kind, m, w.dy_first_step, w.cell)
+        _same(_run(w, inp, kind, m, chain=True), _run(w, inp, kind, m, chain=False), what)

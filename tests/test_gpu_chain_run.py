@@ -164,3 +164,16 @@ def test_input_gradient_over_the_input(widths, B):
     want, out = _run(*args)[0], _run(*args, dx0_over_x0=True)[0]
     assert np.array_equal(out["dx0"], want["dx0"]) and np.array_equal(out["y"], want["y"])
     assert all(np.array_equal(a, b) for f in ("dW", "db") for a, b in zip(out[f], want[f]))
+
+
+@pytest.mark.parametrize("widths,B", [
+    ([70, 2047, 65], 510),       # forward product on 4 x 4 tiles
+    ([130, 1030, 40], 250),      # and on 2 x 2
+])
+def test_forward_products_on_their_largest_blocks(widths, B):
+    W, b, x0, dy = _inputs(widths, B, 199 + B)
+    ref = cb.chain_backprop(W, b, x0, dy)
+    out, _, _ = _run(widths, B, 4096, sum(-(-B * d * 4 // 4096) for d in widths[1:]), W, b, x0, dy)
+    for i in range(len(widths) - 1):
+        assert max(_errs(out["dW"][i], ref.dW[i])) <= TOL and max(_errs(out["db"][i], ref.db[i])) <= TOL, i
+    assert max(_errs(out["dx0"], ref.dx0)) <= TOL and max(_errs(out["y"], ref.y)) <= TOL
