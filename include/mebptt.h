@@ -303,10 +303,11 @@ int32_t mebptt_units_for_bytes(const mebptt_lstm_desc* desc, int32_t kind, size_
  *                unit any launch of this run was handed (rounded up to budget units), tracked by
  *                the executor while it walks the schedule -- it equals mebptt_plan_peak().
  *
- * Library-owned resources.  The time-batched dW and dx GEMMs of finished chunks run on a second,
- * non-blocking HIP stream of default priority that the library creates on the first run on a
+ * Library-owned resources.  On some of the shapes with resident launches (see mebptt_run_status) the
+ * time-batched dW and dx GEMMs of finished chunks run on a second,
+ * non-blocking HIP stream of default priority that the library creates on the first such run on a
  * device, with four events to fork from and join back into `stream` (no host synchronisation:
- * the whole call can be captured into a HIP graph).  They live until mebptt_shutdown().  Because
+ * the whole call can be captured into a HIP graph); on all others on `stream`, in order.  They live until mebptt_shutdown().  Because
  * they are shared, a process-wide mutex serialises the ENQUEUE phase of concurrent mebptt_run
  * calls (any thread, any stream); the device work of two runs on different streams, slot pools
  * and workspaces may overlap.  The measurement hooks below use process-wide state and must not
@@ -489,9 +490,10 @@ int32_t mebptt_stage_steps(const mebptt_lstm_desc* desc);
 /* What one synchronisation of the 256 workgroups of a resident launch costs, alone: `iters`
  * synchronisations inside one kernel on `stream`, microseconds per synchronisation (host memory).
  * variant 0: all workgroups meet at one device-wide counter; 1: the 32 workgroups of each XCD meet
- * at their XCD's counter (what forward chains and sweeps do per time step); 2: as 1, plus an
+ * at their XCD's counter; 2: as 1, plus an
  * exchange of 512 bytes per workgroup that the 32 of the XCD then read through the L2, every word
- * checked.  *status (host memory): 0 ok, 1 a bounded wait gave up, 2 the workgroups were not placed
+ * checked.  (Forward chains and sweeps have no counter: they poll the exchanged operand itself, which
+ * no variant measures.)  *status (host memory): 0 ok, 1 a bounded wait gave up, 2 the workgroups were not placed
  * 32 per XCD, 3 a word read back differed.  Allocates and frees its own small device buffers;
  * synchronises the stream.  Errors: EINVAL, EHIP. */
 int mebptt_measure_sync(int32_t variant, int32_t iters, void* stream, double* us_per_sync, int32_t* status);

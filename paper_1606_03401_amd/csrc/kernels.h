@@ -1,4 +1,4 @@
-// Launch wrappers for the HIP kernels (defined in kernels.hip).  Not part of the ABI.
+// Launch wrappers for the HIP kernels (defined in kernels.hip and resident.hip).  Not part of the ABI.
 //
 // Shapes and padded operand layouts (all chosen so that every vector load of a GEMM operand is
 // 16-byte aligned and in bounds; padding is zero):
@@ -6,7 +6,7 @@
 //   KP = KX + KH,
 //   NX = I rounded up to 16,  BP = B rounded up to 16,  G4 = 4 * HP.
 // The logical matrices below are all stored fragment-tiled (16-row tiles, one contiguous 1 KiB
-// block per tile and macro step; the exact index map is next to ft_offset in kernels.hip):
+// block per tile and macro step; the exact index map is next to ft_offset in device.h):
 //   Wp  [G4][KP]         forward operand: row 4*u + gate is row gate*H + u of [W_ih | W_hh];
 //                        columns [0,KX) hold W_ih, [KX,KP) hold W_hh.  (GRU: the four rows of a
 //                        unit are r, z, n_x = [W_in | 0], n_h = [0 | W_hn]; see packed_gate_x/h.)

@@ -1,8 +1,8 @@
 // Measurement hook: what one synchronisation of the workgroups of a launch costs on this machine.
 // The resident launches (forward chains, sweeps) replace a kernel boundary per time step by an
-// arrival counter per XCD plus an exchange of the new operand through that XCD's L2; this file
-// times exactly those primitives, alone, so that the per-step times of the real kernels can be
-// set against their floor.  Nothing here takes part in a gradient computation.
+// exchange of the new operand through an XCD's L2; this file times meetings of workgroups by counters, device-wide
+// and within an XCD, alone, and such an exchange behind one.  (The real kernels poll the operand itself and have no
+// counter; that exchange is not measured here.)  Nothing here takes part in a gradient computation.
 //
 // Variants (256 workgroups of 256 threads, one per compute unit, 96 KiB of LDS each so that no two
 // share a compute unit):

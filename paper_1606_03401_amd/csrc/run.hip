@@ -55,10 +55,11 @@ int recompute_stage_steps(const Dims& d) {
 //   below 3 GFLOP a chunk: H = 32 (fp32) 163 / 206 us, H = 200, B = 37 1.04 / 1.13 ms, H = 256, B = 64 1.99 / 2.00;
 //   B <= 32 (chunks of 64 steps): H = 512, 768, 1024 0.4 - 3.1 % faster, hidden and internal states stored;
 //   B > 128: H = 384, 512 0.4 - 3.9 % faster;
-//   between: H = 384, 512 with internal states stored 1.6 - 2.3 % slower, with hidden states -0.4 - +1.8 %;
+//   between, -2.3 - +4.4 % (the sign turns with what the plan stores, which the rule does not look at): H = 384, 512
+//   with internal states stored 1.6 - 2.3 % slower, with hidden states -0.4 - +1.8 %;
 //   H = 1024, B = 64 1.4 % slower (GRU 1.8 %), H = 768, B = 128 1.5 % slower;
 //   fp32, whose GEMMs take eight times as long, from 3 GFLOP on: H = 512, B = 32 0.9 % slower, H = 256, B = 256
-//   0.6 % slower with hidden states stored, 7.8 % faster with internal ones.
+//   0.6 % slower with hidden states stored, 7.8 % faster with internal ones (beside all the same: a rule by sizes alone).
 bool gemms_beside(const Dims& d) {
   if (!can_run_forward_chain(d) && !can_run_backward_sweep(d)) return false;
   const double chunk_flops = 8.0 * d.CH * d.B * d.H * ((double)d.I + d.H);
@@ -815,8 +816,8 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
   }));
   if (plan->kind != MEBPTT_ISM) touch(0, 1);
 
-  // Elsewhere, and in the no-allocation path, which creates no stream and no event, the GEMMs stay on
-  // the caller's stream in the same order.
+  // Where the time-batched GEMMs do not go beside the sequential work, and in the no-allocation path, which creates
+  // no stream and no event, they stay on the caller's stream in the same order.
   SideStream* side = nullptr;
   if (resident_ok && gemms_beside(d)) HIP_TRY(get_side_stream(&side));
   hipStream_t st2 = side ? side->stream : st;
@@ -912,8 +913,7 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
   // Forward operations that follow each other (a forward run, or consecutive runs each starting
   // from the state the one before left) form a chain; on shapes whose weights fit on the chip a
   // chain goes out as forward-chain launches of up to forward_chain_max_steps() steps instead of
-  // one launch per step.  Not in the no-allocation path, which owns no event to keep two such runs
-  // from overlapping on the device.
+  // one launch per step.  Not in the no-allocation path, which has no exchange slots.
   const bool chain_ok = resident_ok && can_run_forward_chain(d);
   constexpr int CHAIN_MIN_STEPS = 2;     // two steps in one launch already beat two launches (measured on the paper's 256-wide model)
   unsigned chain_published = 0;   // states exchanged inside this run's earlier chain launches

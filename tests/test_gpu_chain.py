@@ -287,8 +287,8 @@ def test_batched_recomputation_with_the_loss_on_h():
 def test_resident_launches_in_a_captured_graph(B, I, H, t, m):
     """A run whose sequential work goes out as chain, sweep and forward-batch launches, captured into
     a HIP graph: every replay -- with eager runs, clobbered outputs and synchronisations between
-    them -- reproduces the eager result bit for bit and leaves the status word clear (the arrival
-    counters the captured launches count on are cleared by the run's own first kernel)."""
+    them -- reproduces the eager result bit for bit and leaves the status word clear (the rank
+    counters and exchange slots the captured launches start from are reset by the run's own first kernel)."""
     import torch
     from paper_1606_03401_amd.session import Session
     w = wl.Workload("graph-resident", B=B, I=I, H=H, t=t, kind=wl.KIND_HSM, m=m, gemm_dtype=wl.GEMM_BF16,
