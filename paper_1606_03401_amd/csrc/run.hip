@@ -1095,7 +1095,8 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
       // starting with the step a forward chain handed over, if there is one (see below)
       const int nl = handed_src ? 1 : 0;
       const int s_hi = nl ? handed_step : op.step, chunk = (s_hi - 1) / CH;
-      const int reach = may_cross(chunk) ? 1 : 0;
+      // a handed-over step needs a pair beside it: where it is the first of its chunk, the launch crosses in any case
+      const int reach = may_cross(chunk) || (nl && (s_hi - 1) % CH == 0) ? 1 : 0;
       int n = 0;   // pairs
       const float* srcs[64];
       srcs[0] = handed_src;

@@ -603,3 +603,20 @@ def test_random_widths_types_and_budgets_bit_identical():
         inp = wl.make_inputs(w, nonzero_state=True, nonzero_bias=True)
         what = (case, dtype, B, I, H, t, kind, m, w.dy_first_step, w.cell)
         _same(_run(w, inp, kind, m, chain=True), _run(w, inp, kind, m, chain=False), what)
+
+
+def test_step_handed_over_at_the_start_of_a_chunk():
+    """A policy that leads to a chain handing the first step of a chunk over to a sweep launch while the
+    time-batched GEMMs that read the buffers of the chunk below have only just been issued beside it: the launch waits for
+    them.  (Hidden states stored at 31, 33 .. 63 and 65 .., the rest recomputed in runs of two.)"""
+    from paper_1606_03401_amd.session import Session
+    hidden, internal, t = lambda y: (mb.STORE_HIDDEN, y), lambda y: (mb.STORE_INTERNAL, y), 100
+    plan = mb.mebptt_plan_from_policy(t, 90, [hidden(31), hidden(34)] + [hidden(1)] * (t - 66) + [hidden(2)] + [hidden(1)] * 30
+                                      + [internal(2)] * 2 + [hidden(1)] * 30)
+    w = wl.Workload("policy", B=64, I=128, H=512, t=t, kind=wl.KIND_MSM, m=90, gemm_dtype=wl.GEMM_BF16, loss=wl.LOSS_EXTERNAL_DY, seed=9)
+    inp = wl.make_inputs(w, nonzero_state=True, nonzero_bias=True)
+    s = Session(w, inp, plan=plan)
+    assert mb.mebptt_chunk_steps(s.desc) == 32
+    out = s.run_and_fetch()
+    _same(out, _run(w, inp, wl.KIND_HSM, 90, chain=False))
+    assert out.stats.forward_ops == plan.forward_ops and out.stats.backward_ops == t
