@@ -16,7 +16,7 @@ PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG_DIR)
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libmebptt.so")
-SOURCES = ["resident_sweep_bf16.hip", "resident_sweep_fp32.hip", "resident_chain_bf16_k4.hip",
+SOURCES = ["resident_wide_2.hip", "resident_wide_1.hip", "resident_wide_3.hip", "resident_sweep_bf16.hip", "resident_sweep_fp32.hip", "resident_chain_bf16_k4.hip",
            "resident_chain_bf16_k8.hip", "resident_chain_fp32_k8.hip", "resident_back_bf16.hip",
            "resident_chain_fp32_k4.hip", "kernels.hip", "run.hip", "resident.hip", "chain_run.hip", "measure_sync.hip",
            "planner.cpp", "chain_planner.cpp"]

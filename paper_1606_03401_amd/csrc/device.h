@@ -47,11 +47,21 @@ struct Mma<float> {
 };
 
 // Pointwise activations on the hardware exp2 / reciprocal units (a few ulp; the absolute error of
-// tanh stays below 1e-7, far inside the fp32 gradient tolerance).
-__device__ inline float sigmoidf_(float z) { return __frcp_rn(1.0f + __expf(-z)); }
+// tanh stays below 1e-7, far inside the fp32 gradient tolerance).  Both need 1 / (1 + e) for an e in [0, 1] only, where a
+// reciprocal with one Newton step is as good as a division (within an ulp of 2^-24 either way) at a third of its
+// instructions: a step of a resident launch has little else to do between two exchanges.
+__device__ inline float rcp_1_to_2(float d) {
+  const float r = __builtin_amdgcn_rcpf(d);
+  return __fmaf_rn(__fmaf_rn(-d, r, 1.0f), r, r);
+}
+__device__ inline float sigmoidf_(float z) {
+  const float e = __expf(-fabsf(z));                   // in [0, 1]: no overflow
+  const float r = rcp_1_to_2(1.0f + e);
+  return z >= 0.0f ? r : __fmul_rn(e, r);
+}
 __device__ inline float tanhf_(float z) {
-  const float e = __expf(-2.0f * fabsf(z));            // in (0, 1]: no overflow
-  return copysignf((1.0f - e) * __frcp_rn(1.0f + e), z);
+  const float e = __expf(-2.0f * fabsf(z));
+  return copysignf(__fmul_rn(1.0f - e, rcp_1_to_2(1.0f + e)), z);
 }
 
 // ---- the h plane of a hidden-state unit ----------------------------------------------------------
@@ -264,6 +274,45 @@ inline BwdConfig backward_config(const Dims& d) {
   if (nt >= 2 && bt >= 2 && ((nt + 1) / 2) * ((bt + 1) / 2) >= TARGET_WGS) return BWD_22;
   if (bt >= 2 && nt * ((bt + 1) / 2) >= TARGET_WGS) return BWD_12;
   return BWD_11;
+}
+
+// Shapes whose resident launches spread one copy of the weights over `groups` equal parts of the device (see
+// resident_wide.h): bf16 operands too wide, or batches too large, for a copy per XCD.  groups parts of 256 / groups
+// compute units each take `share` sequences; a compute unit has nr 16-row tiles of a product's rows.  groups 0: not such
+// a shape.  The K splits of every kernel that runs a step of such a shape follow from what a compute unit's four
+// waves can add up: see paired_sum and WIDE_BACK_PARTS.
+struct WideShape {
+  int groups, share, nr;
+};
+inline WideShape wide_shape(const Dims& d) {
+  WideShape w{};
+  if (d.dtype == 0 || d.I < 8 || d.KP / 32 <= 20) return w;   // (20: the forward kernels that split K four ways)
+  int groups = 0;
+  if (d.KH > 512 && d.KH <= 1024 && d.B > 128 && d.B <= 256) groups = 4;
+  if (d.KH > 1024 && d.KH <= 2048 && d.B <= 128) groups = 2;
+  if (d.KH > 2048 && d.KH <= 4096 && d.B <= 32) groups = 1;
+  if (!groups) return w;
+  w.groups = groups;
+  w.share = round_up((d.B + groups - 1) / groups, 16);
+  w.nr = (d.KH * groups + 1023) / 1024;
+  return w;
+}
+
+constexpr int WIDE_FWD_KS = 4;   // K split of a forward step of a wide shape
+// Of a backward step of a wide shape: part p has the macro steps p, p + 16, ...; the parts q, q + 4, q + 8, q + 12 are
+// the waves of one workgroup of a resident launch and are added first, then the four workgroups' sums.
+constexpr int WIDE_BACK_PARTS = 16;
+template <class Part>
+__device__ __forceinline__ float sum_back_parts(Part&& part) {
+  float dh = 0.0f;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    float v = 0.0f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) v += part(q + 4 * w);
+    dh += v;
+  }
+  return dh;
 }
 
 }  // namespace mebptt

@@ -129,13 +129,17 @@ void set_resident_wait_ticks(long long ticks);
 // take).  0: only one workgroup per XCD runs, alone.
 void set_resident_patience(long long ticks);
 bool can_run_forward_chain(const Dims& d);
-int forward_chain_max_steps();
+int forward_chain_max_steps(const Dims& d);
 size_t forward_chain_ring_bytes(const Dims& d);
 size_t resident_sync_bytes();
 size_t resident_status_offset();
+// `nth`: the run's earlier launches of this kind (as distinct from `launch`).  `xs`: forward_chain_x_bytes of scratch.
 hipError_t launch_forward_chain(const Dims& d, const void* Wp, const float* bp, const float* x_first, const float* src_unit,
                                 const ChainStep* steps, int count, void* ring, float* spare, unsigned* sync, unsigned published,
-                                unsigned launch, hipStream_t st);
+                                unsigned launch, unsigned nth, void* xs, hipStream_t st);
+size_t forward_chain_x_bytes(const Dims& d);
+// Shapes whose resident launches are the wide ones: every step of a run goes out in them, single steps too.
+bool runs_wide(const Dims& d);
 
 // A run of (forward operation keeping the internal state, backward operation) pairs for steps
 // s_hi, s_hi - 1, ..., in one weight-gradient chunk or two consecutive ones, in one launch with both weight
@@ -160,7 +164,7 @@ struct SweepArgs {
   void* aT[2];
   void* ring;
   unsigned* sync;
-  unsigned published, launch;
+  unsigned published, launch, nth;   // nth: the run's earlier sweep launches
   int s_hi, count;
   const float* const* src;
   const float* const* state;   // NULL, or per step the unit where an earlier launch stored the internal state:
@@ -182,6 +186,9 @@ hipError_t launch_dx_gemm(const Dims& d, const void* WTx, const void* dG, int ns
                           size_t scratch_bytes, hipStream_t st);
 hipError_t launch_dgrad_gemm(const Dims& d, const void* WT, int N, const void* dG, int nslots, float* out,
                              int ld_out, hipStream_t st);
+
+// x of `steps` consecutive steps as fragment-tiled operands [step][BP][KX] (bf16), zero where there is no sequence or column.
+hipError_t launch_x_operands(const Dims& d, const float* x_first, int steps, void* xs, hipStream_t st);
 
 // x of `nslots` consecutive steps -> rows [0,NX) of aT, and ones into row NX+HP for the same columns.
 hipError_t launch_transpose_x(const Dims& d, const float* x_first, int nslots, void* aT, hipStream_t st);

@@ -146,6 +146,25 @@ hipError_t launch_prep_weights(const Dims& d, const float* W_ih, const float* W_
   return hipGetLastError();
 }
 
+// One thread per 16 bytes of a fragment.
+__global__ void x_operands_kernel(const float* __restrict__ x, int B, int I, int nsx, size_t n, bf16x8* __restrict__ xs, int btiles) {
+  const size_t stride = (size_t)gridDim.x * blockDim.x;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+    const int lane = (int)(i & 63), s = (int)((i >> 6) % nsx);
+    const size_t tile = (i >> 6) / nsx;
+    const int b = (int)(tile % btiles) * 16 + (lane & 15), k = s * 32 + (lane >> 4) * 8;
+    const float* row = x + (tile / btiles * B + b) * I;
+    const RawAct<8> v = load_raw<8>(row, k, b < B ? I : 0, (I & 3) == 0);
+    xs[i] = Mma<__bf16>::from_f32(v.v);
+  }
+}
+hipError_t launch_x_operands(const Dims& d, const float* x_first, int steps, void* xs, hipStream_t st) {
+  const size_t n = (size_t)steps * d.BP * d.KX / 8;
+  const size_t blocks = std::min<size_t>((n + 255) / 256, 2048);
+  x_operands_kernel<<<dim3((unsigned)blocks), dim3(256), 0, st>>>(x_first, d.B, d.I, d.KX / 32, n, reinterpret_cast<bf16x8*>(xs), d.BP / 16);
+  return hipGetLastError();
+}
+
 template <class T>
 __global__ void init_state_kernel(Dims d, const float* __restrict__ h0, const float* __restrict__ c0,
                                   float* __restrict__ dst) {
@@ -443,9 +462,11 @@ struct BwdParams {
 // macro steps before the first MFMA.  Partial sums meet in LDS (`red`, KS*NT*BT*256 floats).  The
 // pointwise backward has NT*BT*4 pieces of work (tile x which of the lane's four hidden units),
 // dealt round-robin to the waves.  (bx, by) = (hidden-unit tile group, batch-tile group).
-template <class T, int NT, int BT, int KS, int U>
+// PARTS = 2 (wide shapes): a wave keeps its even and its odd macro steps apart, see sum_back_parts.
+template <class T, int NT, int BT, int KS, int U, int PARTS = 1>
 __device__ inline void backward_body(const BwdParams& p, int bx, int by, float* red) {
   using M = Mma<T>;
+  static_assert(PARTS == 1 || (U % 2 == 0 && KS * PARTS == WIDE_BACK_PARTS), "a slot of the ring always holds the same part");
   constexpr int VEC = M::VEC, KSTEP = 4 * VEC;
   constexpr int NTILE = NT * BT, NPIECE = NTILE * 4, PPW = (NPIECE + KS - 1) / KS;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;   // scalar: see wave_index note
@@ -489,11 +510,13 @@ __device__ inline void backward_body(const BwdParams& p, int bx, int by, float* 
     }
   }
   if (p.dG_next) {
-    f32x4 acc[NT][BT];
+    f32x4 acc[PARTS][NT][BT];
 #pragma unroll
-    for (int i = 0; i < NT; ++i)
+    for (int e = 0; e < PARTS; ++e)
 #pragma unroll
-      for (int j = 0; j < BT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int j = 0; j < BT; ++j) acc[e][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int nsteps = p.G4 / KSTEP;
     const T* abase[NT];
     const T* bbase[BT];
@@ -523,7 +546,7 @@ __device__ inline void backward_body(const BwdParams& p, int bx, int by, float* 
 #pragma unroll
       for (int i = 0; i < NT; ++i)
 #pragma unroll
-        for (int jj = 0; jj < BT; ++jj) acc[i][jj] = M::mma(af[u][i], bf[u][jj], acc[i][jj]);
+        for (int jj = 0; jj < BT; ++jj) acc[u % PARTS][i][jj] = M::mma(af[u][i], bf[u][jj], acc[u % PARTS][i][jj]);
     };
 #pragma unroll
     for (int u = 0; u < U; ++u) load_slot(u, u);   // surplus slots (u >= nw) hold a clamped copy and are never used
@@ -543,11 +566,13 @@ __device__ inline void backward_body(const BwdParams& p, int bx, int by, float* 
       }
     }
 #pragma unroll
-    for (int i = 0; i < NT; ++i)
+    for (int e = 0; e < PARTS; ++e)
 #pragma unroll
-      for (int j = 0; j < BT; ++j)
+      for (int i = 0; i < NT; ++i)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) red[((wave * NTILE + i * BT + j) * 4 + r) * 64 + lane] = acc[i][j][r];
+        for (int j = 0; j < BT; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) red[(((wave + e * KS) * NTILE + i * BT + j) * 4 + r) * 64 + lane] = acc[e][i][j][r];
     __syncthreads();
   }
 #pragma unroll
@@ -555,8 +580,12 @@ __device__ inline void backward_body(const BwdParams& p, int bx, int by, float* 
     const int piece = wave + q * KS;
     if (piece >= NPIECE) break;
     float dh = 0.0f;
-    if (p.dG_next)
-      for (int w = 0; w < KS; ++w) dh += red[(w * NPIECE + piece) * 64 + lane];   // fixed order
+    if (p.dG_next) {   // fixed order
+      if constexpr (PARTS == 1)
+        for (int w = 0; w < KS; ++w) dh += red[(w * NPIECE + piece) * 64 + lane];
+      else
+        dh = sum_back_parts([&](int w) { return red[(w * NPIECE + piece) * 64 + lane]; });
+    }
     if (!epi[q]) continue;
     const size_t e = eidx[q];
     const int n = en[q], b = eb[q];
@@ -600,10 +629,10 @@ __device__ inline void backward_body(const BwdParams& p, int bx, int by, float* 
   }
 }
 
-template <class T, int NT, int BT, int KS, int U>
+template <class T, int NT, int BT, int KS, int U, int PARTS>
 __global__ __launch_bounds__(64 * KS) void backward_kernel(BwdParams p) {
-  __shared__ float red[KS * NT * BT * 4 * 64];
-  backward_body<T, NT, BT, KS, U>(p, blockIdx.x, blockIdx.y, red);
+  __shared__ float red[KS * PARTS * NT * BT * 4 * 64];
+  backward_body<T, NT, BT, KS, U, PARTS>(p, blockIdx.x, blockIdx.y, red);
 }
 
 // ---- fused launch: a backward step and an independent forward step ---------------------------
@@ -646,6 +675,9 @@ static hipError_t launch_forward_cfg(const Dims& d, const FwdParams& p, hipStrea
 
 template <class T>
 static hipError_t launch_forward_t(const Dims& d, const FwdParams& p, hipStream_t st) {
+  if constexpr (sizeof(T) == 2) {
+    if (wide_shape(d).groups) return launch_forward_cfg<T, 4, 2, WIDE_FWD_KS, 2>(d, p, st);   // without resident launches only
+  }
   switch (forward_config<T>(d)) {
     case FWD_TINY: return launch_forward_cfg<T, 1, 1, 4, 2>(d, p, st);   // tiny K: one small workgroup per tile
     case FWD_SMALLK: return launch_forward_cfg<T, 4, 1, 4, 5>(d, p, st);
@@ -735,7 +767,8 @@ static void launch_forward_batch_t(const Dims& d, const FwdParams& p, const FwdB
   const dim3 grid((d.HP / 4 + NG - 1) / NG, (d.BP / 16 + BT - 1) / BT, n);
   const size_t plane = (size_t)d.B * d.H;
   const FwdConfig cfg = forward_config<T>(d);
-  const bool small_k = cfg == FWD_TINY || cfg == FWD_SMALLK;   // the K split of the shape's stand-alone forward kernel
+  // the K split of the shape's stand-alone forward kernel
+  const bool small_k = cfg == FWD_TINY || cfg == FWD_SMALLK || wide_shape(d).groups;
   if (small_k && d.cell)
     forward_batch_kernel<T, NG, BT, 4, FU, 1><<<grid, dim3(64 * 4), 0, st>>>(p, steps, d.hplane, d.unit, plane);
   else if (small_k)
@@ -794,6 +827,10 @@ __global__ __launch_bounds__(512) void stream_panels_kernel(const uint4* __restr
 
 template <class T>
 static void forward_launch_shape(const Dims& d, int& ng, int& bt, int& ks) {
+  if (wide_shape(d).groups) {
+    ng = 4, bt = 2, ks = WIDE_FWD_KS;
+    return;
+  }
   switch (forward_config<T>(d)) {
     case FWD_TINY: ng = 1, bt = 1, ks = 4; break;
     case FWD_SMALLK: ng = 4, bt = 1, ks = 4; break;
@@ -826,7 +863,13 @@ hipError_t launch_forward_stream(const Dims& d, const void* Wp, const void* act,
 template <class T, int NT, int BT, int KS, int U>
 static hipError_t launch_backward_cfg(const Dims& d, const BwdParams& p, hipStream_t st) {
   dim3 grid((d.HP / 16 + NT - 1) / NT, (d.BP / 16 + BT - 1) / BT), block(64 * KS);
-  backward_kernel<T, NT, BT, KS, U><<<grid, block, 0, st>>>(p);
+  if constexpr (KS == 8 && sizeof(T) == 2) {
+    if (wide_shape(d).groups) {
+      backward_kernel<T, NT, BT, KS, U, 2><<<grid, block, 0, st>>>(p);
+      return hipGetLastError();
+    }
+  }
+  backward_kernel<T, NT, BT, KS, U, 1><<<grid, block, 0, st>>>(p);
   return hipGetLastError();
 }
 
@@ -882,6 +925,7 @@ hipError_t launch_backward(const Dims& d, const BackwardArgs& a, hipStream_t st)
 // 1 x 1, 8 waves each); 2 = small-K forward (4 waves) with the 1 x 2 backward (8 waves).  0 = none.
 template <class T>
 static int pair_class(const Dims& d) {
+  if (wide_shape(d).groups) return 0;   // both go out in resident launches
   const FwdConfig fc = forward_config<T>(d);
   const BwdConfig bc = backward_config<T>(d);
   if (fc == FWD_B1 && bc == BWD_11) return 1;

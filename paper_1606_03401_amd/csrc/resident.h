@@ -28,8 +28,9 @@ namespace mebptt {
 constexpr int RES_WGS = 256, RES_GROUPS = 8, RES_MEMBERS = RES_WGS / RES_GROUPS;
 constexpr int RES_RING = 4;   // exchange slots
 // sync words of XCD g from [g * 64] on: the rank word (the counter in its low half, in its high half the launch given
-// up last, + 1), the workgroups that have left that launch; status at [512]
-constexpr int RES_SYNC_RANK = 0, RES_SYNC_LEFT = 2, RES_SYNC_STATUS = 512;
+// up last, + 1), the workgroups that have left that launch; the same two of group g of wide chains and of wide sweeps;
+// status at [512]
+constexpr int RES_SYNC_RANK = 0, RES_SYNC_LEFT = 2, RES_SYNC_CHAIN_GROUP = 4, RES_SYNC_SWEEP_GROUP = 8, RES_SYNC_STATUS = 512;
 
 __device__ inline unsigned xcc_id() {
   unsigned v;
@@ -173,7 +174,7 @@ __device__ __forceinline__ bool slot_is_there(const void* slot, int pieces, int 
   __threadfence();   // what this workgroup's waves have stored for the step can be fetched
   __syncthreads();
   WaitBound bound{wait_ticks, status};
-  for (int m = (int)(threadIdx.x >> 6); m < pieces; m += 8)
+  for (int m = (int)(threadIdx.x >> 6); m < pieces; m += (int)(blockDim.x >> 6))
     for (int t = 0; t < tiles; ++t)
       while (__builtin_amdgcn_ballot_w64(largest_dword(load_slot_16(slot, off(t), m * 1024)) == RES_EMPTY) != 0) {
         if (bound.expired()) {
@@ -315,6 +316,7 @@ struct ResStep {
 };
 constexpr int RES_MAX_STEPS = 192;  // steps of one launch: their destinations travel as kernel arguments (3 KiB of the 4 KiB there are)
 struct ResParams {
+  static constexpr int RING = RES_RING;
   const void* Wp;
   const float* bp;
   const float* x0;     // x of the first step of this launch
@@ -397,9 +399,10 @@ __device__ __forceinline__ void gates_slowly(const void* Wp, int tile, const flo
 // All steps of a launch for units [u0, u1) of the XCD's sequences, by a workgroup that has stopped waiting.  Its waves
 // deal the units out four at a time; the state that stays in registers in a chain goes through `spare`, and the
 // weights are fetched again in every step.
-template <class T, int KS, int CELL>
+template <class P, class T, int KS, int CELL>
 __device__ __forceinline__ void chain_slowly(int b_lo, int b_hi, int u0, int u1, int* s_fail) {
-  const auto& p = *arguments_again<ResParams>();
+  const auto& p = *arguments_again<P>();
+  const int deal = (int)(blockDim.x >> 6) * 4;   // units the workgroup's waves take at a time
   using M = Mma<T>;
   constexpr int VEC = M::VEC, KSTEP = 4 * VEC;
   constexpr bool SPLIT = HPlane<T>::SPLIT;
@@ -408,14 +411,14 @@ __device__ __forceinline__ void chain_slowly(int b_lo, int b_hi, int u0, int u1,
   const int nsx = p.KX / KSTEP, nsh = p.KH / KSTEP;
   const size_t hhalf = (size_t)p.BP * p.KH;
   const unsigned plane = (unsigned)(p.B * p.H);
-  auto slot = [&](unsigned q) { return reinterpret_cast<T*>(p.ring) + (size_t)(q % RES_RING) * hhalf; };
+  auto slot = [&](unsigned q) { return reinterpret_cast<T*>(p.ring) + (size_t)(q % P::RING) * hhalf; };
   auto off = [&](int t) {
     const int b = b_lo + t * 16 + lrow;
     return b < b_hi ? (unsigned)(((b >> 4) * nsh * 64 + lq * 16 + (b & 15)) * 16) : RES_NO_LANE;
   };
   auto publish = [&](unsigned q, int b, int u, float h) {   // as in a chain; all lanes
     const size_t o = ft_offset<T>(b, u, nsh);
-    unsigned *to = reinterpret_cast<unsigned*>(slot(q)), *old = reinterpret_cast<unsigned*>(slot(q + 2));
+    unsigned *to = reinterpret_cast<unsigned*>(slot(q)), *old = reinterpret_cast<unsigned*>(slot(q + P::RING - 2));
     if constexpr (SPLIT) {
       const unsigned hi16 = (__float_as_uint(h) + 0x8000u) >> 16;
       const auto rows = __builtin_amdgcn_permlane16_swap(hi16, hi16, false, false);
@@ -428,7 +431,7 @@ __device__ __forceinline__ void chain_slowly(int b_lo, int b_hi, int u0, int u1,
       old[o] = RES_EMPTY;
     }
   };
-  for (int u4 = u0 + 4 * wave; u4 < u1; u4 += 32)
+  for (int u4 = u0 + 4 * wave; u4 < u1; u4 += deal)
     for (int c = b_lo; c < b_hi; c += 16) {
       const int b = c + lrow, u = u4 + lq;
       float h = 0.0f;
@@ -442,7 +445,7 @@ __device__ __forceinline__ void chain_slowly(int b_lo, int b_hi, int u0, int u1,
     const T* in = slot(p.published + (unsigned)j);
     if (!slot_is_there(in, nsh, (b_hi - b_lo + 15) / 16, off, p.wait_ticks, p.sync + RES_SYNC_STATUS, s_fail)) return;
     float *dst = p.step[j].out, *gates = p.step[j].gates;
-    for (int u4 = u0 + 4 * wave; u4 < u1; u4 += 32)
+    for (int u4 = u0 + 4 * wave; u4 < u1; u4 += deal)
       for (int c = b_lo; c < b_hi; c += 16) {
         const int b = c + lrow, u = u4 + lq;
         const bool own = b < b_hi, real = own && u < p.H;
@@ -739,7 +742,7 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
     Sum::write(red + (size_t)wave * Sum::BLOCKS * 64, lane, acc);
     lds_barrier();
     if (__builtin_amdgcn_readfirstlane(s_fail))   // a wave has stopped waiting: written before the barrier, so all see it
-      stop_waiting<ResParams, UW>(&s_g, &s_rank, &s_fail, [&](int b_lo, int b_hi, int u0, int u1) { chain_slowly<T, KS, CELL>(b_lo, b_hi, u0, u1, &s_fail); });
+      stop_waiting<ResParams, UW>(&s_g, &s_rank, &s_fail, [&](int b_lo, int b_hi, int u0, int u1) { chain_slowly<ResParams, T, KS, CELL>(b_lo, b_hi, u0, u1, &s_fail); });
 #pragma unroll
     for (int q = 0; q < IPT; ++q) {
       if (!mine[q]) continue;

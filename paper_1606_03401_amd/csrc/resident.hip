@@ -2,7 +2,7 @@
 // time steps (see the comments at each kernel).
 #include <algorithm>
 
-#include "resident_sweep.h"
+#include "resident_wide.h"
 
 namespace mebptt {
 
@@ -71,18 +71,45 @@ static const ChainConfig* chain_config(const Dims& d) {
   return nullptr;
 }
 
-bool can_run_forward_chain(const Dims& d) { return chain_config(d) != nullptr; }
-int forward_chain_max_steps() { return RES_MAX_STEPS; }
-size_t forward_chain_ring_bytes(const Dims& d) { return (size_t)RES_RING * d.BP * d.KH * d.op_bytes(); }
+// The wide launches of a shape, or NULL; see wide_shape.
+static const WideConfig* wide_config(const Dims& d) {
+  const WideShape w = wide_shape(d);
+  if (!w.groups) return nullptr;
+  for (const Table<WideConfig>& table : {wide_table_1(), wide_table_2(), wide_table_3()})
+    for (int i = 0; i < table.n; ++i) {
+      const WideConfig& c = table.at[i];
+      if (c.nr == w.nr && c.nhw * 4 * 32 >= d.KH && c.nb * c.ph * 16 >= w.share) return &c;
+    }
+  return nullptr;
+}
+// Blocks of 16 * nr units of a wide sweep, and a slot of its partial sums: every four workgroups of a block send each other
+// a quarter of the block's units of their sequences.
+static int wide_blocks(const Dims& d, const WideConfig& c) { return (d.HP + 16 * c.nr - 1) / (16 * c.nr); }
+static size_t wide_part_bytes(const Dims& d, const WideConfig& c) {
+  return (size_t)wide_shape(d).groups * wide_blocks(d, c) * 16 * (4 * c.nr * 16 * c.nb * c.ph) * sizeof(float);
+}
+
+bool runs_wide(const Dims& d) { return wide_config(d) != nullptr; }
+bool can_run_forward_chain(const Dims& d) { return chain_config(d) != nullptr || runs_wide(d); }
+// A wide chain launch reads x as operands, which a kernel ahead of it lays out for all its steps.
+static size_t x_step_bytes(const Dims& d) { return (size_t)d.BP * d.KX * d.op_bytes(); }
+int forward_chain_max_steps(const Dims& d) {
+  if (!runs_wide(d)) return RES_MAX_STEPS;
+  constexpr size_t X_MAX_BYTES = (size_t)32 << 20;
+  return (int)std::max<size_t>(16, std::min<size_t>(RES_MAX_STEPS, X_MAX_BYTES / x_step_bytes(d)));
+}
+size_t forward_chain_x_bytes(const Dims& d) { return runs_wide(d) ? forward_chain_max_steps(d) * x_step_bytes(d) : 0; }
+size_t forward_chain_ring_bytes(const Dims& d) { return (size_t)(runs_wide(d) ? WIDE_RING : RES_RING) * d.BP * d.KH * d.op_bytes(); }
 size_t resident_sync_bytes() { return (RES_SYNC_STATUS + 64) * sizeof(unsigned); }
 size_t resident_status_offset() { return RES_SYNC_STATUS * sizeof(unsigned); }
 
 hipError_t launch_forward_chain(const Dims& d, const void* Wp, const float* bp, const float* x_first, const float* src_unit,
                                 const ChainStep* steps, int count, void* ring, float* spare, unsigned* sync, unsigned published,
-                                unsigned launch, hipStream_t st) {
-  const ChainConfig* cfg = chain_config(d);
-  if (!cfg || count < 1 || count > RES_MAX_STEPS) return hipErrorInvalidValue;
-  ResParams p{};
+                                unsigned launch, unsigned nth, void* xs, hipStream_t st) {
+  const WideConfig* wide = wide_config(d);
+  const ChainConfig* cfg = wide ? nullptr : chain_config(d);
+  if ((!cfg && !wide) || count < 1 || count > forward_chain_max_steps(d)) return hipErrorInvalidValue;
+  WideChainParams p{};
   p.Wp = Wp;
   p.bp = bp;
   p.x0 = x_first;
@@ -93,7 +120,8 @@ hipError_t launch_forward_chain(const Dims& d, const void* Wp, const float* bp, 
   p.published = published;
   p.launch = launch;
   p.wait_ticks = g_wait_ticks;
-  p.patience = patience(d, count, (size_t)d.G4 * d.KP * (group_share(d) > 16 ? 2 : 1));
+  const int share = wide ? wide_shape(d).share : group_share(d);
+  p.patience = patience(d, count, (size_t)d.G4 * d.KP * ((share + 15) / 16));
   p.alone = g_patience == 0;
   p.count = count;
   p.B = d.B;
@@ -103,10 +131,17 @@ hipError_t launch_forward_chain(const Dims& d, const void* Wp, const float* bp, 
   p.KX = d.KX;
   p.KH = d.KH;
   p.BP = d.BP;
-  p.nb = group_share(d);
+  p.nb = share;
   p.unit = d.unit;
   p.hplane = d.hplane;
   for (int j = 0; j < count; ++j) p.step[j] = ResStep{steps[j].out, steps[j].gates};
+  if (wide) {
+    p.groups = wide_shape(d).groups;
+    p.arrived = nth * (unsigned)((d.KH + 4 * wide->nr - 1) / (4 * wide->nr));
+    p.xs = xs;
+    const hipError_t e = launch_x_operands(d, x_first, count, xs, st);
+    return e == hipSuccess ? wide->chain[d.cell](p, st) : e;
+  }
   return cfg->launch[d.cell](p, st);
 }
 
@@ -140,16 +175,21 @@ static const BackSweepConfig* back_sweep_config(const Dims& d) {
 }
 
 bool can_run_sweep(const Dims& d) { return sweep_config(d) != nullptr; }
-bool can_run_backward_sweep(const Dims& d) { return back_sweep_config(d) != nullptr; }
+bool can_run_backward_sweep(const Dims& d) { return back_sweep_config(d) != nullptr || runs_wide(d); }
 int sweep_max_steps() { return SWEEP_MAX_STEPS; }
-size_t sweep_ring_bytes(const Dims& d) { return (size_t)RES_RING * d.BP * d.G4 * d.op_bytes(); }
+size_t sweep_ring_bytes(const Dims& d) {
+  const size_t slot = (size_t)d.BP * d.G4 * d.op_bytes();
+  if (const WideConfig* c = wide_config(d)) return WIDE_RING * slot + WIDE_PART_RING * wide_part_bytes(d, *c);   // slots of dG, then of partial sums
+  return RES_RING * slot;
+}
 
 hipError_t launch_sweep(const Dims& d, const SweepArgs& a, hipStream_t st) {
+  const WideConfig* wide = a.state ? wide_config(d) : nullptr;
   const SweepConfig* with_forward = a.state ? nullptr : sweep_config(d);
-  const BackSweepConfig* backward_only = a.state ? back_sweep_config(d) : nullptr;
-  if ((!with_forward && !backward_only) || a.count < 1 || a.count > SWEEP_MAX_STEPS) return hipErrorInvalidValue;
+  const BackSweepConfig* backward_only = a.state && !wide ? back_sweep_config(d) : nullptr;
+  if ((!with_forward && !backward_only && !wide) || a.count < 1 || a.count > SWEEP_MAX_STEPS) return hipErrorInvalidValue;
   if ((a.s_hi - 1) / d.CH - (a.s_hi - a.count) / d.CH > 1) return hipErrorInvalidValue;   // two chunk buffers
-  SweepParams p{};
+  WideSweepParams p{};
   p.Wp = a.Wp;
   p.WTh = a.WTh;
   p.bp = a.bp;
@@ -170,7 +210,8 @@ hipError_t launch_sweep(const Dims& d, const SweepArgs& a, hipStream_t st) {
   p.published = a.published;
   p.launch = a.launch;
   p.wait_ticks = g_wait_ticks;
-  p.patience = patience(d, a.count, (size_t)d.G4 * (d.HP + (a.state ? 0 : d.KP)) * (group_share(d) > 16 ? 2 : 1));
+  const int share = wide ? wide_shape(d).share : group_share(d);
+  p.patience = patience(d, a.count, (size_t)d.G4 * (d.HP + (a.state ? 0 : d.KP)) * ((share + 15) / 16));
   p.alone = g_patience == 0;
   p.s_hi = a.s_hi;
   p.count = a.count;
@@ -181,7 +222,7 @@ hipError_t launch_sweep(const Dims& d, const SweepArgs& a, hipStream_t st) {
   p.KX = d.KX;
   p.KH = d.KH;
   p.BP = d.BP;
-  p.nb = group_share(d);
+  p.nb = share;
   p.G4 = d.G4;
   p.NX = d.NX;
   p.KC = d.KC;
@@ -191,6 +232,12 @@ hipError_t launch_sweep(const Dims& d, const SweepArgs& a, hipStream_t st) {
   for (int j = 0; j < a.count; ++j) {
     p.src[j] = a.src[j];
     p.state[j] = a.state ? a.state[j] : nullptr;
+  }
+  if (wide) {
+    p.groups = wide_shape(d).groups;
+    p.arrived = a.nth * 4u * (unsigned)wide_blocks(d, *wide);
+    p.parts = reinterpret_cast<char*>(a.ring) + (size_t)WIDE_RING * d.BP * d.G4 * d.op_bytes();
+    return wide->sweep[d.cell](p, st);
   }
   return with_forward ? with_forward->launch(p, st) : backward_only->launch[d.cell](p, st);
 }

@@ -8,6 +8,7 @@ namespace mebptt {
 
 constexpr int SWEEP_MAX_STEPS = 32;
 struct SweepParams {
+  static constexpr int RING = RES_RING;
   const void* Wp;
   const void* WTh;
   const float* bp;
@@ -37,9 +38,10 @@ __device__ inline int units_of(const __attribute__((address_space(4))) SweepPara
 // All steps of a launch for units [u0, u1) of the XCD's sequences, by a workgroup that has stopped waiting (see
 // chain_slowly).  Its waves deal the units out sixteen at a time: dh of a tile passes through LDS from the MFMA's layout (a lane has four
 // consecutive units) to that of the gate sums (a lane has one unit of each four).
-template <class T, bool FWD, int KSF, int KSB, int CELL>
+template <class P, class T, bool FWD, int KSF, int KSB, int CELL>
 __device__ __forceinline__ void sweep_slowly(int b_lo, int b_hi, int u0, int u1, float* smem, int* s_fail) {
-  const auto& p = *arguments_again<SweepParams>();
+  const auto& p = *arguments_again<P>();
+  const int waves = (int)(blockDim.x >> 6);
   using M = Mma<T>;
   constexpr int VEC = M::VEC, KSTEP = 4 * VEC, FRAG = 64 * VEC;
   constexpr bool SPLIT = HPlane<T>::SPLIT;
@@ -50,7 +52,7 @@ __device__ __forceinline__ void sweep_slowly(int b_lo, int b_hi, int u0, int u1,
   const size_t hhalf = (size_t)p.BP * p.KH, dG_step = (size_t)p.BP * p.G4;
   const unsigned plane = (unsigned)(p.B * p.H);
   float* dhs = smem + wave * 256;   // [16 units][16 sequences]
-  auto slot = [&](unsigned q) { return reinterpret_cast<T*>(p.ring) + (size_t)(q % RES_RING) * dG_step; };
+  auto slot = [&](unsigned q) { return reinterpret_cast<T*>(p.ring) + (size_t)(q % P::RING) * dG_step; };
   auto off = [&](int t) {
     const int b = b_lo + t * 16 + lrow;
     return b < b_hi ? (unsigned)(((b >> 4) * nsteps * 64 + lq * 16 + (b & 15)) * 16) : RES_NO_LANE;
@@ -60,9 +62,9 @@ __device__ __forceinline__ void sweep_slowly(int b_lo, int b_hi, int u0, int u1,
 #pragma unroll
     for (int r = 0; r < (int)sizeof(T); ++r) empty[r] = RES_EMPTY;
     *reinterpret_cast<vec*>(slot(q) + o) = v;
-    *reinterpret_cast<vec*>(slot(q + 2) + o) = empty;
+    *reinterpret_cast<vec*>(slot(q + P::RING - 2) + o) = empty;
   };
-  for (int tile = wave; tile < tiles; tile += 8)
+  for (int tile = wave; tile < tiles; tile += waves)
     for (int c = b_lo; c < b_hi; c += 16) {
       const int b = c + lrow;
 #pragma unroll
@@ -84,7 +86,7 @@ __device__ __forceinline__ void sweep_slowly(int b_lo, int b_hi, int u0, int u1,
     T* dG_cur = reinterpret_cast<T*>(p.dG_chunk[buf]) + (size_t)step_slot * dG_step;
     T *dGT = reinterpret_cast<T*>(p.dGT[buf]), *aT = reinterpret_cast<T*>(p.aT[buf]);
     const float *src = p.src[j], *stp = FWD ? src : p.state[j];
-    for (int tile = wave; tile < tiles; tile += 8)
+    for (int tile = wave; tile < tiles; tile += waves)
       for (int c = b_lo; c < b_hi; c += 16) {
         const int b = c + lrow, row = b < b_hi ? b : b_lo;
         const bool own = b < b_hi;
@@ -112,9 +114,14 @@ __device__ __forceinline__ void sweep_slowly(int b_lo, int b_hi, int u0, int u1,
             __builtin_amdgcn_sched_barrier(0);
           }
 #pragma unroll
-        for (int w = 0; w < KSB; ++w)   // fixed order, as in backward_body
+        for (int r = 0; r < 4; ++r) {   // fixed order, as in backward_body
+          if constexpr (KSB == WIDE_BACK_PARTS) {
+            dh4[r] = sum_back_parts([&](int w) { return acc[w][r]; });
+          } else {
 #pragma unroll
-          for (int r = 0; r < 4; ++r) dh4[r] += acc[w][r];
+            for (int w = 0; w < KSB; ++w) dh4[r] += acc[w][r];
+          }
+        }
 #pragma unroll
         for (int r = 0; r < 4; ++r) dhs[(4 * lq + r) * 16 + lrow] = dh4[r];
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the wave's own part: no barrier
@@ -613,7 +620,7 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
     lds_barrier();
     if (__builtin_amdgcn_readfirstlane(s_fail))   // a wave has stopped waiting: written before the barrier, so all see it
       stop_waiting<SweepParams, UW>(&s_g, &s_rank, &s_fail, [&](int b_lo, int b_hi, int u0, int u1) {
-        sweep_slowly<T, FWD, KSF, KSB, CELL>(b_lo, b_hi, u0, u1, reinterpret_cast<float*>(smem), &s_fail);
+        sweep_slowly<SweepParams, T, FWD, KSF, KSB, CELL>(b_lo, b_hi, u0, u1, reinterpret_cast<float*>(smem), &s_fail);
       });
     // pointwise backward of step s on the internal state held in registers
 #pragma unroll

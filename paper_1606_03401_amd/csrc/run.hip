@@ -28,7 +28,7 @@ constexpr size_t ALIGN = 256;
 inline size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
 struct Workspace {
-  size_t Wp, bp, WTh, WTx, state, dWacc, dc, sync, dG[2], dGT[2], aT[2], ring, gring, ring_bytes, spare, stage, total;
+  size_t Wp, bp, WTh, WTx, state, dWacc, dc, sync, dG[2], dGT[2], aT[2], ring, gring, ring_bytes, spare, xs, stage, total;
   size_t total_no_stage;   // what a run without resident launches needs (the no-allocation path): no rings, no stage
   int stage_steps;         // internal states the stage holds
 };
@@ -61,7 +61,7 @@ int recompute_stage_steps(const Dims& d) {
 //   fp32, whose GEMMs take eight times as long, from 3 GFLOP on: H = 512, B = 32 0.9 % slower, H = 256, B = 256
 //   0.6 % slower with hidden states stored, 7.8 % faster with internal ones (beside all the same: a rule by sizes alone).
 bool gemms_beside(const Dims& d) {
-  if (!can_run_forward_chain(d) && !can_run_backward_sweep(d)) return false;
+  if ((!can_run_forward_chain(d) && !can_run_backward_sweep(d)) || runs_wide(d)) return false;
   const double chunk_flops = 8.0 * d.CH * d.B * d.H * ((double)d.I + d.H);
   return chunk_flops >= 3e9 && (d.dtype == 0 || (d.B > 32 && d.B <= 128));
 }
@@ -92,6 +92,7 @@ Workspace layout(const Dims& d) {
   w.gring = take(can_run_backward_sweep(d) || can_run_sweep(d) ? sweep_ring_bytes(d) : 0);
   w.ring_bytes = off - w.ring;   // both exchange rings
   w.spare = take(can_run_forward_chain(d) ? (size_t)d.B * d.H * sizeof(float) : 0);
+  w.xs = take(forward_chain_x_bytes(d));
   w.stage_steps = recompute_stage_steps(d);
   w.stage = take((size_t)w.stage_steps * 3 * unit);   // last: nothing ever clears it
   w.total = off;
@@ -581,7 +582,8 @@ int32_t mebptt_chunk_steps(const mebptt_lstm_desc* desc) {
 int32_t mebptt_stage_steps(const mebptt_lstm_desc* desc) {
   int rc = check_desc(desc);
   if (rc) return rc;
-  return recompute_stage_steps(make_dims(desc->B, desc->I, desc->H, desc->gemm_dtype, desc->cell));
+  const Dims d = make_dims(desc->B, desc->I, desc->H, desc->gemm_dtype, desc->cell);
+  return runs_wide(d) ? 0 : recompute_stage_steps(d);
 }
 
 int mebptt_measure_gemms(const mebptt_lstm_desc* desc, void* workspace, size_t workspace_bytes, int32_t reps,
@@ -915,10 +917,13 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
   // chain goes out as forward-chain launches of up to forward_chain_max_steps() steps instead of
   // one launch per step.  Not in the no-allocation path, which has no exchange slots.
   const bool chain_ok = resident_ok && can_run_forward_chain(d);
-  constexpr int CHAIN_MIN_STEPS = 2;     // two steps in one launch already beat two launches (measured on the paper's 256-wide model)
+  // On wide shapes every step runs in a resident launch: their sums are split as no other default path splits them.
+  const bool wide = resident_ok && runs_wide(d);
+  const int chain_min_steps = wide ? 1 : 2;   // two steps in one launch already beat two launches (measured on the paper's 256-wide model)
   unsigned chain_published = 0;   // states exchanged inside this run's earlier chain launches
   unsigned sweep_published = 0;   // the same for the sweep launches
   unsigned chain_launches = 0;    // resident launches of this run so far
+  unsigned nth_chain = 0, nth_sweep = 0;   // of either kind
   bool chain_used = false;
   struct FStep {
     int step;
@@ -995,6 +1000,7 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
     a.ring = ws + w.gring;
     a.published = sweep_published;
     a.launch = chain_launches;
+    a.nth = nth_sweep;
     a.s_hi = s_hi;
     a.count = n;
     a.src = srcs;
@@ -1004,6 +1010,7 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
     if (use_profiler && g_prof.every_n > 0 && !states) g_prof.sweep_forward_steps += n;
     sweep_published += (unsigned)n;
     ++chain_launches;
+    ++nth_sweep;
     bwd += n;
     if (!states) fwd += n;
     for (int c = chunk_hi; c >= chunk_lo; --c)   // chunks whose first step the launch has back-propagated
@@ -1018,18 +1025,23 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
   int handed_step = 0;
   for (size_t oi = 0; oi < ops.size();) {
     const mebptt_op& op = ops[oi];
-    if (bsweep_ok && stored_bwd_at(oi) && stored_bwd_at(oi + 1)) {
+    // A backward operation whose internal state a forward run has just left in the working core,
+    // followed by such pairs for the steps below it, leads their launch: it is the first step of
+    // the sweep launch, on the state in the core, the others on the states in the stage.
+    const bool lead = batch_ok && op.op == MEBPTT_OP_BWD && op.dst == MEBPTT_LOC_CORE && pair_at(oi + 1) &&
+                      ops[oi + 1].step == op.step - 1;
+    if (bsweep_ok && !lead && (wide ? op.op == MEBPTT_OP_BWD : stored_bwd_at(oi) && stored_bwd_at(oi + 1))) {
       const int s_hi = op.step, chunk = (s_hi - 1) / CH;
       int n = 0;
       const float *srcs[64], *states[64];
       const int reach = may_cross(chunk) ? 1 : 0;   // (store-everything BPTT: these launches follow each other directly)
-      while (n < sweep_max_steps() && stored_bwd_at(oi + (size_t)n) && ops[oi + (size_t)n].step == s_hi - n &&
+      while (n < sweep_max_steps() && (stored_bwd_at(oi + (size_t)n) || (wide && n == 0)) && ops[oi + (size_t)n].step == s_hi - n &&
              chunk - (s_hi - n - 1) / CH <= reach) {
         srcs[n] = loc(ops[oi + (size_t)n].src);
         states[n] = loc(ops[oi + (size_t)n].dst);
         ++n;
       }
-      if (n >= 2) {
+      if (n >= (wide ? 1 : 2)) {
         for (int j = 0; j < n; ++j) {
           touch(ops[oi + (size_t)j].dst, 3);
           touch(ops[oi + (size_t)j].src, 1);
@@ -1040,11 +1052,6 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
         continue;
       }
     }
-    // A backward operation whose internal state a forward run has just left in the working core,
-    // followed by such pairs for the steps below it, leads their launch: it is the first step of
-    // the sweep launch, on the state in the core, the others on the states in the stage.
-    const bool lead = batch_ok && op.op == MEBPTT_OP_BWD && op.dst == MEBPTT_LOC_CORE && pair_at(oi + 1) &&
-                      ops[oi + 1].step == op.step - 1;
     if (batch_ok && (lead || pair_at(oi))) {
       // A run of such pairs for steps going down (in at most two chunks), every step's input state in a
       // slot: the forward operations do not depend on each other and go out as one launch that
@@ -1166,10 +1173,10 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
           if (rc) return rc;
         }
       }
-      if (chain_ok && total - fi >= (size_t)CHAIN_MIN_STEPS) {
+      if (chain_ok && total - fi >= (size_t)chain_min_steps) {
         rc = order_resident_launches();
         if (rc) return rc;
-        const int max_steps = forward_chain_max_steps();
+        const int max_steps = forward_chain_max_steps(d);
         ChainStep cs[256];   // >= forward_chain_max_steps()
         while (fi < total) {
           const int n = (int)std::min<size_t>(total - fi, (size_t)max_steps);
@@ -1181,10 +1188,11 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
           const float* x_first = x_of(fsteps[fi].step);
           rc = whole_launch(MEBPTT_K_CHAIN, n, st, [&] {
             return launch_forward_chain(d, Wp, bp, x_first, cur, cs, n, ws + w.ring, reinterpret_cast<float*>(ws + w.spare),
-                                        reinterpret_cast<unsigned*>(ws + w.sync), chain_published, chain_launches, st);
+                                        reinterpret_cast<unsigned*>(ws + w.sync), chain_published, chain_launches, nth_chain, ws + w.xs, st);
           });
           if (rc) return rc;
           ++chain_launches;
+          ++nth_chain;
           chain_published += (unsigned)n;
           cur = fsteps[fi + n - 1].dst;
           fi += n;
