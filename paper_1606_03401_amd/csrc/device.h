@@ -299,7 +299,7 @@ inline WideShape wide_shape(const Dims& d) {
 }
 
 constexpr int WIDE_FWD_KS = 4;   // K split of a forward step of a wide shape
-// Of a backward step of a wide shape: part p has the macro steps p, p + 16, ...; the parts q, q + 4, q + 8, q + 12 are
+// Of a backward step of a wide shape: part p has the macro steps p, p + 16, ...; the parts 4q .. 4q + 3 are
 // the waves of one workgroup of a resident launch and are added first, then the four workgroups' sums.
 constexpr int WIDE_BACK_PARTS = 16;
 template <class Part>
@@ -309,7 +309,7 @@ __device__ __forceinline__ float sum_back_parts(Part&& part) {
   for (int q = 0; q < 4; ++q) {
     float v = 0.0f;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) v += part(q + 4 * w);
+    for (int w = 0; w < 4; ++w) v += part(4 * q + w);
     dh += v;
   }
   return dh;

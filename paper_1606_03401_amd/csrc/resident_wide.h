@@ -388,11 +388,11 @@ struct WideProduct {
 // ---- forward chain -----------------------------------------------------------------------------------------
 // Consecutive forward operations in one launch, see forward_chain_kernel.  A phase (a step of one half of the sequences):
 //   1. the x part of the gate product: x as operands, laid out by a kernel before the launch and fetched a phase ahead; its
-//      weights in LDS, NXL macro steps a wave of them (what goes beyond is fetched again in every phase);
+//      weights in registers, NX macro steps a wave of them, or in LDS (NXL); what goes beyond is fetched again in every phase;
 //   2. the h part on the exchanged fragments, macro step by macro step as they come;
 //   3. partial sums through LDS; the next phase's first fragments requested; the pointwise step;
 //   4. h published, and stored where the schedule keeps it.
-template <int NR, int NXL, int NHW, int NHL, int NHS, int NB, int PH, int CELL>
+template <int NR, int NX, int NXL, int NHW, int NHL, int NHS, int NB, int PH, int CELL>
 __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1))) void wide_chain_kernel(WideChainParams p) {
   using T = __bf16;
   using M = Mma<T>;
@@ -486,13 +486,19 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
   }
 
   WideWeights<NR, NHW, NHL, NHS> w(WideOperand(p.Wp, nsteps), member * NR, p.HP / 4, wl + (size_t)wave * NR * NHL * FRAG);
-  T* wxl = wl + (size_t)WIDE_WAVES * NR * NHL * FRAG + (size_t)wave * NR * NXL * FRAG + lane * 8;
   auto h_step = [&](int i) { return mh0 + 4 * i; };
+  T* wxl = wl + (size_t)WIDE_WAVES * NR * NHL * FRAG + (size_t)wave * NR * NXL * FRAG + lane * 8;
+  constexpr int NXH = NX + NXL;   // macro steps of x held, one way or the other
 #pragma unroll
   for (int i = 0; i < NXL; ++i)
 #pragma unroll
     for (int r = 0; r < NR; ++r)
-      *reinterpret_cast<bf16x8*>(wxl + (r * NXL + i) * FRAG) = w.w.load(w.tile(r), i < nx ? wave + 4 * i : 0, i < nx);
+      *reinterpret_cast<bf16x8*>(wxl + (r * NXL + i) * FRAG) = w.w.load(w.tile(r), NX + i < nx ? wave + 4 * (NX + i) : 0, NX + i < nx);
+  bf16x8 wx[NX > 0 ? NX : 1][NR];
+#pragma unroll
+  for (int i = 0; i < NX; ++i)
+#pragma unroll
+    for (int r = 0; r < NR; ++r) wx[i][r] = w.w.load(w.tile(r), i < nx ? wave + 4 * i : 0, i < nx);
   w.load(nh, [&](int i) { return nsx + h_step(i); });
   if (threadIdx.x == 0) s_role = at(group).all_here(p.patience) ? WIDE_GO : WIDE_LEAVE;
   __syncthreads();
@@ -517,10 +523,10 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
     return xw.load(min((j * p.BP + b_lo) / 16 + half * NB + t, xtiles - 1), i < nx ? wave + 4 * i : 0, i < nx);
   };
   f32x4 acc[NR][NB];
-  bf16x8 xf[NXL > 0 ? NXL : 1][NB];
+  bf16x8 xf[NXH > 0 ? NXH : 1][NB];
   auto fetch_x = [&](int j, int half) {
 #pragma unroll
-    for (int i = 0; i < NXL; ++i)
+    for (int i = 0; i < NXH; ++i)
 #pragma unroll
       for (int t = 0; t < NB; ++t) xf[i][t] = x_load(j, half, t, i);
   };
@@ -529,15 +535,20 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
     for (int r = 0; r < NR; ++r)
 #pragma unroll
       for (int t = 0; t < NB; ++t) acc[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto held = [&](int i0, int i1) {
 #pragma unroll
-    for (int i = 0; i < NXL; ++i)
+      for (int i = i0; i < i1 && i < NXH; ++i)
 #pragma unroll
-      for (int r = 0; r < NR; ++r) {
-        const bf16x8 a = *reinterpret_cast<const bf16x8*>(wxl + (r * NXL + i) * FRAG);
+        for (int r = 0; r < NR; ++r) {
+          const bf16x8 a = i < NX ? wx[i < NX ? i : 0][r] : *reinterpret_cast<const bf16x8*>(wxl + (r * NXL + (i < NX ? 0 : i - NX)) * FRAG);
 #pragma unroll
-        for (int t = 0; t < NB; ++t) acc[r][t] = M::mma(a, xf[i][t], acc[r][t]);
-      }
-    if (nx > NXL) {   // wider inputs: UX macro steps in flight
+          for (int t = 0; t < NB; ++t) acc[r][t] = M::mma(a, xf[i][t], acc[r][t]);
+        }
+    };
+    held(0, 2);   // macro steps past nx are zeros; few branches: each costs more than two macro steps' MFMAs
+    if (nx > 2) held(2, 4);
+    if (nx > 4) held(4, NXH);
+    if (nx > NXH) {   // wider inputs: UX macro steps in flight
       constexpr int UX = NB == 4 ? 2 : 3;
       bf16x8 a[UX][NR], f[UX][NB];
       auto fetch = [&](int e, int i) {
@@ -547,8 +558,8 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
         for (int t = 0; t < NB; ++t) f[e][t] = x_load(j, half, t, i);
       };
 #pragma unroll
-      for (int e = 0; e < UX; ++e) fetch(e, NXL + e);
-      for (int i = NXL; i < nx; i += UX) {
+      for (int e = 0; e < UX; ++e) fetch(e, NXH + e);
+      for (int i = NXH; i < nx; i += UX) {
 #pragma unroll
         for (int e = 0; e < UX; ++e) {
 #pragma unroll
@@ -592,14 +603,15 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
   };
 
   WideProduct<NR, NHW, NHL, NHS, NB, U> product;
+  const int two = PH > 1 && b_hi - b_lo > COLS;   // whether there is a second half
   fetch_x(0, 0);
   place(0);
-  product.begin(slot(0), off, nh, h_step);
-  const int two = PH > 1 && b_hi - b_lo > COLS;   // whether there is a second half
+  if (two) product.begin(slot(0), off, nh, h_step);
 #pragma unroll 1
   for (int it = 0; it < p.count << two; ++it) {
     const int j = it >> two, half = it & two;
     x_part(j, half);
+    if (!two) product.begin(slot(j), off, nh, h_step);
     WaitBound bound{p.wait_ticks, p.sync + RES_SYNC_STATUS};
     place(half);
     product.run(w, nsx, slot(j), off, nh, h_step, acc, bound, &s_fail);
@@ -638,7 +650,6 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
       fetch_x(min(j + 1, p.count - 1), 0);
     }
     store_kept(j, half);
-    if (!two) product.begin(slot(min(j + 1, p.count - 1)), off, nh, h_step);
   }
 }
 
@@ -660,7 +671,7 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
   using Tile = WideTile<NR, NB>;
   constexpr int VEC = M::VEC, KSTEP = 4 * VEC, FRAG = 64 * VEC, UW = Tile::UW, QU = Tile::QU, UG = Tile::UG, COLS = Tile::COLS;
   constexpr int UB = 16 * NR;          // units of a block
-  constexpr int U = NB == 4 ? 4 : 6;   // macro steps of dG in flight
+  constexpr int U = NB == 4 || NHS > 0 ? 4 : 6;   // macro steps of dG in flight
   constexpr int KROW = COLS + 8;       // row of the kept values in LDS
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int RED = WIDE_WAVES * NR * NB * Tile::BLOCK, KEPT = 5 * UW * KROW;
@@ -754,8 +765,8 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
   }
 
   WideWeights<NR, NHW, NHL, NHS> w(WideOperand(p.WTh, nsteps), ub * NR, p.HP / 16, wl + (size_t)wave * NR * NHL * FRAG);
-  const int n = (nsh - wave + 3) / 4;   // this wave's macro steps
-  auto g_step = [&](int i) { return kq + 4 * (wave + 4 * i); };
+  const int part = 4 * kq + wave, n = (nsteps - part + WIDE_BACK_PARTS - 1) / WIDE_BACK_PARTS;   // this wave's macro steps: part, part + 16, ...
+  auto g_step = [&](int i) { return part + WIDE_BACK_PARTS * i; };
   w.load(n, g_step);
   if (threadIdx.x == 0) s_role = at(group).all_here(p.patience) ? WIDE_GO : WIDE_LEAVE;
   __syncthreads();
@@ -1019,9 +1030,10 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
 
 // ---- launchers -------------------------------------------------------------------------------------------------
 // What a shape's two kernels keep where, see WideWeights and wide_chain_kernel.
-template <int NR_, int NHW_, int NHL_, int NHS_, int NXL_, int NB_, int PH_>
+template <int NR_, int NHW_, int NHL_, int NHS_, int NX_, int NXL_, int GHL_, int GHS_, int NB_, int PH_>
 struct WideKind {
-  static constexpr int NR = NR_, NHW = NHW_, NHL = NHL_, NHS = NHS_, NXL = NXL_, NB = NB_, PH = PH_;
+  static constexpr int NR = NR_, NHW = NHW_, NHL = NHL_, NHS = NHS_, NX = NX_, NXL = NXL_, NB = NB_, PH = PH_;   // the chain's
+  static constexpr int GHL = GHL_, GHS = GHS_;                                                       // the sweep's NHL, NHS
   using Tile = WideTile<NR, NB>;
   static constexpr size_t RED = (size_t)PH * WIDE_WAVES * NR * NB * Tile::BLOCK * 16;
 };
@@ -1029,7 +1041,7 @@ template <class K, int CELL>
 hipError_t launch_wide_chain_cell(const WideChainParams& p, hipStream_t st) {
   constexpr size_t lds = K::RED + (size_t)WIDE_WAVES * K::NR * (K::NHL + K::NXL) * 1024;
   static_assert(lds <= 160 * 1024 - 64, "LDS of a compute unit");
-  constexpr auto kernel = wide_chain_kernel<K::NR, K::NXL, K::NHW, K::NHL, K::NHS, K::NB, K::PH, CELL>;
+  constexpr auto kernel = wide_chain_kernel<K::NR, K::NX, K::NXL, K::NHW, K::NHL, K::NHS, K::NB, K::PH, CELL>;
   hipError_t e = allow_dynamic_lds<kernel>(lds);
   if (e != hipSuccess) return e;
   kernel<<<dim3(RES_WGS), dim3(WIDE_THREADS), lds, st>>>(p);
@@ -1037,9 +1049,9 @@ hipError_t launch_wide_chain_cell(const WideChainParams& p, hipStream_t st) {
 }
 template <class K, int CELL>
 hipError_t launch_wide_sweep_cell(const WideSweepParams& p, hipStream_t st) {
-  constexpr size_t lds = K::RED + (size_t)WIDE_WAVES * K::NR * K::NHL * 1024 + (size_t)2 * 5 * K::Tile::UW * (K::Tile::COLS + 8) * 2;
+  constexpr size_t lds = K::RED + (size_t)WIDE_WAVES * K::NR * K::GHL * 1024 + (size_t)2 * 5 * K::Tile::UW * (K::Tile::COLS + 8) * 2;
   static_assert(lds >= 4 * 1024 && lds <= 160 * 1024 - 64, "4 KiB for a workgroup that runs alone; LDS of a compute unit");
-  constexpr auto kernel = wide_sweep_kernel<K::NR, K::NHW, K::NHL, K::NHS, K::NB, K::PH, CELL>;
+  constexpr auto kernel = wide_sweep_kernel<K::NR, K::NHW, K::GHL, K::GHS, K::NB, K::PH, CELL>;
   hipError_t e = allow_dynamic_lds<kernel>(lds);
   if (e != hipSuccess) return e;
   kernel<<<dim3(RES_WGS), dim3(WIDE_THREADS), lds, st>>>(p);
