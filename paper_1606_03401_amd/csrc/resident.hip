@@ -78,7 +78,7 @@ static const WideConfig* wide_config(const Dims& d) {
   for (const Table<WideConfig>& table : {wide_table_1(), wide_table_2(), wide_table_3()})
     for (int i = 0; i < table.n; ++i) {
       const WideConfig& c = table.at[i];
-      if (c.nr == w.nr && c.nhw * 4 * 32 >= d.KH && c.nb * c.ph * 16 >= w.share) return &c;
+      if (c.nr == w.nr && c.nhw * 4 * 32 >= d.KH && c.nb * 16 >= w.share) return &c;
     }
   return nullptr;
 }
@@ -86,7 +86,7 @@ static const WideConfig* wide_config(const Dims& d) {
 // a quarter of the block's units of their sequences.
 static int wide_blocks(const Dims& d, const WideConfig& c) { return (d.HP + 16 * c.nr - 1) / (16 * c.nr); }
 static size_t wide_part_bytes(const Dims& d, const WideConfig& c) {
-  return (size_t)wide_shape(d).groups * wide_blocks(d, c) * 16 * (4 * c.nr * 16 * c.nb * c.ph) * sizeof(float);
+  return (size_t)wide_shape(d).groups * wide_blocks(d, c) * 16 * (4 * c.nr * 16 * c.nb) * sizeof(float);
 }
 
 bool runs_wide(const Dims& d) { return wide_config(d) != nullptr; }

@@ -215,11 +215,6 @@ __device__ __forceinline__ void pack_half(const unsigned (&v)[N], unsigned (&d)[
 // w + 4, ...; with one wave per SIMD a lane has 512 registers.  A wave's weights are NHW macro steps: the first in
 // registers, NHL in LDS, the last NHS fetched again in every step.
 //
-// Phases.  Where PH = 2 the sequences of a group are two halves that take turns: while what one half has published
-// travels (1.6 - 1.9 us), the workgroups work on the other, and the next half's first fragments are fetched during the
-// pointwise work.  A step of H = 2048, B = 128 as one phase: 9.9 us, of which the exchange and the first fragments' way were
-// more than three.
-//
 // Items: an item is QU consecutive units of one sequence, so that planes are touched 4 * QU bytes at a time; the
 // units of a workgroup are fastest.  QU grows with the batch so that there are 64 * NR items for any NB.
 template <int NR, int NB>
@@ -251,7 +246,7 @@ struct WideOperand {
 };
 
 // This wave's resident weights: rows of the tiles tile0 .. tile0 + NR - 1, macro steps step(0), step(1), ... n of them.
-template <int NR, int NHW, int NHL, int NHS>
+template <int NR, int NHW, int NHL, int NHS, int NB>
 struct WideWeights {
   static constexpr int FRAG = 512, NHR = NHW - NHL - NHS;
   static constexpr int NMIN = NHW * (NR - 1) / NR;   // macro steps a wave has at least: below, fewer row tiles would do
@@ -259,7 +254,8 @@ struct WideWeights {
   // The first NHA macro steps are held to the accumulation registers, where the matrix instructions read them in place (on its
   // own the compiler keeps them there too, but copies each fragment back before every use); the rest and whatever
   // else a lane holds share the other 256.
-  static constexpr int NHA = NHR * NR * 4 <= 208 ? NHR : 208 / (NR * 4);
+  // (The sums, 4 * NR * NB, are there too.)
+  static constexpr int ACC = NB == 4 ? 192 : 208, NHA = NHR * NR * 4 <= ACC ? NHR : ACC / (NR * 4);
   u32x4 reg[NR][NHR];
   WideOperand w;
   int tile0, ntiles;
@@ -295,7 +291,7 @@ struct WideWeights {
 // first U from begin() on: what is not there yet is fetched again, what came stays.
 template <int NR, int NHW, int NHL, int NHS, int NB, int U>
 struct WideProduct {
-  using W = WideWeights<NR, NHW, NHL, NHS>;
+  using W = WideWeights<NR, NHW, NHL, NHS, NB>;
   static constexpr int G = 2;                                     // macro steps looked at together
   static_assert(U % G == 0 && U > G, "the next ones are in flight");
   static constexpr int US = NHS > 0 ? (NHS < 2 ? NHS : 2) : 1;   // macro steps of streamed weights in flight
@@ -386,23 +382,33 @@ struct WideProduct {
 };
 
 // ---- forward chain -----------------------------------------------------------------------------------------
-// Consecutive forward operations in one launch, see forward_chain_kernel.  A phase (a step of one half of the sequences):
-//   1. the x part of the gate product: x as operands, laid out by a kernel before the launch and fetched a phase ahead; its
-//      weights in registers, NX macro steps a wave of them, or in LDS (NXL); what goes beyond is fetched again in every phase;
+// Consecutive forward operations in one launch, see forward_chain_kernel.  A step:
+//   1. while h of the step before travels, the x part of the gate product: x as operands, laid out by a kernel before the
+//      launch and fetched a step ahead; its weights in registers, NX macro steps a wave of them, or in LDS (NXL); what goes
+//      beyond is fetched again in every step;
 //   2. the h part on the exchanged fragments, macro step by macro step as they come;
-//   3. partial sums through LDS; the next phase's first fragments requested; the pointwise step;
+//   3. partial sums through LDS, the pointwise step;
 //   4. h published, and stored where the schedule keeps it.
-template <int NR, int NX, int NXL, int NHW, int NHL, int NHS, int NB, int PH, int CELL>
+// X_EARLY: the next x is requested in front of the pointwise step instead of behind the published h, where it is waited for as
+// long as that takes to reach the memory (operations of a wave complete in order).  Worth 2 - 3 % where a lane has the registers
+// (64 sequences, H up to 1024: a run of H = 1024, B = 200 1858 -> 1818 us), and -2 % at H = 2048, which spills.
+// H_EARLY: the first fragments of h are requested in the middle of the x part, 1 - 2 % with up to 32 sequences; with 64 they hold
+// registers the x part needs (H = 2048 3 % slower), and where weights are streamed the x part is long enough for the exchange.
+// Two halves of the batch that take turns, so that one travels while the other is worked on, were 1 - 18 % slower than all
+// at once: a step's fixed costs come twice.
+template <int NR, int NX, int NXL, int NHW, int NHL, int NHS, int NB, int CELL>
 __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1))) void wide_chain_kernel(WideChainParams p) {
   using T = __bf16;
   using M = Mma<T>;
   using Tile = WideTile<NR, NB>;
-  constexpr int KSTEP = 32, FRAG = 512, UW = Tile::UW, QU = Tile::QU, UG = Tile::UG, COLS = Tile::COLS;
+  constexpr int KSTEP = 32, FRAG = 512, UW = Tile::UW, QU = Tile::QU, UG = Tile::UG;
   constexpr int U = NB == 4 ? 4 : 6;   // macro steps of h in flight
+  constexpr bool H_EARLY = NHS == 0 && NB <= 2;
+  constexpr bool X_EARLY = NB == 4 && NHW <= 8;
   constexpr int RED = WIDE_WAVES * NR * NB * Tile::BLOCK;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  f32x4* red = reinterpret_cast<f32x4*>(smem);                     // [PH][4 waves][NR][NB] blocks
-  T* wl = reinterpret_cast<T*>(red + PH * RED);                    // [4][NR][NHL] fragments of W_hh, [4][NR][NXL] of W_ih
+  f32x4* red = reinterpret_cast<f32x4*>(smem);                     // [4 waves][NR][NB] blocks
+  T* wl = reinterpret_cast<T*>(red + RED);                    // [4][NR][NHL] fragments of W_hh, [4][NR][NXL] of W_ih
   __shared__ int s_role, s_xcd, s_rank, s_fail;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
   const int lrow = lane & 15;
@@ -434,15 +440,14 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
   // this wave's macro steps of a gate row: wave, wave + 4, ...; nx of x, then nh of h, from mh0 on
   const int nx = (nsx - wave + 3) / 4, mh0 = wave + 4 * nx - nsx, nh = (nsh - mh0 + 3) / 4;
 
-  // items: QU units u0 .. of the sequences col, col + COLS (the second half)
-  const int ug = (int)threadIdx.x % UG, col = (int)threadIdx.x / UG, u0 = member * UW + ug * QU;
-  const bool item = (int)threadIdx.x < Tile::ITEMS && u0 < p.KH;
-  const unsigned io0 = item ? (unsigned)ft_offset<T>(b_lo + col, u0, nsh) : 0u;
+  const int ug = (int)threadIdx.x % UG, col = (int)threadIdx.x / UG, b = b_lo + col, u0 = member * UW + ug * QU;
+  const bool item = (int)threadIdx.x < Tile::ITEMS && b < b_hi && u0 < p.KH;
+  const unsigned at_h = item ? (unsigned)ft_offset<T>(b, u0, nsh) * 2 : RES_NO_LANE;
   const f32x4* cell = red + (((ug * QU) >> 2) * NB + (col >> 4)) * Tile::BLOCK + ((ug * QU) & 3) * 16 + (col & 15);
   float4 bias[QU];
-  float c_state[PH][QU], keep_h[QU], keep_second[QU], keep_gate[4][QU];
-  // publishes keep_h of a half as step number q and resets this thread's part of the slot two steps back
-  auto publish = [&](unsigned q, int half) {
+  float c_state[QU], keep_h[QU], keep_second[QU], keep_gate[4][QU];
+  // publishes keep_h as step number q and resets this thread's part of the slot two steps back
+  auto publish = [&](unsigned q) {
     T* now = reinterpret_cast<T*>(p.ring) + (size_t)(q % WIDE_RING) * hhalf;
     T* old = reinterpret_cast<T*>(p.ring) + (size_t)((q + WIDE_RING - 2) % WIDE_RING) * hhalf;
     unsigned hi[QU];
@@ -461,31 +466,23 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
       v[i] = not_empty(v[i]);
       empty[i] = RES_EMPTY;
     }
-    if (item && b_lo + half * COLS + col < b_hi && (QU > 1 || (ug & 1) == 0)) {
-      const unsigned to = (io0 + (unsigned)(half * NB * nsh * FRAG)) * 2;
-      store_slot<DW>(now, to, v);
-      store_slot<DW>(old, to, empty);
-    }
+    const unsigned to = QU > 1 || (ug & 1) == 0 ? at_h : RES_NO_LANE;
+    store_slot<DW>(now, to, v);
+    store_slot<DW>(old, to, empty);
   };
 #pragma unroll
-  for (int half = PH - 1; half >= 0; --half) {   // the input state: published while the weights are fetched
-    const int b = b_lo + half * COLS + col;
-#pragma unroll
-    for (int i = 0; i < QU; ++i) {
-      bias[i] = float4{0.f, 0.f, 0.f, 0.f};
-      c_state[half][i] = keep_h[i] = keep_second[i] = 0.0f;
-      if (item && u0 + i < p.H) {
-        bias[i] = *reinterpret_cast<const float4*>(p.bp + 4 * (u0 + i));
-        if (b < b_hi) {
-          keep_h[i] = HPlane<T>::load(p.src, b, u0 + i, p.KH / 32, p.H, hhalf);
-          c_state[half][i] = CELL ? keep_h[i] : (p.src + p.hplane)[(size_t)b * p.H + u0 + i];
-        }
-      }
+  for (int i = 0; i < QU; ++i) {
+    bias[i] = float4{0.f, 0.f, 0.f, 0.f};
+    c_state[i] = keep_h[i] = keep_second[i] = 0.0f;
+    if (item && u0 + i < p.H) {
+      bias[i] = *reinterpret_cast<const float4*>(p.bp + 4 * (u0 + i));
+      keep_h[i] = HPlane<T>::load(p.src, b, u0 + i, p.KH / 32, p.H, hhalf);
+      c_state[i] = CELL ? keep_h[i] : (p.src + p.hplane)[(size_t)b * p.H + u0 + i];
     }
-    publish(p.published, half);
   }
+  publish(p.published);   // travels while the weights are fetched
 
-  WideWeights<NR, NHW, NHL, NHS> w(WideOperand(p.Wp, nsteps), member * NR, p.HP / 4, wl + (size_t)wave * NR * NHL * FRAG);
+  WideWeights<NR, NHW, NHL, NHS, NB> w(WideOperand(p.Wp, nsteps), member * NR, p.HP / 4, wl + (size_t)wave * NR * NHL * FRAG);
   auto h_step = [&](int i) { return mh0 + 4 * i; };
   T* wxl = wl + (size_t)WIDE_WAVES * NR * NHL * FRAG + (size_t)wave * NR * NXL * FRAG + lane * 8;
   constexpr int NXH = NX + NXL;   // macro steps of x held, one way or the other
@@ -507,30 +504,27 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
     return;
   }
 
-  // where this lane's operands come from in a half; columns that belong to no sequence of the group fetch no h
+  // where this lane's operands come from; columns that belong to no sequence of the group fetch no h
   unsigned off[NB];
-  auto place = [&](int half) {
 #pragma unroll
-    for (int t = 0; t < NB; ++t) {
-      const int tile = half * NB + t, b = b_lo + tile * 16 + lrow;
-      off[t] = b < b_hi ? (unsigned)((((b_lo >> 4) + tile) * nsh * 64 + lane) * 16) : RES_NO_LANE;
-    }
-  };
+  for (int t = 0; t < NB; ++t)
+    off[t] = b_lo + t * 16 + lrow < b_hi ? (unsigned)((((b_lo >> 4) + t) * nsh * 64 + lane) * 16) : RES_NO_LANE;
   auto slot = [&](int j) { return reinterpret_cast<const T*>(p.ring) + (size_t)((p.published + (unsigned)j) % WIDE_RING) * hhalf; };
   const WideOperand xw(p.xs, nsx);
   const int xtiles = p.count * p.BP / 16;
-  auto x_load = [&](int j, int half, int t, int i) {   // x of macro step i of this wave
-    return xw.load(min((j * p.BP + b_lo) / 16 + half * NB + t, xtiles - 1), i < nx ? wave + 4 * i : 0, i < nx);
+  auto x_load = [&](int j, int t, int i) {   // x of macro step i of this wave
+    return xw.load(min((j * p.BP + b_lo) / 16 + t, xtiles - 1), i < nx ? wave + 4 * i : 0, i < nx);
   };
   f32x4 acc[NR][NB];
   bf16x8 xf[NXH > 0 ? NXH : 1][NB];
-  auto fetch_x = [&](int j, int half) {
+  auto fetch_x = [&](int j) {
 #pragma unroll
     for (int i = 0; i < NXH; ++i)
 #pragma unroll
-      for (int t = 0; t < NB; ++t) xf[i][t] = x_load(j, half, t, i);
+      for (int t = 0; t < NB; ++t) xf[i][t] = x_load(j, t, i);
   };
-  auto x_part = [&](int j, int half) {
+  WideProduct<NR, NHW, NHL, NHS, NB, U> product;
+  auto x_part = [&](int j) {
 #pragma unroll
     for (int r = 0; r < NR; ++r)
 #pragma unroll
@@ -546,6 +540,7 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
         }
     };
     held(0, 2);   // macro steps past nx are zeros; few branches: each costs more than two macro steps' MFMAs
+    if (H_EARLY) product.begin(slot(j), off, nh, h_step);
     if (nx > 2) held(2, 4);
     if (nx > 4) held(4, NXH);
     if (nx > NXH) {   // wider inputs: UX macro steps in flight
@@ -555,7 +550,7 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
 #pragma unroll
         for (int r = 0; r < NR; ++r) a[e][r] = w.w.load(w.tile(r), i < nx ? wave + 4 * i : 0, i < nx);
 #pragma unroll
-        for (int t = 0; t < NB; ++t) f[e][t] = x_load(j, half, t, i);
+        for (int t = 0; t < NB; ++t) f[e][t] = x_load(j, t, i);
       };
 #pragma unroll
       for (int e = 0; e < UX; ++e) fetch(e, NXH + e);
@@ -574,12 +569,10 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
   const bool ragged = p.H % QU != 0;
   const int real = p.H - u0;   // units of an item that exist: QU or more, but for the last of a row
   const size_t plane = (size_t)p.B * p.H;
-  const unsigned at_plane = (unsigned)((b_lo + col) * p.H + u0) * 4, half_plane = (unsigned)(COLS * p.H) * 4;
-  auto store_kept = [&](int j, int half) {   // what the schedule wants of step j
+  const unsigned at_plane = item && real > 0 ? (unsigned)(b * p.H + u0) * 4 : RES_NO_LANE;
+  auto store_kept = [&](int j) {   // what the schedule wants of step j
     const ResStep dst = p.step[j];
     if (!dst.out && !dst.gates) return;
-    const bool there = item && b_lo + half * COLS + col < b_hi;
-    const unsigned to = there && real > 0 ? at_plane + half * half_plane : RES_NO_LANE;
     if (dst.out) {   // padding columns of the split h plane are part of the operand other launches fetch: zero
       unsigned hi[QU], lo[QU], d[(QU + 1) / 2];
 #pragma unroll
@@ -587,69 +580,50 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
         hi[i] = (__float_as_uint(keep_h[i]) + 0x8000u) >> 16;
         lo[i] = __float_as_uint(keep_h[i]) & 0xffffu;
       }
-      const unsigned to_h = there ? (io0 + (unsigned)(half * NB * nsh * FRAG)) * 2 : RES_NO_LANE;
       pack_half<QU>(hi, d);
-      store_half<QU>(dst.out, to_h, d);
+      store_half<QU>(dst.out, at_h, d);
       pack_half<QU>(lo, d);
-      store_half<QU>(reinterpret_cast<unsigned short*>(dst.out) + hhalf, to_h, d);
-      store_run<QU>(dst.out + p.hplane, to, ragged, real, keep_second);
+      store_half<QU>(reinterpret_cast<unsigned short*>(dst.out) + hhalf, at_h, d);
+      store_run<QU>(dst.out + p.hplane, at_plane, ragged, real, keep_second);
     }
     if (dst.gates) {
-      store_run<QU>(dst.gates, to, ragged, real, keep_gate[0]);
-      store_run<QU>(dst.gates + plane, to, ragged, real, keep_gate[1]);
-      store_run<QU>(dst.gates + p.unit, to, ragged, real, keep_gate[2]);
-      if (CELL == 0) store_run<QU>(dst.gates + p.unit + plane, to, ragged, real, keep_gate[3]);
+      store_run<QU>(dst.gates, at_plane, ragged, real, keep_gate[0]);
+      store_run<QU>(dst.gates + plane, at_plane, ragged, real, keep_gate[1]);
+      store_run<QU>(dst.gates + p.unit, at_plane, ragged, real, keep_gate[2]);
+      if (CELL == 0) store_run<QU>(dst.gates + p.unit + plane, at_plane, ragged, real, keep_gate[3]);
     }
   };
 
-  WideProduct<NR, NHW, NHL, NHS, NB, U> product;
-  const int two = PH > 1 && b_hi - b_lo > COLS;   // whether there is a second half
-  fetch_x(0, 0);
-  place(0);
-  if (two) product.begin(slot(0), off, nh, h_step);
+  fetch_x(0);
 #pragma unroll 1
-  for (int it = 0; it < p.count << two; ++it) {
-    const int j = it >> two, half = it & two;
-    x_part(j, half);
-    if (!two) product.begin(slot(j), off, nh, h_step);
+  for (int j = 0; j < p.count; ++j) {
+    x_part(j);
+    if (!H_EARLY) product.begin(slot(j), off, nh, h_step);
     WaitBound bound{p.wait_ticks, p.sync + RES_SYNC_STATUS};
-    place(half);
     product.run(w, nsx, slot(j), off, nh, h_step, acc, bound, &s_fail);
-    wide_write_sums<NR, NB>(red + half * RED, wave, lane, acc);
+    if (X_EARLY) fetch_x(min(j + 1, p.count - 1));
+    wide_write_sums<NR, NB>(red, wave, lane, acc);
     lds_barrier();
     if (__builtin_amdgcn_readfirstlane(s_fail)) wide_fail<WideChainParams>();
-    if (two) {
-      const int next = min(it + 1, 2 * p.count - 1);   // (the last phase fetches its own once more)
-      fetch_x(next >> 1, next & 1);
-      place(next & 1);
-      product.begin(slot(next >> 1), off, nh, h_step);
-    }
 #pragma unroll
     for (int i = 0; i < QU; ++i) {
       float G[4] = {0.f, 0.f, 0.f, 0.f}, gate[4];
 #pragma unroll
       for (int v = 0; v < WIDE_WAVES; ++v) {   // fixed order, as in forward_body
-        const f32x4 q = item ? cell[half * RED + v * NR * NB * Tile::BLOCK + i * 16] : f32x4{0.f, 0.f, 0.f, 0.f};
+        const f32x4 q = item ? cell[v * NR * NB * Tile::BLOCK + i * 16] : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int r = 0; r < 4; ++r) G[r] += q[r];
       }
-      const float h = cell_forward<CELL>(G, bias[i], c_state[0][i], keep_second[i], gate);
+      const float h = cell_forward<CELL>(G, bias[i], c_state[i], keep_second[i], gate);
       keep_h[i] = u0 + i < p.H ? h : 0.0f;
-      c_state[0][i] = CELL ? keep_h[i] : keep_second[i];
+      c_state[i] = CELL ? keep_h[i] : keep_second[i];
 #pragma unroll
       for (int r = 0; r < 4; ++r) keep_gate[r][i] = gate[r];
-      if (two) {   // the other half's turn
-        const float c = c_state[0][i];
-        c_state[0][i] = c_state[PH - 1][i];
-        c_state[PH - 1][i] = c;
-      }
     }
-    if (j + 1 < p.count) publish(p.published + (unsigned)j + 1, half);
-    if (!two) {
-      lds_barrier();   // the partial sums have been read: the next step may overwrite them
-      fetch_x(min(j + 1, p.count - 1), 0);
-    }
-    store_kept(j, half);
+    if (j + 1 < p.count) publish(p.published + (unsigned)j + 1);
+    lds_barrier();   // the partial sums have been read: the next step may overwrite them
+    if (!X_EARLY) fetch_x(min(j + 1, p.count - 1));
+    store_kept(j);
   }
 }
 
@@ -658,13 +632,12 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
 // every fourth macro step of their K = 4 H columns: with whole rows it would have to fetch all of dG, 1 MiB a step for 64
 // sequences of H = 2048 where a quarter takes 2.1 us.  The four workgroups of a block of units sit on one XCD; each adds up dh
 // for a quarter of the block's units, to which the others send their sums through that XCD's L2 (the polled
-// exchange once more, fp32).  A phase:
+// exchange once more, fp32).  A step:
 //   1. this workgroup's part of dh = dG W_hh on the exchanged fragments as they come;
-//   2. partial sums through LDS, the others' quarters sent; what only later launches read of the phase before
-//      stored (its transposed copies turned over in LDS); the own quarter completed;
-//   3. the next phase's first fragments requested; the pointwise step;
-//   4. dG published, the stored state of the next phase fetched.
-template <int NR, int NHW, int NHL, int NHS, int NB, int PH, int CELL>
+//   2. partial sums through LDS, the others' quarters sent, the own one completed; the pointwise step;
+//   3. dG published; while it travels, the stored state of the next step is fetched, and what only later launches read
+//      is stored (transposed copies turned over in LDS).
+template <int NR, int NHW, int NHL, int NHS, int NB, int CELL>
 __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1))) void wide_sweep_kernel(WideSweepParams p) {
   using T = __bf16;
   using M = Mma<T>;
@@ -674,10 +647,10 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
   constexpr int U = NB == 4 || NHS > 0 ? 4 : 6;   // macro steps of dG in flight
   constexpr int KROW = COLS + 8;       // row of the kept values in LDS
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  constexpr int RED = WIDE_WAVES * NR * NB * Tile::BLOCK, KEPT = 5 * UW * KROW;
-  f32x4* red = reinterpret_cast<f32x4*>(smem);               // [PH][4 waves][NR][NB] blocks
-  T* wl = reinterpret_cast<T*>(red + PH * RED);              // [4][NR][NHL] fragments
-  T* kept = wl + (size_t)WIDE_WAVES * NR * NHL * FRAG;       // [2][5 UW][KROW]: rows 4 u + gate, then h_{s-1}; of this phase and the one before
+  constexpr int RED = WIDE_WAVES * NR * NB * Tile::BLOCK;
+  f32x4* red = reinterpret_cast<f32x4*>(smem);               // [4 waves][NR][NB] blocks
+  T* wl = reinterpret_cast<T*>(red + RED);              // [4][NR][NHL] fragments
+  T* kept = wl + (size_t)WIDE_WAVES * NR * NHL * FRAG;       // [5 UW][KROW]: rows 4 u + gate, then h_{s-1}
   __shared__ int s_role, s_xcd, s_rank, s_fail;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
   const int lrow = lane & 15;
@@ -701,70 +674,62 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
   const int group = xcd / per, ub = (rank >> 2) * per + xcd % per, kq = rank & 3;
   const int b_lo = group * p.nb, b_hi = min(p.B, b_lo + p.nb);
   constexpr int SEND = Tile::ITEMS * QU;   // values one workgroup sends another
-  const size_t part_slot = (size_t)p.groups * blocks * 16 * PH * SEND;
-  float* parts = reinterpret_cast<float*>(p.parts) + ((size_t)group * blocks + ub) * 16 * PH * SEND;   // of this block, slot 0: [half][receiver][sender][item]
+  const size_t part_slot = (size_t)p.groups * blocks * 16 * SEND;
+  float* parts = reinterpret_cast<float*>(p.parts) + ((size_t)group * blocks + ub) * 16 * SEND;   // of this block, slot 0: [receiver][sender][item]
   if (role == WIDE_ALONE) {
     sweep_slowly<WideSweepParams, T, false, 8, WIDE_BACK_PARTS, CELL>(b_lo, b_hi, 0, p.HP, reinterpret_cast<float*>(smem), &s_fail);
     // nothing was sent: what the launch before left in its last slots is cleared for the next one
     for (int s = 0; s < WIDE_PART_RING; ++s)
-      for (size_t i = threadIdx.x; i < (size_t)blocks * 16 * PH * SEND; i += WIDE_THREADS)
-        reinterpret_cast<unsigned*>(p.parts)[s * part_slot + (size_t)group * blocks * 16 * PH * SEND + i] = RES_EMPTY;
+      for (size_t i = threadIdx.x; i < (size_t)blocks * 16 * SEND; i += WIDE_THREADS)
+        reinterpret_cast<unsigned*>(p.parts)[s * part_slot + (size_t)group * blocks * 16 * SEND + i] = RES_EMPTY;
     return;
   }
   const int nsh = p.KH / KSTEP, nsteps = p.G4 / KSTEP;   // nsteps = 4 nsh
   const size_t hhalf = (size_t)p.BP * p.KH, dG_step = (size_t)p.BP * p.G4, plane = (size_t)p.B * p.H;
 
-  // items: QU units u0 .. (of the quarter kq of the block's units) of the sequences col, col + COLS (the second half)
+  // items: QU units u0 .. (of the quarter kq of the block's units) of one sequence
   const int ug = (int)threadIdx.x % UG, col = (int)threadIdx.x / UG, u0 = ub * UB + kq * UW + ug * QU;
+  const int b = b_lo + col;
   const bool in = (int)threadIdx.x < Tile::ITEMS, ragged = p.H % QU != 0;
-  auto seq = [&](int half) { return b_lo + half * COLS + col; };
-  auto has = [&](int half) { return in && seq(half) < b_hi && u0 < p.HP; };         // has something to publish
-  auto real = [&](int half) { return in && seq(half) < b_hi && u0 < p.H; };         // at least one real unit
+  const bool has = in && b < b_hi && u0 < p.HP, real = has && u0 < p.H;      // something to publish; at least one real unit
   const int units = p.H - u0, back = max(0, QU - units);   // units of an item that exist; how far the window on them is moved back
-  // places of an item in a plane, a split h plane, a dG block
-  const unsigned at_plane = (unsigned)((b_lo + col) * p.H + u0) * 4, half_plane = (unsigned)(COLS * p.H) * 4;
-  const unsigned at_h = in && u0 < p.HP ? (unsigned)ft_offset<T>(b_lo + col, u0, nsh) * 2 : 0u, half_h = (unsigned)(NB * nsh * FRAG) * 2;
-  const unsigned at_g = in && u0 < p.HP ? (unsigned)ft_offset<T>(b_lo + col, 4 * u0, nsteps) * 2 : 0u, half_g = (unsigned)(NB * nsteps * FRAG) * 2;
-  auto of_plane = [&](int half) { return real(half) ? at_plane + half * half_plane : RES_NO_LANE; };
-  auto of_h = [&](int half) { return has(half) ? at_h + half * half_h : RES_NO_LANE; };
-  auto of_g = [&](int half) { return has(half) ? at_g + half * half_g : RES_NO_LANE; };
+  // places of an item in a plane (and of the window on it), a split h plane, a dG block
+  const unsigned at_plane = real ? (unsigned)(b * p.H + u0) * 4 : RES_NO_LANE, at_window = real ? at_plane - 4 * back : RES_NO_LANE;
+  const unsigned at_h = has ? (unsigned)ft_offset<T>(b, u0, nsh) * 2 : RES_NO_LANE, at_g = has ? (unsigned)ft_offset<T>(b, 4 * u0, nsteps) * 2 : RES_NO_LANE;
+  const unsigned at_dg = real ? at_g : RES_NO_LANE;
   constexpr int NV = QU == 4 ? 2 : 1, DW = QU == 1 ? 2 : 4;   // stores of an item's dG, dwords each; 16-byte slots lie 256 bytes apart
   unsigned dg[NV][DW];
-  float dc_run[PH][QU], kp_h[QU];
+  float dc_run[QU], kp_h[QU];
   unsigned short kp_hprev[QU];   // as operands
-  auto publish = [&](unsigned q, int half) {
+  auto publish = [&](unsigned q) {
     T* now = reinterpret_cast<T*>(p.ring) + (size_t)(q % WIDE_RING) * dG_step;
     T* old = reinterpret_cast<T*>(p.ring) + (size_t)((q + WIDE_RING - 2) % WIDE_RING) * dG_step;   // two steps back
     unsigned empty[DW];
 #pragma unroll
     for (int i = 0; i < DW; ++i) empty[i] = RES_EMPTY;
-    const unsigned to = of_g(half);
 #pragma unroll
-    for (int k = 0; k < NV; ++k) store_slot<DW>(now, to + k * 256, dg[k]);
+    for (int k = 0; k < NV; ++k) store_slot<DW>(now, at_g + k * 256, dg[k]);
 #pragma unroll
-    for (int k = 0; k < NV; ++k) store_slot<DW>(old, to + k * 256, empty);
+    for (int k = 0; k < NV; ++k) store_slot<DW>(old, at_g + k * 256, empty);
   };
 #pragma unroll
-  for (int half = PH - 1; half >= 0; --half) {   // dG of the step above: published while the weights are fetched
-#pragma unroll
-    for (int i = 0; i < QU; ++i) {
-      dc_run[half][i] = real(half) && i < units ? p.dc[(size_t)seq(half) * p.H + u0 + i] : 0.0f;
-      kp_h[i] = 0.0f;
-    }
-#pragma unroll
-    for (int k = 0; k < NV; ++k) {
-#pragma unroll
-      for (int i = 0; i < DW; ++i) dg[k][i] = 0u;
-      if (p.dG_next) {
-        load_dwords<DW>(p.dG_next, real(half) ? of_g(half) + k * 256 : RES_NO_LANE, dg[k]);
-#pragma unroll
-        for (int i = 0; i < DW; ++i) dg[k][i] = not_empty(dg[k][i]);
-      }
-    }
-    publish(p.published, half);
+  for (int i = 0; i < QU; ++i) {
+    dc_run[i] = real && i < units ? p.dc[(size_t)b * p.H + u0 + i] : 0.0f;
+    kp_h[i] = 0.0f;
   }
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+#pragma unroll
+    for (int i = 0; i < DW; ++i) dg[k][i] = 0u;
+    if (p.dG_next) {
+      load_dwords<DW>(p.dG_next, at_dg + k * 256, dg[k]);
+#pragma unroll
+      for (int i = 0; i < DW; ++i) dg[k][i] = not_empty(dg[k][i]);
+    }
+  }
+  publish(p.published);   // travels while the weights are fetched
 
-  WideWeights<NR, NHW, NHL, NHS> w(WideOperand(p.WTh, nsteps), ub * NR, p.HP / 16, wl + (size_t)wave * NR * NHL * FRAG);
+  WideWeights<NR, NHW, NHL, NHS, NB> w(WideOperand(p.WTh, nsteps), ub * NR, p.HP / 16, wl + (size_t)wave * NR * NHL * FRAG);
   const int part = 4 * kq + wave, n = (nsteps - part + WIDE_BACK_PARTS - 1) / WIDE_BACK_PARTS;   // this wave's macro steps: part, part + 16, ...
   auto g_step = [&](int i) { return part + WIDE_BACK_PARTS * i; };
   w.load(n, g_step);
@@ -775,13 +740,9 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
     return;
   }
   unsigned off[NB];
-  auto place = [&](int half) {
 #pragma unroll
-    for (int t = 0; t < NB; ++t) {
-      const int tile = half * NB + t, b = b_lo + tile * 16 + lrow;
-      off[t] = b < b_hi ? (unsigned)((((b_lo >> 4) + tile) * nsteps * 64 + lane) * 16) : RES_NO_LANE;
-    }
-  };
+  for (int t = 0; t < NB; ++t)
+    off[t] = b_lo + t * 16 + lrow < b_hi ? (unsigned)((((b_lo >> 4) + t) * nsteps * 64 + lane) * 16) : RES_NO_LANE;
   auto slot = [&](int j) { return reinterpret_cast<const T*>(p.ring) + (size_t)((p.published + (unsigned)j) % WIDE_RING) * dG_step; };
 
   // the stored internal state of the step about to run, its input state, its loss gradient, as fetched
@@ -793,25 +754,24 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
   auto whole = [&](const unsigned (&hi)[HD], const unsigned (&lo)[HD], int i) {   // h in full precision
     return __uint_as_float(((half_of(hi, i) - (half_of(lo, i) >> 15)) << 16) | half_of(lo, i));
   };
-  auto fetch = [&](int j, int half) {
+  auto fetch = [&](int j) {
     const int s = p.s_hi - j;
     const float *src = p.src[j], *stp = p.state[j];
-    const unsigned at = real(half) ? at_plane + half * half_plane - 4 * back : RES_NO_LANE, io = of_h(half);
-    load_dwords<QU>(stp + p.unit, at, gate[0].v);
-    load_dwords<QU>(stp + p.unit + plane, at, gate[1].v);
-    load_dwords<QU>(stp + 2 * p.unit, at, gate[2].v);
-    if (CELL == 0) load_dwords<QU>(stp + 2 * p.unit + plane, at, gate[3].v);   // the GRU has three gates
-    load_dwords<QU>(stp + p.hplane, at, c_s.v);                               // c_s, or the GRU's n_h
-    if (CELL == 0) load_dwords<QU>(src + p.hplane, at, c_prev.v);
+    load_dwords<QU>(stp + p.unit, at_window, gate[0].v);
+    load_dwords<QU>(stp + p.unit + plane, at_window, gate[1].v);
+    load_dwords<QU>(stp + 2 * p.unit, at_window, gate[2].v);
+    if (CELL == 0) load_dwords<QU>(stp + 2 * p.unit + plane, at_window, gate[3].v);   // the GRU has three gates
+    load_dwords<QU>(stp + p.hplane, at_window, c_s.v);                               // c_s, or the GRU's n_h
+    if (CELL == 0) load_dwords<QU>(src + p.hplane, at_window, c_prev.v);
     if (want_h) {
-      load_half<QU>(stp, io, hs_hi);
-      load_half<QU>(reinterpret_cast<const unsigned short*>(stp) + hhalf, io, hs_lo);
+      load_half<QU>(stp, at_h, hs_hi);
+      load_half<QU>(reinterpret_cast<const unsigned short*>(stp) + hhalf, at_h, hs_lo);
     }
-    load_half<QU>(src, io, hp_hi);
-    if (CELL != 0) load_half<QU>(reinterpret_cast<const unsigned short*>(src) + hhalf, io, hp_lo);   // the GRU blends with h_{s-1}
+    load_half<QU>(src, at_h, hp_hi);
+    if (CELL != 0) load_half<QU>(reinterpret_cast<const unsigned short*>(src) + hhalf, at_h, hp_lo);   // the GRU blends with h_{s-1}
     // no loss gradient at this step: nothing is fetched, zeros
     const bool injected = p.dy != nullptr && s >= p.dy_first;
-    load_dwords<QU>(injected ? p.dy + (size_t)(s - p.dy_first) * plane : stp, injected ? at : RES_NO_LANE, dy.v);
+    load_dwords<QU>(injected ? p.dy + (size_t)(s - p.dy_first) * plane : stp, injected ? at_window : RES_NO_LANE, dy.v);
   };
   auto settle = [&]() {   // rows that end inside an item
     if (!ragged) return;
@@ -822,16 +782,16 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
     shift_run(dy, back);
   };
   const bool slots_whole = p.B % VEC == 0;   // a 16-byte slot of the transposed operands holds sequences of one step only
-  auto keep_transposed = [&](int half, T* to) {
-    if (!slots_whole || !in || seq(half) >= b_hi) return;
+  auto keep_transposed = [&]() {
+    if (!slots_whole || !in || b >= b_hi) return;
 #pragma unroll
     for (int i = 0; i < QU; ++i) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const unsigned v = dg[i / 2][(i % 2) * 2 + r / 2];
-        reinterpret_cast<unsigned short*>(to)[((ug * QU + i) * 4 + r) * KROW + col] = (unsigned short)(r % 2 ? v >> 16 : v & 0xffffu);
+        reinterpret_cast<unsigned short*>(kept)[((ug * QU + i) * 4 + r) * KROW + col] = (unsigned short)(r % 2 ? v >> 16 : v & 0xffffu);
       }
-      reinterpret_cast<unsigned short*>(to)[(4 * UW + ug * QU + i) * KROW + col] = kp_hprev[i];
+      reinterpret_cast<unsigned short*>(kept)[(4 * UW + ug * QU + i) * KROW + col] = kp_hprev[i];
     }
   };
   const unsigned tid = threadIdx.x;
@@ -839,24 +799,23 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
   constexpr unsigned CG = 4 * UW, CH_G = CG * (COLS / VEC), CH_H = UW * (COLS / VEC);   // rows of dG; chunks of VEC sequences of one row
   auto chunk_row = [&](int rowid) { return (unsigned)(((rowid >> 4) * ncs * 64 + (rowid & 15)) * VEC) * 2; };   // bytes, column 0
   const int uq = ub * UB + kq * UW;
-  auto store_kept = [&](int s, int half, const T* from) {
+  auto store_kept = [&](int s) {
     const int cslot = (s - 1) % p.CH, buf = ((s - 1) / p.CH) & 1;   // where step s lives in the chunk buffers
     T* dG_cur = reinterpret_cast<T*>(p.dG_chunk[buf]) + (size_t)cslot * dG_step;
     T* dGT = reinterpret_cast<T*>(p.dGT[buf]);
     T* aT = reinterpret_cast<T*>(p.aT[buf]);
 #pragma unroll
-    for (int k = 0; k < NV; ++k) store_dwords<DW>(dG_cur, real(half) ? of_g(half) + k * 256 : RES_NO_LANE, dg[k]);
-    if (p.y_out) store_run<QU>(p.y_out + (size_t)(s - 1) * plane, of_plane(half), ragged, units, kp_h);
-    const int b0 = b_lo + half * COLS;
+    for (int k = 0; k < NV; ++k) store_dwords<DW>(dG_cur, at_dg + k * 256, dg[k]);
+    if (p.y_out) store_run<QU>(p.y_out + (size_t)(s - 1) * plane, at_plane, ragged, units, kp_h);
     if (slots_whole) {
       // chunks of VEC sequences of one row; rows fastest: 16 of them lie side by side
-      const unsigned c8 = (unsigned)(cslot * p.B + b0) / VEC;
-      auto move = [&](T* base, unsigned c, unsigned rows, int row0, int first) {   // row0: in `from`; first: in the operand
+      const unsigned c8 = (unsigned)(cslot * p.B + b_lo) / VEC;
+      auto move = [&](T* base, unsigned c, unsigned rows, int row0, int first) {   // row0: in `kept`; first: in the operand
         const unsigned r = c % rows, cb = c / rows, at = c8 + cb;
         const unsigned to = chunk_row(first + (int)r) + ((at >> 2) * 64 + (at & 3) * 16) * VEC * 2;
-        const bool there = b0 + (int)cb * VEC < b_hi && (rows == CG ? (int)(r >> 2) : (int)r) < p.H - uq;
+        const bool there = b_lo + (int)cb * VEC < b_hi && (rows == CG ? (int)(r >> 2) : (int)r) < p.H - uq;
         union { u32x4 q; unsigned v[4]; } cv;
-        cv.q = *reinterpret_cast<const u32x4*>(from + (row0 + r) * KROW + cb * VEC);
+        cv.q = *reinterpret_cast<const u32x4*>(kept + (row0 + r) * KROW + cb * VEC);
         store_dwords<4>(base, there ? to : RES_NO_LANE, cv.v);
       };
 #pragma unroll
@@ -865,8 +824,8 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
 #pragma unroll
       for (unsigned c0 = 0; c0 < CH_H; c0 += WIDE_THREADS)
         if (c0 + WIDE_THREADS <= CH_H || c0 + tid < CH_H) move(aT, c0 + tid, UW, CG, p.NX + uq);
-    } else if (real(half)) {
-      const int cc = cslot * p.B + seq(half);
+    } else if (real) {
+      const int cc = cslot * p.B + b;
 #pragma unroll
       for (int i = 0; i < QU; ++i)
         if (i < units) {
@@ -881,10 +840,10 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
     }
   };
   // this thread's value i of quarter q of the block: row q * UW + ug * QU + i
-  auto sum_at = [&](const f32x4* sums, int q, float (&v)[QU]) {
+  auto sum_at = [&](int q, float (&v)[QU]) {
     const int n0 = q * UW + ug * QU;
     const int c = in ? col : 0;
-    const f32x4* at = sums + ((n0 >> 4) * NB + (c >> 4)) * Tile::BLOCK + ((n0 & 15) >> 2) * 16 + (c & 15);
+    const f32x4* at = red + ((n0 >> 4) * NB + (c >> 4)) * Tile::BLOCK + ((n0 & 15) >> 2) * 16 + (c & 15);
 #pragma unroll
     for (int i = 0; i < QU; ++i) v[i] = 0.0f;
 #pragma unroll
@@ -905,28 +864,23 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
   };
 
   WideProduct<NR, NHW, NHL, NHS, NB, U> product;
-  const int two = PH > 1 && b_hi - b_lo > COLS;   // whether there is a second half
-  fetch(0, 0);
-  place(0);
-  product.begin(slot(0), off, n, g_step);
+  fetch(0);
 #pragma unroll 1
-  for (int it = 0; it < p.count << two; ++it) {
-    const int j = it >> two, half = it & two;
+  for (int j = 0; j < p.count; ++j) {
+    product.begin(slot(j), off, n, g_step);
     WaitBound bound{p.wait_ticks, p.sync + RES_SYNC_STATUS};
     f32x4 acc[NR][NB];
 #pragma unroll
     for (int r = 0; r < NR; ++r)
 #pragma unroll
       for (int t = 0; t < NB; ++t) acc[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    place(half);
     product.run(w, 0, slot(j), off, n, g_step, acc, bound, &s_fail);
-    f32x4* sums = red + half * RED;
-    wide_write_sums<NR, NB>(sums, wave, lane, acc);
+    wide_write_sums<NR, NB>(red, wave, lane, acc);
     lds_barrier();
     if (__builtin_amdgcn_readfirstlane(s_fail)) wide_fail<WideSweepParams>();
     // the other quarters' sums, for the workgroups that complete them
-    float* now = parts + ((p.published + (unsigned)j) % WIDE_PART_RING) * part_slot + (size_t)half * 16 * SEND;
-    float* old = parts + ((p.published + (unsigned)j + WIDE_PART_RING - 2) % WIDE_PART_RING) * part_slot + (size_t)half * 16 * SEND;
+    float* now = parts + ((p.published + (unsigned)j) % WIDE_PART_RING) * part_slot;
+    float* old = parts + ((p.published + (unsigned)j + WIDE_PART_RING - 2) % WIDE_PART_RING) * part_slot;
     if (in) {
       typedef float vec __attribute__((ext_vector_type(QU)));
       vec empty;
@@ -936,7 +890,7 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
       for (int k = 1; k < 4; ++k) {
         const int q = (kq + k) & 3;
         float v[QU];
-        sum_at(sums, q, v);
+        sum_at(q, v);
         vec o;
 #pragma unroll
         for (int i = 0; i < QU; ++i) o[i] = __uint_as_float(not_empty(__float_as_uint(v[i])));
@@ -945,7 +899,7 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
       }
     }
     float own[QU], dh[QU];
-    sum_at(sums, kq, own);
+    sum_at(kq, own);
     unsigned got[3][QU];
     auto look = [&]() {
 #pragma unroll
@@ -960,7 +914,6 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
       return __builtin_amdgcn_ballot_w64(top == RES_EMPTY) != 0;
     };
     look();
-    if (it > 0) store_kept(p.s_hi - ((it - 1) >> two), (it - 1) & two, kept + ((it - 1) & 1) * KEPT);
     while (missing()) {
       if (bound.expired()) {
         s_fail = 1;
@@ -980,11 +933,6 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
         dh[i] += v;
       }
     }
-    if (two) {
-      const int next = min(it + 1, 2 * p.count - 1);   // (the last phase fetches its own once more)
-      place(next & 1);
-      product.begin(slot(next >> 1), off, n, g_step);
-    }
     settle();
 #pragma unroll
     for (int i = 0; i < QU; ++i) {
@@ -992,14 +940,10 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
       const float before = CELL ? whole(hp_hi, hp_lo, i) : c_prev[i];
       float d = dh[i] + (p.dy_is_h ? h_s : dy[i]), dG[4], dc_out;
       if (CELL == 0)
-        lstm_backward_point(d, dc_run[0][i], gate[0][i], gate[1][i], gate[2][i], gate[3][i], c_s[i], before, dG, dc_out);
+        lstm_backward_point(d, dc_run[i], gate[0][i], gate[1][i], gate[2][i], gate[3][i], c_s[i], before, dG, dc_out);
       else   // the running plane carries dh_{s+1} * z_{s+1}, as in backward_body
-        gru_backward_point(__fadd_rn(d, dc_run[0][i]), gate[0][i], gate[1][i], gate[2][i], c_s[i], before, dG, dc_out);
-      dc_run[0][i] = dc_out;
-      if (two) {   // the other half's turn
-        dc_run[0][i] = dc_run[PH - 1][i];
-        dc_run[PH - 1][i] = dc_out;
-      }
+        gru_backward_point(__fadd_rn(d, dc_run[i]), gate[0][i], gate[1][i], gate[2][i], c_s[i], before, dG, dc_out);
+      dc_run[i] = dc_out;
       union { T t[4]; unsigned u[2]; } pk;
 #pragma unroll
       for (int r = 0; r < 4; ++r) pk.t[r] = (T)dG[r];
@@ -1008,40 +952,32 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
       kp_h[i] = h_s;
       kp_hprev[i] = (unsigned short)half_of(hp_hi, i);
     }
-    if (j + 1 < p.count) publish(p.published + (unsigned)j + 1, half);
-    keep_transposed(half, kept + (it & 1) * KEPT);
-    const int next = min(it + 1, (p.count << two) - 1);
-    fetch(next >> two, next & two);
-    if (!two) {
-      lds_barrier();   // the partial sums have been read: the next step may overwrite them
-      product.begin(slot(min(j + 1, p.count - 1)), off, n, g_step);
-    }
+    if (j + 1 < p.count) publish(p.published + (unsigned)j + 1);
+    fetch(min(j + 1, p.count - 1));
+    keep_transposed();
+    lds_barrier();   // the partial sums have been read, the kept values are there
+    if (__builtin_amdgcn_readfirstlane(s_fail)) wide_fail<WideSweepParams>();
+    store_kept(p.s_hi - j);
   }
-  lds_barrier();
-  if (__builtin_amdgcn_readfirstlane(s_fail)) wide_fail<WideSweepParams>();
-  store_kept(p.s_hi - p.count + 1, two, kept + (((p.count << two) - 1) & 1) * KEPT);
-  // dc_run[0] is the half whose turn it would be: the first
 #pragma unroll
-  for (int half = 0; half < PH; ++half)
-#pragma unroll
-    for (int i = 0; i < QU; ++i)
-      if (real(half) && i < units) p.dc[(size_t)seq(half) * p.H + u0 + i] = dc_run[half][i];
+  for (int i = 0; i < QU; ++i)
+    if (real && i < units) p.dc[(size_t)b * p.H + u0 + i] = dc_run[i];
 }
 
 // ---- launchers -------------------------------------------------------------------------------------------------
 // What a shape's two kernels keep where, see WideWeights and wide_chain_kernel.
-template <int NR_, int NHW_, int NHL_, int NHS_, int NX_, int NXL_, int GHL_, int GHS_, int NB_, int PH_>
+template <int NR_, int NHW_, int NHL_, int NHS_, int NX_, int NXL_, int GHL_, int GHS_, int NB_>
 struct WideKind {
-  static constexpr int NR = NR_, NHW = NHW_, NHL = NHL_, NHS = NHS_, NX = NX_, NXL = NXL_, NB = NB_, PH = PH_;   // the chain's
+  static constexpr int NR = NR_, NHW = NHW_, NHL = NHL_, NHS = NHS_, NX = NX_, NXL = NXL_, NB = NB_; // the chain's
   static constexpr int GHL = GHL_, GHS = GHS_;                                                       // the sweep's NHL, NHS
   using Tile = WideTile<NR, NB>;
-  static constexpr size_t RED = (size_t)PH * WIDE_WAVES * NR * NB * Tile::BLOCK * 16;
+  static constexpr size_t RED = (size_t)WIDE_WAVES * NR * NB * Tile::BLOCK * 16;
 };
 template <class K, int CELL>
 hipError_t launch_wide_chain_cell(const WideChainParams& p, hipStream_t st) {
   constexpr size_t lds = K::RED + (size_t)WIDE_WAVES * K::NR * (K::NHL + K::NXL) * 1024;
   static_assert(lds <= 160 * 1024 - 64, "LDS of a compute unit");
-  constexpr auto kernel = wide_chain_kernel<K::NR, K::NX, K::NXL, K::NHW, K::NHL, K::NHS, K::NB, K::PH, CELL>;
+  constexpr auto kernel = wide_chain_kernel<K::NR, K::NX, K::NXL, K::NHW, K::NHL, K::NHS, K::NB, CELL>;
   hipError_t e = allow_dynamic_lds<kernel>(lds);
   if (e != hipSuccess) return e;
   kernel<<<dim3(RES_WGS), dim3(WIDE_THREADS), lds, st>>>(p);
@@ -1049,22 +985,22 @@ hipError_t launch_wide_chain_cell(const WideChainParams& p, hipStream_t st) {
 }
 template <class K, int CELL>
 hipError_t launch_wide_sweep_cell(const WideSweepParams& p, hipStream_t st) {
-  constexpr size_t lds = K::RED + (size_t)WIDE_WAVES * K::NR * K::GHL * 1024 + (size_t)2 * 5 * K::Tile::UW * (K::Tile::COLS + 8) * 2;
+  constexpr size_t lds = K::RED + (size_t)WIDE_WAVES * K::NR * K::GHL * 1024 + (size_t)5 * K::Tile::UW * (K::Tile::COLS + 8) * 2;
   static_assert(lds >= 4 * 1024 && lds <= 160 * 1024 - 64, "4 KiB for a workgroup that runs alone; LDS of a compute unit");
-  constexpr auto kernel = wide_sweep_kernel<K::NR, K::NHW, K::GHL, K::GHS, K::NB, K::PH, CELL>;
+  constexpr auto kernel = wide_sweep_kernel<K::NR, K::NHW, K::GHL, K::GHS, K::NB, CELL>;
   hipError_t e = allow_dynamic_lds<kernel>(lds);
   if (e != hipSuccess) return e;
   kernel<<<dim3(RES_WGS), dim3(WIDE_THREADS), lds, st>>>(p);
   return hipGetLastError();
 }
 struct WideConfig {
-  int nr, nhw, nb, ph;
+  int nr, nhw, nb;
   hipError_t (*chain[2])(const WideChainParams&, hipStream_t);   // by cell
   hipError_t (*sweep[2])(const WideSweepParams&, hipStream_t);
 };
 template <class K>
 WideConfig wide_config_of() {
-  return WideConfig{K::NR, K::NHW, K::NB, K::PH, {launch_wide_chain_cell<K, 0>, launch_wide_chain_cell<K, 1>},
+  return WideConfig{K::NR, K::NHW, K::NB, {launch_wide_chain_cell<K, 0>, launch_wide_chain_cell<K, 1>},
                     {launch_wide_sweep_cell<K, 0>, launch_wide_sweep_cell<K, 1>}};
 }
 Table<WideConfig> wide_table_1(), wide_table_2(), wide_table_3();

@@ -5,11 +5,11 @@ namespace mebptt {
 
 Table<WideConfig> wide_table_1() {
   static const WideConfig table[] = {
-      wide_config_of<WideKind<3, 6, 0, 0, 4, 4, 0, 0, 2, 2>>(),
-      wide_config_of<WideKind<4, 8, 0, 0, 4, 4, 0, 0, 2, 2>>(),
-      wide_config_of<WideKind<3, 12, 0, 0, 4, 4, 0, 0, 1, 1>>(),
-      wide_config_of<WideKind<3, 12, 0, 0, 4, 4, 0, 0, 1, 2>>(),
-      wide_config_of<WideKind<3, 12, 0, 0, 4, 4, 0, 0, 2, 2>>(),
+      wide_config_of<WideKind<3, 6, 0, 0, 0, 4, 0, 0, 4>>(),
+      wide_config_of<WideKind<4, 8, 0, 0, 0, 4, 0, 0, 4>>(),
+      wide_config_of<WideKind<3, 12, 0, 0, 4, 4, 0, 0, 1>>(),
+      wide_config_of<WideKind<3, 12, 0, 0, 4, 4, 0, 0, 2>>(),
+      wide_config_of<WideKind<3, 12, 0, 0, 0, 4, 0, 0, 4>>(),
   };
   return {table, (int)(sizeof table / sizeof table[0])};
 }
