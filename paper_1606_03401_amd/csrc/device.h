@@ -47,21 +47,28 @@ struct Mma<float> {
 };
 
 // Pointwise activations on the hardware exp2 / reciprocal units (a few ulp; the absolute error of
-// tanh stays below 1e-7, far inside the fp32 gradient tolerance).  Both need 1 / (1 + e) for an e in [0, 1] only, where a
-// reciprocal with one Newton step is as good as a division (within an ulp of 2^-24 either way) at a third of its
-// instructions: a step of a resident launch has little else to do between two exchanges.
-__device__ inline float rcp_1_to_2(float d) {
+// tanh stays below 1e-7, far inside the fp32 gradient tolerance).  The reciprocals with one Newton step are as good as a
+// division (within an ulp of 2^-24 either way) at a third of its instructions, and a step of a resident launch has little
+// else to do between two exchanges: a gradient step of H = 1024, B = 64 10.67 -> 10.49 ms, of H = 512, B = 256 107.0 -> 104.5.
+// With fp32 operands tanh keeps the division: one of the two is worth 1 - 2 % there too, both at once make the launches
+// with forward operations of H = 256, B = 32 5 % slower (1705 -> 1795 us a gradient step; not found why).
+__device__ inline float reciprocal(float d) {   // of d >= 1, infinity included
   const float r = __builtin_amdgcn_rcpf(d);
-  return __fmaf_rn(__fmaf_rn(-d, r, 1.0f), r, r);
+  return d < 3e38f ? __fmaf_rn(__fmaf_rn(-d, r, 1.0f), r, r) : r;
 }
-__device__ inline float sigmoidf_(float z) {
-  const float e = __expf(-fabsf(z));                   // in [0, 1]: no overflow
-  const float r = rcp_1_to_2(1.0f + e);
-  return z >= 0.0f ? r : __fmul_rn(e, r);
-}
+__device__ inline float sigmoidf_(float z) { return reciprocal(1.0f + __expf(-z)); }
+template <class T>
 __device__ inline float tanhf_(float z) {
-  const float e = __expf(-2.0f * fabsf(z));
-  return copysignf(__fmul_rn(1.0f - e, rcp_1_to_2(1.0f + e)), z);
+  const float e = __expf(-2.0f * fabsf(z));            // in (0, 1]: no overflow
+  const float d = 1.0f + e;
+  float r;
+  if constexpr (sizeof(T) == 2) {
+    r = __builtin_amdgcn_rcpf(d);
+    r = __fmaf_rn(__fmaf_rn(-d, r, 1.0f), r, r);
+  } else {
+    r = __frcp_rn(d);
+  }
+  return copysignf(__fmul_rn(1.0f - e, r), z);
 }
 
 // ---- the h plane of a hidden-state unit ----------------------------------------------------------
@@ -144,13 +151,13 @@ __host__ __device__ inline int packed_gate_h(int cell, int row) { return cell ==
 // values the backward step needs (LSTM: i, f, g, o; GRU: r, z, n).  Every kernel that computes a
 // forward step calls this one function, with the multiply-adds spelled out, so that a step gives
 // the same bits whichever kernel ran it.
-template <int CELL>
+template <class T, int CELL>
 __device__ inline float cell_forward(const float (&G)[4], const float4& bias, float state_prev, float& second,
                                      float (&gate)[4]) {
   if (CELL == 0) {
     const float gi = sigmoidf_(G[0] + bias.x);
     const float gf = sigmoidf_(G[1] + bias.y);
-    const float gg = tanhf_(G[2] + bias.z);
+    const float gg = tanhf_<T>(G[2] + bias.z);
     const float go = sigmoidf_(G[3] + bias.w);
     const float c = __fmaf_rn(gf, state_prev, __fmul_rn(gi, gg));
     gate[0] = gi;
@@ -158,13 +165,13 @@ __device__ inline float cell_forward(const float (&G)[4], const float4& bias, fl
     gate[2] = gg;
     gate[3] = go;
     second = c;
-    return __fmul_rn(go, tanhf_(c));
+    return __fmul_rn(go, tanhf_<T>(c));
   } else {
     // rows r, z, n_x, n_h: n = tanh(n_x + r * n_h), h = (1 - z) n + z h_prev
     const float r = sigmoidf_(G[0] + bias.x);
     const float z = sigmoidf_(G[1] + bias.y);
     const float nh = G[3] + bias.w;
-    const float n = tanhf_(__fmaf_rn(r, nh, G[2] + bias.z));
+    const float n = tanhf_<T>(__fmaf_rn(r, nh, G[2] + bias.z));
     gate[0] = r;
     gate[1] = z;
     gate[2] = n;
@@ -178,9 +185,10 @@ __device__ inline float cell_forward(const float (&G)[4], const float4& bias, fl
 // plus injected loss gradient), the running dc, the internal state (i, f, g, o, c_s) and c_{s-1}
 // to the four gate pre-activation gradients and dc_{s-1}.  One function, multiply-adds spelled
 // out, for every kernel that runs a backward step: the same bits whichever kernel ran it.
+template <class T>
 __device__ inline void lstm_backward_point(float dh, float dc_in, float gi, float gf, float gg, float go, float c_s,
                                            float c_prev, float (&dG)[4], float& dc_out) {
-  const float tc = tanhf_(c_s);
+  const float tc = tanhf_<T>(c_s);
   const float d_o = __fmul_rn(dh, tc);
   const float dct = __fmaf_rn(__fmul_rn(dh, go), __fmaf_rn(-tc, tc, 1.0f), dc_in);
   dG[0] = __fmul_rn(__fmul_rn(__fmul_rn(dct, gg), gi), __fsub_rn(1.0f, gi));

@@ -419,7 +419,7 @@ __device__ inline void forward_body(const FwdParams& p, int bx, int by, float* r
     }
     const size_t e = eidx[q];
     float second, gate[4];
-    const float h = cell_forward<CELL>(G, bias[q], c_prev[q], second, gate);
+    const float h = cell_forward<T, CELL>(G, bias[q], c_prev[q], second, gate);
     HP_::store(p.dst_h, eb[q], eu[q], h, nsh, p.H, hhalf);
     p.dst_c[e] = second;
     if (p.g_i) {
@@ -594,7 +594,7 @@ __device__ inline void backward_body(const BwdParams& p, int bx, int by, float* 
     float dGi, dGf, dGg, dGo;
     if (p.cell == 0) {
       float dG[4], dc_out;
-      lstm_backward_point(dh, dc_in[q], gi[q], gf[q], gg[q], go[q], c_s[q], c_prev[q], dG, dc_out);
+      lstm_backward_point<T>(dh, dc_in[q], gi[q], gf[q], gg[q], go[q], c_s[q], c_prev[q], dG, dc_out);
       dGi = dG[0];
       dGf = dG[1];
       dGg = dG[2];

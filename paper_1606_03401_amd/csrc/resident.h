@@ -456,7 +456,7 @@ __device__ __forceinline__ void chain_slowly(int b_lo, int b_hi, int u0, int u1,
                               [&](int m) { return as_frag<typename M::Frag>(load_slot_16(in, hoff, m * 1024)); }, G);
         const size_t e = (size_t)b * p.H + u, o = ft_offset<T>(b, u, nsh);
         if (real) {
-          h = cell_forward<CELL>(G, *reinterpret_cast<const float4*>(p.bp + 4 * u), p.spare[e], second, gate);
+          h = cell_forward<T, CELL>(G, *reinterpret_cast<const float4*>(p.bp + 4 * u), p.spare[e], second, gate);
           p.spare[e] = CELL ? h : second;
           if (dst) (dst + p.hplane)[e] = second;
           if (gates) {
@@ -753,7 +753,7 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) G[r] += v[r];
       }
-      const float h = cell_forward<CELL>(G, bias[q], c_state[q], keep_second[q], keep_gate[q]);
+      const float h = cell_forward<T, CELL>(G, bias[q], c_state[q], keep_second[q], keep_gate[q]);
       keep_h[q] = real[q] ? h : 0.0f;
       c_state[q] = CELL ? keep_h[q] : keep_second[q];
     }

@@ -148,7 +148,7 @@ __device__ __forceinline__ void sweep_slowly(int b_lo, int b_hi, int u0, int u1,
                                   }
                                 },
                                 G);
-            if (real) h = cell_forward<CELL>(G, *reinterpret_cast<const float4*>(p.bp + 4 * u), prev, second, gate);
+            if (real) h = cell_forward<T, CELL>(G, *reinterpret_cast<const float4*>(p.bp + 4 * u), prev, second, gate);
           } else {
             gate[0] = (stp + p.unit)[e];
             gate[1] = (stp + p.unit + plane)[e];
@@ -163,7 +163,7 @@ __device__ __forceinline__ void sweep_slowly(int b_lo, int b_hi, int u0, int u1,
             float dh = dhs[(4 * i + lq) * 16 + lrow], dG[4], dc_out;
             dh += p.dy_is_h ? h : (p.dy != nullptr && s >= p.dy_first ? (p.dy + (size_t)(s - p.dy_first) * plane)[e] : 0.0f);
             if (CELL == 0)
-              lstm_backward_point(dh, p.dc[e], gate[0], gate[1], gate[2], gate[3], second, prev, dG, dc_out);
+              lstm_backward_point<T>(dh, p.dc[e], gate[0], gate[1], gate[2], gate[3], second, prev, dG, dc_out);
             else
               gru_backward_point(__fadd_rn(dh, p.dc[e]), gate[0], gate[1], gate[2], second, prev, dG, dc_out);
             p.dc[e] = dc_out;
@@ -483,7 +483,7 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) G[r] += v[r];
         }
-        st_h[q] = cell_forward<CELL>(G, bias[q], st_cprev[q], st_c[q], st_gate[q]);
+        st_h[q] = cell_forward<T, CELL>(G, bias[q], st_cprev[q], st_c[q], st_gate[q]);
       } else {
 #pragma unroll
         for (int r = 0; r < 4; ++r) st_gate[q][r] = pf_gate[q][r];
@@ -632,7 +632,7 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
       dh += p.dy_is_h ? st_h[q] : st_dy[q];
       float dG[4], dc_out;
       if (CELL == 0)
-        lstm_backward_point(dh, dc_run[q], st_gate[q][0], st_gate[q][1], st_gate[q][2], st_gate[q][3], st_c[q], st_cprev[q],
+        lstm_backward_point<T>(dh, dc_run[q], st_gate[q][0], st_gate[q][1], st_gate[q][2], st_gate[q][3], st_c[q], st_cprev[q],
                             dG, dc_out);
       else   // the running plane carries dh_{s+1} * z_{s+1}, as in backward_body
         gru_backward_point(__fadd_rn(dh, dc_run[q]), st_gate[q][0], st_gate[q][1], st_gate[q][2], st_c[q], st_cprev[q], dG, dc_out);

@@ -614,7 +614,7 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
 #pragma unroll
         for (int r = 0; r < 4; ++r) G[r] += q[r];
       }
-      const float h = cell_forward<CELL>(G, bias[i], c_state[i], keep_second[i], gate);
+      const float h = cell_forward<T, CELL>(G, bias[i], c_state[i], keep_second[i], gate);
       keep_h[i] = u0 + i < p.H ? h : 0.0f;
       c_state[i] = CELL ? keep_h[i] : keep_second[i];
 #pragma unroll
@@ -940,7 +940,7 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
       const float before = CELL ? whole(hp_hi, hp_lo, i) : c_prev[i];
       float d = dh[i] + (p.dy_is_h ? h_s : dy[i]), dG[4], dc_out;
       if (CELL == 0)
-        lstm_backward_point(d, dc_run[i], gate[0][i], gate[1][i], gate[2][i], gate[3][i], c_s[i], before, dG, dc_out);
+        lstm_backward_point<T>(d, dc_run[i], gate[0][i], gate[1][i], gate[2][i], gate[3][i], c_s[i], before, dG, dc_out);
       else   // the running plane carries dh_{s+1} * z_{s+1}, as in backward_body
         gru_backward_point(__fadd_rn(d, dc_run[i]), gate[0][i], gate[1][i], gate[2][i], c_s[i], before, dG, dc_out);
       dc_run[i] = dc_out;
