@@ -317,8 +317,11 @@ def measure(w, inp, *, kind=None, m=None, steps=3, warmup=1, graph=True, profile
         out["time_share_us"] = share
         if share:
             dom = max(share, key=share.get)
+            # chains and sweeps whose weights are spread over several XCDs have kernels of their own
+            wide = w.gemm_dtype == 1 and (w.H > 1024 or (w.H > 512 and w.B > 128))
             kernel = {"forward": "forward_kernel", "backward": "backward_kernel", "backward+forward": "pair_kernel",
-                      "forward chain": "forward_chain_kernel", "sweep": "sweep_kernel",
+                      "forward chain": "wide_chain_kernel" if wide else "forward_chain_kernel",
+                      "sweep": "wide_sweep_kernel" if wide else "sweep_kernel",
                       "forward batch": "forward_batch_kernel"}[dom]
             if dom == "sweep":
                 # the weight operands stay on the chip; a step carries the dh GEMM and, in the launches

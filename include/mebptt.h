@@ -272,7 +272,7 @@ size_t mebptt_slot_pool_bytes(const mebptt_lstm_desc* desc, const mebptt_plan_t*
  * implementation adds around it: operand copies of the weights in the GEMM type, the running
  * gradients, a dW accumulator, staging of dG / [x; h] for the steps of two chunks of the
  * time-batched weight-gradient GEMM and, on shapes with resident launches (see mebptt_run_status), their
- * exchange slots and, where the way back through a stretch of stored hidden states recomputes the
+ * exchange slots, for the wide ones among them also x of one launch's steps as GEMM operands (at most 32 MiB), and, where the way back through a stretch of stored hidden states recomputes the
  * stretch's internal states in one launch, a stage for those internal states (at most 32 of them and at
  * most 48 MiB).  Independent of t and
  * of the budget. */
@@ -351,10 +351,14 @@ int mebptt_run_prepared(const mebptt_lstm_desc* desc, const mebptt_plan_t* plan,
  * each other, every input state being in a slot already -- go out as one "forward-batch" launch that leaves the
  * internal states in the workspace's stage, followed by one sweep launch of
  * backward operations on them; backward operations on internal states stored in slots go out as
- * such sweep launches as well.  Results are bit-identical to the launch-per-step path.  The workgroups of
- * such a launch that share an XCD wait for each other and have to be on the chip together.  Where other work (another
+ * such sweep launches as well.  With bf16 operands, H up to 1024 with B of 129 to 256, H up to 2048 with B up to 128 and H up to
+ * 4096 with B up to 32 (I of at least 8, where the weights fit) have "wide" launches: chains and sweeps on stored
+ * internal states whose weights are spread once over a quarter, a half or all of the device, which then exchange across XCDs.
+ * Every forward and backward operation of these shapes runs in such a launch (the independent ones in
+ * forward batches).  Results are bit-identical to the launch-per-step path.  The workgroups of
+ * such a launch that share an XCD (wide: that part of the device) wait for each other and have to be on the chip together.  Where other work (another
  * stream, the replay of a captured graph, another process, perhaps another such launch) keeps some of them
- * off it, the launch is given up for that XCD after a while and one workgroup there runs its steps alone: the same
+ * off it, the launch is given up for that XCD (that part) after a while and one workgroup there runs its steps alone: the same
  * results, slowly.  Runs may therefore overlap in any way; the library orders its own eager runs across streams
  * with an event, which is faster, and so is ordering what else wants the device.  The launch relies on its 256
  * workgroups being dealt round-robin to the XCDs; each workgroup checks this, every wait inside is bounded by a wall
@@ -382,8 +386,8 @@ int mebptt_forward_chain_enable(int32_t on);
  * after the call. */
 int mebptt_resident_wait_limit(int64_t ticks);
 /* How long the workgroups of a forward-chain or sweep launch wait for each other before the launch is given up for
- * their XCD and one of them runs alone, in the same ticks (negative, the default: about as long as that would
- * take, at least 0.5 ms; never longer than the bound above).  0: one workgroup per XCD runs alone from the start.  For
+ * their XCD (wide launches: their part of the device) and one of them runs alone, in the same ticks (negative, the default: about as long as that would
+ * take, at least 0.5 ms; never longer than the bound above).  0: one workgroup per XCD (part) runs alone from the start.  For
  * tests of that path.  Process-wide; applies to launches enqueued after the call. */
 int mebptt_resident_patience(int64_t ticks);
 
@@ -422,7 +426,8 @@ enum {
   MEBPTT_K_DGRAD = 3,    /* time-batched dx GEMM and the final dh0 GEMM                       */
   MEBPTT_K_SETUP = 4,    /* operand copies of the weights, zero fills, start-state copy       */
   MEBPTT_K_PAIR = 5,     /* one launch carrying a backward step and an independent forward op */
-  MEBPTT_K_CHAIN = 6,    /* one launch carrying a chain of forward operations, weights resident  */
+  MEBPTT_K_CHAIN = 6,    /* one launch carrying a chain of forward operations, weights resident (wide ones: with the
+                            launch ahead of it that lays out x)                                   */
   MEBPTT_K_SWEEP = 7,    /* one launch carrying a run of backward steps (with or without the forward
                             operations that recompute their internal states), weights resident */
   MEBPTT_K_FWD_BATCH = 8, /* one launch carrying forward operations that do not depend on each other */
@@ -482,9 +487,9 @@ int mebptt_measure_forward_stream(const mebptt_lstm_desc* desc, void* workspace,
 /* Time steps per chunk of the time-batched GEMMs for this shape (the K extent of the dW GEMM is
  * this many times B), or a negative error code. */
 int32_t mebptt_chunk_steps(const mebptt_lstm_desc* desc);
-/* Internal states the recomputation stage inside the workspace holds for this shape (0: the shape
- * has no stage: its recomputation runs do not go out as a forward batch plus a backward-only sweep
- * launch), or a negative error code. */
+/* Internal states the recomputation stage inside the workspace holds for this shape (0: its recomputation runs do not
+ * go out as a forward batch plus a backward-only sweep launch that shares an XCD -- shapes with wide launches have a
+ * stage that is not counted here), or a negative error code. */
 int32_t mebptt_stage_steps(const mebptt_lstm_desc* desc);
 
 /* What one synchronisation of the 256 workgroups of a resident launch costs, alone: `iters`

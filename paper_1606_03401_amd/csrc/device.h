@@ -287,7 +287,10 @@ inline BwdConfig backward_config(const Dims& d) {
 // Shapes whose resident launches spread one copy of the weights over `groups` equal parts of the device (see
 // resident_wide.h): bf16 operands too wide, or batches too large, for a copy per XCD.  groups parts of 256 / groups
 // compute units each take `share` sequences; a compute unit has nr 16-row tiles of a product's rows.  groups 0: not such
-// a shape.  The K splits of every kernel that runs a step of such a shape follow from what a compute unit's four
+// a shape.  Against a launch per step, a gradient step of 22 shapes of these ranges takes 0.40 - 0.87 of the time (H = 2048,
+// B = 128, t = 1000 54.5 -> 31 ms; H = 4096, B = 32 103.7 -> 51 ms).  The sums of more sequences do not fit beside the weights; up
+// to H = 1024 and B = 128 a copy per XCD fits, whose steps take 2 - 2.5 us for a wide one's 5 - 7.
+// The K splits of every kernel that runs a step of such a shape follow from what a compute unit's four
 // waves can add up: see paired_sum and WIDE_BACK_PARTS.
 struct WideShape {
   int groups, share, nr;

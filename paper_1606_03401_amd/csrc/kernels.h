@@ -53,12 +53,20 @@ inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
 
 Dims make_dims(int B, int I, int H, int dtype, int cell);
 
-// Zeroes p, and fills `empty` with 0xff (what the exchange rings of resident launches start from); sizes multiples of 16.
-hipError_t launch_fill(void* p, size_t bytes, void* empty, size_t empty_bytes, hipStream_t st);
-hipError_t launch_prep_weights(const Dims& d, const float* W_ih, const float* W_hh, const float* b, void* Wp,
-                               float* bp, void* WTh, void* WTx, hipStream_t st);
-// dst unit <- (h0, c0), NULL meaning zeros.
-hipError_t launch_init_state(const Dims& d, const float* h0, const float* c0, float* dst_unit, hipStream_t st);
+// Everything a run prepares, in one launch; what is NULL (of size 0) is left out.
+struct SetupArgs {
+  const float *W_ih, *W_hh, *b;   // -> the operand copies Wp, bp, WTh, WTx
+  void* Wp;
+  float* bp;
+  void *WTh, *WTx;
+  void* zero;        // cleared; sizes are multiples of 16
+  size_t zero_bytes;
+  void* empty;       // filled with 0xff: what the exchange rings of resident launches start from
+  size_t empty_bytes;
+  const float *h0, *c0;   // -> the unit at state, NULL meaning zeros
+  float* state;
+};
+hipError_t launch_setup(const Dims& d, const SetupArgs& a, hipStream_t st);
 
 // One forward operation: reads x_s [B,I] and the hidden state at src; writes (h,c) to dst and,
 // when gates != NULL, (i,f) and (g,o) to the two units starting at `gates`.
@@ -197,14 +205,12 @@ hipError_t launch_transpose_x(const Dims& d, const float* x_first, int nslots, v
 hipError_t launch_zero_operand_columns(const Dims& d, void* dGT, void* aT, int c0, int c1, hipStream_t st);
 
 // Tile-ordered running sum of [dW | db] (+)= dGT * aT^T over K = nslots*B columns.
-// launch_wgrad_finish writes the caller's row-major dW_ih, dW_hh and db from it.
+// launch_wgrad_finish writes the caller's row-major dW_ih, dW_hh and db from it, and the start state's gradients from the
+// running plane dc: LSTM dc0 = dc; GRU dh0 += dc, dc0 = 0.
 size_t wgrad_accumulator_bytes(const Dims& d);
 hipError_t launch_wgrad(const Dims& d, const void* dGT, const void* aT, int nslots, int accumulate, float* dWacc,
                         hipStream_t st);
-hipError_t launch_wgrad_finish(const Dims& d, const float* dWacc, float* dW_ih, float* dW_hh, float* db,
-                               hipStream_t st);
-
-// One [B,H] plane: dst = src (accumulate 0), dst += src (1), dst = 0 (2; src unused).
-hipError_t launch_copy_plane(const Dims& d, const float* src, float* dst, int accumulate, hipStream_t st);
+hipError_t launch_wgrad_finish(const Dims& d, const float* dWacc, float* dW_ih, float* dW_hh, float* db, const float* dc,
+                               float* dh0, float* dc0, hipStream_t st);
 
 }  // namespace mebptt

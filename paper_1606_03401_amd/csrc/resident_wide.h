@@ -211,7 +211,7 @@ __device__ __forceinline__ void pack_half(const unsigned (&v)[N], unsigned (&d)[
 // ---- the shared product ---------------------------------------------------------------------------------
 // Both kernels multiply 16 * NR resident rows with the operand that was exchanged, 16 * NB sequences of it, over nsh macro
 // steps: a forward workgroup its units' gate rows with all of h, a backward workgroup a block of units of W_hh^T with a
-// quarter of dG's columns (every fourth macro step), which is as long.  Four waves share the macro steps: wave w has w,
+// quarter of dG's columns (four consecutive macro steps of every sixteen), which is as long.  Four waves share the macro steps: wave w has w,
 // w + 4, ...; with one wave per SIMD a lane has 512 registers.  A wave's weights are NHW macro steps: the first in
 // registers, NHL in LDS, the last NHS fetched again in every step.
 //
@@ -629,7 +629,8 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
 
 // ---- backward sweep on stored internal states --------------------------------------------------------------
 // Consecutive backward operations in one launch, see sweep_kernel.  A workgroup holds 16 * NR rows (units) of W_hh^T and
-// every fourth macro step of their K = 4 H columns: with whole rows it would have to fetch all of dG, 1 MiB a step for 64
+// four consecutive macro steps of every sixteen of their K = 4 H columns (4 KiB at a time: 128 KB into every compute unit in
+// 4.75 us, every fourth macro step 5.26): with whole rows it would have to fetch all of dG, 1 MiB a step for 64
 // sequences of H = 2048 where a quarter takes 2.1 us.  The four workgroups of a block of units sit on one XCD; each adds up dh
 // for a quarter of the block's units, to which the others send their sums through that XCD's L2 (the polled
 // exchange once more, fp32).  A step:

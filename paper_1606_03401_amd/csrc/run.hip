@@ -60,6 +60,7 @@ int recompute_stage_steps(const Dims& d) {
 //   H = 1024, B = 64 1.4 % slower (GRU 1.8 %), H = 768, B = 128 1.5 % slower;
 //   fp32, whose GEMMs take eight times as long, from 3 GFLOP on: H = 512, B = 32 0.9 % slower, H = 256, B = 256
 //   0.6 % slower with hidden states stored, 7.8 % faster with internal ones (beside all the same: a rule by sizes alone).
+//   wide launches: H = 2048, B = 128 0.4 % faster on the run's own stream, H = 4096, B = 32 even.
 bool gemms_beside(const Dims& d) {
   if ((!can_run_forward_chain(d) && !can_run_backward_sweep(d)) || runs_wide(d)) return false;
   const double chunk_flops = 8.0 * d.CH * d.B * d.H * ((double)d.I + d.H);
@@ -447,10 +448,17 @@ int mebptt_prepare(const mebptt_lstm_desc* desc, const float* W_ih, const float*
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   char* ws = reinterpret_cast<char*>(workspace);
   std::lock_guard<std::mutex> lock(g_run_mutex);   // the measurement hooks' state is shared with runs
-  HIP_TRY(timed(MEBPTT_K_SETUP, st, [&] {
-    return launch_prep_weights(d, W_ih, W_hh, b, ws + w.Wp, reinterpret_cast<float*>(ws + w.bp), ws + w.WTh, ws + w.WTx, st);
-  }));
-  HIP_TRY(timed(MEBPTT_K_SETUP, st, [&] { return launch_fill(ws + w.dc, w.ring - w.dc, nullptr, 0, st); }));
+  SetupArgs up{};
+  up.W_ih = W_ih;
+  up.W_hh = W_hh;
+  up.b = b;
+  up.Wp = ws + w.Wp;
+  up.bp = reinterpret_cast<float*>(ws + w.bp);
+  up.WTh = ws + w.WTh;
+  up.WTx = ws + w.WTx;
+  up.zero = ws + w.dc;
+  up.zero_bytes = w.ring - w.dc;
+  HIP_TRY(timed(MEBPTT_K_SETUP, st, [&] { return launch_setup(d, up, st); }));
   remember_prepared(workspace, d);
   return MEBPTT_OK;
 }
@@ -616,7 +624,10 @@ int mebptt_measure_gemms(const mebptt_lstm_desc* desc, void* workspace, size_t w
     if (e == hipSuccess) e = hipEventSynchronize(ev[2]);
   }
   // a prepared workspace stays prepared: the staging's padding has to be zero
-  if (e == hipSuccess) e = launch_fill(ws + w.dG[0], w.ring - w.dG[0], nullptr, 0, st);
+  SetupArgs up{};
+  up.zero = ws + w.dG[0];
+  up.zero_bytes = w.ring - w.dG[0];
+  if (e == hipSuccess) e = launch_setup(d, up, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   float ms_w = 0.0f, ms_d = 0.0f;
   if (e == hipSuccess) e = hipEventElapsedTime(&ms_w, ev[0], ev[1]);
@@ -796,15 +807,28 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
   const size_t ring_fill = resident_ok ? w.ring_bytes : 0;   // the no-allocation path's workspace ends before the ring
 
   // Set-up: operand copies of the weights, zeroed staging (the padding must stay zero), start state.
+  SetupArgs up{};
+  up.zero = ws + w.dc;
+  up.empty = ws + w.ring;
+  up.empty_bytes = ring_fill;
+  up.h0 = h0;
+  up.c0 = c0;
+  up.state = plan->kind == MEBPTT_ISM ? loc(MEBPTT_LOC_INIT) : loc(0);
   if (mode != RUN_PREPARED) {
-    HIP_TRY(tm(MEBPTT_K_SETUP, st, [&] { return launch_prep_weights(d, W_ih, W_hh, b, Wp, bp, WTh, WTx, st); }));
-    HIP_TRY(tm(MEBPTT_K_SETUP, st, [&] { return launch_fill(ws + w.dc, w.ring - w.dc, ws + w.ring, ring_fill, st); }));
+    up.W_ih = W_ih;
+    up.W_hh = W_hh;
+    up.b = b;
+    up.Wp = Wp;
+    up.bp = bp;
+    up.WTh = WTh;
+    up.WTx = WTx;
+    up.zero_bytes = w.ring - w.dc;
   } else {
     // The staging keeps what the previous run left.  Only the running gradient plane must start
     // at zero, and -- when the last chunk in time is short and its K is padded -- the operand
     // columns between its last step and the padded K, which a full chunk of the previous run
     // filled.
-    HIP_TRY(tm(MEBPTT_K_SETUP, st, [&] { return launch_fill(ws + w.dc, w.dG[0] - w.dc, ws + w.ring, ring_fill, st); }));
+    up.zero_bytes = w.dG[0] - w.dc;
     const int last_chunk = (t - 1) / CH, nslots = t - last_chunk * CH;
     const int cols = nslots * d.B, kstep = d.dtype ? 32 : 16;
     if (cols % kstep != 0)
@@ -813,9 +837,7 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
                                            round_up(cols, kstep), st);
       }));
   }
-  HIP_TRY(tm(MEBPTT_K_SETUP, st, [&] {
-    return launch_init_state(d, h0, c0, plan->kind == MEBPTT_ISM ? loc(MEBPTT_LOC_INIT) : loc(0), st);
-  }));
+  HIP_TRY(tm(MEBPTT_K_SETUP, st, [&] { return launch_setup(d, up, st); }));
   if (plan->kind != MEBPTT_ISM) touch(0, 1);
 
   // Where the time-batched GEMMs do not go beside the sequential work, and in the no-allocation path, which creates
@@ -1267,17 +1289,12 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
   }
   // LSTM: dh_0 = dG_1 W_hh ; dc_0 is the running cell gradient after step 1.
   // GRU:  dh_0 = dG_1 W_hh + dh_1 * z_1 (the running plane) ; there is no cell state: dc_0 = 0.
+  // What comes from the running plane launch_wgrad_finish writes.
   HIP_TRY(tm(MEBPTT_K_DGRAD, st, [&] { return launch_dgrad_gemm(d, WTh, d.H, ws + w.dG[0], 1, dh0, d.H, st); }));
-  if (d.cell == MEBPTT_CELL_LSTM) {
-    HIP_TRY(tm(MEBPTT_K_SETUP, st, [&] { return launch_copy_plane(d, dc, dc0, 0, st); }));
-  } else {
-    HIP_TRY(tm(MEBPTT_K_SETUP, st, [&] { return launch_copy_plane(d, dc, dh0, 1, st); }));
-    HIP_TRY(launch_copy_plane(d, dc, dc0, 2, st));
-  }
   for (int i = 0; i < 2; ++i)   // join: everything is ordered before whatever follows on `st`
     if (pending[i]) HIP_TRY(hipStreamWaitEvent(st, side->done[i], 0));
   HIP_TRY(tm(MEBPTT_K_WGRAD, st, [&] {
-    return launch_wgrad_finish(d, reinterpret_cast<const float*>(ws + w.dWacc), dW_ih, dW_hh, db, st);
+    return launch_wgrad_finish(d, reinterpret_cast<const float*>(ws + w.dWacc), dW_ih, dW_hh, db, dc, dh0, dc0, st);
   }));
 
   if (use_profiler) HIP_TRY(close_group());
