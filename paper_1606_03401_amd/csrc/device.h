@@ -50,13 +50,18 @@ struct Mma<float> {
 // tanh stays below 1e-7, far inside the fp32 gradient tolerance).  The reciprocals with one Newton step are as good as a
 // division (within an ulp of 2^-24 either way) at a third of its instructions, and a step of a resident launch has little
 // else to do between two exchanges: a gradient step of H = 1024, B = 64 10.67 -> 10.49 ms, of H = 512, B = 256 107.0 -> 104.5.
-// With fp32 operands tanh keeps the division: one of the two is worth 1 - 2 % there too, both at once make the launches
-// with forward operations of H = 256, B = 32 5 % slower (1705 -> 1795 us a gradient step; not found why).
+// With fp32 operands both keep the division: tanh alone with it is worth -1 - +1 % over eleven shapes (H = 100, B = 24, t = 150
+// 1322 -> 1335 us), neither makes the launches with forward operations of H = 256, B = 32 5 % slower (1705 -> 1795 us a gradient
+// step; not found why).
 __device__ inline float reciprocal(float d) {   // of d >= 1, infinity included
   const float r = __builtin_amdgcn_rcpf(d);
   return d < 3e38f ? __fmaf_rn(__fmaf_rn(-d, r, 1.0f), r, r) : r;
 }
-__device__ inline float sigmoidf_(float z) { return reciprocal(1.0f + __expf(-z)); }
+template <class T>
+__device__ inline float sigmoidf_(float z) {
+  const float d = 1.0f + __expf(-z);
+  return sizeof(T) == 2 ? reciprocal(d) : __frcp_rn(d);
+}
 template <class T>
 __device__ inline float tanhf_(float z) {
   const float e = __expf(-2.0f * fabsf(z));            // in (0, 1]: no overflow
@@ -155,10 +160,10 @@ template <class T, int CELL>
 __device__ inline float cell_forward(const float (&G)[4], const float4& bias, float state_prev, float& second,
                                      float (&gate)[4]) {
   if (CELL == 0) {
-    const float gi = sigmoidf_(G[0] + bias.x);
-    const float gf = sigmoidf_(G[1] + bias.y);
+    const float gi = sigmoidf_<T>(G[0] + bias.x);
+    const float gf = sigmoidf_<T>(G[1] + bias.y);
     const float gg = tanhf_<T>(G[2] + bias.z);
-    const float go = sigmoidf_(G[3] + bias.w);
+    const float go = sigmoidf_<T>(G[3] + bias.w);
     const float c = __fmaf_rn(gf, state_prev, __fmul_rn(gi, gg));
     gate[0] = gi;
     gate[1] = gf;
@@ -168,8 +173,8 @@ __device__ inline float cell_forward(const float (&G)[4], const float4& bias, fl
     return __fmul_rn(go, tanhf_<T>(c));
   } else {
     // rows r, z, n_x, n_h: n = tanh(n_x + r * n_h), h = (1 - z) n + z h_prev
-    const float r = sigmoidf_(G[0] + bias.x);
-    const float z = sigmoidf_(G[1] + bias.y);
+    const float r = sigmoidf_<T>(G[0] + bias.x);
+    const float z = sigmoidf_<T>(G[1] + bias.y);
     const float nh = G[3] + bias.w;
     const float n = tanhf_<T>(__fmaf_rn(r, nh, G[2] + bias.z));
     gate[0] = r;
