@@ -487,9 +487,9 @@ int mebptt_measure_forward_stream(const mebptt_lstm_desc* desc, void* workspace,
 /* Time steps per chunk of the time-batched GEMMs for this shape (the K extent of the dW GEMM is
  * this many times B), or a negative error code. */
 int32_t mebptt_chunk_steps(const mebptt_lstm_desc* desc);
-/* Internal states the recomputation stage inside the workspace holds for this shape (0: its recomputation runs do not
- * go out as a forward batch plus a backward-only sweep launch that shares an XCD -- shapes with wide launches have a
- * stage that is not counted here), or a negative error code. */
+/* Internal states the recomputation stage inside the workspace holds for this shape (0: the shape
+ * has no stage: its recomputation runs do not go out as a forward batch plus a backward-only sweep
+ * launch), or a negative error code. */
 int32_t mebptt_stage_steps(const mebptt_lstm_desc* desc);
 
 /* What one synchronisation of the 256 workgroups of a resident launch costs, alone: `iters`

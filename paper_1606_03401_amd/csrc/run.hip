@@ -590,8 +590,7 @@ int32_t mebptt_chunk_steps(const mebptt_lstm_desc* desc) {
 int32_t mebptt_stage_steps(const mebptt_lstm_desc* desc) {
   int rc = check_desc(desc);
   if (rc) return rc;
-  const Dims d = make_dims(desc->B, desc->I, desc->H, desc->gemm_dtype, desc->cell);
-  return runs_wide(d) ? 0 : recompute_stage_steps(d);
+  return recompute_stage_steps(make_dims(desc->B, desc->I, desc->H, desc->gemm_dtype, desc->cell));
 }
 
 int mebptt_measure_gemms(const mebptt_lstm_desc* desc, void* workspace, size_t workspace_bytes, int32_t reps,

@@ -30,9 +30,10 @@ def test_every_declared_symbol_is_exported_and_bound():
 def test_recomputation_stage_in_the_workspace():
     """The workspace carries a stage for recomputed internal states exactly on the shapes whose way
     back through stored hidden states is a forward-batch launch plus a backward-only sweep launch:
-    bf16 operands, a shape the backward-only sweep kernel covers, and no sweep launch that recomputes
-    internal states itself (the LSTM has those up to H = 512; the GRU has none).  As many states as
-    a sweep launch carries (32), at most 48 MiB, three units each."""
+    bf16 operands, a shape a backward-only sweep kernel covers (with a copy of the weights per XCD or
+    spread over several), and no sweep launch that recomputes internal states itself (the LSTM has
+    those up to H = 512; the GRU has none).  As many states as a sweep launch carries (32), at most
+    48 MiB, three units each."""
     def desc(B, I, H, cell=0, dtype=1):
         return mb.make_desc(B, I, H, 100, dtype, 0, 1, cell)
     unit = lambda B, H: mb.mebptt_unit_bytes(desc(B, 64, H))
@@ -41,7 +42,10 @@ def test_recomputation_stage_in_the_workspace():
     for B, I, H in ((256, 128, 512), (64, 256, 256), (64, 128, 128)):      # the sweep launch recomputes the states itself
         assert mb.mebptt_stage_steps(desc(B, I, H)) == 0
         assert mb.mebptt_stage_steps(desc(B, I, H, cell=1)) > 0           # the GRU has no such launch
-    for B, I, H in ((128, 512, 2048), (200, 64, 1024), (32, 1024, 4096)):  # no backward-only sweep launch for the shape
+    for B, I, H in ((128, 512, 2048), (200, 64, 1024), (32, 1024, 4096)):  # weights spread over several XCDs
+        want = min(32, (48 << 20) // (3 * unit(B, H)))
+        assert want > 0 and mb.mebptt_stage_steps(desc(B, I, H)) == want == mb.mebptt_stage_steps(desc(B, I, H, cell=1))
+    for B, I, H in ((129, 512, 2048), (257, 64, 1024), (33, 1024, 4096), (16, 64, 4100), (64, 7, 2048)):  # no backward-only sweep launch
         assert mb.mebptt_stage_steps(desc(B, I, H)) == 0 and mb.mebptt_stage_steps(desc(B, I, H, cell=1)) == 0
     assert mb.mebptt_stage_steps(desc(64, 256, 1024, dtype=0)) == 0       # fp32 operands: launch-per-step kernels only
     # the stage is part of the workspace, which does not depend on t
