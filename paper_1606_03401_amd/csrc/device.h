@@ -308,6 +308,10 @@ inline WideShape wide_shape(const Dims& d) {
   if (d.KH > 1024 && d.KH <= 2048 && d.B <= 128) groups = 2;
   if (d.KH > 2048 && d.KH <= 4096 && d.B <= 32) groups = 1;
   if (!groups) return w;
+  // The resident launches address these operands by 32-bit byte offsets, and offsets from 2^31 on mean that there is nothing to
+  // fetch: inputs of more than 61 000 columns (H = 4096) go out a launch per step, whose kernels have 64-bit offsets.
+  constexpr size_t LIMIT = (size_t)1 << 31;
+  if ((size_t)d.G4 * d.KP * 2 >= LIMIT || (size_t)d.G4 * d.KC * 2 >= LIMIT || (size_t)d.NA * d.KC * 2 >= LIMIT) return w;
   w.groups = groups;
   w.share = round_up((d.B + groups - 1) / groups, 16);
   w.nr = (d.KH * groups + 1023) / 1024;

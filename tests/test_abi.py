@@ -76,3 +76,36 @@ def test_dense_chain_workspace_holds_two_activations_and_two_gradients():
     desc = mb.make_chain_desc([70, 2047, 65], 510, 4096)
     slab = (510 * 2047 * 4 + 255) // 256 * 256
     assert mb.mebptt_chain_workspace_bytes(desc) == 4 * slab
+
+
+def _round_up(v, n):
+    return (v + n - 1) // n * n
+
+
+def _wide_operand_bytes(desc):
+    """The largest of the arrays that the launches with weights spread over several XCDs address by 32-bit byte offsets:
+    the gate weights and the two transposed operands of the weight gradient."""
+    KX, KH, NX = _round_up(desc.I, 32), _round_up(desc.H, 32), _round_up(desc.I, 16)
+    KC = _round_up(mb.mebptt_chunk_steps(desc) * desc.B, 32)
+    return max(4 * KH * (KX + KH) * 2, (NX + KH + 16) * KC * 2, 4 * KH * KC * 2)
+
+
+def test_launches_that_address_by_32_bits_are_not_used_beyond_them():
+    """Inputs so wide that an operand reaches 2 GiB are accepted, and run by the launch-per-step kernels, whose offsets are
+    64 bits wide.  (The recomputation stage is there exactly where the other launches are: these shapes have no copy of the weights
+    per XCD.)"""
+    for B, H in ((32, 4096), (9, 2100), (128, 2048), (70, 1056), (16, 1100), (200, 1024), (129, 600)):
+        def desc(I):
+            return mb.make_desc(B, I, H, 10, 1, 0, 1, 0)
+        lo, hi = 64, (1 << 31) // (4 * H) - H                     # hi: the widest input that is accepted
+        assert _wide_operand_bytes(desc(lo)) < 1 << 31 <= _wide_operand_bytes(desc(hi))
+        while hi - lo > 1:
+            mid = (lo + hi) // 2
+            if _wide_operand_bytes(desc(mid)) < 1 << 31:
+                lo = mid
+            else:
+                hi = mid
+        assert mb.mebptt_stage_steps(desc(lo)) > 0 and mb.mebptt_stage_steps(desc(hi)) == 0, (B, H, lo)
+        for I in (2 * hi, 3 * hi, (1 << 31) // (4 * H) - H):
+            if 4 * H * (I + H) <= 1 << 31:
+                assert mb.mebptt_stage_steps(desc(I)) == 0 and mb.mebptt_workspace_bytes(desc(I)) > 1 << 31, (B, H, I)
