@@ -300,6 +300,7 @@ inline BwdConfig backward_config(const Dims& d) {
 struct WideShape {
   int groups, share, nr;
 };
+constexpr size_t WIDE_X_BYTES = (size_t)32 << 20;   // x of a chain launch's steps as operands: as many steps as this holds
 inline WideShape wide_shape(const Dims& d) {
   WideShape w{};
   if (d.dtype == 0 || d.I < 8 || d.KP / 32 <= 20) return w;   // (20: the forward kernels that split K four ways)
@@ -312,6 +313,7 @@ inline WideShape wide_shape(const Dims& d) {
   // fetch: inputs of more than 61 000 columns (H = 4096) go out a launch per step, whose kernels have 64-bit offsets.
   constexpr size_t LIMIT = (size_t)1 << 31;
   if ((size_t)d.G4 * d.KP * 2 >= LIMIT || (size_t)d.G4 * d.KC * 2 >= LIMIT || (size_t)d.NA * d.KC * 2 >= LIMIT) return w;
+  if ((size_t)d.BP * d.KX * 2 > WIDE_X_BYTES) return w;   // not one step's x fits the staging
   w.groups = groups;
   w.share = round_up((d.B + groups - 1) / groups, 16);
   w.nr = (d.KH * groups + 1023) / 1024;

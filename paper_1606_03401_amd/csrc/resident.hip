@@ -94,9 +94,7 @@ bool can_run_forward_chain(const Dims& d) { return chain_config(d) != nullptr ||
 // A wide chain launch reads x as operands, which a kernel ahead of it lays out for all its steps.
 static size_t x_step_bytes(const Dims& d) { return (size_t)d.BP * d.KX * d.op_bytes(); }
 int forward_chain_max_steps(const Dims& d) {
-  if (!runs_wide(d)) return RES_MAX_STEPS;
-  constexpr size_t X_MAX_BYTES = (size_t)32 << 20;
-  return (int)std::max<size_t>(16, std::min<size_t>(RES_MAX_STEPS, X_MAX_BYTES / x_step_bytes(d)));
+  return runs_wide(d) ? (int)std::min<size_t>(RES_MAX_STEPS, WIDE_X_BYTES / x_step_bytes(d)) : RES_MAX_STEPS;
 }
 size_t forward_chain_x_bytes(const Dims& d) { return runs_wide(d) ? forward_chain_max_steps(d) * x_step_bytes(d) : 0; }
 size_t forward_chain_ring_bytes(const Dims& d) { return (size_t)(runs_wide(d) ? WIDE_RING : RES_RING) * d.BP * d.KH * d.op_bytes(); }

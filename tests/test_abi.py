@@ -82,12 +82,13 @@ def _round_up(v, n):
     return (v + n - 1) // n * n
 
 
-def _wide_operand_bytes(desc):
-    """The largest of the arrays that the launches with weights spread over several XCDs address by 32-bit byte offsets:
-    the gate weights and the two transposed operands of the weight gradient."""
+def _wide_operands_fit(desc):
+    """The arrays that the launches with weights spread over several XCDs address by 32-bit byte offsets -- the gate weights and
+    the two transposed operands of the weight gradient -- below 2 GiB, and x of one step within its staging."""
     KX, KH, NX = _round_up(desc.I, 32), _round_up(desc.H, 32), _round_up(desc.I, 16)
     KC = _round_up(mb.mebptt_chunk_steps(desc) * desc.B, 32)
-    return max(4 * KH * (KX + KH) * 2, (NX + KH + 16) * KC * 2, 4 * KH * KC * 2)
+    largest = max(4 * KH * (KX + KH) * 2, (NX + KH + 16) * KC * 2, 4 * KH * KC * 2)
+    return largest < 1 << 31 and _round_up(desc.B, 16) * KX * 2 <= 32 << 20
 
 
 def test_launches_that_address_by_32_bits_are_not_used_beyond_them():
@@ -98,14 +99,41 @@ def test_launches_that_address_by_32_bits_are_not_used_beyond_them():
         def desc(I):
             return mb.make_desc(B, I, H, 10, 1, 0, 1, 0)
         lo, hi = 64, (1 << 31) // (4 * H) - H                     # hi: the widest input that is accepted
-        assert _wide_operand_bytes(desc(lo)) < 1 << 31 <= _wide_operand_bytes(desc(hi))
+        assert _wide_operands_fit(desc(lo)) and not _wide_operands_fit(desc(hi))
         while hi - lo > 1:
             mid = (lo + hi) // 2
-            if _wide_operand_bytes(desc(mid)) < 1 << 31:
+            if _wide_operands_fit(desc(mid)):
                 lo = mid
             else:
                 hi = mid
         assert mb.mebptt_stage_steps(desc(lo)) > 0 and mb.mebptt_stage_steps(desc(hi)) == 0, (B, H, lo)
         for I in (2 * hi, 3 * hi, (1 << 31) // (4 * H) - H):
             if 4 * H * (I + H) <= 1 << 31:
-                assert mb.mebptt_stage_steps(desc(I)) == 0 and mb.mebptt_workspace_bytes(desc(I)) > 1 << 31, (B, H, I)
+                assert mb.mebptt_stage_steps(desc(I)) == 0 and mb.mebptt_workspace_bytes(desc(I)) > 0, (B, H, I)
+
+
+def _common_workspace_bytes(desc):
+    """What the workspace of a bf16 LSTM holds on any shape, without the weight-gradient accumulator (which does not depend on B)."""
+    KX, KH, NX, BP = _round_up(desc.I, 32), _round_up(desc.H, 32), _round_up(desc.I, 16), _round_up(desc.B, 16)
+    G4, CH = 4 * KH, mb.mebptt_chunk_steps(desc)
+    KC = _round_up(CH * desc.B, 32)
+    weights = 2 * G4 * (KX + KH) + 4 * G4 + 2 * KH * G4 + 2 * NX * G4
+    return (weights + 9 * mb.mebptt_unit_bytes(desc) + 4 * desc.B * desc.H
+            + 2 * 2 * (CH * BP * G4 + G4 * KC + (NX + KH + 16) * KC))
+
+
+def test_staged_input_of_a_launch_is_at_most_32_mib():
+    """Chain launches with weights spread over several XCDs read x of all their steps as operands from the workspace: as
+    many steps as 32 MiB hold.  Seen in the workspace of the largest such batch, against that of a batch one larger, which has no
+    resident launches."""
+    for B, H, groups, nr in ((128, 2048, 2, 4), (256, 1024, 4, 4)):
+        for I in (512, 8192, 16384, 30000, 60000):
+            d, beyond = mb.make_desc(B, I, H, 10, 1, 0, 1, 0), mb.make_desc(B + 1, I, H, 10, 1, 0, 1, 0)
+            assert mb.mebptt_stage_steps(d) > 0 and mb.mebptt_stage_steps(beyond) == 0
+            more = (mb.mebptt_workspace_bytes(d) - _common_workspace_bytes(d)
+                    - mb.mebptt_workspace_bytes(beyond) + _common_workspace_bytes(beyond))
+            part = groups * (H // (16 * nr)) * 16 * (4 * nr * 64) * 4
+            rings = 8 * B * H * 2 + 8 * B * 4 * H * 2 + 4 * part + 4 * B * H
+            staged = more - rings - 3 * mb.mebptt_unit_bytes(d) * mb.mebptt_stage_steps(d)
+            step = B * _round_up(I, 32) * 2
+            assert abs(staged - min(192, (32 << 20) // step) * step) < 8192 and staged < (32 << 20) + 8192, (B, I, H, staged)
