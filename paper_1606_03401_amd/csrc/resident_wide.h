@@ -409,7 +409,7 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   f32x4* red = reinterpret_cast<f32x4*>(smem);                     // [4 waves][NR][NB] blocks
   T* wl = reinterpret_cast<T*>(red + RED);                    // [4][NR][NHL] fragments of W_hh, [4][NR][NXL] of W_ih
-  __shared__ int s_role, s_xcd, s_rank, s_fail;
+  __shared__ int s_role, s_xcd, s_rank, s_fail, s_here;   // s_here: not s_role again, which late waves may still read
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
   const int lrow = lane & 15;
   const int per = RES_GROUPS / p.groups;   // XCDs of a group
@@ -497,9 +497,9 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
 #pragma unroll
     for (int r = 0; r < NR; ++r) wx[i][r] = w.w.load(w.tile(r), i < nx ? wave + 4 * i : 0, i < nx);
   w.load(nh, [&](int i) { return nsx + h_step(i); });
-  if (threadIdx.x == 0) s_role = at(group).all_here(p.patience) ? WIDE_GO : WIDE_LEAVE;
+  if (threadIdx.x == 0) s_here = at(group).all_here(p.patience);
   __syncthreads();
-  if (__builtin_amdgcn_readfirstlane(s_role) != WIDE_GO) {
+  if (!__builtin_amdgcn_readfirstlane(s_here)) {
     at(group).leave();
     return;
   }
@@ -652,7 +652,7 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
   f32x4* red = reinterpret_cast<f32x4*>(smem);               // [4 waves][NR][NB] blocks
   T* wl = reinterpret_cast<T*>(red + RED);              // [4][NR][NHL] fragments
   T* kept = wl + (size_t)WIDE_WAVES * NR * NHL * FRAG;       // [5 UW][KROW]: rows 4 u + gate, then h_{s-1}
-  __shared__ int s_role, s_xcd, s_rank, s_fail;
+  __shared__ int s_role, s_xcd, s_rank, s_fail, s_here;   // s_here: not s_role again, which late waves may still read
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
   const int lrow = lane & 15;
   const int per = RES_GROUPS / p.groups, blocks = (p.HP + UB - 1) / UB;
@@ -734,9 +734,9 @@ __global__ __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(1,
   const int part = 4 * kq + wave, n = (nsteps - part + WIDE_BACK_PARTS - 1) / WIDE_BACK_PARTS;   // this wave's macro steps: part, part + 16, ...
   auto g_step = [&](int i) { return part + WIDE_BACK_PARTS * i; };
   w.load(n, g_step);
-  if (threadIdx.x == 0) s_role = at(group).all_here(p.patience) ? WIDE_GO : WIDE_LEAVE;
+  if (threadIdx.x == 0) s_here = at(group).all_here(p.patience);
   __syncthreads();
-  if (__builtin_amdgcn_readfirstlane(s_role) != WIDE_GO) {
+  if (!__builtin_amdgcn_readfirstlane(s_here)) {
     at(group).leave();
     return;
   }
