@@ -265,7 +265,7 @@ __device__ inline RawAct<VEC> load_raw_whole(const float* __restrict__ row, int 
 // stays near one workgroup per compute unit while every operand byte is reused as often as
 // possible; the choice depends on the shape only, never on the schedule.
 enum FwdConfig { FWD_TINY, FWD_SMALLK, FWD_B1, FWD_42, FWD_82 };
-enum BwdConfig { BWD_SMALLK, BWD_11, BWD_12, BWD_22 };
+enum BwdConfig { BWD_SMALLK, BWD_11, BWD_12, BWD_21, BWD_22 };
 constexpr int TARGET_WGS = 256;
 
 template <class T>
@@ -296,7 +296,7 @@ inline BwdConfig backward_config(const Dims& d) {
 // B = 128, t = 1000 54.5 -> 31 ms; H = 4096, B = 32 103.7 -> 51 ms).  The sums of more sequences do not fit beside the weights; up
 // to H = 1024 and B = 128 a copy per XCD fits, whose steps take 2 - 2.5 us for a wide one's 5 - 7.
 // The K splits of every kernel that runs a step of such a shape follow from what a compute unit's four
-// waves can add up: see paired_sum and WIDE_BACK_PARTS.
+// waves can add up: see WIDE_FWD_KS and sum_back_parts.
 struct WideShape {
   int groups, share, nr;
 };
@@ -321,6 +321,31 @@ inline WideShape wide_shape(const Dims& d) {
 }
 
 constexpr int WIDE_FWD_KS = 4;   // K split of a forward step of a wide shape
+// Tiles of a wide shape's launch-per-step kernels, which run it where resident launches do not (switched off, or fewer than 256
+// compute units), with the resident launches' K splits and so their bits.  unit groups x batch tiles of a workgroup, macro steps in
+// flight.  Four waves a workgroup instead of the other shapes' eight, so small tiles pay longer: 2 x 2 (a batch tile: 2 x 1) up to
+// half a workgroup per compute unit (us a launch, 4 x 2 against it: B = 8, H = 1100 5.5 / 4.5; B = 32, I = 512, H = 2048 12.7 / 10.4;
+// at B = 64, H = 1280, 160 workgroups, 7.1 / 9.6).  Four macro steps in flight instead of two where a workgroup has the compute
+// unit to itself and the x part of a wave is at least four long (it is fetched in whole fours): B = 64, I = 512, H = 2048
+// 13.0 -> 11.9, B = 32, I = 1024, H = 4096 30.2 -> 28.0; at B = 64, I = 128, H = 1280 7.1 -> 8.1.  8 x 2 where that still gives every
+// compute unit one: B = 128, I = 512, H = 2048 17.9 -> 16.4.  Gradient steps of 33 such shapes against eight waves and an eight-way
+// split: 0.70 - 1.00 of the time for 27 of them, 1.01 - 1.05 where a launch has exactly 256 large tiles (B = 128, H = 2048 2752 -> 2888
+// us), 1.08 at worst (B = 16, I = 700, H = 1536: rows of x that are no whole fragments).
+enum WideFwdConfig { WIDE_FWD_21, WIDE_FWD_22, WIDE_FWD_42_2, WIDE_FWD_42_4, WIDE_FWD_82 };
+inline WideFwdConfig wide_forward_config(const Dims& d) {
+  const int ngroups = d.HP / 4, bt = d.BP / 16, wgs = ((ngroups + 3) / 4) * ((bt + 1) / 2);
+  if (wgs <= TARGET_WGS / 2) return bt == 1 ? WIDE_FWD_21 : WIDE_FWD_22;
+  if (d.KX < 512) return WIDE_FWD_42_2;
+  if (((ngroups + 7) / 8) * ((bt + 1) / 2) >= TARGET_WGS) return WIDE_FWD_82;
+  return wgs <= TARGET_WGS ? WIDE_FWD_42_4 : WIDE_FWD_42_2;
+}
+// Backward: row tiles x batch tiles, the smallest of 1 x 1, 2 x 1, 2 x 2 that gives no compute unit two workgroups (us a launch, against
+// the other shapes' rule: B = 64, H = 1280 11.4 -> 10.4; B = 128, H = 1280 19.4 -> 15.0; B = 32, H = 4096 25.9 -> 25.2).
+inline BwdConfig wide_backward_config(const Dims& d) {
+  const int nt = d.HP / 16, bt = d.BP / 16;
+  if (nt * bt <= TARGET_WGS) return BWD_11;
+  return (nt + 1) / 2 * bt <= TARGET_WGS ? BWD_21 : BWD_22;
+}
 // Of a backward step of a wide shape: part p has the macro steps p, p + 16, ...; the parts 4q .. 4q + 3 are
 // the waves of one workgroup of a resident launch and are added first, then the four workgroups' sums.
 constexpr int WIDE_BACK_PARTS = 16;

@@ -658,16 +658,16 @@ constexpr int PAIR_FKS = 8, PAIR_NG = 4, PAIR_FU = 1, PAIR_BKS = 8, PAIR_BU = 4;
 // macro steps a wave keeps in flight, are smaller than the stand-alone kernels': two resident
 // workgroups share a compute unit's load path, and measured launch times fall as the queues get
 // shorter (large-K class: 9.98 us at FU, BU = 2, 8; 9.47 us at 1, 4; small-K class 12.2 -> 10.8 us).
-template <class T, int CELL, int FNG, int FKS, int FU, int BNT, int BBT, int BKS, int BU>
+template <class T, int CELL, int FNG, int FKS, int FU, int BNT, int BBT, int BKS, int BU, int PARTS = 1>
 __global__ __launch_bounds__(64 * (FKS > BKS ? FKS : BKS), 4) void pair_kernel(FwdParams f, BwdParams b, int nfx, int nf,
                                                                              int nbx) {
-  constexpr int FRED = forward_red_floats(FNG, 1, FKS), BRED = BKS * BNT * BBT * 4 * 64;
+  constexpr int FRED = forward_red_floats(FNG, 1, FKS), BRED = BKS * PARTS * BNT * BBT * 4 * 64;
   __shared__ __attribute__((aligned(16))) float red[FRED > BRED ? FRED : BRED];
   const int id = blockIdx.x;
   if (id < nf)
     forward_body<T, FNG, 1, FKS, FU, CELL>(f, id % nfx, id / nfx, red);
   else
-    backward_body<T, BNT, BBT, BKS, BU>(b, (id - nf) % nbx, (id - nf) / nbx, red);
+    backward_body<T, BNT, BBT, BKS, BU, PARTS>(b, (id - nf) % nbx, (id - nf) / nbx, red);
 }
 
 template <class T, int NG, int BT, int KS, int U>
@@ -683,7 +683,13 @@ static hipError_t launch_forward_cfg(const Dims& d, const FwdParams& p, hipStrea
 template <class T>
 static hipError_t launch_forward_t(const Dims& d, const FwdParams& p, hipStream_t st) {
   if constexpr (sizeof(T) == 2) {
-    if (wide_shape(d).groups) return launch_forward_cfg<T, 4, 2, WIDE_FWD_KS, 2>(d, p, st);   // without resident launches only
+    if (wide_shape(d).groups) switch (wide_forward_config(d)) {
+      case WIDE_FWD_21: return launch_forward_cfg<T, 2, 1, WIDE_FWD_KS, 5>(d, p, st);
+      case WIDE_FWD_22: return launch_forward_cfg<T, 2, 2, WIDE_FWD_KS, 4>(d, p, st);
+      case WIDE_FWD_42_2: return launch_forward_cfg<T, 4, 2, WIDE_FWD_KS, 2>(d, p, st);
+      case WIDE_FWD_42_4: return launch_forward_cfg<T, 4, 2, WIDE_FWD_KS, 4>(d, p, st);
+      case WIDE_FWD_82: return launch_forward_cfg<T, 8, 2, WIDE_FWD_KS, 4>(d, p, st);
+    }
   }
   switch (forward_config<T>(d)) {
     case FWD_TINY: return launch_forward_cfg<T, 1, 1, 4, 2>(d, p, st);   // tiny K: one small workgroup per tile
@@ -835,7 +841,8 @@ __global__ __launch_bounds__(512) void stream_panels_kernel(const uint4* __restr
 template <class T>
 static void forward_launch_shape(const Dims& d, int& ng, int& bt, int& ks) {
   if (wide_shape(d).groups) {
-    ng = 4, bt = 2, ks = WIDE_FWD_KS;
+    const WideFwdConfig c = wide_forward_config(d);
+    ng = c == WIDE_FWD_82 ? 8 : (c == WIDE_FWD_21 || c == WIDE_FWD_22 ? 2 : 4), bt = c == WIDE_FWD_21 ? 1 : 2, ks = WIDE_FWD_KS;
     return;
   }
   switch (forward_config<T>(d)) {
@@ -867,21 +874,22 @@ hipError_t launch_forward_stream(const Dims& d, const void* Wp, const void* act,
   return hipGetLastError();
 }
 
-template <class T, int NT, int BT, int KS, int U>
+template <class T, int NT, int BT, int KS, int U, int PARTS = 1>
 static hipError_t launch_backward_cfg(const Dims& d, const BwdParams& p, hipStream_t st) {
   dim3 grid((d.HP / 16 + NT - 1) / NT, (d.BP / 16 + BT - 1) / BT), block(64 * KS);
-  if constexpr (KS == 8 && sizeof(T) == 2) {
-    if (wide_shape(d).groups) {
-      backward_kernel<T, NT, BT, KS, U, 2><<<grid, block, 0, st>>>(p);
-      return hipGetLastError();
-    }
-  }
-  backward_kernel<T, NT, BT, KS, U, 1><<<grid, block, 0, st>>>(p);
+  backward_kernel<T, NT, BT, KS, U, PARTS><<<grid, block, 0, st>>>(p);
   return hipGetLastError();
 }
 
 template <class T>
 static hipError_t launch_backward_t(const Dims& d, const BwdParams& p, hipStream_t st) {
+  if constexpr (sizeof(T) == 2) {
+    if (wide_shape(d).groups) switch (wide_backward_config(d)) {
+      case BWD_11: return launch_backward_cfg<T, 1, 1, 8, PAIR_BU, 2>(d, p, st);
+      case BWD_21: return launch_backward_cfg<T, 2, 1, 8, 4, 2>(d, p, st);
+      default: return launch_backward_cfg<T, 2, 2, 8, 4, 2>(d, p, st);
+    }
+  }
   switch (backward_config<T>(d)) {
     case BWD_SMALLK: return launch_backward_cfg<T, 1, 1, 4, 4>(d, p, st);
     case BWD_22: return launch_backward_cfg<T, 2, 2, 8, 4>(d, p, st);
@@ -929,13 +937,14 @@ hipError_t launch_backward(const Dims& d, const BackwardArgs& a, hipStream_t st)
 }
 
 // Shape classes for which a fused launch is instantiated: 1 = large K (forward 4 x 1, backward
-// 1 x 1, 8 waves each); 2 = small-K forward (4 waves) with the 1 x 2 backward (8 waves).  0 = none.
+// 1 x 1, 8 waves each); 2 = small-K forward (4 waves) with the 1 x 2 backward (8 waves); 3 = as 1 with the K splits of
+// a wide shape (forward 2 x 1 by four waves: a gradient step without resident launches, B = 8, H = 1100 859 us apart, 741 fused,
+// B = 32, H = 2048 1975 and 1905).  0 = none.
 template <class T>
 static int pair_class(const Dims& d) {
-  if (wide_shape(d).groups) return 0;   // both go out in resident launches
   const FwdConfig fc = forward_config<T>(d);
   const BwdConfig bc = backward_config<T>(d);
-  if (fc == FWD_B1 && bc == BWD_11) return 1;
+  if (fc == FWD_B1 && bc == BWD_11) return wide_shape(d).groups ? 3 : 1;
   if (fc == FWD_SMALLK && bc == BWD_12) return 2;
   return 0;
 }
@@ -944,8 +953,17 @@ bool can_fuse_pair(const Dims& d) { return (d.dtype ? pair_class<__bf16>(d) : pa
 
 template <class T, int CELL>
 static void launch_pair_t(const Dims& d, const FwdParams& f, const BwdParams& b, hipStream_t st) {
-  const int nfx = (d.HP / 4 + PAIR_NG - 1) / PAIR_NG, nfy = d.BP / 16;   // both classes: forward 4 x 1
-  if (pair_class<T>(d) == 1) {
+  const int nfx = (d.HP / 4 + PAIR_NG - 1) / PAIR_NG, nfy = d.BP / 16;   // classes 1 and 2: forward 4 x 1
+  const int cls = pair_class<T>(d);
+  if constexpr (sizeof(T) == 2) {
+    if (cls == 3) {
+      const int nwx = (d.HP / 4 + 1) / 2, nbx = d.HP / 16, nby = d.BP / 16;
+      pair_kernel<T, CELL, 2, WIDE_FWD_KS, 2, 1, 1, PAIR_BKS, PAIR_BU, 2>
+          <<<dim3(nwx * nfy + nbx * nby), dim3(64 * PAIR_BKS), 0, st>>>(f, b, nwx, nwx * nfy, nbx);
+      return;
+    }
+  }
+  if (cls == 1) {
     const int nbx = d.HP / 16, nby = d.BP / 16;
     pair_kernel<T, CELL, PAIR_NG, PAIR_FKS, PAIR_FU, 1, 1, PAIR_BKS, PAIR_BU>
         <<<dim3(nfx * nfy + nbx * nby), dim3(64 * PAIR_BKS), 0, st>>>(f, b, nfx, nfx * nfy, nbx);

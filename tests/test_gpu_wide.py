@@ -51,6 +51,42 @@ def test_every_instantiation(B, I, H, cell):
         assert prof.sweep_steps == t and prof.chain_steps + prof.batch_steps == out.stats.forward_ops
 
 
+# (B, I, H), forward tile (unit groups x batch tiles, macro steps in flight), backward tile, whether steps are fused
+PER_STEP = [(8, 64, 1100, True),       # 2 x 1; 1 x 1
+            (1, 700, 1537, True),      # the same, rows of x that are no whole fragments
+            (20, 33, 1056, True),      # 2 x 2; 1 x 1
+            (32, 512, 2048, True),     # the same, as many workgroups as that tile is used for
+            (40, 520, 2040, False),    # 4 x 2, four; 2 x 1
+            (61, 130, 1270, True),     # 4 x 2, two; 2 x 1
+            (129, 64, 600, True),      # the same, four groups of XCDs
+            (100, 100, 1500, False),   # 4 x 2, two; 2 x 2
+            (120, 513, 2041, False),   # 8 x 2; 2 x 2
+            (250, 520, 1000, False)]   # the same, four groups of XCDs
+
+
+@pytest.mark.parametrize("cell", [0, 1], ids=["lstm", "gru"])
+@pytest.mark.parametrize("B,I,H,fused", PER_STEP)
+def test_launch_per_step_kernels(B, I, H, fused, cell):
+    """What runs these shapes where resident launches do not: every tile, alone and fused, the same bits as the wide launches."""
+    from paper_1606_03401_amd.session import Session
+    w = _workload(B, I, H, 9, cell)
+    inp = wl.make_inputs(w, nonzero_state=True, nonzero_bias=True)
+    want = _run(w, inp, wl.KIND_HSM, 3, chain=True)
+    mb.mebptt_forward_chain_enable(False)
+    try:
+        for kind, m in ((wl.KIND_HSM, 3), (wl.KIND_ISM, 9)):
+            s = Session(w, inp, kind=kind, m=m)
+            mb.mebptt_profile_enable(1)
+            out = s.run_and_fetch()
+            prof = mb.mebptt_profile_collect()
+            mb.mebptt_profile_enable(0)
+            _same(out, want, (kind, m))
+            pairs = prof.launches[5]
+            assert (pairs > 0) == (fused and kind == wl.KIND_HSM) and prof.chain_steps + prof.sweep_steps + prof.batch_steps == 0
+    finally:
+        mb.mebptt_forward_chain_enable(True)
+
+
 @pytest.mark.parametrize("B,I,H", [(3, 20, 1056), (40, 40, 1100)])
 def test_chains_longer_than_a_launch(B, I, H):
     """More steps than one launch carries and several chunks of time-batched work, every strategy."""
