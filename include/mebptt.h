@@ -355,7 +355,7 @@ int mebptt_run_prepared(const mebptt_lstm_desc* desc, const mebptt_plan_t* plan,
  * 4096 with B up to 32 (I of at least 8, operands below 2 GiB) have "wide" launches: chains and sweeps on stored
  * internal states whose weights are spread once over a quarter, a half or all of the device, which then exchange across XCDs.
  * Every forward and backward operation of these shapes runs in such a launch (the independent ones in
- * forward batches).  Results are bit-identical to the launch-per-step path.  The workgroups of
+ * forward batches), but for sequences of one or two steps and, where states are recomputed again and again, of up to five.  Results are bit-identical to the launch-per-step path.  The workgroups of
  * such a launch that share an XCD (wide: that part of the device) wait for each other and have to be on the chip together.  Where other work (another
  * stream, the replay of a captured graph, another process, perhaps another such launch) keeps some of them
  * off it, the launch is given up for that XCD (that part) after a while and one workgroup there runs its steps alone: the same

@@ -802,7 +802,17 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
     g_prof.open.cls = -1;
   }
 
-  const bool resident_ok = mode != RUN_STATIC && g_chain_enabled && device_fits_resident_launches();
+  // Wide launches fetch their weights and meet before their first step, and their exchange slots have to be filled: sequences of one
+  // or two steps, and of up to five that are recomputed in runs of one to three steps, go out a launch per step.  A gradient step,
+  // wide / per step: B = 200, H = 768, t = 1 124 / 99 us, t = 2 154 / 126, t = 3 and one state stored 184 / 162, all stored 148 / 144,
+  // t = 6 and one stored 327 / 313, t = 8 439 / 451; B = 8, H = 1100, t = 5 and one stored 206 / 174, B = 128, H = 2048 628 / 617.
+  auto short_for_wide = [&]() {
+    if (t > 5 || !runs_wide(d)) return false;
+    int64_t ops = 0;
+    for (const mebptt_op& op : plan->ops) ops += op.op == MEBPTT_OP_FWD_RUN ? op.count : 0;
+    return t <= 2 || ops >= 2 * t;
+  };
+  const bool resident_ok = mode != RUN_STATIC && g_chain_enabled && !short_for_wide() && device_fits_resident_launches();
   const size_t ring_fill = resident_ok ? w.ring_bytes : 0;   // the no-allocation path's workspace ends before the ring
 
   // Set-up: operand copies of the weights, zeroed staging (the padding must stay zero), start state.

@@ -87,6 +87,24 @@ def test_launch_per_step_kernels(B, I, H, fused, cell):
         mb.mebptt_forward_chain_enable(True)
 
 
+@pytest.mark.parametrize("B,I,H", [(20, 60, 1100), (140, 80, 600)])
+def test_short_sequences_go_out_a_launch_per_step(B, I, H):
+    """One or two steps, and up to five that are recomputed again and again; the same bits either way."""
+    from paper_1606_03401_amd.session import Session
+    for t, kind, m, wide in ((1, wl.KIND_HSM, 1, False), (1, wl.KIND_ISM, 1, False), (2, wl.KIND_HSM, 2, False), (2, wl.KIND_ISM, 2, False),
+                             (3, wl.KIND_HSM, 1, False), (3, wl.KIND_ISM, 3, True), (5, wl.KIND_ISM, 1, False), (5, wl.KIND_HSM, 5, True),
+                             (6, wl.KIND_HSM, 1, True)):
+        w = _workload(B, I, H, t, 0).scaled(dy_first_step=1)
+        inp = wl.make_inputs(w, nonzero_state=True, nonzero_bias=True)
+        s = Session(w, inp, kind=kind, m=m)
+        mb.mebptt_profile_enable(1)
+        out = s.run_and_fetch()
+        prof = mb.mebptt_profile_collect()
+        mb.mebptt_profile_enable(0)
+        assert (prof.chain_steps + prof.batch_steps + prof.sweep_steps > 0) == wide, (t, kind, m)
+        _same(out, _run(w, inp, kind, m, chain=False), (t, kind, m))
+
+
 @pytest.mark.parametrize("B,I,H", [(3, 20, 1056), (40, 40, 1100)])
 def test_chains_longer_than_a_launch(B, I, H):
     """More steps than one launch carries and several chunks of time-batched work, every strategy."""
