@@ -160,6 +160,10 @@ __device__ inline void init_state_part(const Dims& d, const float* __restrict__ 
 // copies of the weights, the next nfill the cleared staging and the exchange rings, the rest the start state; none reads
 // what another writes.  Three launches before; with dc_0 written by wgrad_finish_kernel a gradient step of
 // H = 32, t = 20 164 -> 159 us, others 6 - 12 us less.
+// Large weights go ahead alone: with the fills behind them in one launch they take longer than in turn (H = 3000, I = 128: 303 us, apart
+// 247 + 37).  A gradient step of a single time step, together / apart: H = 1600, I = 512 196 / 213 us, H = 2048, I = 512 387 / 395 (42 million
+// elements), H = 3000, I = 128 587 / 569 (75 million), H = 4096, I = 1024 1249 / 1235.
+constexpr size_t SETUP_APART = (size_t)1 << 26;   // elements of the operand copies
 struct SetupParams {
   Dims d;
   const float *W_ih, *W_hh, *b;
@@ -201,14 +205,24 @@ hipError_t launch_setup(const Dims& d, const SetupArgs& a, hipStream_t st) {
   p.c0 = a.c0;
   p.state = a.state;
   auto blocks = [](size_t n, size_t most) { return (int)std::min<size_t>((n + 255) / 256, most); };
-  p.nprep = a.W_ih ? blocks((size_t)d.G4 * d.KP + (size_t)d.HP * d.G4 + (size_t)d.NX * d.G4 + d.G4, 2048) : 0;
-  p.nfill = blocks(p.n_zero + p.n_empty, 4096);
-  const dim3 grid(p.nprep + p.nfill + (a.state ? blocks((size_t)d.B * d.KH, 2048) : 0));
-  if (d.dtype)
-    setup_kernel<__bf16><<<grid, dim3(256), 0, st>>>(p);
-  else
-    setup_kernel<float><<<grid, dim3(256), 0, st>>>(p);
-  return hipGetLastError();
+  const size_t nweights = (size_t)d.G4 * d.KP + (size_t)d.HP * d.G4 + (size_t)d.NX * d.G4 + d.G4;
+  const int nprep = a.W_ih ? blocks(nweights, 2048) : 0, nfill = blocks(p.n_zero + p.n_empty, 4096);
+  const int ninit = a.state ? blocks((size_t)d.B * d.KH, 2048) : 0;
+  auto launch = [&](int prep, int fill, int init) {
+    p.nprep = prep;
+    p.nfill = fill;
+    if (prep + fill + init == 0) return hipSuccess;
+    if (d.dtype)
+      setup_kernel<__bf16><<<dim3(prep + fill + init), dim3(256), 0, st>>>(p);
+    else
+      setup_kernel<float><<<dim3(prep + fill + init), dim3(256), 0, st>>>(p);
+    return hipGetLastError();
+  };
+  if (nprep && nweights >= SETUP_APART) {
+    const hipError_t e = launch(nprep, 0, 0);
+    return e == hipSuccess ? launch(0, nfill, ninit) : e;
+  }
+  return launch(nprep, nfill, ninit);
 }
 
 // ---- forward step: gate GEMM + LSTM pointwise -------------------------------------------------
