@@ -1594,21 +1594,26 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const T* __restrict__ dGT, c
 // The accumulator's column NX + HP (operand row of ones) holds the bias gradient.  ngates = 4
 // (LSTM: db [4H]) or 3 (GRU: db = [db_ih | db_hh], 6H); the packed row of a gate block differs
 // between the input and the recurrent side for the GRU (packed_gate_x / packed_gate_h).
+// The first `nw` blocks do this, those behind them write the start state's gradients, whose arguments take scalar registers: seven
+// waves per SIMD instead of eight.  2048 blocks, which filled eight, then leave an eighth part to wait for the others; 8192 do
+// not (H = 3000, I = 128 121 us without the start state's part, 141 with it, 114 with 8192 blocks; H = 4096 325, 330, 209).
 __global__ void wgrad_finish_kernel(const float* __restrict__ dWacc, int WT, int grid_y, int nsplit, size_t split_stride,
                                     int NX, int HP, int I, int H, int cell, float* __restrict__ dW_ih,
                                     float* __restrict__ dW_hh, float* __restrict__ db, int blocks, const float* __restrict__ dc,
-                                    float* __restrict__ dh0, float* __restrict__ dc0, size_t plane) {
+                                    float* __restrict__ dh0, float* __restrict__ dc0, size_t plane, unsigned nw) {
   const int ngates = cell ? 3 : 4;
   const size_t nih = (size_t)ngates * H * I, nhh = (size_t)ngates * H * H, nb = (size_t)(cell ? 6 : 4) * H;
   const size_t total = nih + nhh + nb;
-  const size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total + plane; idx += stride) {
-    if (idx >= total) {   // the start state's gradients from the running plane (dh0 holds dG_1 W_hh already)
-      const size_t e = idx - total;
+  const size_t stride = (size_t)nw * blockDim.x;
+  if (blockIdx.x >= nw) {   // the start state's gradients from the running plane (dh0 holds dG_1 W_hh already)
+    const size_t e = (size_t)(blockIdx.x - nw) * blockDim.x + threadIdx.x;
+    if (e < plane) {
       if (cell) dh0[e] += dc[e];
       dc0[e] = cell ? 0.0f : dc[e];
-      continue;
     }
+    return;
+  }
+  for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += stride) {
     int row, np;
     bool recurrent;
     float* dst;
@@ -1731,19 +1736,22 @@ hipError_t launch_wgrad(const Dims& d, const void* dGT, const void* aT, int nslo
 hipError_t launch_wgrad_finish(const Dims& d, const float* dWacc, float* dW_ih, float* dW_hh, float* db, const float* dc,
                                float* dh0, float* dc0, hipStream_t st) {
   const size_t plane = (size_t)d.B * d.H;
+  const size_t values = (size_t)(d.cell ? 3 : 4) * d.H * ((size_t)d.I + d.H) + (size_t)(d.cell ? 6 : 4) * d.H;
+  const unsigned nw = (unsigned)std::min<size_t>((values + 255) / 256, 8192);
+  const dim3 grid(nw + (unsigned)((plane + 255) / 256));
   if (wgrad_uses_big_tiles(d)) {
     const int gx = (d.G4 / 16 + 15) / 16, gy = (d.NA / 16 + 15) / 16;
     int full, split;
     tgemm_shares(gx * gy, full, split);
     // nsplit and split_stride: here the shares of the left-over blocks and the first of those blocks
-    wgrad_finish_kernel<<<dim3(2048), dim3(256), 0, st>>>(dWacc, 0, gy, split, (size_t)full, d.NX, d.HP, d.I, d.H, d.cell,
-                                                          dW_ih, dW_hh, db, gx * gy, dc, dh0, dc0, plane);
+    wgrad_finish_kernel<<<grid, dim3(256), 0, st>>>(dWacc, 0, gy, split, (size_t)full, d.NX, d.HP, d.I, d.H, d.cell,
+                                                          dW_ih, dW_hh, db, gx * gy, dc, dh0, dc0, plane, nw);
     return hipGetLastError();
   }
   const int WT = wgrad_wave_tile(d);
   const int grid_y = (d.NA / 16 + 2 * WT - 1) / (2 * WT);
-  wgrad_finish_kernel<<<dim3(2048), dim3(256), 0, st>>>(dWacc, WT, grid_y, wgrad_splits(d), wgrad_partial_floats(d), d.NX, d.HP,
-                                                        d.I, d.H, d.cell, dW_ih, dW_hh, db, 0, dc, dh0, dc0, plane);
+  wgrad_finish_kernel<<<grid, dim3(256), 0, st>>>(dWacc, WT, grid_y, wgrad_splits(d), wgrad_partial_floats(d), d.NX, d.HP,
+                                                        d.I, d.H, d.cell, dW_ih, dW_hh, db, 0, dc, dh0, dc0, plane, nw);
   return hipGetLastError();
 }
 
