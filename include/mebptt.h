@@ -352,7 +352,7 @@ int mebptt_run_prepared(const mebptt_lstm_desc* desc, const mebptt_plan_t* plan,
  * internal states in the workspace's stage, followed by one sweep launch of
  * backward operations on them; backward operations on internal states stored in slots go out as
  * such sweep launches as well.  With bf16 operands, H up to 1024 with B of 129 to 256, H up to 2048 with B up to 128 and H up to
- * 4096 with B up to 32 (I of at least 8, operands below 2 GiB) have "wide" launches: chains and sweeps on stored
+ * 4096 with B up to 32 (I of at least 8, operands below 2 GiB, and on some shapes with B up to 32 I up to 4096) have "wide" launches: chains and sweeps on stored
  * internal states whose weights are spread once over a quarter, a half or all of the device, which then exchange across XCDs.
  * Every forward and backward operation of these shapes runs in such a launch (the independent ones in
  * forward batches), but for sequences of one or two steps and, where states are recomputed again and again, of up to five.  Results are bit-identical to the launch-per-step path.  The workgroups of

@@ -314,6 +314,13 @@ inline WideShape wide_shape(const Dims& d) {
   constexpr size_t LIMIT = (size_t)1 << 31;
   if ((size_t)d.G4 * d.KP * 2 >= LIMIT || (size_t)d.G4 * d.KC * 2 >= LIMIT || (size_t)d.NA * d.KC * 2 >= LIMIT) return w;
   if ((size_t)d.BP * d.KX * 2 > WIDE_X_BYTES) return w;   // not one step's x fits the staging
+  // Weights of x beyond what stays on the chip are streamed in every step, by one wave per SIMD with three macro steps in flight;
+  // where a batch is small and half of the device streams them all, launches per step with eight waves a compute unit
+  // are as fast from I = 4096 on.  A gradient step of t = 40, wide against per step: B = 1, H = 2048, I = 4096 0.95, 5000 1.03, 10000
+  // 1.14; B = 1, I = 10000, H = 1792 1.11, H = 1536 1.04, H = 1280 0.98; B = 32, H = 2048, I = 4096 0.93, 6000 1.04, 10000 1.10, H = 1536
+  // 0.96.  (With two batch tiles only if both tiles of a row land on one XCD, or the launches per step fetch the weights
+  // twice: H = 1600, 1856, 1984 0.82 - 0.83.  More sequences, wider states, more groups: 0.55 - 0.97 at any I measured, to 24576.)
+  if (groups == 2 && d.KX > 4096 && (d.BP == 16 ? d.KH > 1280 : d.BP == 32 && d.KH > 1536 && d.HP % 128 == 0)) return w;
   w.groups = groups;
   w.share = round_up((d.B + groups - 1) / groups, 16);
   w.nr = (d.KH * groups + 1023) / 1024;

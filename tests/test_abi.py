@@ -112,6 +112,16 @@ def test_launches_that_address_by_32_bits_are_not_used_beyond_them():
                 assert mb.mebptt_stage_steps(desc(I)) == 0 and mb.mebptt_workspace_bytes(desc(I)) > 0, (B, H, I)
 
 
+def test_small_batches_of_very_wide_inputs_have_no_wide_launches():
+    """The line beyond which streaming the input's weights through them is slower than a launch per step."""
+    def stage(B, I, H):
+        return mb.mebptt_stage_steps(mb.make_desc(B, I, H, 10, 1, 0, 1, 0))
+    for B, H in ((1, 2048), (16, 1281), (9, 1600), (17, 2048), (32, 1537 + 127), (32, 1770)):
+        assert stage(B, 4096, H) > 0 and stage(B, 4097, H) == 0
+    for B, H in ((33, 2048), (16, 1280), (32, 1536), (32, 1600), (20, 2000), (32, 2049), (130, 1000)):
+        assert stage(B, 4097, H) > 0 and stage(B, 30000, H) > 0
+
+
 def _common_workspace_bytes(desc):
     """What the workspace of a bf16 LSTM holds on any shape, without the weight-gradient accumulator (which does not depend on B)."""
     KX, KH, NX, BP = _round_up(desc.I, 32), _round_up(desc.H, 32), _round_up(desc.I, 16), _round_up(desc.B, 16)
