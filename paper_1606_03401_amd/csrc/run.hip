@@ -1058,9 +1058,10 @@ int run_impl(RunMode mode, const mebptt_lstm_desc* desc, const mebptt_plan_t* pl
     const mebptt_op& op = ops[oi];
     // A backward operation whose internal state a forward run has just left in the working core,
     // followed by such pairs for the steps below it, leads their launch: it is the first step of
-    // the sweep launch, on the state in the core, the others on the states in the stage.
+    // the sweep launch, on the state in the core, the others on the states in the stage.  (Pairs that start from a
+    // state in no slot are not batched, and nothing leads them.)
     const bool lead = batch_ok && op.op == MEBPTT_OP_BWD && op.dst == MEBPTT_LOC_CORE && pair_at(oi + 1) &&
-                      ops[oi + 1].step == op.step - 1;
+                      ops[oi + 1].step == op.step - 1 && ops[oi + 1].src >= 0;
     if (bsweep_ok && !lead && (wide ? op.op == MEBPTT_OP_BWD : stored_bwd_at(oi) && stored_bwd_at(oi + 1))) {
       const int s_hi = op.step, chunk = (s_hi - 1) / CH;
       int n = 0;

@@ -87,6 +87,24 @@ def test_launch_per_step_kernels(B, I, H, fused, cell):
         mb.mebptt_forward_chain_enable(True)
 
 
+@pytest.mark.parametrize("cell", [0, 1], ids=["lstm", "gru"])
+def test_every_backward_step_goes_out_in_a_sweep(cell):
+    """Also the last but one of a stretch whose first state is the run's start, which is in no slot."""
+    from paper_1606_03401_amd.session import Session
+    w = _workload(18, 40, 1100, 12, cell)
+    inp = wl.make_inputs(w, nonzero_state=True, nonzero_bias=True)
+    base = _run(w, inp, wl.KIND_ISM, 1, chain=False)
+    for kind, m in ((wl.KIND_ISM, 1), (wl.KIND_ISM, 2), (wl.KIND_ISM, 3), (wl.KIND_HSM, 1), (wl.KIND_MSM, 2), (wl.KIND_MSM, 5)):
+        s = Session(w, inp, kind=kind, m=m)
+        mb.mebptt_profile_enable(1)
+        out = s.run_and_fetch()
+        prof = mb.mebptt_profile_collect()
+        mb.mebptt_profile_enable(0)
+        _same(out, base, (kind, m))
+        assert prof.sweep_steps == w.t and prof.launches[1] == 0, (kind, m)
+        assert prof.chain_steps + prof.batch_steps == out.stats.forward_ops and prof.launches[0] == 0, (kind, m)
+
+
 @pytest.mark.parametrize("B,I,H", [(20, 60, 1100), (140, 80, 600)])
 def test_short_sequences_go_out_a_launch_per_step(B, I, H):
     """One or two steps, and up to five that are recomputed again and again; the same bits either way."""
