@@ -1,31 +1,32 @@
 """GPU tests of the wide resident launches (weights spread once over the device or a part of it, exchange across
-XCDs): bit for bit the launch-per-step path on every instantiation, at the edges of its range, for every strategy,
-however the launches come about (together, one workgroup alone, given up by some), and in replays of graphs."""
+XCDs): against the float64 oracle, bit for bit the launch-per-step path on every instantiation, at the edges of its range, for
+every strategy, however the launches come about (together, one workgroup alone, given up by some), on infinities and NaNs, and in
+replays of graphs."""
 import numpy as np
 import pytest
 
 from paper_1606_03401_amd import binding as mb
 from paper_1606_03401_amd import workloads as wl
+import test_gpu_chain
 from test_gpu_chain import _run, _same
 
 pytestmark = pytest.mark.gpu
 
-# (B, I, H): row tiles per compute unit and batch tiles x halves of a group in the comment.  Widths that are a multiple of
-# nothing, rows of x shorter than a macro step and wider than the weights of x that stay in LDS, batches that leave a
-# second half, a batch tile or a whole group empty.
+# (B, I, H): row tiles and batch tiles of a compute unit in the comment.  Widths that are a multiple of nothing, rows of x
+# shorter than a macro step and wider than the weights of x that stay on the chip, batches that leave a part of a batch tile, whole
+# batch tiles or a whole group empty.
 SHAPES = [
-    (129, 130, 530), (256, 64, 768), (200, 700, 601),             # 3, 2 x 2, four groups
-    (130, 77, 700), (193, 40, 800), (256, 256, 1024), (140, 1100, 1001),   # (3 and) 4, 2 x 2, four groups
-    (1, 8, 1025), (20, 100, 1301), (32, 256, 1536),               # 3, 1 x 1, two groups
-    (33, 9, 1100), (50, 513, 1499),                               # 3, 1 x 2
-    (65, 60, 1057), (128, 128, 1280), (100, 333, 1500),           # 3, 2 x 2
-    (5, 64, 1700), (32, 900, 1601),                               # 4, 1 x 1
-    (40, 128, 1990), (64, 512, 2048),                             # 4, 1 x 2
-    (70, 31, 1537), (100, 640, 2001), (128, 512, 2048),           # 4, 2 x 2
-    (9, 65, 2050), (16, 200, 3000), (17, 64, 3071), (32, 300, 2560),   # 3, one group
-    (7, 40, 3073), (16, 128, 4000), (20, 33, 3301), (32, 96, 4096),    # 4, one group
+    (129, 130, 530), (256, 64, 768), (200, 700, 601),             # 3 x 4, four groups
+    (130, 77, 700), (193, 40, 800), (256, 256, 1024), (140, 1100, 1001),   # (3 and) 4 x 4, four groups
+    (1, 8, 1025), (20, 100, 1301), (32, 256, 1536),               # 3 x 1, two groups
+    (33, 9, 1100), (50, 513, 1499),                               # 3 x 2
+    (65, 60, 1057), (128, 128, 1280), (100, 333, 1500),           # 3 x 4
+    (5, 64, 1700), (32, 900, 1601),                               # 4 x 1
+    (40, 128, 1990), (64, 512, 2048),                             # 4 x 2
+    (70, 31, 1537), (100, 640, 2001), (128, 512, 2048),           # 4 x 4
+    (9, 65, 2050), (16, 200, 3000), (17, 64, 3071), (32, 300, 2560),   # 3 x 1 and 3 x 2, one group
+    (7, 40, 3073), (16, 128, 4000), (20, 33, 3301), (32, 96, 4096),    # 4 x 1 and 4 x 2, one group
 ]
-
 
 def _workload(B, I, H, t, cell, **kw):
     return wl.Workload("wide", B=B, I=I, H=H, t=t, kind=wl.KIND_ISM, m=4, gemm_dtype=wl.GEMM_BF16, loss=wl.LOSS_EXTERNAL_DY,
@@ -49,6 +50,30 @@ def test_every_instantiation(B, I, H, cell):
         mb.mebptt_profile_enable(0)
         _same(out, base, (kind, m))
         assert prof.sweep_steps == t and prof.chain_steps + prof.batch_steps == out.stats.forward_ops
+
+
+@pytest.mark.parametrize("cell", [0, 1], ids=["lstm", "gru"])
+@pytest.mark.parametrize("B,I,H", [(130, 77, 700), (33, 1100, 1101), (66, 40, 1600), (9, 65, 2050), (20, 33, 3301)])
+def test_against_the_oracle(B, I, H, cell):
+    """One, two and four groups of XCDs, one, two and four batch tiles, weights that are fetched again in every step."""
+    from test_gpu_parity import TOL, check_against_oracle, oracle_gradients
+    w = _workload(B, I, H, 6, cell)
+    inp = wl.make_inputs(w, nonzero_state=True, nonzero_bias=True)
+    ref = oracle_gradients(w, inp)
+    for kind, m in ((wl.KIND_ISM, 2), (wl.KIND_HSM, 6)):
+        check_against_oracle(w, inp, _run(w, inp, kind, m, chain=True), ref, TOL[w.gemm_dtype], label=f"wide {B}x{I}x{H} {cell}: ")
+
+
+@pytest.mark.parametrize("B,I,H", [(40, 64, 1100), (130, 77, 700), (20, 40, 2051)])
+def test_every_nan_is_passed_on(B, I, H):
+    test_gpu_chain.test_resident_launches_pass_on_every_nan(wl.GEMM_BF16, B, I, H)
+
+
+def test_input_wider_than_a_launch_stages():
+    """x of seven steps fills the staging: a chain of eleven goes out in two launches, nearly all weights of x streamed."""
+    w = _workload(128, 16500, 1040, 11, 0)
+    inp = wl.make_inputs(w, nonzero_state=True, nonzero_bias=True)
+    _same(_run(w, inp, wl.KIND_ISM, 4, chain=True), _run(w, inp, wl.KIND_ISM, 4, chain=False))
 
 
 # (B, I, H), forward tile (unit groups x batch tiles, macro steps in flight), backward tile, whether steps are fused
