@@ -5,12 +5,13 @@
 
 A "step" is one call of ``mebptt_run``: every forward operation, every recomputation and every
 backward operation of the schedule for one batch of synthetic sequences.  Inputs are resident in
-device memory before the timed region.  Prints ONE JSON line on stdout (everything else goes to
+device memory before the timed region.  Prints ONE short JSON line on stdout (everything else goes to
 stderr): throughput in time-steps/s at the named budget, the measured and theoretical cost
 ratio against store-everything BPTT, the roofline position of the dominant kernel measured
-with HIP events on the run's stream, and the CPU oracle timed on this host as a baseline.  Unless
---only is given the same line carries `configs` (every named configuration, a few steps each,
-config 5 at each budget of its sweep) and `fig2b` (the shape of the paper's timing experiment).
+with HIP events on the run's stream, and the CPU oracle timed on this host as a baseline; unless
+--only is given, also the milliseconds per step of every named configuration (a few steps each, config 5 at each
+budget of its sweep).  All details, with the shape of the paper's timing experiment (`fig2b`), are one JSON line on
+stderr, behind "[bench] details ".
 """
 from __future__ import annotations
 
@@ -445,6 +446,30 @@ def floors(args) -> int:
     return 0
 
 
+LINE_BYTES = 1900   # what keeps only the end of a program's output keeps the whole line
+
+
+def summary(result):
+    """The line on stdout: what names and places the headline value, without the details."""
+    r4 = lambda v: float(f"{v:.4g}") if isinstance(v, float) else v
+    out = {k: result[k] for k in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better",
+                                  "scaling", "vs_baseline", "dtype", "data", "config")}
+    out["host_enqueue_ms"] = r4(result["host_enqueue_ms"])
+    out["cost_ratio_vs_store_all"] = {k: r4(v) for k, v in result["cost_ratio_vs_store_all"].items()}
+    roof = result.get("roofline")
+    if roof:
+        out["roofline"] = {k: r4(roof[k]) for k in ("bound", "kernel", "achieved", "peak", "unit", "frac", "traffic")}
+    cpu = result.get("cpu_baseline")
+    if cpu:
+        out["cpu_baseline"] = {k: r4(cpu[k]) for k in ("value", "unit", "cores", "kind", "sample")}
+    if "configs" in result:
+        out["configs_ms_per_step"] = {f"{c['name']} m={c['budget_m']}": r4(c["ms_per_step"]) for c in result["configs"]}
+    for extra in ("cpu_baseline", "roofline", "configs_ms_per_step"):
+        if len(json.dumps(out)) > LINE_BYTES:
+            out.pop(extra, None)
+    return out
+
+
 def main() -> int:
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -546,7 +571,8 @@ def main() -> int:
         "ms_per_step_stream_launches": head["ms_per_step_stream_launches"], "ms_per_step_graph_replay": head["ms_per_step_graph_replay"],
         "host_enqueue_ms": head["host_enqueue_ms"], "higher_is_better": True,
         "scaling": "weak", "vs_baseline": None, "dtype": head["dtype"], "data": "synthetic",
-        "config": {"workload": head["workload"], "launch": head["launch"], "budget_m": head["budget_m"],
+        "config": {"model": f"{'GRU' if w.cell else 'LSTM'} {w.I}->{w.H}", "global_batch": w.B, "seq_len": w.t, "parallelism": "one GPU",
+                   "workload": head["workload"], "launch": head["launch"], "budget_m": head["budget_m"],
                    "forward_ops": head["forward_ops"], "peak_slots": head["peak_slots"],
                    "slot_pool_bytes": head["memory"]["slot_pool_bytes"], "workspace_bytes": head["memory"]["workspace_bytes"]},
         "cost_ratio_vs_store_all": head["cost_ratio_vs_store_all"],
@@ -588,7 +614,8 @@ def main() -> int:
         result["configs"] = configs
         result["fig2b"] = {"shape": "LSTM I=256 H=256 B=64, bf16 GEMM operands, HSM budgets and store-all",
                            "rows": fig2b_rows(3, 1)}
-    print(json.dumps(result), flush=True)
+    log("[bench] details " + json.dumps(result))
+    print(json.dumps(summary(result)), flush=True)
     return 0
 
 
