@@ -52,7 +52,7 @@ struct Mma<float> {
 // else to do between two exchanges: a gradient step of H = 1024, B = 64 10.67 -> 10.49 ms, of H = 512, B = 256 107.0 -> 104.5.
 // With fp32 operands both keep the division: tanh alone with it is worth -1 - +1 % over eleven shapes (H = 100, B = 24, t = 150
 // 1322 -> 1335 us), neither makes the launches with forward operations of H = 256, B = 32 5 % slower (1705 -> 1795 us a gradient
-// step; not found why).
+// step; unexplained).
 __device__ inline float reciprocal(float d) {   // of d >= 1, infinity included
   const float r = __builtin_amdgcn_rcpf(d);
   return d < 3e38f ? __fmaf_rn(__fmaf_rn(-d, r, 1.0f), r, r) : r;
@@ -292,8 +292,9 @@ inline BwdConfig backward_config(const Dims& d) {
 // Shapes whose resident launches spread one copy of the weights over `groups` equal parts of the device (see
 // resident_wide.h): bf16 operands too wide, or batches too large, for a copy per XCD.  groups parts of 256 / groups
 // compute units each take `share` sequences; a compute unit has nr 16-row tiles of a product's rows.  groups 0: not such
-// a shape.  Against a launch per step, a gradient step of 22 shapes of these ranges takes 0.40 - 0.87 of the time (H = 2048,
-// B = 128, t = 1000 54.5 -> 31 ms; H = 4096, B = 32 103.7 -> 51 ms).  The sums of more sequences do not fit beside the weights; up
+// a shape.  Against a launch per step with eight-way split sums, a gradient step of 121 calls in these ranges takes 0.48 - 0.99 of the
+// time (H = 2048, B = 128, t = 1000 54.5 -> 32.3 ms; H = 4096, B = 32 103.8 -> 50.9 ms; B = 1 and 16, which leave one of two groups
+// without sequences, t = 40 0.48 - 0.80).  The sums of more sequences do not fit beside the weights; up
 // to H = 1024 and B = 128 a copy per XCD fits, whose steps take 2 - 2.5 us for a wide one's 5 - 7.
 // The K splits of every kernel that runs a step of such a shape follow from what a compute unit's four
 // waves can add up: see WIDE_FWD_KS and sum_back_parts.
@@ -335,9 +336,9 @@ constexpr int WIDE_FWD_KS = 4;   // K split of a forward step of a wide shape
 // at B = 64, H = 1280, 160 workgroups, 7.1 / 9.6).  Four macro steps in flight instead of two where a workgroup has the compute
 // unit to itself and the x part of a wave is at least four long (it is fetched in whole fours): B = 64, I = 512, H = 2048
 // 13.0 -> 11.9, B = 32, I = 1024, H = 4096 30.2 -> 28.0; at B = 64, I = 128, H = 1280 7.1 -> 8.1.  8 x 2 where that still gives every
-// compute unit one: B = 128, I = 512, H = 2048 17.9 -> 16.4.  Gradient steps of 33 such shapes against eight waves and an eight-way
-// split: 0.70 - 1.00 of the time for 27 of them, 1.01 - 1.05 where a launch has exactly 256 large tiles (B = 128, H = 2048 2752 -> 2888
-// us), 1.08 at worst (B = 16, I = 700, H = 1536: rows of x that are no whole fragments).
+// compute unit one: B = 128, I = 512, H = 2048 17.9 -> 16.4.  Against eight waves and an eight-way split, as other shapes have, 40 of 48
+// gradient steps take 0.70 - 1.00 of the time, the others 1.01 - 1.05 (where a launch has exactly 256 large tiles: B = 128, H = 2048 2752
+// -> 2867 us) and 1.07 (B = 16, I = 700, H = 1536: rows of x that are no whole fragments).
 enum WideFwdConfig { WIDE_FWD_21, WIDE_FWD_22, WIDE_FWD_42_2, WIDE_FWD_42_4, WIDE_FWD_82 };
 inline WideFwdConfig wide_forward_config(const Dims& d) {
   const int ngroups = d.HP / 4, bt = d.BP / 16, wgs = ((ngroups + 3) / 4) * ((bt + 1) / 2);
