@@ -781,6 +781,232 @@ __global__ __launch_bounds__(64 * KS) void forward_batch_kernel(FwdParams p, Fwd
   forward_body<T, NG, BT, KS, U, CELL>(p, blockIdx.x, blockIdx.y, red);
 }
 
+// The same on larger tiles, bf16: a workgroup of four waves computes 64 NR packed rows x NC batch tiles, which may be of several
+// operations.  A wave owns NR row tiles and covers all columns: its weight fragments go straight into the MFMA registers, those
+// of the activations (x converted on the way) through LDS, where the four waves share them.  Macro steps are taken in the order
+// of the K parts of the shape's stand-alone kernel -- w, w + KS, ... for each part w in turn -- and a part's sums are added to the
+// total when it ends, so a step gives the same bits here too.
+// What bounds it: delivery of the panels to the compute units (128 x 64 tiles half the bytes of 64 x 32; H = 1024, B = 64, 31 operations
+// 55.3 -> 49.9 us), with few workgroups the rounds in turn: LDS, MFMAs, a barrier. Sixty-four more columns a workgroup, or 256 rows, leave
+// compute units idle (52 - 82 us), three or four rounds in flight instead of two gain nothing. Two waves per SIMD are asked for because
+// with all 512 registers to use the compiler keeps the sums in accumulation registers and copies them in and out in every macro step (63 us).
+constexpr int ORDER_MAX = 128, ORDER_ENDS = 0x8000;
+struct MacroStepOrder {   // two macro steps a round, the first in the low half; ORDER_ENDS: its K part ends with it
+  unsigned at[ORDER_MAX];
+};
+static bool macro_step_order(int nsteps, int ks, MacroStepOrder& o) {
+  if (nsteps > 2 * ORDER_MAX) return false;
+  int i = 0;
+  unsigned last = 0;
+  o = MacroStepOrder{};
+  for (int w = 0; w < ks; ++w)
+    for (int s = w; s < nsteps; s += ks, ++i) o.at[i / 2] |= (last = (unsigned)(s | (s + ks >= nsteps ? ORDER_ENDS : 0))) << 16 * (i % 2);
+  return true;
+}
+template <int NR, int NC, int CELL>
+__global__ __launch_bounds__(256, 2) void forward_batch_tiles_kernel(FwdParams p, FwdBatchSteps steps, MacroStepOrder order, int n, int row_blocks,
+                                                                     size_t hplane, size_t unit, size_t plane) {
+  using T = __bf16;
+  using M = Mma<T>;
+  using HP_ = HPlane<T>;
+  constexpr int VEC = M::VEC, KSTEP = 4 * VEC, FRAG = 64 * VEC;
+  constexpr int UW = 16 * NR, SEQ = 16 * NC, RS = UW + 1, NQ = NC / 2;   // NQ: activation fragments a wave stages per round
+  constexpr int STAGE = 2 * NC * FRAG;                                   // elements: two macro steps
+  constexpr size_t LDS = (size_t)2 * STAGE * sizeof(T) > (size_t)SEQ * RS * 16 ? (size_t)2 * STAGE * sizeof(T) : (size_t)SEQ * RS * 16;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[LDS];
+  T* lds = reinterpret_cast<T*>(smem);
+  f32x4* red = reinterpret_cast<f32x4*>(smem);
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;   // scalar: see wave_index note
+  const int lrow = lane & 15, lq = lane >> 4;
+  // ids equal modulo 8 share an XCD: each works through a contiguous range of row blocks, whose weights its L2 then holds
+  const int id = (int)blockIdx.x, total_wgs = (int)gridDim.x, xcd = id & 7;
+  const int work = xcd * (total_wgs >> 3) + min(xcd, total_wgs & 7) + (id >> 3), col_blocks = total_wgs / row_blocks;
+  const int by = work % col_blocks, bx = work / col_blocks;
+  const int btiles = p.BP / 16;
+  const int nsx = p.KX / KSTEP, nsh = p.KH / KSTEP, nsteps = nsx + nsh;
+  const size_t hhalf = (size_t)p.BP * p.KH;
+
+  // the workgroup's batch tiles: operation and tile of it (scalars; one division)
+  int op[NC], bt[NC];
+  op[0] = by * NC / btiles;
+  bt[0] = by * NC - op[0] * btiles;
+#pragma unroll
+  for (int t = 1; t < NC; ++t) {
+    const bool over = bt[t - 1] + 1 == btiles;
+    op[t] = op[t - 1] + (over ? 1 : 0);
+    bt[t] = over ? 0 : bt[t - 1] + 1;
+  }
+  auto op_in = [&](int t) { return min(op[t], n - 1); };   // for fetches: tiles past the last operation read it again
+
+  // epilogue items: unit fastest; a thread's items are of one unit, item q of a sequence of batch tile q * ROWS / 16
+  constexpr int ROWS = 256 / UW, IPT = SEQ / ROWS;
+  static_assert(ROWS <= 16, "items of one q are of one batch tile");
+  const int u = bx * UW + (int)threadIdx.x % UW;
+  auto row_of = [&](int q) { return bt[q * ROWS / 16] * 16 + q * ROWS % 16 + (int)threadIdx.x / UW; };
+  const int uc = min(u, p.H - 1);   // an item without a unit or sequence fetches a neighbour's values
+  const float4 bias = *reinterpret_cast<const float4*>(p.bp + 4 * uc);
+  float c_prev[IPT];
+#pragma unroll
+  for (int q = 0; q < IPT; ++q) {
+    const float* src = steps.src[op_in(q * ROWS / 16)];
+    const int b = min(row_of(q), p.B - 1);
+    c_prev[q] = CELL ? HP_::load(src, b, uc, nsh, p.H, hhalf) : (src + hplane)[(size_t)b * p.H + uc];
+  }
+
+  const int FB = FRAG * (int)sizeof(T);
+  int wrow[NR];   // of each row tile, the first fragment (bytes)
+#pragma unroll
+  for (int r = 0; r < NR; ++r) wrow[r] = min((bx * 4 + wave) * NR + r, (p.HP >> 2) - 1) * nsteps * FB;
+  const __amdgpu_buffer_rsrc_t weights = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.Wp), 0, 0x7fffffff, 0x00020000);
+  // the batch tile whose activations this wave stages
+  int my_op = op_in(0), my_bt = bt[0];
+#pragma unroll
+  for (int t = 1; t < NC; ++t)
+    if (wave % NC == t) {
+      my_op = op_in(t);
+      my_bt = bt[t];
+    }
+  const float *x_op = steps.x[my_op], *h_op = steps.src[my_op];
+  const unsigned xrow = (unsigned)(min(my_bt * 16 + lrow, p.B - 1) * p.I) * 4, hoff = (unsigned)((my_bt * nsh * 64 + lane) * 16);
+
+  typename M::Frag a[2][2][NR];
+  u32x4 raw[NQ][2];
+  int raw_s[NQ];
+  auto step_of = [&](int q) { return (wave + 4 * q) / NC; };   // of the round's two macro steps, the one fragment q belongs to
+  auto first = [](unsigned o) { return (int)(o & 0x7fff); };
+  auto second = [](unsigned o) { return (int)(o >> 16 & 0x7fff); };
+  auto fetch_a = [&](int set, unsigned o) {
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      a[set][0][r] = as_frag<typename M::Frag>(__builtin_amdgcn_raw_buffer_load_b128(weights, lane * 16, wrow[r] + first(o) * FB, 0));
+      a[set][1][r] = as_frag<typename M::Frag>(__builtin_amdgcn_raw_buffer_load_b128(weights, lane * 16, wrow[r] + second(o) * FB, 0));
+    }
+  };
+  // Without branches: a fragment of x is 32 bytes of a row (a window that ends inside it, see load_window), one of h 16 bytes,
+  // whose second load lies outside the buffer and moves nothing.
+  const unsigned xlane = xrow + 32u * (unsigned)lq;
+  const int over = p.I - VEC - VEC * lq;
+  auto fetch_b = [&](unsigned o) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const int s = step_of(q) ? second(o) : first(o);
+      const bool is_x = s < nsx;
+      const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(is_x ? x_op : h_op), 0, 0x7fffffff, 0x00020000);
+      const unsigned xo = xlane + 4u * (unsigned)min(s * KSTEP, over);
+      const int so = is_x ? 0 : 1024 * (s - nsx);
+      raw[q][0] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(is_x ? xo : hoff), so, 0);
+      raw[q][1] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(is_x ? xo + 16u : 0x80000000u), 0, 0);
+      raw_s[q] = s;
+    }
+  };
+  auto stash = [&](int stage) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const int s = raw_s[q];
+      typename M::Frag f = as_frag<typename M::Frag>(raw[q][0]);
+      if (s < nsx) {
+        RawAct<VEC> v;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) v.v[e] = __uint_as_float(raw[q][e / 4][e % 4]);
+        if ((s + 1) * KSTEP > p.I) shift_tail<VEC>(v, s * KSTEP + VEC * lq, p.I);
+        f = M::from_f32(v.v);
+      }
+      *reinterpret_cast<typename M::Frag*>(&lds[(size_t)stage * STAGE + (size_t)(wave + 4 * q) * FRAG + lane * VEC]) = f;
+    }
+  };
+  f32x4 part[NR][NC], sum[NR][NC];
+#pragma unroll
+  for (int r = 0; r < NR; ++r)
+#pragma unroll
+    for (int t = 0; t < NC; ++t) part[r][t] = sum[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto read_b = [&](int stage, int e, typename M::Frag (&bf)[NC]) {
+#pragma unroll
+    for (int t = 0; t < NC; ++t) bf[t] = M::load(&lds[(size_t)stage * STAGE + (size_t)(e * NC + t) * FRAG + lane * VEC]);
+  };
+  auto compute = [&](const typename M::Frag (&af)[NR], const typename M::Frag (&bf)[NC], bool ends) {
+#pragma unroll
+    for (int t = 0; t < NC; ++t)
+#pragma unroll
+      for (int r = 0; r < NR; ++r) part[r][t] = M::mma(af[r], bf[t], part[r][t]);
+    if (ends) {
+#pragma unroll
+      for (int r = 0; r < NR; ++r)
+#pragma unroll
+        for (int t = 0; t < NC; ++t) {
+          sum[r][t] += part[r][t];
+          part[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+  };
+  // Round r: two macro steps.  Its weights sit in register set r & 1, its activations in LDS stage r & 1; those of the next round
+  // are on their way.  One barrier per round.
+  const int rounds = (nsteps + 1) / 2;
+  unsigned o_now = order.at[0], o_next = order.at[min(1, rounds - 1)];
+  fetch_b(o_now);
+  fetch_a(0, o_now);
+  stash(0);
+  fetch_b(o_next);
+  fetch_a(1, o_next);
+  lds_barrier();
+  auto round = [&](int r, int set) {
+    typename M::Frag b0[NC], b1[NC];
+    read_b(set, 0, b0);
+    read_b(set, 1, b1);
+    stash(set ^ 1);   // past the last round: what nobody reads
+    const unsigned o_then = order.at[min(r + 2, rounds - 1)];
+    fetch_b(o_then);
+    compute(a[set][0], b0, o_now & ORDER_ENDS);
+    if (2 * r + 1 < nsteps) compute(a[set][1], b1, o_now >> 16 & ORDER_ENDS);
+    fetch_a(set, o_then);
+    o_now = o_next;
+    o_next = o_then;
+    lds_barrier();
+  };
+  for (int r = 0; r < rounds; r += 2) {
+    round(r, 0);
+    if (r + 1 < rounds) round(r + 1, 1);
+  }
+
+  // sums -> red[sequence][unit], four gates each
+#pragma unroll
+  for (int r = 0; r < NR; ++r)
+#pragma unroll
+    for (int t = 0; t < NC; ++t) red[(t * 16 + lrow) * RS + (wave * NR + r) * 4 + lq] = sum[r][t];
+  lds_barrier();
+#pragma unroll
+  for (int q = 0; q < IPT; ++q) {
+    const int b = row_of(q);
+    if (op[q * ROWS / 16] >= n || b >= p.B) continue;
+    float* dst = steps.dst[op[q * ROWS / 16]];
+    if (u >= p.H) {   // padding columns are part of the operand other launches fetch: zero
+      if (u < p.KH) HP_::store(dst, b, u, 0.0f, nsh, p.H, hhalf);
+      continue;
+    }
+    const f32x4 v = red[(q * ROWS + (int)threadIdx.x / UW) * RS + (int)threadIdx.x % UW];
+    const float G[4] = {v[0], v[1], v[2], v[3]};
+    float second, gate[4];
+    const float h = cell_forward<T, CELL>(G, bias, c_prev[q], second, gate);
+    const size_t e = (size_t)b * p.H + u;
+    HP_::store(dst, b, u, h, nsh, p.H, hhalf);
+    (dst + hplane)[e] = second;
+    (dst + unit)[e] = gate[0];
+    (dst + unit + plane)[e] = gate[1];
+    (dst + 2 * unit)[e] = gate[2];
+    if (CELL == 0) (dst + 2 * unit + plane)[e] = gate[3];
+  }
+}
+
+template <int NR, int NC>
+static void launch_forward_batch_tiles(const Dims& d, const FwdParams& p, const FwdBatchSteps& steps, const MacroStepOrder& order, int n, hipStream_t st) {
+  const int rows = (d.HP / 4 + 4 * NR - 1) / (4 * NR), cols = (n * (d.BP / 16) + NC - 1) / NC;
+  const dim3 grid(rows * cols), block(256);
+  const size_t plane = (size_t)d.B * d.H;
+  if (d.cell)
+    forward_batch_tiles_kernel<NR, NC, 1><<<grid, block, 0, st>>>(p, steps, order, n, rows, d.hplane, d.unit, plane);
+  else
+    forward_batch_tiles_kernel<NR, NC, 0><<<grid, block, 0, st>>>(p, steps, order, n, rows, d.hplane, d.unit, plane);
+}
+
 int forward_batch_max_steps() { return FWD_BATCH_MAX_STEPS; }
 
 template <class T>
@@ -796,6 +1022,28 @@ static void launch_forward_batch_t(const Dims& d, const FwdParams& p, const FwdB
   const FwdConfig cfg = forward_config<T>(d);
   // the K split of the shape's stand-alone forward kernel
   const bool small_k = cfg == FWD_TINY || cfg == FWD_SMALLK || wide_shape(d).groups;
+  if constexpr (sizeof(T) == 2) {
+    // Larger tiles where they still make enough workgroups, see forward_batch_tiles_kernel.  us a launch of n operations, this
+    // kernel's 64 x 32 / 128 x 32 / 128 x 64 tiles:
+    //   H = 1024, I = 256, B = 64:  n = 4 10.6 / 14.2 / 18.8, n = 8 17.4 / 17.3 / 20.0, n = 16 29.6 / 28.9 / 25.0, n = 31 55.3 / 54.7 / 49.9
+    //   H = 768, I = 128, B = 128:  n = 4 11.4 / 12.9 / 15.2, n = 8 19.1 / 17.8 / 18.9, n = 16 33.8 / 31.3 / 32.5, n = 31 68.0 / 65.6 / 68.1
+    //   H = 2048, I = 512, B = 128: n = 4 31.4 / 25.5 / 29.2, n = 8 57.8 / 46.1 / 39.2
+    //   H = 4096, I = 1024, B = 32 (whose weights no L2 holds, and which 64 x 32 tiles fetch once per operation):
+    //                               n = 2 46.8 / 39.9 / 50.8, n = 4 89.9 / 45.9 / 50.6, n = 8 178 / 84.6 / 66.6
+    //   H = 650, I = 650, B = 20:   n = 4 11.6 / 13.2 / 17.8, n = 8 18.2 / 13.4 / 17.9, n = 31 45.9 / 22.4 / 23.7
+    // In the last, rows of x are no whole fragments, which the smaller tiles' loader fetches value by value.
+    MacroStepOrder order;
+    constexpr size_t LIMIT = (size_t)1 << 31;   // 32-bit byte offsets
+    if (d.I >= 8 && (size_t)d.G4 * d.KP * 2 < LIMIT && (size_t)d.B * d.I * 4 < LIMIT && macro_step_order(d.KP / 32, small_k ? 4 : 8, order)) {
+      const int rows = d.HP / 32, tiles = n * (d.BP / 16), wide = rows * ((tiles + 3) / 4), narrow = rows * ((tiles + 1) / 2);
+      const int least = d.I % 8 != 0 ? TARGET_WGS / 2 : (d.KP > 2048 ? TARGET_WGS : 2 * TARGET_WGS);
+      // (With the weight-gradient GEMMs beside it, which is where whole fragments and 33 - 128 sequences meet, a gradient step of H = 1024,
+      // B = 64 gains nothing: 10 489 us, 10 539 with the larger tiles.)
+      const bool alone = d.B <= 32 || d.B > 128 || d.KP > 2048;
+      if (wide >= 2 * TARGET_WGS && (alone || d.I % 8 != 0)) return launch_forward_batch_tiles<2, 4>(d, p, steps, order, n, st);
+      if (narrow >= least && (alone || d.I % 8 != 0)) return launch_forward_batch_tiles<2, 2>(d, p, steps, order, n, st);
+    }
+  }
   if (small_k && d.cell)
     forward_batch_kernel<T, NG, BT, 4, FU, 1><<<grid, dim3(64 * 4), 0, st>>>(p, steps, d.hplane, d.unit, plane);
   else if (small_k)

@@ -78,8 +78,6 @@ __device__ inline bool draw_rank(unsigned* sync, unsigned launch, int& g, int& r
 // of a run, so the slots a launch starts with are the ones the launch before left reset.
 constexpr unsigned RES_EMPTY = 0xffffffffu;
 
-typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
-
 // A wave's 16 bytes per lane of an exchange slot: past the compute unit's vector cache (sc1), from the
 // XCD's L2.  byte_off at or above 2^31 lies outside the buffer: such a lane gets zeros and moves no data.
 constexpr unsigned RES_NO_LANE = 0x80000000u;
@@ -186,51 +184,6 @@ __device__ __forceinline__ bool slot_is_there(const void* slot, int pieces, int 
       }
   __syncthreads();
   return *s_fail == 0;
-}
-
-// A barrier that orders LDS only: stores to memory stay in flight across it.
-__device__ inline void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-template <class F>
-__device__ inline F as_frag(u32x4 v) {
-  union { u32x4 u; F f; } cv;
-  cv.u = v;
-  return cv.f;
-}
-
-// Fragments of fp32 rows of any length.  A lane's VEC values start at k; where they would run over the end
-// of the row (`limit` values, at least VEC) the VEC last values of the row are fetched instead, and
-// shift_tail puts them where they belong when they are used: fetching has no branches (loads under
-// branches make the compiler wait for everything outstanding), and needs only a float's alignment.
-template <int VEC>
-__device__ inline RawAct<VEC> load_window(const float* __restrict__ base, unsigned row, int k, int limit) {
-  typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
-  RawAct<VEC> r;
-  const unsigned off = row + (unsigned)min(k, limit - VEC);
-#pragma unroll
-  for (int e = 0; e < VEC; e += 4) {
-    const f4u q = *reinterpret_cast<const f4u*>(base + (size_t)off + e);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) r.v[e + i] = q[i];
-  }
-  return r;
-}
-template <int VEC>
-__device__ inline void shift_tail(RawAct<VEC>& r, int k, int limit) {
-  const int d = k + VEC - limit;   // how far the window was moved back: <= 0 not at all, >= VEC all of it lies outside
-#pragma unroll
-  for (int bit = 1; bit < VEC; bit *= 2)
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-      const float from = e + bit < VEC ? r.v[e + bit] : 0.0f;
-      r.v[e] = (d > 0 && (d & bit)) ? from : r.v[e];
-    }
-#pragma unroll
-  for (int e = 0; e < VEC; ++e) r.v[e] = d >= VEC ? 0.0f : r.v[e];
 }
 
 // h of one element in full precision, and as the GEMM operand: `e` = b * H + u (plain plane), `o` its place

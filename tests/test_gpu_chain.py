@@ -137,6 +137,22 @@ def test_batched_recomputation(B, I, H, t):
     check_against_oracle(w, inp, base, ref, TOL[w.gemm_dtype], label=f"batched recomputation {B}x{I}x{H}: ")
 
 
+# batches of n operations on 128 x 32 and 128 x 64 tiles: rows of x that are no whole fragments, and fewer than a macro step; operations of one, two
+# and three batch tiles whose tiles straddle workgroups, the last one partly empty; odd numbers of macro steps; K split 8 and 4 ways; padding units
+@pytest.mark.parametrize("B,I,H,t,cell", [(20, 650, 650, 33, 0), (37, 100, 600, 33, 0), (48, 9, 1024, 33, 0), (10, 33, 990, 33, 0), (32, 256, 1024, 33, 1),
+                                          (120, 94, 520, 33, 1), (16, 1000, 800, 20, 0), (33, 40, 1100, 20, 0), (20, 72, 2100, 12, 1)])
+def test_batches_on_large_tiles(B, I, H, t, cell):
+    w = wl.Workload("tiles", B=B, I=I, H=H, t=t, kind=wl.KIND_HSM, m=t, gemm_dtype=wl.GEMM_BF16, loss=wl.LOSS_EXTERNAL_DY, dy_first_step=2,
+                    cell=cell, seed=B + I + H)
+    inp = wl.make_inputs(w, nonzero_state=True, nonzero_bias=True)
+    mb.mebptt_profile_enable(1)
+    out = _run(w, inp, wl.KIND_HSM, t, chain=True)
+    prof = mb.mebptt_profile_collect()
+    mb.mebptt_profile_enable(0)
+    assert prof.batch_steps >= t - 4
+    _same(out, _run(w, inp, wl.KIND_HSM, t, chain=False), (B, I, H))
+
+
 def test_chains_from_two_host_threads():
     """Two host threads with their own streams run chain-eligible workloads at the same time: the
     library orders the two runs on the device (each chain launch wants the whole chip) and both
