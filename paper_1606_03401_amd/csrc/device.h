@@ -10,6 +10,7 @@
 namespace mebptt {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(16))) __bf16 bf16x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
@@ -307,6 +308,55 @@ __device__ inline void shift_tail(RawAct<VEC>& r, int k, int limit) {
   for (int e = 0; e < VEC; ++e) r.v[e] = d >= VEC ? 0.0f : r.v[e];
 }
 
+// Products with at most eight columns (sequences), bf16.  A 16 x 16 tile would be half empty and the matrix unit take as
+// long, so the idle half takes another part of K: in the structured-sparse instruction every row of the first operand picks two of
+// each four k of the dense one.  The dense operand holds two macro steps of 16 weight rows side by side, k in twos; rows 0 - 7
+// of the other are the sequences' fragments of the first macro step, picking those twos, rows 8 - 15 their fragments of the
+// second.  One instruction in the time of a dense one (16 cycles) thus does two macro steps, every lane of a fetched fragment
+// carries data, and each of the two sums has the bits the dense instruction gives (measured on random operands of several
+// magnitudes, all 51 200 values alike).
+// D: lane (column j = weight row, group lq) holds sequences 4 lq .. 4 lq + 3 of the first macro step's sums (lq < 2), then of the second's.
+struct Halves {
+  __device__ static int picks(int lane) { return lane & 8 ? 0xeeee : 0x4444; }   // of each four k, the last or the first two
+  // The dense operand, loaded: `row` is the byte offset of row j of the tile's fragment of macro step 0, e and o the two macro steps;
+  // zeros from `end` on.  A lane fetches two whole slots, of e where lq is even, of o where it is odd (lane groups lq / 2 and
+  // 2 + lq / 2 of the fragment), and neighbouring groups swap the halves they need.  (Fetching 8 bytes of each of four fragments
+  // instead: launches of few steps 2 - 4 % slower, H = 832, B = 15, t = 22 292 against 303 us a gradient step.)
+  __device__ static bf16x16 load(const void* weights, unsigned row, int e, int o, int end, int lq) {
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(weights), 0, 0x7fffffff, 0x00020000);
+    const int mine = lq & 1 ? o : e;
+    const unsigned at = mine < end ? row + 1024u * (unsigned)mine + 256u * (unsigned)(lq >> 1) : 0x80000000u;
+    union { unsigned u[8]; bf16x16 f; } r;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)at, 512 * k, 0);
+      const auto a = __builtin_amdgcn_permlane16_swap(v.x, v.z, false, false), b = __builtin_amdgcn_permlane16_swap(v.y, v.w, false, false);
+      r.u[4 * k] = a[0];
+      r.u[4 * k + 1] = a[1];
+      r.u[4 * k + 2] = b[0];
+      r.u[4 * k + 3] = b[1];
+    }
+    return r.f;
+  }
+  __device__ static f32x4 mma(bf16x8 h, bf16x16 w, f32x4 c, int picks) {
+    return __builtin_amdgcn_smfmac_f32_16x16x64_bf16(h, w, c, picks, 0, 0);
+  }
+  // Both sums added: of lane (j, lq), element r: sequence 4 (lq & 1) + 2 (lq >> 1) + r.
+  struct Sum {
+    float v[2];
+  };
+  __device__ static Sum fold(f32x4 a) {
+    Sum s;
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(a[r]), __float_as_uint(a[r + 2]), false, false);
+      s.v[r] = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+    }
+    return s;
+  }
+  __device__ static int lane_of(int j, int seq) { return j + 16 * (seq >> 2) + 32 * ((seq >> 1) & 1); }
+};
+
 // Kernel configurations by shape.  Tiles per workgroup grow with the problem so that the grid
 // stays near one workgroup per compute unit while every operand byte is reused as often as
 // possible; the choice depends on the shape only, never on the schedule.
@@ -372,6 +422,27 @@ inline WideShape wide_shape(const Dims& d) {
   w.share = round_up((d.B + groups - 1) / groups, 16);
   w.nr = (d.KH * groups + 1023) / 1024;
   return w;
+}
+
+// Gate sums of a forward step whose K is split eight ways, bf16 operands: neighbouring parts are added first, then the four pairs
+// in order.  (One instruction gives both parts of a pair in the launches of up to 64 sequences, see Halves.)  Other splits add
+// one part after the other.
+template <class T, int KS, class V, class Part>
+__device__ __forceinline__ V sum_forward_parts(V zero, Part&& part) {
+  V v = zero;
+  if constexpr (sizeof(T) == 2 && KS == 8) {
+#pragma unroll
+    for (int w = 0; w < KS; w += 2) v += part(w) + part(w + 1);
+  } else {
+#pragma unroll
+    for (int w = 0; w < KS; ++w) v += part(w);
+  }
+  return v;
+}
+// Backward steps of up to 64 sequences, bf16 operands, K split eight ways: each of the eight keeps its even and its odd macro
+// steps apart and adds the two sums before the eight are added in order.
+inline bool backward_in_halves(const Dims& d) {
+  return d.dtype && d.B <= 64 && d.KH <= 1024 && !wide_shape(d).groups && backward_config<__bf16>(d) == BWD_11;
 }
 
 constexpr int WIDE_FWD_KS = 4;   // K split of a forward step of a wide shape

@@ -425,13 +425,8 @@ __device__ inline void forward_body(const FwdParams& p, int bx, int by, float* r
     const int item = (int)threadIdx.x + q * NTHR;
     if (item >= ITEMS) break;
     const int cell = ((item / UW) % (BT * 16)) * RS + item % UW;
-    float G[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int w = 0; w < KS; ++w) {   // fixed order: results do not depend on scheduling
-      const f32x4 v = red4[w * BT * 16 * RS + cell];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) G[r] += v[r];
-    }
+    const f32x4 v = sum_forward_parts<T, KS>(f32x4{0.f, 0.f, 0.f, 0.f}, [&](int w) { return red4[w * BT * 16 * RS + cell]; });   // fixed order
+    const float G[4] = {v[0], v[1], v[2], v[3]};
     if (!epi[q]) {
       // split layout: the padding columns H..KH of a valid row are part of the operand other
       // launches fetch, so they are (re)written as zero with every state
@@ -483,11 +478,13 @@ struct BwdParams {
 // macro steps before the first MFMA.  Partial sums meet in LDS (`red`, KS*NT*BT*256 floats).  The
 // pointwise backward has NT*BT*4 pieces of work (tile x which of the lane's four hidden units),
 // dealt round-robin to the waves.  (bx, by) = (hidden-unit tile group, batch-tile group).
-// PARTS = 2 (wide shapes): a wave keeps its even and its odd macro steps apart, see sum_back_parts.
-template <class T, int NT, int BT, int KS, int U, int PARTS = 1>
+// PARTS = 2: a wave keeps its even and its odd macro steps apart; wide shapes see sum_back_parts, HALVES: the two are added here
+// (backward_in_halves).
+template <class T, int NT, int BT, int KS, int U, int PARTS = 1, bool HALVES = false>
 __device__ inline void backward_body(const BwdParams& p, int bx, int by, float* red) {
   using M = Mma<T>;
   static_assert(PARTS == 1 || (U % 2 == 0 && KS * PARTS == WIDE_BACK_PARTS), "a slot of the ring always holds the same part");
+  constexpr int OUT = HALVES ? 1 : PARTS;   // sums of a wave that go through LDS
   constexpr int VEC = M::VEC, KSTEP = 4 * VEC;
   constexpr int NTILE = NT * BT, NPIECE = NTILE * 4, PPW = (NPIECE + KS - 1) / KS;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;   // scalar: see wave_index note
@@ -586,8 +583,14 @@ __device__ inline void backward_body(const BwdParams& p, int bx, int by, float* 
         if (j0 + u + U < nw) load_slot(u, j0 + u + U);
       }
     }
+    if constexpr (HALVES) {
 #pragma unroll
-    for (int e = 0; e < PARTS; ++e)
+      for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int j = 0; j < BT; ++j) acc[0][i][j] += acc[PARTS - 1][i][j];
+    }
+#pragma unroll
+    for (int e = 0; e < OUT; ++e)
 #pragma unroll
       for (int i = 0; i < NT; ++i)
 #pragma unroll
@@ -602,7 +605,7 @@ __device__ inline void backward_body(const BwdParams& p, int bx, int by, float* 
     if (piece >= NPIECE) break;
     float dh = 0.0f;
     if (p.dG_next) {   // fixed order
-      if constexpr (PARTS == 1)
+      if constexpr (OUT == 1)
         for (int w = 0; w < KS; ++w) dh += red[(w * NPIECE + piece) * 64 + lane];
       else
         dh = sum_back_parts([&](int w) { return red[(w * NPIECE + piece) * 64 + lane]; });
@@ -650,10 +653,10 @@ __device__ inline void backward_body(const BwdParams& p, int bx, int by, float* 
   }
 }
 
-template <class T, int NT, int BT, int KS, int U, int PARTS>
+template <class T, int NT, int BT, int KS, int U, int PARTS, bool HALVES>
 __global__ __launch_bounds__(64 * KS) void backward_kernel(BwdParams p) {
-  __shared__ float red[KS * PARTS * NT * BT * 4 * 64];
-  backward_body<T, NT, BT, KS, U, PARTS>(p, blockIdx.x, blockIdx.y, red);
+  __shared__ float red[KS * (HALVES ? 1 : PARTS) * NT * BT * 4 * 64];
+  backward_body<T, NT, BT, KS, U, PARTS, HALVES>(p, blockIdx.x, blockIdx.y, red);
 }
 
 // ---- fused launch: a backward step and an independent forward step ---------------------------
@@ -672,16 +675,16 @@ constexpr int PAIR_FKS = 8, PAIR_NG = 4, PAIR_FU = 1, PAIR_BKS = 8, PAIR_BU = 4;
 // macro steps a wave keeps in flight, are smaller than the stand-alone kernels': two resident
 // workgroups share a compute unit's load path, and measured launch times fall as the queues get
 // shorter (large-K class: 9.98 us at FU, BU = 2, 8; 9.47 us at 1, 4; small-K class 12.2 -> 10.8 us).
-template <class T, int CELL, int FNG, int FKS, int FU, int BNT, int BBT, int BKS, int BU, int PARTS = 1>
+template <class T, int CELL, int FNG, int FKS, int FU, int BNT, int BBT, int BKS, int BU, int PARTS = 1, bool HALVES = false>
 __global__ __launch_bounds__(64 * (FKS > BKS ? FKS : BKS), 4) void pair_kernel(FwdParams f, BwdParams b, int nfx, int nf,
                                                                              int nbx) {
-  constexpr int FRED = forward_red_floats(FNG, 1, FKS), BRED = BKS * PARTS * BNT * BBT * 4 * 64;
+  constexpr int FRED = forward_red_floats(FNG, 1, FKS), BRED = BKS * (HALVES ? 1 : PARTS) * BNT * BBT * 4 * 64;
   __shared__ __attribute__((aligned(16))) float red[FRED > BRED ? FRED : BRED];
   const int id = blockIdx.x;
   if (id < nf)
     forward_body<T, FNG, 1, FKS, FU, CELL>(f, id % nfx, id / nfx, red);
   else
-    backward_body<T, BNT, BBT, BKS, BU, PARTS>(b, (id - nf) % nbx, (id - nf) / nbx, red);
+    backward_body<T, BNT, BBT, BKS, BU, PARTS, HALVES>(b, (id - nf) % nbx, (id - nf) / nbx, red);
 }
 
 template <class T, int NG, int BT, int KS, int U>
@@ -785,22 +788,21 @@ __global__ __launch_bounds__(64 * KS) void forward_batch_kernel(FwdParams p, Fwd
 // operations.  A wave owns NR row tiles and covers all columns: its weight fragments go straight into the MFMA registers, those
 // of the activations (x converted on the way) through LDS, where the four waves share them.  Macro steps are taken in the order
 // of the K parts of the shape's stand-alone kernel -- w, w + KS, ... for each part w in turn -- and a part's sums are added to the
-// total when it ends, so a step gives the same bits here too.
+// total when it ends (of an eight-way split, those of two parts: sum_forward_parts), so a step gives the same bits here too.
 // What bounds it: delivery of the panels to the compute units (128 x 64 tiles half the bytes of 64 x 32; H = 1024, B = 64, 31 operations
 // 55.3 -> 49.9 us), with few workgroups the rounds in turn: LDS, MFMAs, a barrier. Sixty-four more columns a workgroup, or 256 rows, leave
 // compute units idle (52 - 82 us), three or four rounds in flight instead of two gain nothing. Two waves per SIMD are asked for because
 // with all 512 registers to use the compiler keeps the sums in accumulation registers and copies them in and out in every macro step (63 us).
-constexpr int ORDER_MAX = 128, ORDER_ENDS = 0x8000;
-struct MacroStepOrder {   // two macro steps a round, the first in the low half; ORDER_ENDS: its K part ends with it
+constexpr int ORDER_MAX = 128, ORDER_ENDS = 0x8000, ORDER_WAITS = 0x4000;
+struct MacroStepOrder {   // two macro steps a round, the first in the low half; ORDER_ENDS: its K part ends with it (and ORDER_WAITS for the next)
   unsigned at[ORDER_MAX];
 };
 static bool macro_step_order(int nsteps, int ks, MacroStepOrder& o) {
   if (nsteps > 2 * ORDER_MAX) return false;
   int i = 0;
-  unsigned last = 0;
   o = MacroStepOrder{};
   for (int w = 0; w < ks; ++w)
-    for (int s = w; s < nsteps; s += ks, ++i) o.at[i / 2] |= (last = (unsigned)(s | (s + ks >= nsteps ? ORDER_ENDS : 0))) << 16 * (i % 2);
+    for (int s = w; s < nsteps; s += ks, ++i) o.at[i / 2] |= (unsigned)(s | (s + ks >= nsteps ? (ks == 8 && w % 2 == 0 ? ORDER_ENDS | ORDER_WAITS : ORDER_ENDS) : 0)) << 16 * (i % 2);
   return true;
 }
 template <int NR, int NC, int CELL>
@@ -873,8 +875,8 @@ __global__ __launch_bounds__(256, 2) void forward_batch_tiles_kernel(FwdParams p
   u32x4 raw[NQ][2];
   int raw_s[NQ];
   auto step_of = [&](int q) { return (wave + 4 * q) / NC; };   // of the round's two macro steps, the one fragment q belongs to
-  auto first = [](unsigned o) { return (int)(o & 0x7fff); };
-  auto second = [](unsigned o) { return (int)(o >> 16 & 0x7fff); };
+  auto first = [](unsigned o) { return (int)(o & 0x3fff); };
+  auto second = [](unsigned o) { return (int)(o >> 16 & 0x3fff); };
   auto fetch_a = [&](int set, unsigned o) {
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
@@ -914,26 +916,29 @@ __global__ __launch_bounds__(256, 2) void forward_batch_tiles_kernel(FwdParams p
       *reinterpret_cast<typename M::Frag*>(&lds[(size_t)stage * STAGE + (size_t)(wave + 4 * q) * FRAG + lane * VEC]) = f;
     }
   };
-  f32x4 part[NR][NC], sum[NR][NC];
+  f32x4 part[NR][NC], waits[NR][NC], sum[NR][NC];
 #pragma unroll
   for (int r = 0; r < NR; ++r)
 #pragma unroll
-    for (int t = 0; t < NC; ++t) part[r][t] = sum[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < NC; ++t) part[r][t] = waits[r][t] = sum[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
   auto read_b = [&](int stage, int e, typename M::Frag (&bf)[NC]) {
 #pragma unroll
     for (int t = 0; t < NC; ++t) bf[t] = M::load(&lds[(size_t)stage * STAGE + (size_t)(e * NC + t) * FRAG + lane * VEC]);
   };
-  auto compute = [&](const typename M::Frag (&af)[NR], const typename M::Frag (&bf)[NC], bool ends) {
+  auto compute = [&](const typename M::Frag (&af)[NR], const typename M::Frag (&bf)[NC], unsigned o) {
 #pragma unroll
     for (int t = 0; t < NC; ++t)
 #pragma unroll
       for (int r = 0; r < NR; ++r) part[r][t] = M::mma(af[r], bf[t], part[r][t]);
-    if (ends) {
+    if (o & ORDER_ENDS) {
 #pragma unroll
       for (int r = 0; r < NR; ++r)
 #pragma unroll
         for (int t = 0; t < NC; ++t) {
-          sum[r][t] += part[r][t];
+          if (o & ORDER_WAITS)
+            waits[r][t] = part[r][t];
+          else
+            sum[r][t] += waits[r][t] + part[r][t];
           part[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
     }
@@ -955,8 +960,8 @@ __global__ __launch_bounds__(256, 2) void forward_batch_tiles_kernel(FwdParams p
     stash(set ^ 1);   // past the last round: what nobody reads
     const unsigned o_then = order.at[min(r + 2, rounds - 1)];
     fetch_b(o_then);
-    compute(a[set][0], b0, o_now & ORDER_ENDS);
-    if (2 * r + 1 < nsteps) compute(a[set][1], b1, o_now >> 16 & ORDER_ENDS);
+    compute(a[set][0], b0, o_now);
+    if (2 * r + 1 < nsteps) compute(a[set][1], b1, o_now >> 16);
     fetch_a(set, o_then);
     o_now = o_next;
     o_next = o_then;
@@ -1136,10 +1141,10 @@ hipError_t launch_forward_stream(const Dims& d, const void* Wp, const void* act,
   return hipGetLastError();
 }
 
-template <class T, int NT, int BT, int KS, int U, int PARTS = 1>
+template <class T, int NT, int BT, int KS, int U, int PARTS = 1, bool HALVES = false>
 static hipError_t launch_backward_cfg(const Dims& d, const BwdParams& p, hipStream_t st) {
   dim3 grid((d.HP / 16 + NT - 1) / NT, (d.BP / 16 + BT - 1) / BT), block(64 * KS);
-  backward_kernel<T, NT, BT, KS, U, PARTS><<<grid, block, 0, st>>>(p);
+  backward_kernel<T, NT, BT, KS, U, PARTS, HALVES><<<grid, block, 0, st>>>(p);
   return hipGetLastError();
 }
 
@@ -1151,6 +1156,7 @@ static hipError_t launch_backward_t(const Dims& d, const BwdParams& p, hipStream
       case BWD_21: return launch_backward_cfg<T, 2, 1, 8, 4, 2>(d, p, st);
       default: return launch_backward_cfg<T, 2, 2, 8, 4, 2>(d, p, st);
     }
+    if (backward_in_halves(d)) return launch_backward_cfg<T, 1, 1, PAIR_BKS, PAIR_BU, 2, true>(d, p, st);
   }
   switch (backward_config<T>(d)) {
     case BWD_SMALLK: return launch_backward_cfg<T, 1, 1, 4, 4>(d, p, st);
@@ -1222,6 +1228,14 @@ static void launch_pair_t(const Dims& d, const FwdParams& f, const BwdParams& b,
       const int nwx = (d.HP / 4 + 1) / 2, nbx = d.HP / 16, nby = d.BP / 16;
       pair_kernel<T, CELL, 2, WIDE_FWD_KS, 2, 1, 1, PAIR_BKS, PAIR_BU, 2>
           <<<dim3(nwx * nfy + nbx * nby), dim3(64 * PAIR_BKS), 0, st>>>(f, b, nwx, nwx * nfy, nbx);
+      return;
+    }
+  }
+  if constexpr (sizeof(T) == 2) {
+    if (cls == 1 && backward_in_halves(d)) {
+      const int nbx = d.HP / 16, nby = d.BP / 16;
+      pair_kernel<T, CELL, PAIR_NG, PAIR_FKS, PAIR_FU, 1, 1, PAIR_BKS, PAIR_BU, 2, true>
+          <<<dim3(nfx * nfy + nbx * nby), dim3(64 * PAIR_BKS), 0, st>>>(f, b, nfx, nfx * nfy, nbx);
       return;
     }
   }

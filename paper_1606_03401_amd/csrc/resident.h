@@ -241,6 +241,16 @@ __device__ inline f32x4 join_halves(f32x4 a, f32x4 b) {
     r[i] = __uint_as_float(__builtin_amdgcn_update_dpp(__float_as_uint(a[i]), __float_as_uint(b[i]), 0x128 /* row_ror:8 */, 0xf, 0xc, false));
   return r;
 }
+// Two row tiles of Halves products, whose rows are the gates 0 and 1 of eight units (lanes j: gate j / 8, unit j % 8), and the
+// gates 2 and 3: lane (j, lq) gets all four gates of unit j % 8 for sequence 4 (lq & 1) + 2 (lq >> 1) + j / 8.
+__device__ inline f32x4 join_gates(const Halves::Sum& a, const Halves::Sum& b) {
+  auto dpp = [](float own, float other, auto banks) {   // lanes of these banks of four take the value eight lanes on
+    return __uint_as_float(__builtin_amdgcn_update_dpp(__float_as_uint(own), __float_as_uint(other), 0x128 /* row_ror:8 */, 0xf, decltype(banks)::value, false));
+  };
+  using upper = std::integral_constant<int, 0xc>;
+  using lower = std::integral_constant<int, 0x3>;
+  return f32x4{dpp(a.v[0], a.v[1], upper{}), dpp(a.v[1], a.v[0], lower{}), dpp(b.v[0], b.v[1], upper{}), dpp(b.v[1], b.v[0], lower{})};
+}
 // Blocks a wave writes for its NR row tiles x NB batch tiles, and the block and lane of (row tile, row group lq, column).
 template <int NR, int NBT>
 struct Sums {
@@ -341,12 +351,9 @@ __device__ __forceinline__ void gates_slowly(const void* Wp, int tile, const flo
       __builtin_amdgcn_sched_barrier(0);
     }
   }
+  const f32x4 v = sum_forward_parts<T, KS>(f32x4{0.f, 0.f, 0.f, 0.f}, [&](int w) { return acc[w]; });
 #pragma unroll
-  for (int r = 0; r < 4; ++r) G[r] = 0.0f;
-#pragma unroll
-  for (int w = 0; w < KS; ++w)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) G[r] += acc[w][r];
+  for (int r = 0; r < 4; ++r) G[r] = v[r];
 }
 
 // All steps of a launch for units [u0, u1) of the XCD's sequences, by a workgroup that has stopped waiting.  Its waves
@@ -452,16 +459,31 @@ __device__ __forceinline__ void chain_slowly(int b_lo, int b_hi, int u0, int u1,
 // Of the 2.27 us, in cycles of 2.2 GHz: x part 560, polls 620 - 820 (1.0 - 1.4 of them), h part with the
 // stores and the next x 1280, barrier 250 - 520, pointwise step 1050, publishing 170.
 // Sums are formed exactly as forward_body forms them (KS partial sums over the macro steps
-// w, w+KS, ..., added in the order 0..KS-1), so a step gives the same bits either way.  A wave whose part of
+// w, w+KS, ..., added by sum_forward_parts), so a step gives the same bits either way.  A wave whose part of
 // x or h is shorter than the others' runs its surplus macro steps on zeros.
-// NXW, NHW: macro steps of x and of h per wave; the weights of the last NXL of x are parked in LDS (they are
+// Up to 64 sequences (half tiles), bf16, K split eight ways: each instruction does two of the eight parts (Halves), so four waves
+// split K and the two halves of the workgroup take half of the units each, in pairs of row tiles that hold eight units.  Against
+// eight waves with a part and all rows each: half the matrix instructions, half the partial sums through LDS (a 1 KiB block
+// costs a compute unit 30 cycles to write and 17 to read, and there were 32; the matrix unit was busy for 1024 of the h part's 1280 cycles):
+// H = 1024, B = 64 85.7 -> 79.4 us a launch of 41 steps on average.
+// NXW, NHW: macro steps of x and of h per wave (Halves: per part); the weights of the last NXL of x are parked in LDS (they are
 // read while the wave would wait anyway); NBT: batch tiles of the XCD's share (0: half a tile).
+// With an even number of pairs of row tiles: up to two tiles half of the waves would have none, and of five or six one half has twice
+// the other's, more than the registers hold with many columns of x (H = 640, I = 502, B = 5 2.4 % slower a gradient step, H = 576, B = 47
+// GRU 3 %, H = 650, I = 650 7 %; H = 641, I = 229, B = 64, t = 22 1.5 %).
+template <class T, int NRT, int KS, int NBT>
+constexpr bool chain_in_halves = sizeof(T) == 2 && KS == 8 && NBT == 0 && (NRT == 4 || NRT > 6);
+template <class T, int NRT, int KS, int NBT>   // row tiles of a wave
+constexpr int chain_row_tiles = chain_in_halves<T, NRT, KS, NBT> ? (NRT + 1) / 2 : (KS == 4 && NBT != 2 ? (NRT + 1) / 2 : NRT);
 template <class T, int NRT, int NXW, int NXL, int NHW, int KS, int NBT, int CELL>
 __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
   using M = Mma<T>;
   constexpr int VEC = M::VEC, KSTEP = 4 * VEC, FRAG = 64 * VEC;
-  constexpr int GROUPS = 8 / KS, FTB = (GROUPS == 2 && NBT == 2) ? 2 : 1, FTR = GROUPS / FTB;
-  constexpr int NRTW = (NRT + FTR - 1) / FTR, BTW = (NBT ? NBT : 1) / FTB;   // row and batch tiles of one wave
+  constexpr bool HALVES = chain_in_halves<T, NRT, KS, NBT>;
+  constexpr int KW = HALVES ? KS / 2 : KS;         // waves that split K
+  constexpr int GROUPS = 8 / KW, FTB = (GROUPS == 2 && NBT == 2) ? 2 : 1, FTR = GROUPS / FTB;
+  constexpr int NRTW = chain_row_tiles<T, NRT, KS, NBT>, BTW = (NBT ? NBT : 1) / FTB;   // row and batch tiles of one wave
+  using Weights = std::conditional_t<HALVES, bf16x16, typename M::Frag>;
   constexpr int NXR = NXW - NXL, COLS = NBT ? NBT * 16 : 8;
   constexpr int UW = NRT * 4;
   using It = Items<UW, COLS, NBT == 0>;
@@ -470,7 +492,7 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
   constexpr bool SPLIT = HPlane<T>::SPLIT;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   f32x4* red = reinterpret_cast<f32x4*>(smem);                                     // [8 waves][Sum::BLOCKS][64]
-  T* wl = reinterpret_cast<T*>(red + 8 * Sum::BLOCKS * 64);                        // [8][NRTW][NXL] fragments
+  T* wl = reinterpret_cast<T*>(red + 8 * Sum::BLOCKS * 64);                        // [8][NRTW][NXL] fragments (Halves: of two macro steps)
   __shared__ int s_go, s_g, s_rank, s_fail;
   // the wave index as a scalar: conditions on it become scalar branches (an MFMA under a lane mask
   // that is empty would still execute)
@@ -491,10 +513,12 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
   if (b_lo >= p.B || rank * UW >= p.KH || (p.alone && rank)) return;
   const int nsx = p.KX / KSTEP, nsh = p.KH / KSTEP, nsteps = nsx + nsh;
   const size_t hhalf = (size_t)p.BP * p.KH;
-  const int ks = wave % KS, grp = wave / KS;
+  const int ks = wave % KW, grp = wave / KW;
   const int rt0 = (FTR > 1 ? grp : 0) * NRTW, bt0 = (FTB > 1 ? grp : 0) * BTW;   // wave = group * KS + K part
   const int ngroups = p.HP / 4;                    // 16-row tiles of the packed weights
-  const int mh0 = (ks + KS - nsx % KS) % KS;       // this wave's h macro steps: mh0, mh0 + KS, ... (below nsh)
+  // this wave's part of K (Halves: this lane's of the two); its h macro steps: mh0, mh0 + KS, ... (below nsh)
+  const int kpart = HALVES ? 2 * ks + (lrow >> 3) : ks;
+  const int mh0 = (kpart + KS - nsx % KS) % KS;
 
   // Pointwise items of this thread; c stays in registers.  A unit between H and the padded KH has no
   // weights: its h is zero, and is published as such.
@@ -509,8 +533,11 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
     const int ul = It::unit(item), col = It::column(item), b = b_lo + col, u = rank * UW + ul, rt = ul >> 2;
     // the wave that holds it: row group (or batch group) of the workgroup, then its block
     const int w0 = FTR > 1 ? rt / NRTW : (FTB > 1 ? (col >> 4) / BTW : 0);
-    cell[q] = red + (size_t)(w0 * KS * Sum::BLOCKS + Sum::block(FTR > 1 ? rt % NRTW : rt, FTB > 1 ? col % (BTW * 16) : col)) * 64 +
-              Sum::lane(FTR > 1 ? rt % NRTW : rt, ul & 3, col);
+    if constexpr (HALVES)
+      cell[q] = red + (size_t)(w0 * KW * Sum::BLOCKS + rt % NRTW / 2) * 64 + Halves::lane_of((ul & 7) + 8 * (col & 1), col);
+    else
+      cell[q] = red + (size_t)(w0 * KS * Sum::BLOCKS + Sum::block(FTR > 1 ? rt % NRTW : rt, FTB > 1 ? col % (BTW * 16) : col)) * 64 +
+                Sum::lane(FTR > 1 ? rt % NRTW : rt, ul & 3, col);
     mine[q] = item < ITEMS && b < b_hi && u < p.KH;
     real[q] = u < p.H;
     ie[q] = (unsigned)(b * p.H + u);
@@ -555,26 +582,50 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
   publish(p.published);   // travels while the weights are fetched
 
   // this wave's packed weight rows; the last NXL macro steps of x are parked in LDS (read back by this wave only)
-  typename M::Frag wx[NRTW][NXR > 0 ? NXR : 1], wh[NRTW][NHW];
+  Weights wx[NRTW][NXR > 0 ? NXR : 1], wh[NRTW][NHW];
+  if constexpr (HALVES) {
+    const int me = (2 * ks + KS - nsx % KS) % KS, mo = (2 * ks + 1 + KS - nsx % KS) % KS;   // the two parts' first macro steps of h
 #pragma unroll
-  for (int rt = 0; rt < NRTW; ++rt) {
-    const int row_tile = min(rank * NRT + min(rt0 + rt, NRT - 1), ngroups - 1);
-    const T* base = reinterpret_cast<const T*>(p.Wp) + ((size_t)row_tile * nsteps * 64 + lane) * VEC;
+    for (int rt = 0; rt < NRTW; ++rt) {
+      // lane j of tile rt: unit j % 8 of the pair of tiles, gate 2 * (rt % 2) + j / 8; packed row 4 * unit + gate
+      const int row = 4 * (lrow & 7) + 2 * (rt & 1) + (lrow >> 3);
+      const int row_tile = min(rank * NRT + min(rt0 + (rt & ~1) + (row >> 4), NRT - 1), ngroups - 1);
+      const unsigned at = (unsigned)((row_tile * nsteps * 64 + (row & 15)) * 16);
 #pragma unroll
-    for (int i = 0; i < NXW; ++i) {
-      const int s = ks + KS * i;
-      typename M::Frag f = M::load(base + (size_t)min(s, nsx - 1) * FRAG);
-      if (s >= nsx) f = typename M::Frag{};
-      if (i < NXR)
-        wx[rt][i < NXR ? i : 0] = f;
-      else
-        *reinterpret_cast<typename M::Frag*>(&wl[((size_t)(wave * NRTW + rt) * NXL + (i - NXR)) * FRAG + lane * VEC]) = f;
+      for (int i = 0; i < NXW; ++i) {
+        const bf16x16 f = Halves::load(p.Wp, at, 2 * ks + KS * i, 2 * ks + 1 + KS * i, nsx, lq);
+        if (i < NXR) {
+          wx[rt][i < NXR ? i : 0] = f;
+        } else {
+          typename M::Frag* to = reinterpret_cast<typename M::Frag*>(wl) + ((size_t)(wave * NRTW + rt) * NXL + (i - NXR)) * 128 + lane;
+          to[0] = __builtin_shufflevector(f, f, 0, 1, 2, 3, 4, 5, 6, 7);
+          to[64] = __builtin_shufflevector(f, f, 8, 9, 10, 11, 12, 13, 14, 15);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < NHW; ++i) wh[rt][i] = Halves::load(p.Wp, at, nsx + me + KS * i, nsx + mo + KS * i, nsteps, lq);
     }
+  } else {
 #pragma unroll
-    for (int i = 0; i < NHW; ++i) {
-      const int m = mh0 + KS * i;
-      wh[rt][i] = M::load(base + (size_t)(nsx + min(m, nsh - 1)) * FRAG);
-      if (m >= nsh) wh[rt][i] = typename M::Frag{};
+    for (int rt = 0; rt < NRTW; ++rt) {
+      const int row_tile = min(rank * NRT + min(rt0 + rt, NRT - 1), ngroups - 1);
+      const T* base = reinterpret_cast<const T*>(p.Wp) + ((size_t)row_tile * nsteps * 64 + lane) * VEC;
+#pragma unroll
+      for (int i = 0; i < NXW; ++i) {
+        const int s = ks + KS * i;
+        typename M::Frag f = M::load(base + (size_t)min(s, nsx - 1) * FRAG);
+        if (s >= nsx) f = typename M::Frag{};
+        if (i < NXR)
+          wx[rt][i < NXR ? i : 0] = f;
+        else
+          *reinterpret_cast<typename M::Frag*>(&wl[((size_t)(wave * NRTW + rt) * NXL + (i - NXR)) * FRAG + lane * VEC]) = f;
+      }
+#pragma unroll
+      for (int i = 0; i < NHW; ++i) {
+        const int m = mh0 + KS * i;
+        wh[rt][i] = M::load(base + (size_t)(nsx + min(m, nsh - 1)) * FRAG);
+        if (m >= nsh) wh[rt][i] = typename M::Frag{};
+      }
     }
   }
 
@@ -583,7 +634,7 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
   unsigned xrow[BTW], hoff[BTW];
 #pragma unroll
   for (int t = 0; t < BTW; ++t) {
-    const int b = b_lo + (bt0 + t) * 16 + lrow;
+    const int b = b_lo + (bt0 + t) * 16 + (HALVES ? lrow & 7 : lrow);
     const bool own = b < b_hi;
     xrow[t] = (unsigned)((own ? b : b_lo) * p.I);
     hoff[t] = own ? (unsigned)(((b >> 4) * nsh * 64 + lq * 16 + (b & 15)) * 16) : RES_NO_LANE;
@@ -594,7 +645,7 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
 #pragma unroll
     for (int i = 0; i < NXW; ++i)
 #pragma unroll
-      for (int t = 0; t < BTW; ++t) xraw[i][t] = load_window<VEC>(x_j, xrow[t], (ks + KS * i) * KSTEP + VEC * lq, p.I);
+      for (int t = 0; t < BTW; ++t) xraw[i][t] = load_window<VEC>(x_j, xrow[t], (kpart + KS * i) * KSTEP + VEC * lq, p.I);
   };
   fetch_x(0);
 
@@ -625,6 +676,13 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
     }
   };
 
+  const int picks = Halves::picks(lane);
+  auto mma = [&](const Weights& w, const typename M::Frag& f, f32x4 c) {
+    if constexpr (HALVES)
+      return Halves::mma(f, w, c, picks);
+    else
+      return M::mma(w, f, c);
+  };
   for (int j = 0; j < p.count; ++j) {
     f32x4 acc[NRTW][BTW];
 #pragma unroll
@@ -635,8 +693,8 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
     // that of forward_body)
 #pragma unroll
     for (int i = 0; i < NXW; ++i) {
-      const int s = ks + KS * i;
-      if ((s + 1) * KSTEP > p.I) {   // over the end of the row, or a surplus step
+      const int s = kpart + KS * i;
+      if (((HALVES ? 2 * ks + 1 : ks) + KS * i + 1) * KSTEP > p.I) {   // over the end of the row, or a surplus step
 #pragma unroll
         for (int t = 0; t < BTW; ++t) shift_tail<VEC>(xraw[i][t], s * KSTEP + VEC * lq, p.I);
       }
@@ -645,13 +703,17 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
       for (int t = 0; t < BTW; ++t) xf[t] = M::from_f32(xraw[i][t].v);
 #pragma unroll
       for (int rt = 0; rt < NRTW; ++rt) {
-        typename M::Frag a;
-        if (i < NXR)
+        Weights a;
+        if (i < NXR) {
           a = wx[rt][i < NXR ? i : 0];
-        else
+        } else if constexpr (HALVES) {
+          const typename M::Frag* from = reinterpret_cast<const typename M::Frag*>(wl) + ((size_t)(wave * NRTW + rt) * NXL + (i - NXR)) * 128 + lane;
+          a = __builtin_shufflevector(from[0], from[64], 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
+        } else {
           a = M::load(&wl[((size_t)(wave * NRTW + rt) * NXL + (i - NXR)) * FRAG + lane * VEC]);
+        }
 #pragma unroll
-        for (int t = 0; t < BTW; ++t) acc[rt][t] = M::mma(a, xf[t], acc[rt][t]);
+        for (int t = 0; t < BTW; ++t) acc[rt][t] = mma(a, xf[t], acc[rt][t]);
       }
     }
     // h fragments of the step before
@@ -666,7 +728,9 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
         for (int i = 0; i < NHW; ++i) {
           const int m = mh0 + KS * i;
 #pragma unroll
-          for (int t = 0; t < BTW; ++t) raw[i][t] = load_slot_16(slot, m < nsh ? hoff[t] : RES_NO_LANE, m * 1024);
+          for (int t = 0; t < BTW; ++t)
+            raw[i][t] = HALVES ? load_slot_16(slot, m < nsh ? hoff[t] + (unsigned)mh0 * 1024 : RES_NO_LANE, KS * i * 1024)
+                               : load_slot_16(slot, m < nsh ? hoff[t] : RES_NO_LANE, m * 1024);
         }
 #pragma unroll
         for (int i = 0; i < NHW; ++i)
@@ -691,21 +755,28 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
 #pragma unroll
       for (int rt = 0; rt < NRTW; ++rt)
 #pragma unroll
-        for (int t = 0; t < BTW; ++t) acc[rt][t] = M::mma(wh[rt][i], hf[i][t], acc[rt][t]);
-    Sum::write(red + (size_t)wave * Sum::BLOCKS * 64, lane, acc);
+        for (int t = 0; t < BTW; ++t) acc[rt][t] = mma(wh[rt][i], hf[i][t], acc[rt][t]);
+    f32x4* sums = red + (size_t)wave * Sum::BLOCKS * 64;
+    if constexpr (HALVES) {
+#pragma unroll
+      for (int rt = 0; rt < NRTW; rt += 2) sums[rt / 2 * 64 + lane] = join_gates(Halves::fold(acc[rt][0]), Halves::fold(acc[rt + 1][0]));
+    } else {
+      Sum::write(sums, lane, acc);
+    }
     lds_barrier();
     if (__builtin_amdgcn_readfirstlane(s_fail))   // a wave has stopped waiting: written before the barrier, so all see it
       stop_waiting<ResParams, UW>(&s_g, &s_rank, &s_fail, [&](int b_lo, int b_hi, int u0, int u1) { chain_slowly<ResParams, T, KS, CELL>(b_lo, b_hi, u0, u1, &s_fail); });
 #pragma unroll
     for (int q = 0; q < IPT; ++q) {
       if (!mine[q]) continue;
-      float G[4] = {0.f, 0.f, 0.f, 0.f};
+      f32x4 v{0.f, 0.f, 0.f, 0.f};   // fixed order, as in forward_body
+      if constexpr (HALVES) {
 #pragma unroll
-      for (int w = 0; w < KS; ++w) {   // fixed order, as in forward_body
-        const f32x4 v = cell[q][w * Sum::BLOCKS * 64];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) G[r] += v[r];
+        for (int w = 0; w < KW; ++w) v += cell[q][w * Sum::BLOCKS * 64];
+      } else {
+        v = sum_forward_parts<T, KS>(v, [&](int w) { return cell[q][w * Sum::BLOCKS * 64]; });
       }
+      const float G[4] = {v[0], v[1], v[2], v[3]};
       const float h = cell_forward<T, CELL>(G, bias[q], c_state[q], keep_second[q], keep_gate[q]);
       keep_h[q] = real[q] ? h : 0.0f;
       c_state[q] = CELL ? keep_h[q] : keep_second[q];
@@ -718,9 +789,9 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
 
 template <class T, int NRT, int NXW, int NXL, int NHW, int KS, int NBT, int CELL>
 hipError_t launch_chain_cell(const ResParams& p, hipStream_t st) {
-  constexpr int GROUPS = 8 / KS, FTB = (GROUPS == 2 && NBT == 2) ? 2 : 1, FTR = GROUPS / FTB, NRTW = (NRT + FTR - 1) / FTR;
+  constexpr int FTB = (KS == 4 && NBT == 2) ? 2 : 1, NRTW = chain_row_tiles<T, NRT, KS, NBT>;
   constexpr int BLOCKS = Sums<NRTW, NBT == 0 ? 0 : NBT / FTB>::BLOCKS;
-  constexpr size_t lds = (size_t)8 * BLOCKS * 1024 + (size_t)8 * NRTW * NXL * 1024;
+  constexpr size_t lds = (size_t)8 * BLOCKS * 1024 + (size_t)8 * NRTW * NXL * (chain_in_halves<T, NRT, KS, NBT> ? 2048 : 1024);
   static_assert(lds <= 160 * 1024 - 64, "LDS of a compute unit");
   hipError_t e = allow_dynamic_lds<forward_chain_kernel<T, NRT, NXW, NXL, NHW, KS, NBT, CELL>>(lds);
   if (e != hipSuccess) return e;

@@ -38,7 +38,8 @@ __device__ inline int units_of(const __attribute__((address_space(4))) SweepPara
 // All steps of a launch for units [u0, u1) of the XCD's sequences, by a workgroup that has stopped waiting (see
 // chain_slowly).  Its waves deal the units out sixteen at a time: dh of a tile passes through LDS from the MFMA's layout (a lane has four
 // consecutive units) to that of the gate sums (a lane has one unit of each four).
-template <class P, class T, bool FWD, int KSF, int KSB, int CELL>
+// HALVES: the odd macro steps of the KSB / 2 parts of K are the upper half of KSB (backward_in_halves).
+template <class P, class T, bool FWD, int KSF, int KSB, int CELL, bool HALVES = false>
 __device__ __forceinline__ void sweep_slowly(int b_lo, int b_hi, int u0, int u1, float* smem, int* s_fail) {
   const auto& p = *arguments_again<P>();
   const int waves = (int)(blockDim.x >> 6);
@@ -115,7 +116,10 @@ __device__ __forceinline__ void sweep_slowly(int b_lo, int b_hi, int u0, int u1,
           }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {   // fixed order, as in backward_body
-          if constexpr (KSB == WIDE_BACK_PARTS) {
+          if constexpr (HALVES) {
+#pragma unroll
+            for (int w = 0; w < KSB / 2; ++w) dh4[r] += acc[w][r] + acc[w + KSB / 2][r];
+          } else if constexpr (KSB == WIDE_BACK_PARTS) {
             dh4[r] = sum_back_parts([&](int w) { return acc[w][r]; });
           } else {
 #pragma unroll
@@ -210,9 +214,14 @@ __device__ __forceinline__ void sweep_slowly(int b_lo, int b_hi, int u0, int u1,
 // (4.1 - 4.4 with the GEMMs in order).
 // K splits and summation orders are those of forward_body and backward_body for the shape, the
 // pointwise steps are the shared functions: bit-identical to the launch-per-step path.
+// Up to 64 sequences (half tiles), bf16, K split eight ways: the backward product takes two macro steps an instruction
+// (Halves), half the matrix instructions and half the fetches of dG, whose every lane then carries data: H = 1024, B = 64 62.2 -> 57.9 us a
+// launch of 18 steps on average.
 // NXW, NHW, KSF: macro steps of x and h per wave and K split of the forward part; NBW, KSB: macro steps of
 // dG per wave (the weights of the last NBL are parked in LDS: registers are what the two largest
 // instantiations are short of) and K split of the backward part; NBT: batch tiles of the XCD's share.
+template <class T, int KSB, int NBT>
+constexpr bool sweep_in_halves = sizeof(T) == 2 && KSB == 8 && NBT == 0;
 constexpr int SWEEP_KEPT = 320;   // values a wave turns over per step: 64 items' dG and h_{s-1}
 template <class T, bool FWD, int NRT, int NXW, int NHW, int KSF, int NBW, int NBL, int KSB, int NBT, int CELL>
 __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
@@ -229,6 +238,10 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
   constexpr int GF = 8 / KSF, FTB = (GF == 2 && NBT == 2) ? 2 : 1, FTR = GF / FTB;   // forward: groups of waves along batch, rows
   constexpr int NRTW = (NRT + FTR - 1) / FTR, BTWF = NB / FTB;
   constexpr int GB = 8 / KSB, BTB = (GB == 2 && NBT == 2) ? 2 : 1, BTWB = NB / BTB;   // backward: along the batch, or one group idles
+  constexpr bool HALVES = sweep_in_halves<T, KSB, NBT>;
+  static_assert(!HALVES || (NBW % 2 == 0 && NBL % 2 == 0), "macro steps in twos");
+  constexpr int NBF = HALVES ? NBW / 2 : NBW, NBP = HALVES ? NBL / 2 : NBL;   // a wave's fetches of dG; weights of the last NBP parked
+  using Weights = std::conditional_t<HALVES, bf16x16, typename M::Frag>;
   using SumF = Sums<NRTW, NBT == 0 ? 0 : BTWF>;
   using SumB = Sums<NTB, NBT == 0 ? 0 : BTWB>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -281,8 +294,11 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
       const int rt = ul >> 2, rw = FTR > 1 ? rt % NRTW : rt, wf = FTR > 1 ? rt / NRTW : (FTB > 1 ? (col >> 4) / BTWF : 0);
       cellF[q] = redF + (size_t)(wf * KSF * SumF::BLOCKS + SumF::block(rw, FTB > 1 ? col % (BTWF * 16) : col)) * 64 + SumF::lane(rw, ul & 3, col);
       const int tb = ul >> 4, wB = BTB > 1 ? (col >> 4) / BTWB : 0;
-      cellB[q] = reinterpret_cast<const float*>(redB + (size_t)(wB * KSB * SumB::BLOCKS + SumB::block(tb, BTB > 1 ? col % (BTWB * 16) : col)) * 64 +
-                                                SumB::lane(tb, (ul & 15) >> 2, col)) + (ul & 3);
+      if constexpr (HALVES)
+        cellB[q] = reinterpret_cast<const float*>(redB + (tb >> 1) * 64 + Halves::lane_of(ul & 15, col)) + 2 * (tb & 1) + (col & 1);
+      else
+        cellB[q] = reinterpret_cast<const float*>(redB + (size_t)(wB * KSB * SumB::BLOCKS + SumB::block(tb, BTB > 1 ? col % (BTWB * 16) : col)) * 64 +
+                                                  SumB::lane(tb, (ul & 15) >> 2, col)) + (ul & 3);
     }
     mine[q] = item < ITEMS && b < b_hi && u < p.HP;
     real[q] = mine[q] && u < p.H;
@@ -321,7 +337,8 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
   publish(p.published);   // travels while the weights are fetched
 
   // resident weights: the forward rows of this workgroup's units, and the rows of W_hh^T for the same units
-  typename M::Frag wx[FWD ? NRTW : 1][FWD ? NXW : 1], wh[FWD ? NRTW : 1][FWD ? NHW : 1], wb[NTB][NBW - NBL > 0 ? NBW - NBL : 1];
+  typename M::Frag wx[FWD ? NRTW : 1][FWD ? NXW : 1], wh[FWD ? NRTW : 1][FWD ? NHW : 1];
+  Weights wb[NTB][NBF - NBP > 0 ? NBF - NBP : 1];
   if constexpr (FWD) {
 #pragma unroll
     for (int rt = 0; rt < NRTW; ++rt) {
@@ -346,14 +363,25 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
     const int n = min(rank * UW + min(tb * 16 + lrow, UW - 1), p.HP - 1);   // this lane's row (a row past the units is never used)
     const T* base = reinterpret_cast<const T*>(p.WTh) + ((size_t)(n >> 4) * nstepsB * 64 + lq * 16 + (n & 15)) * VEC;
 #pragma unroll
-    for (int k = 0; k < NBW; ++k) {
-      const int m = bk + KSB * k;
-      typename M::Frag f = M::load(base + (size_t)min(m, nstepsB - 1) * FRAG);
-      if (m >= nstepsB) f = typename M::Frag{};
-      if (k < NBW - NBL)
-        wb[tb][k < NBW - NBL ? k : 0] = f;
-      else
-        *reinterpret_cast<typename M::Frag*>(&wl[((size_t)(wave * NTB + tb) * NBL + (k - (NBW - NBL))) * FRAG + lane * VEC]) = f;
+    for (int k = 0; k < NBF; ++k) {
+      if constexpr (HALVES) {
+        const bf16x16 f = Halves::load(p.WTh, (unsigned)(((n >> 4) * nstepsB * 64 + (n & 15)) * 16), bk + 2 * KSB * k, bk + 2 * KSB * k + KSB, nstepsB, lq);
+        if (k < NBF - NBP) {
+          wb[tb][k < NBF - NBP ? k : 0] = f;
+        } else {
+          typename M::Frag* to = reinterpret_cast<typename M::Frag*>(wl) + ((size_t)(wave * NTB + tb) * NBP + (k - (NBF - NBP))) * 128 + lane;
+          to[0] = __builtin_shufflevector(f, f, 0, 1, 2, 3, 4, 5, 6, 7);
+          to[64] = __builtin_shufflevector(f, f, 8, 9, 10, 11, 12, 13, 14, 15);
+        }
+      } else {
+        const int m = bk + KSB * k;
+        typename M::Frag f = M::load(base + (size_t)min(m, nstepsB - 1) * FRAG);
+        if (m >= nstepsB) f = typename M::Frag{};
+        if (k < NBW - NBL)
+          wb[tb][k < NBW - NBL ? k : 0] = f;
+        else
+          *reinterpret_cast<typename M::Frag*>(&wl[((size_t)(wave * NTB + tb) * NBL + (k - (NBW - NBL))) * FRAG + lane * VEC]) = f;
+      }
     }
   }
 
@@ -368,7 +396,7 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
   }
 #pragma unroll
   for (int t = 0; t < BTWB; ++t) {
-    const int b = b_lo + (btb0 + t) * 16 + lrow;
+    const int b = b_lo + (btb0 + t) * 16 + (HALVES ? lrow & 7 : lrow);
     goff[t] = b < b_hi ? (unsigned)(((b >> 4) * nstepsB * 64 + lq * 16 + (b & 15)) * 16) : RES_NO_LANE;
   }
 
@@ -476,13 +504,8 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
       st_dy[q] = pf_dy[q];
       if constexpr (FWD) {
         if (!mine[q]) continue;
-        float G[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int w = 0; w < KSF; ++w) {   // fixed order, as in forward_body
-          const f32x4 v = cellF[q][w * SumF::BLOCKS * 64];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) G[r] += v[r];
-        }
+        const f32x4 v = sum_forward_parts<T, KSF>(f32x4{0.f, 0.f, 0.f, 0.f}, [&](int w) { return cellF[q][w * SumF::BLOCKS * 64]; });   // as in forward_body
+        const float G[4] = {v[0], v[1], v[2], v[3]};
         st_h[q] = cell_forward<T, CELL>(G, bias[q], st_cprev[q], st_c[q], st_gate[q]);
       } else {
 #pragma unroll
@@ -559,27 +582,30 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
     }
   };
 
+  const int picks = Halves::picks(lane);
   fetch(0);
   advance();
 
   for (int j = 0; j < p.count; ++j) {
     const int s = p.s_hi - j;                       // the step back-propagated now
     // dG of step s + 1, all columns of the XCD's sequences
-    typename M::Frag gfr[NBW][BTWB];
+    typename M::Frag gfr[NBF][BTWB];
     if (bwd_wave) {
       const T* slot = reinterpret_cast<const T*>(p.ring) + (size_t)((p.published + (unsigned)j) % RES_RING) * dG_step;
       WaitBound bound{j == 0 ? p.patience : p.wait_ticks, p.sync + RES_SYNC_STATUS};
       while (true) {
-        u32x4 raw[NBW][BTWB];
+        u32x4 raw[NBF][BTWB];
         unsigned top = 0;
 #pragma unroll
-        for (int k = 0; k < NBW; ++k) {
-          const int m = bk + KSB * k;
+        for (int k = 0; k < NBF; ++k) {
+          const int m = bk + (HALVES ? KSB * (2 * k + (lrow >> 3)) : KSB * k);
 #pragma unroll
-          for (int t = 0; t < BTWB; ++t) raw[k][t] = load_slot_16(slot, m < nstepsB ? goff[t] : RES_NO_LANE, m * 1024);
+          for (int t = 0; t < BTWB; ++t)
+            raw[k][t] = HALVES ? load_slot_16(slot, m < nstepsB ? goff[t] + KSB * 1024u * (unsigned)(lrow >> 3) : RES_NO_LANE, (bk + 2 * KSB * k) * 1024)
+                               : load_slot_16(slot, m < nstepsB ? goff[t] : RES_NO_LANE, m * 1024);
         }
 #pragma unroll
-        for (int k = 0; k < NBW; ++k)
+        for (int k = 0; k < NBF; ++k)
 #pragma unroll
           for (int t = 0; t < BTWB; ++t) {
             top = max(top, largest_dword(raw[k][t]));
@@ -598,29 +624,47 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
     __builtin_amdgcn_sched_barrier(0);
     // dh = dG_{s+1} W_hh for this workgroup's units
     if (bwd_wave) {
+      f32x4* sums = redB + (size_t)wave * SumB::BLOCKS * 64;
       f32x4 acc[NTB][BTWB];
 #pragma unroll
       for (int tb = 0; tb < NTB; ++tb)
 #pragma unroll
         for (int t = 0; t < BTWB; ++t) acc[tb][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int k = 0; k < NBW; ++k)
+      for (int k = 0; k < NBF; ++k)
 #pragma unroll
         for (int tb = 0; tb < NTB; ++tb) {
-          typename M::Frag a;
-          if (k < NBW - NBL)
-            a = wb[tb][k < NBW - NBL ? k : 0];
-          else
+          Weights a;
+          if (k < NBF - NBP) {
+            a = wb[tb][k < NBF - NBP ? k : 0];
+          } else if constexpr (HALVES) {
+            const typename M::Frag* from = reinterpret_cast<const typename M::Frag*>(wl) + ((size_t)(wave * NTB + tb) * NBP + (k - (NBF - NBP))) * 128 + lane;
+            a = __builtin_shufflevector(from[0], from[64], 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
+          } else {
             a = M::load(&wl[((size_t)(wave * NTB + tb) * NBL + (k - (NBW - NBL))) * FRAG + lane * VEC]);
+          }
 #pragma unroll
-          for (int t = 0; t < BTWB; ++t) acc[tb][t] = M::mma(a, gfr[k][t], acc[tb][t]);
+          for (int t = 0; t < BTWB; ++t) {
+            if constexpr (HALVES)
+              acc[tb][t] = Halves::mma(gfr[k][t], a, acc[tb][t], picks);
+            else
+              acc[tb][t] = M::mma(a, gfr[k][t], acc[tb][t]);
+          }
         }
-      SumB::write(redB + (size_t)wave * SumB::BLOCKS * 64, lane, acc);
+      if constexpr (HALVES) {
+#pragma unroll
+        for (int tb = 0; tb < NTB; tb += 2) {
+          const Halves::Sum lo = Halves::fold(acc[tb][0]), hi = tb + 1 < NTB ? Halves::fold(acc[tb + 1 < NTB ? tb + 1 : tb][0]) : Halves::Sum{};
+          sums[tb / 2 * 64 + lane] = f32x4{lo.v[0], lo.v[1], hi.v[0], hi.v[1]};
+        }
+      } else {
+        SumB::write(sums, lane, acc);
+      }
     }
     lds_barrier();
     if (__builtin_amdgcn_readfirstlane(s_fail))   // a wave has stopped waiting: written before the barrier, so all see it
       stop_waiting<SweepParams, UW>(&s_g, &s_rank, &s_fail, [&](int b_lo, int b_hi, int u0, int u1) {
-        sweep_slowly<SweepParams, T, FWD, KSF, KSB, CELL>(b_lo, b_hi, u0, u1, reinterpret_cast<float*>(smem), &s_fail);
+        sweep_slowly<SweepParams, T, FWD, KSF, HALVES ? 2 * KSB : KSB, CELL, HALVES>(b_lo, b_hi, u0, u1, reinterpret_cast<float*>(smem), &s_fail);
       });
     // pointwise backward of step s on the internal state held in registers
 #pragma unroll
@@ -648,7 +692,10 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
     if (j + 1 < p.count) {
       publish(p.published + (unsigned)j + 1);
       keep_transposed();
-      if constexpr (!FWD) lds_barrier();   // the partial sums have been read: the next step may overwrite them (FWD: advance() meets)
+      // The partial sums have been read: the next step may overwrite them (FWD: advance() meets).  Two buffers in turn without this
+      // barrier are slower, here and in chains: the waves that have no items ask for the next step sooner, and ask in vain (a gradient
+      // step of H = 1024, B = 64 10.0 -> 10.5 ms, of H = 512, B = 256 104.6 -> 108.9).
+      if constexpr (!FWD) lds_barrier();
       advance();
     }
   }

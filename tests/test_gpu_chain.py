@@ -601,6 +601,29 @@ def test_every_instantiation(dtype, B, I, H, cell):
             assert prof.batch_steps == 0 and prof.sweep_forward_steps > 0
 
 
+# Half tiles, where one matrix instruction takes two macro steps: a group of sequences that is full, has one or lacks one; row tiles in
+# pairs of four, six and eight, the last one short; parts of K of unequal length, and x that ends inside a macro step.
+@pytest.mark.parametrize("B,I,H,cell", [(1, 200, 500, 0), (9, 520, 512, 1), (8, 40, 705, 0), (63, 264, 769, 0), (57, 33, 1000, 1), (64, 1, 1024, 0),
+                                        (16, 130, 897, 0), (64, 256, 1024, 1)])
+def test_two_macro_steps_per_instruction(B, I, H, cell):
+    from oracle import gru_bptt as og
+    from test_gpu_parity import TOL
+    t = 12
+    w = wl.Workload("halves", B=B, I=I, H=H, t=t, kind=wl.KIND_ISM, m=t, gemm_dtype=wl.GEMM_BF16, loss=wl.LOSS_EXTERNAL_DY,
+                    dy_first_step=1, seed=70 + B + I + H, cell=cell)
+    inp = wl.make_inputs(w, nonzero_state=True, nonzero_bias=True)
+    base = _run(w, inp, wl.KIND_HSM, 3, chain=False)
+    if cell:
+        ref = og.gru_bptt(inp.W_ih, inp.W_hh, inp.b, inp.x, inp.h0, inp.dy, w.dy_first_step)
+    else:
+        ref = ob.lstm_bptt(inp.W_ih, inp.W_hh, inp.b, inp.x, inp.h0, inp.c0, inp.dy, w.dy_first_step)
+    for name in ("dW_ih", "dW_hh", "db", "dh0", "dx", "y") + (() if cell else ("dc0",)):
+        got, want = getattr(base, name).astype(np.float64), getattr(ref, name)
+        assert np.linalg.norm(got - want) <= TOL[w.gemm_dtype] * np.linalg.norm(want), name
+    for kind, m in ((wl.KIND_HSM, 3), (wl.KIND_ISM, t)):
+        _same(_run(w, inp, kind, m, chain=True), base, (kind, m))
+
+
 def test_random_widths_types_and_budgets_bit_identical():
     """As the seeded random cases above, over any width, both operand types, batches up to 256 and inputs
     wider and narrower than the state."""
