@@ -110,10 +110,18 @@ __device__ inline int tile_row(int r0, int rows, int t, int x) {
 // loop.  Partial sums meet in LDS and are added in a fixed order.  What bounds a product is the delivery of its
 // panels through the L2s: the next macro step is requested when the MFMAs of this one have been issued, and more
 // steps in flight are slower (twelve layers of 256 to 2048 units, batch 256: 455 us a gradient step at one
-// step ahead, 468 and 494 us at two and three), as are workgroups for 512 or 128 places instead of 256 (514 and
+// step ahead, 468 and 494 us at two and three; 438 with forward products staged), as are workgroups for 512 or 128 places instead of 256 (514 and
 // 488 us), and macro steps of a whole cache line per row (474 us).  The kernel before this one (a tile per wave, strided scalar
 // loads, separate launches for dz, db and the copy of y) took 3543 us.
-template <bool A_ACROSS, bool B_ACROSS, int TM, int TN, int EPI, bool NARROW>
+// STAGED (both operands stored along k): they pass through LDS, each wave's own part of it (no barrier).  A fragment straight from memory
+// takes 16 bytes of each of 16 rows in neighbouring lanes, which the address path takes one by one; eight lanes
+// that fetch a row's 128 bytes straight into LDS take it a line at a time.  A step is then 32 of k; slot c of row r holds the row's
+// 16 bytes c ^ (r % 8), so that the reads of 16 rows fall into different banks.  The next step's fetches go out when the fragments
+// of this one are in registers, and arrive behind its MFMAs.
+constexpr int STEP = 32;   // of k, staged
+template <int TM, int TN, bool STAGED>
+constexpr size_t product_lds = std::max((size_t)KS * TM * TN * 256 * sizeof(float), STAGED ? (size_t)KS * 16 * (TM + TN) * STEP * sizeof(float) : 0);
+template <bool A_ACROSS, bool B_ACROSS, int TM, int TN, int EPI, bool NARROW, bool STAGED>
 __device__ inline void product_body(const Product& p, int id, float* red) {
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;   // scalar: conditions on it are scalar branches
   const int lrow = lane & 15, lq = lane >> 4;
@@ -142,26 +150,80 @@ __device__ inline void product_body(const Product& p, int id, float* red) {
         for (int e = 0; e < 4; ++e) rowsum[i] += a[i][e];
     }
   };
-  const int full = p.K / 16;   // macro steps wholly inside K
-  const int nw = (full - wave + KS - 1) / KS;   // this wave's macro steps: wave, wave + KS, ...
-  float a[TM][4], b[TN][4];
-  auto fetch = [&](int n) {
-    const int k0 = (wave + n * KS) * 16;
-    fetch_tiles<A_ACROSS, TM, false, NARROW>(a, p.A, p.lda, i0, p.M, k0, p.K, lrow, lq);
-    fetch_tiles<B_ACROSS, TN, false, NARROW>(b, p.Bm, p.ldb, j0, p.N, k0, p.K, lrow, lq);
-  };
-  if (nw > 0) {
-    fetch(0);
-    for (int n = 0; n + 1 < nw; ++n) {
-      use(a, b);
-      fetch(n + 1);
+  if constexpr (STAGED) {
+    static_assert(!A_ACROSS && !B_ACROSS, "both operands along k");
+    typedef __attribute__((address_space(1))) const void global_void;
+    typedef __attribute__((address_space(3))) void lds_void;
+    constexpr int R = 16 * (TM + TN), NQ = R / 8;
+    float* stage = red + wave * R * STEP;
+    const int full = p.K / STEP, nw = (full - wave + KS - 1) / KS;   // steps wholly inside K; this wave's: wave, wave + KS, ...
+    const float* src[NQ];   // this lane's 16 bytes of row 8 q + lane / 8, step 0 of the wave
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const int r = 8 * q + (lane >> 3);
+      const float* row = 8 * q < 16 * TM ? p.A + (long)min(i0 + r, p.M - 1) * p.lda : p.Bm + (long)min(j0 + r - 16 * TM, p.N - 1) * p.ldb;
+      src[q] = row + wave * STEP + 4 * ((lane & 7) ^ (r & 7));
     }
-    use(a, b);
-  }
-  if (p.K % 16 != 0 && wave == full % KS) {
-    fetch_tiles<A_ACROSS, TM, true, NARROW>(a, p.A, p.lda, i0, p.M, full * 16, p.K, lrow, lq);
-    fetch_tiles<B_ACROSS, TN, true, NARROW>(b, p.Bm, p.ldb, j0, p.N, full * 16, p.K, lrow, lq);
-    use(a, b);
+    auto issue = [&](int n) {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+        __builtin_amdgcn_global_load_lds((global_void*)(src[q] + n * (KS * STEP)), (lds_void*)(stage + q * 256), 16, 0, 0);
+    };
+    auto staged = [&](float (&v)[4], int r, int h) {
+      const f32x4 x = *reinterpret_cast<const f32x4*>(stage + r * STEP + 4 * ((4 * h + lq) ^ (r & 7)));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = x[e];
+    };
+    if (nw > 0) issue(0);
+    for (int n = 0; n < nw; ++n) {
+      float a[2][TM][4], b[2][TN][4];
+      __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): the step is here
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) staged(a[h][i], 16 * i + lrow, h);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) staged(b[h][j], 16 * (TM + j) + lrow, h);
+      }
+      __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): read, the stage may be filled again
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      if (n + 1 < nw) issue(n + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      use(a[0], b[0]);
+      use(a[1], b[1]);
+    }
+    if (wave == full % KS)
+      for (int k0 = full * STEP; k0 < p.K; k0 += 16) {
+        float a[TM][4], b[TN][4];
+        fetch_tiles<A_ACROSS, TM, true, NARROW>(a, p.A, p.lda, i0, p.M, k0, p.K, lrow, lq);
+        fetch_tiles<B_ACROSS, TN, true, NARROW>(b, p.Bm, p.ldb, j0, p.N, k0, p.K, lrow, lq);
+        use(a, b);
+      }
+    __syncthreads();   // the sums take the place of the stages
+  } else {
+    const int full = p.K / 16;   // macro steps wholly inside K
+    const int nw = (full - wave + KS - 1) / KS;   // this wave's macro steps: wave, wave + KS, ...
+    float a[TM][4], b[TN][4];
+    auto fetch = [&](int n) {
+      const int k0 = (wave + n * KS) * 16;
+      fetch_tiles<A_ACROSS, TM, false, NARROW>(a, p.A, p.lda, i0, p.M, k0, p.K, lrow, lq);
+      fetch_tiles<B_ACROSS, TN, false, NARROW>(b, p.Bm, p.ldb, j0, p.N, k0, p.K, lrow, lq);
+    };
+    if (nw > 0) {
+      fetch(0);
+      for (int n = 0; n + 1 < nw; ++n) {
+        use(a, b);
+        fetch(n + 1);
+      }
+      use(a, b);
+    }
+    if (p.K % 16 != 0 && wave == full % KS) {
+      fetch_tiles<A_ACROSS, TM, true, NARROW>(a, p.A, p.lda, i0, p.M, full * 16, p.K, lrow, lq);
+      fetch_tiles<B_ACROSS, TN, true, NARROW>(b, p.Bm, p.ldb, j0, p.N, full * 16, p.K, lrow, lq);
+      use(a, b);
+    }
   }
   // red[wave][tile][r][lane]
 #pragma unroll
@@ -217,19 +279,19 @@ __device__ inline void product_body(const Product& p, int id, float* red) {
   }
 }
 
-template <int TM, int TN, bool NARROW>
+template <int TM, int TN, bool NARROW, bool STAGED>
 __global__ __launch_bounds__(KS * 64) void chain_forward_kernel(Product p) {
   extern __shared__ __attribute__((aligned(16))) float chain_smem[];
-  product_body<false, false, TM, TN, BIAS_TANH, NARROW>(p, blockIdx.x, chain_smem);
+  product_body<false, false, TM, TN, BIAS_TANH, NARROW, STAGED>(p, blockIdx.x, chain_smem);
 }
 // The first nd workgroups compute the data product (none: nd = 0), the others, if any, the weight product.
 template <int DTM, int DTN, int WTM, int WTN, bool NARROW>
 __global__ __launch_bounds__(KS * 64) void chain_backward_kernel(Product data, int nd, Product weight) {
   extern __shared__ __attribute__((aligned(16))) float chain_smem[];
   if ((int)blockIdx.x < nd)
-    product_body<false, true, DTM, DTN, TIMES_DTANH, NARROW>(data, blockIdx.x, chain_smem);
+    product_body<false, true, DTM, DTN, TIMES_DTANH, NARROW, false>(data, blockIdx.x, chain_smem);
   else
-    product_body<true, true, WTM, WTN, STORE_AND_DB, NARROW>(weight, blockIdx.x - nd, chain_smem);
+    product_body<true, true, WTM, WTN, STORE_AND_DB, NARROW, false>(weight, blockIdx.x - nd, chain_smem);
 }
 
 // dz = g * (1 - y^2), elementwise over B * d values.
@@ -241,25 +303,31 @@ __global__ void chain_dz_kernel(const float* __restrict__ g, const float* __rest
 int blocks_of(int rows, int tiles) { return (rows + 16 * tiles - 1) / (16 * tiles); }
 constexpr int FILL = 256;   // workgroups that give every compute unit one
 
-template <int TM, int TN, bool NARROW>
+template <int TM, int TN, bool NARROW, bool STAGED>
 hipError_t launch_forward_tiles(Product& p, hipStream_t st) {
-  constexpr size_t lds = (size_t)KS * TM * TN * 256 * sizeof(float);
-  hipError_t e = allow_dynamic_lds<chain_forward_kernel<TM, TN, NARROW>>(lds);
+  constexpr size_t lds = product_lds<TM, TN, STAGED>;
+  hipError_t e = allow_dynamic_lds<chain_forward_kernel<TM, TN, NARROW, STAGED>>(lds);
   if (e != hipSuccess) return e;
   p.gx = blocks_of(p.N, TN);
-  chain_forward_kernel<TM, TN, NARROW><<<dim3(p.gx * blocks_of(p.M, TM)), dim3(KS * 64), lds, st>>>(p);
+  chain_forward_kernel<TM, TN, NARROW, STAGED><<<dim3(p.gx * blocks_of(p.M, TM)), dim3(KS * 64), lds, st>>>(p);
   return hipGetLastError();
 }
 
 // The largest output block per workgroup that still gives every compute unit one.  Vectors of four along
 // k (or along a row, for operands stored across k) need dimensions of at least four.
-hipError_t launch_chain_forward(Product p, hipStream_t st) {
-  if (p.K < 4) return launch_forward_tiles<1, 1, true>(p, st);
-  if (blocks_of(p.N, 4) * blocks_of(p.M, 4) >= FILL) return launch_forward_tiles<4, 4, false>(p, st);
-  if (blocks_of(p.N, 4) * blocks_of(p.M, 2) >= FILL) return launch_forward_tiles<2, 4, false>(p, st);
-  if (blocks_of(p.N, 2) * blocks_of(p.M, 2) >= FILL) return launch_forward_tiles<2, 2, false>(p, st);
-  if (blocks_of(p.N, 2) * blocks_of(p.M, 1) >= FILL) return launch_forward_tiles<1, 2, false>(p, st);
-  return launch_forward_tiles<1, 1, false>(p, st);
+// Operands pass through LDS (product_body) where all rows are whole 16-byte slots -- `slots`, which for a layer has to be the same wherever
+// its input sits, or a recomputed activation would not have the first one's bits -- and every wave has a step of 32.  us a launch, direct and staged:
+// batch 256, 1024 -> 1024 (2 x 2 tiles) 11.6 and 11.8, 1536 -> 1000 (1 x 2) 14.1 and 11.3, 900 -> 256 (1 x 1) 6.7 and 4.4.  On 2 x 4
+// tiles 11.6 and 15.7: there the stages leave a compute unit one workgroup.  Two stages a wave, two steps in flight: 13.3 on 2 x 2, 12.4 for
+// 10.1 on 1 x 2.  Gradient steps of twelve drawn chains take 0.94 - 1.00 of the time.
+hipError_t launch_chain_forward(Product p, bool slots, hipStream_t st) {
+  if (p.K < 4) return launch_forward_tiles<1, 1, true, false>(p, st);
+  if (blocks_of(p.N, 4) * blocks_of(p.M, 4) >= FILL) return launch_forward_tiles<4, 4, false, false>(p, st);
+  if (blocks_of(p.N, 4) * blocks_of(p.M, 2) >= FILL) return launch_forward_tiles<2, 4, false, false>(p, st);
+  const bool staged = slots && p.K >= KS * STEP;
+  if (blocks_of(p.N, 2) * blocks_of(p.M, 2) >= FILL) return staged ? launch_forward_tiles<2, 2, false, true>(p, st) : launch_forward_tiles<2, 2, false, false>(p, st);
+  if (blocks_of(p.N, 2) * blocks_of(p.M, 1) >= FILL) return staged ? launch_forward_tiles<1, 2, false, true>(p, st) : launch_forward_tiles<1, 2, false, false>(p, st);
+  return staged ? launch_forward_tiles<1, 1, false, true>(p, st) : launch_forward_tiles<1, 1, false, false>(p, st);
 }
 
 template <int DTM, int DTN, int WTM, int WTN, bool NARROW>
@@ -445,7 +513,10 @@ int mebptt_chain_run(const mebptt_chain_desc* desc, const mebptt_chain_plan_t* p
         p.N = dout;
         p.K = din;
         p.bias = b[L - 1];
-        HIP_TRY(launch_chain_forward(p, st));
+        // the input sits in x0, in the pool (256-byte aligned, units apart) or in the workspace
+        auto aligned = [](const float* q) { return reinterpret_cast<uintptr_t>(q) % 16 == 0; };
+        const bool slots = din % 4 == 0 && aligned(W[L - 1]) && (L == 1 ? aligned(x0) : unit % 16 == 0);
+        HIP_TRY(launch_chain_forward(p, slots, st));
         forward_cost += layers[L - 1].cost;
         before = a;
         a = out;
