@@ -425,8 +425,8 @@ __device__ inline void forward_body(const FwdParams& p, int bx, int by, float* r
     const int item = (int)threadIdx.x + q * NTHR;
     if (item >= ITEMS) break;
     const int cell = ((item / UW) % (BT * 16)) * RS + item % UW;
-    const f32x4 v = sum_forward_parts<T, KS>(f32x4{0.f, 0.f, 0.f, 0.f}, [&](int w) { return red4[w * BT * 16 * RS + cell]; });   // fixed order
-    const float G[4] = {v[0], v[1], v[2], v[3]};
+    float G[4];
+    sum_forward_parts<T, KS>(G, [&](int w) { return red4[w * BT * 16 * RS + cell]; });   // fixed order
     if (!epi[q]) {
       // split layout: the padding columns H..KH of a valid row are part of the operand other
       // launches fetch, so they are (re)written as zero with every state

@@ -351,9 +351,7 @@ __device__ __forceinline__ void gates_slowly(const void* Wp, int tile, const flo
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  const f32x4 v = sum_forward_parts<T, KS>(f32x4{0.f, 0.f, 0.f, 0.f}, [&](int w) { return acc[w]; });
-#pragma unroll
-  for (int r = 0; r < 4; ++r) G[r] = v[r];
+  sum_forward_parts<T, KS>(G, [&](int w) { return acc[w]; });
 }
 
 // All steps of a launch for units [u0, u1) of the XCD's sequences, by a workgroup that has stopped waiting.  Its waves
@@ -769,14 +767,8 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
 #pragma unroll
     for (int q = 0; q < IPT; ++q) {
       if (!mine[q]) continue;
-      f32x4 v{0.f, 0.f, 0.f, 0.f};   // fixed order, as in forward_body
-      if constexpr (HALVES) {
-#pragma unroll
-        for (int w = 0; w < KW; ++w) v += cell[q][w * Sum::BLOCKS * 64];
-      } else {
-        v = sum_forward_parts<T, KS>(v, [&](int w) { return cell[q][w * Sum::BLOCKS * 64]; });
-      }
-      const float G[4] = {v[0], v[1], v[2], v[3]};
+      float G[4];   // fixed order, as in forward_body; a sum of Halves is that of two parts
+      sum_forward_parts<T, KW>(G, [&](int w) { return cell[q][w * Sum::BLOCKS * 64]; });
       const float h = cell_forward<T, CELL>(G, bias[q], c_state[q], keep_second[q], keep_gate[q]);
       keep_h[q] = real[q] ? h : 0.0f;
       c_state[q] = CELL ? keep_h[q] : keep_second[q];

@@ -504,8 +504,8 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
       st_dy[q] = pf_dy[q];
       if constexpr (FWD) {
         if (!mine[q]) continue;
-        const f32x4 v = sum_forward_parts<T, KSF>(f32x4{0.f, 0.f, 0.f, 0.f}, [&](int w) { return cellF[q][w * SumF::BLOCKS * 64]; });   // as in forward_body
-        const float G[4] = {v[0], v[1], v[2], v[3]};
+        float G[4];
+        sum_forward_parts<T, KSF>(G, [&](int w) { return cellF[q][w * SumF::BLOCKS * 64]; });   // as in forward_body
         st_h[q] = cell_forward<T, CELL>(G, bias[q], st_cprev[q], st_c[q], st_gate[q]);
       } else {
 #pragma unroll

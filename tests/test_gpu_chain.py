@@ -408,6 +408,19 @@ def test_resident_launches_pass_on_every_nan(dtype, B, I, H):
     assert np.array_equal(np.isnan(out.y), np.isnan(base.y)) and np.array_equal(out.y[:, bad + 2], base.y[:, bad + 2], equal_nan=True)
 
 
+# Weights that are infinite: a macro step that shares an instruction with an infinite weight's has to keep out of it (zero times
+# infinity would be a NaN), and so has a zero that stands for a part's missing macro step.
+@pytest.mark.parametrize("B,I,H,cell", [(64, 64, 1024, 0), (20, 650, 650, 0), (16, 40, 705, 1)])
+def test_infinite_weights(B, I, H, cell):
+    w = wl.Workload("inf", B=B, I=I, H=H, t=20, kind=wl.KIND_HSM, m=6, gemm_dtype=wl.GEMM_BF16, loss=wl.LOSS_EXTERNAL_DY, seed=6, cell=cell)
+    inp = wl.make_inputs(w, nonzero_state=True, nonzero_bias=True)
+    inp.W_hh[5, 7], inp.W_hh[H + 9, H - 1], inp.W_ih[11, I - 1] = np.inf, -np.inf, np.inf
+    base = _run(w, inp, wl.KIND_HSM, 6, chain=False)
+    assert np.isfinite(base.y).all()     # an infinite gate sum is a gate of 0 or 1
+    for kind, m in ((wl.KIND_HSM, 6), (wl.KIND_HSM, 20), (wl.KIND_ISM, 20)):
+        assert np.array_equal(_run(w, inp, kind, m, chain=True).y, base.y)   # gradients: zero times infinity
+
+
 @pytest.mark.parametrize("B,I,H", [(32, 128, 512), (33, 300, 512), (128, 130, 384), (129, 130, 384), (40, 64, 256)])
 def test_gemms_beside_or_between_resident_launches(B, I, H):
     """On both sides of every line of the rule that puts the time-batched GEMMs on a stream of their own:
