@@ -1748,7 +1748,12 @@ hipError_t launch_zero_operand_columns(const Dims& d, void* dGT, void* aT, int c
 // them; the fragments of aT every wave fetches straight into its MFMA registers.  Both are fetched PD macro steps
 // ahead.  (Both operands through LDS: 39.6 us per chunk on H = 1024, B = 64, so: 37.0; two macro steps per barrier: 37.8.)  gridDim.z workgroups may share one
 // output block, each with its own part of K and its own partial accumulator.
-template <class T, int WT>
+// gridDim.z workgroups: see wgrad_splits.
+// EXTRA: aT has one row tile (the row of ones, whose product is the bias gradient) more than whole blocks, which would cost a column of
+// blocks that are nearly empty.  Its 2 * WT products per row block are dealt out over the waves of the first blocks instead: one more
+// MFMA per macro step; the fragment comes through a buffer that gives waves without a product zeros and moves nothing for them.
+// A chunk of H = 256, I = 256, B = 64 12.4 -> 10.5 us.
+template <class T, int WT, bool EXTRA>
 __global__ __launch_bounds__(256) void wgrad_kernel(const T* __restrict__ dGT, const T* __restrict__ aT, int K, int KC,
                                                     int G4, int NTOT, int accumulate, float* __restrict__ dWacc) {
   using M = Mma<T>;
@@ -1775,10 +1780,17 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const T* __restrict__ dGT, c
   for (int q = 0; q < SW; ++q) src[q] = dGT + (((size_t)min(mt_wg + q * 4 + wave, MT - 1) * ncs + k_begin) * 64 + lane) * VEC;
 #pragma unroll
   for (int i = 0; i < WT; ++i) srcB[i] = aT + (((size_t)min(nt_wg + wn * WT + i, NT - 1) * ncs + k_begin) * 64 + lane) * VEC;
+  const int extra_i = (int)blockIdx.y * 2 + wn;   // of this wave's row tiles, the one it multiplies with the extra tile (from WT on: none)
+  const __amdgpu_buffer_rsrc_t extra_src =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(aT + (size_t)(NT - 1) * ncs * FRAG), 0, 0x7fffffff, 0x00020000);
+  const int extra_off = extra_i < WT ? lane * 16 : (int)0x80000000u;
+  const T* extra_a = &lds[0][(wm * WT + min(extra_i, WT - 1)) * FRAG + lane * VEC];
   u32x4 ring[PD][SW];
-  typename M::Frag ringB[PD][WT];
+  typename M::Frag ringB[PD][WT], ringE[PD];
   auto fetch = [&](int stage, int ks) {
     const size_t off = (size_t)min(ks, nk - 1) * FRAG;
+    if constexpr (EXTRA)
+      ringE[stage] = as_frag<typename M::Frag>(__builtin_amdgcn_raw_buffer_load_b128(extra_src, extra_off, (k_begin + min(ks, nk - 1)) * 1024, 0));
 #pragma unroll
     for (int q = 0; q < SW; ++q) ring[stage][q] = *reinterpret_cast<const u32x4*>(src[q] + off);
 #pragma unroll
@@ -1789,7 +1801,7 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const T* __restrict__ dGT, c
     for (int q = 0; q < SW; ++q)
       *reinterpret_cast<u32x4*>(&lds[buf][(q * 4 + wave) * FRAG + lane * VEC]) = ring[stage][q];
   };
-  f32x4 acc[WT][WT];
+  f32x4 acc[WT][WT], acc_extra{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int i = 0; i < WT; ++i)
 #pragma unroll
@@ -1821,6 +1833,8 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const T* __restrict__ dGT, c
           __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
         __builtin_amdgcn_sched_group_barrier(0x008, 2 * WT, 0);
+        if constexpr (EXTRA)
+          if (extra_i < WT) acc_extra = M::mma(M::load(extra_a + (ks & 1) * 2 * WT * FRAG), ringE[j], acc_extra);   // a scalar branch
         fetch(j, ks + PD);             // ring slot j has been used for step ks; refill it PD steps ahead
         if (ks + 1 < nk) stash((j + 1) % PD, (ks + 1) & 1);
       }
@@ -1833,8 +1847,15 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const T* __restrict__ dGT, c
   // contiguous run, a lane's four accumulator rows one float4), so the
   // read-modify-write of every chunk is fully coalesced; wgrad_finish_kernel converts it to the
   // caller's row-major dW once at the end of the run.
-  float4* accp = reinterpret_cast<float4*>(dWacc) +
-                 (((size_t)blockIdx.z * gridDim.x * gridDim.y + blockIdx.x * gridDim.y + blockIdx.y) * 4 + wave) * (WT * WT) * 64 + lane;
+  // A part's accumulator: all blocks' tiles, then the extra tile's products, one after the other.
+  const size_t whole = (size_t)gridDim.x * gridDim.y * 4 * (WT * WT) * 64;
+  float4* part_acc = reinterpret_cast<float4*>(dWacc) + blockIdx.z * (whole + (EXTRA ? (size_t)gridDim.x * 2 * WT * 64 : 0));
+  float4* accp = part_acc + ((size_t)(blockIdx.x * gridDim.y + blockIdx.y) * 4 + wave) * (WT * WT) * 64 + lane;
+  if (EXTRA && extra_i < WT) {
+    float4* to = part_acc + whole + (size_t)(mt_wg + wm * WT + extra_i) * 64 + lane;
+    const float4 old = accumulate ? *to : float4{0.f, 0.f, 0.f, 0.f};
+    *to = float4{acc_extra[0] + old.x, acc_extra[1] + old.y, acc_extra[2] + old.z, acc_extra[3] + old.w};
+  }
   if (accumulate) {
     float4 old[WT * WT];
 #pragma unroll
@@ -1919,7 +1940,10 @@ __global__ void wgrad_finish_kernel(const float* __restrict__ dWacc, int WT, int
     } else {
       const int wgx = mt / (2 * WT), wm = (mt % (2 * WT)) / WT, i = mt % WT;
       const int wgy = nt / (2 * WT), wn = (nt % (2 * WT)) / WT, jj = nt % WT;
-      off = ((((size_t)(wgx * grid_y + wgy) * 4 + (wm + 2 * wn)) * (WT * WT) + (i * WT + jj)) * 64 + (lq * 16 + lrow)) * 4 + r;
+      if (wgy == grid_y)   // the extra tile
+        off = ((size_t)blocks * 4 * (WT * WT) * 64 + (size_t)mt * 64 + (lq * 16 + lrow)) * 4 + r;
+      else
+        off = ((((size_t)(wgx * grid_y + wgy) * 4 + (wm + 2 * wn)) * (WT * WT) + (i * WT + jj)) * 64 + (lq * 16 + lrow)) * 4 + r;
     }
     float v = dWacc[off];
     for (int sp = 1; sp < nsplit; ++sp) v += dWacc[(size_t)sp * split_stride + off];   // partial sums, fixed order
@@ -1927,24 +1951,43 @@ __global__ void wgrad_finish_kernel(const float* __restrict__ dWacc, int WT, int
   }
 }
 
-// Wave tile of the weight-gradient GEMM (4 x 4 MFMA tiles, 128 x 128 per workgroup, whenever the
-// output has at least one such tile in each direction; else 2 x 2) and the number of workgroups
-// that split K for one output tile: enough to give the chip about 1.5 workgroups per compute unit
-// when the output alone has too few tiles (long chunks of small matrices).
+// Wave tile of the weight-gradient GEMM: 4 x 4 MFMA tiles, 128 x 128 per workgroup, whenever the
+// output has at least one such tile in each direction; else 2 x 2.
 static int wgrad_wave_tile(const Dims& d) {
   const int MT = d.G4 / 16, NT = d.NA / 16;
   return (MT >= 8 && NT >= 8) ? 4 : 2;
 }
+// Output blocks, and whether the operand of ones has no block of its own (EXTRA; its products need 2 * gy >= WT blocks a row).  Above one
+// block per compute unit, where K is not split, the blocks saved shorten no compute unit's work and the extra products cost: H = 1024,
+// I = 256, 352 -> 320 blocks 36.3 -> 39.3 us.
+struct WgradBlocks {
+  int gx, gy;
+  bool extra;
+};
+static WgradBlocks wgrad_blocks(const Dims& d) {
+  const int WT = wgrad_wave_tile(d), NT = d.NA / 16;
+  WgradBlocks b{(d.G4 / 16 + 2 * WT - 1) / (2 * WT), (NT + 2 * WT - 1) / (2 * WT), false};
+  if (NT % (2 * WT) == 1 && 2 * (b.gy - 1) >= WT && b.gx * b.gy <= TARGET_WGS) {
+    --b.gy;
+    b.extra = true;
+  }
+  return b;
+}
+// Workgroups that split K for one output block, where the blocks alone do not fill the chip.  bf16 up to 128 sequences, whose GEMMs run
+// beside the sweeps: about 1.5 workgroups per compute unit (with two, H = 512, B = 128 takes 21.5 us a chunk for 22.1 but a gradient step
+// that stores everything 1192 us for 1185).  More sequences have the chip to themselves, and fp32 products take longer than they wait:
+// two per compute unit, as many as it holds at a time.  us a chunk, 1.5 and two: H = 512, I = 128, B = 256 37.6 and 32.0 (a gradient
+// step of t = 10 000 104.8 and 103.3 ms), fp32 H = 512, I = 256, B = 64 90 and 61.
 static int wgrad_splits(const Dims& d) {
-  const int WT = wgrad_wave_tile(d);
-  const int tiles = ((d.G4 / 16 + 2 * WT - 1) / (2 * WT)) * ((d.NA / 16 + 2 * WT - 1) / (2 * WT));
-  const int s = (384 + tiles / 2) / tiles;
-  return s < 1 ? 1 : (s > 8 ? 8 : s);
+  const WgradBlocks b = wgrad_blocks(d);
+  const int tiles = b.gx * b.gy;
+  if (!d.dtype || d.B > 128) return std::max(1, std::min(2 * TARGET_WGS / tiles, 8));
+  return std::max(1, std::min((384 + tiles / 2) / tiles, 8));
 }
 static size_t wgrad_partial_floats(const Dims& d) {   // one partial accumulator
   const int WT = wgrad_wave_tile(d);
-  const size_t gx = (d.G4 / 16 + 2 * WT - 1) / (2 * WT), gy = (d.NA / 16 + 2 * WT - 1) / (2 * WT);
-  return gx * gy * 4 * WT * WT * 64 * 4;
+  const WgradBlocks b = wgrad_blocks(d);
+  return ((size_t)b.gx * b.gy * 4 * WT * WT + (b.extra ? (size_t)b.gx * 2 * WT : 0)) * 64 * 4;
 }
 
 size_t wgrad_accumulator_bytes(const Dims& d) {
@@ -1960,12 +2003,13 @@ size_t wgrad_accumulator_bytes(const Dims& d) {
 template <class T>
 static void launch_wgrad_t(const Dims& d, const void* dGT, const void* aT, int K, int accumulate, float* dWacc,
                            hipStream_t st) {
-  const int NTOT = d.NA, WT = wgrad_wave_tile(d);
-  dim3 grid((d.G4 / 16 + 2 * WT - 1) / (2 * WT), (NTOT / 16 + 2 * WT - 1) / (2 * WT), wgrad_splits(d)), block(256);
-  if (WT == 4)
-    wgrad_kernel<T, 4><<<grid, block, 0, st>>>((const T*)dGT, (const T*)aT, K, d.KC, d.G4, NTOT, accumulate, dWacc);
+  const WgradBlocks b = wgrad_blocks(d);
+  const dim3 grid(b.gx, b.gy, wgrad_splits(d)), block(256);
+  auto launch = [&](auto kernel) { kernel<<<grid, block, 0, st>>>((const T*)dGT, (const T*)aT, K, d.KC, d.G4, d.NA, accumulate, dWacc); };
+  if (wgrad_wave_tile(d) == 4)
+    b.extra ? launch(wgrad_kernel<T, 4, true>) : launch(wgrad_kernel<T, 4, false>);
   else
-    wgrad_kernel<T, 2><<<grid, block, 0, st>>>((const T*)dGT, (const T*)aT, K, d.KC, d.G4, NTOT, accumulate, dWacc);
+    b.extra ? launch(wgrad_kernel<T, 2, true>) : launch(wgrad_kernel<T, 2, false>);
 }
 
 hipError_t launch_wgrad(const Dims& d, const void* dGT, const void* aT, int nslots, int accumulate, float* dWacc,
@@ -2011,9 +2055,9 @@ hipError_t launch_wgrad_finish(const Dims& d, const float* dWacc, float* dW_ih, 
     return hipGetLastError();
   }
   const int WT = wgrad_wave_tile(d);
-  const int grid_y = (d.NA / 16 + 2 * WT - 1) / (2 * WT);
-  wgrad_finish_kernel<<<grid, dim3(256), 0, st>>>(dWacc, WT, grid_y, wgrad_splits(d), wgrad_partial_floats(d), d.NX, d.HP,
-                                                        d.I, d.H, d.cell, dW_ih, dW_hh, db, 0, dc, dh0, dc0, plane, nw);
+  const WgradBlocks b = wgrad_blocks(d);
+  wgrad_finish_kernel<<<grid, dim3(256), 0, st>>>(dWacc, WT, b.gy, wgrad_splits(d), wgrad_partial_floats(d), d.NX, d.HP,
+                                                        d.I, d.H, d.cell, dW_ih, dW_hh, db, b.gx * b.gy, dc, dh0, dc0, plane, nw);
   return hipGetLastError();
 }
 
