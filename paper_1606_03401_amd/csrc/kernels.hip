@@ -425,8 +425,17 @@ __device__ inline void forward_body(const FwdParams& p, int bx, int by, float* r
     const int item = (int)threadIdx.x + q * NTHR;
     if (item >= ITEMS) break;
     const int cell = ((item / UW) % (BT * 16)) * RS + item % UW;
-    float G[4];
-    sum_forward_parts<T, KS>(G, [&](int w) { return red4[w * BT * 16 * RS + cell]; });   // fixed order
+    float G[4] = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (parts_in_pairs<T, KS>) {   // fixed order: results do not depend on scheduling
+      add_pairs<KS>(G, [&](int w) { return red4[w * BT * 16 * RS + cell]; });
+    } else {
+#pragma unroll
+      for (int w = 0; w < KS; ++w) {
+        const f32x4 v = red4[w * BT * 16 * RS + cell];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) G[r] += v[r];
+      }
+    }
     if (!epi[q]) {
       // split layout: the padding columns H..KH of a valid row are part of the operand other
       // launches fetch, so they are (re)written as zero with every state
@@ -788,7 +797,7 @@ __global__ __launch_bounds__(64 * KS) void forward_batch_kernel(FwdParams p, Fwd
 // operations.  A wave owns NR row tiles and covers all columns: its weight fragments go straight into the MFMA registers, those
 // of the activations (x converted on the way) through LDS, where the four waves share them.  Macro steps are taken in the order
 // of the K parts of the shape's stand-alone kernel -- w, w + KS, ... for each part w in turn -- and a part's sums are added to the
-// total when it ends (of an eight-way split, those of two parts: sum_forward_parts), so a step gives the same bits here too.
+// total when it ends (of an eight-way split, those of two parts: add_pairs), so a step gives the same bits here too.
 // What bounds it: delivery of the panels to the compute units (128 x 64 tiles half the bytes of 64 x 32; H = 1024, B = 64, 31 operations
 // 55.3 -> 49.9 us), with few workgroups the rounds in turn: LDS, MFMAs, a barrier. Sixty-four more columns a workgroup, or 256 rows, leave
 // compute units idle (52 - 82 us), three or four rounds in flight instead of two gain nothing. Two waves per SIMD are asked for because

@@ -351,7 +351,16 @@ __device__ __forceinline__ void gates_slowly(const void* Wp, int tile, const flo
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  sum_forward_parts<T, KS>(G, [&](int w) { return acc[w]; });
+#pragma unroll
+  for (int r = 0; r < 4; ++r) G[r] = 0.0f;
+  if constexpr (parts_in_pairs<T, KS>) {
+    add_pairs<KS>(G, [&](int w) { return acc[w]; });
+  } else {
+#pragma unroll
+    for (int w = 0; w < KS; ++w)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) G[r] += acc[w][r];
+  }
 }
 
 // All steps of a launch for units [u0, u1) of the XCD's sequences, by a workgroup that has stopped waiting.  Its waves
@@ -457,7 +466,7 @@ __device__ __forceinline__ void chain_slowly(int b_lo, int b_hi, int u0, int u1,
 // Of the 2.27 us, in cycles of 2.2 GHz: x part 560, polls 620 - 820 (1.0 - 1.4 of them), h part with the
 // stores and the next x 1280, barrier 250 - 520, pointwise step 1050, publishing 170.
 // Sums are formed exactly as forward_body forms them (KS partial sums over the macro steps
-// w, w+KS, ..., added by sum_forward_parts), so a step gives the same bits either way.  A wave whose part of
+// w, w+KS, ..., added in order, or as add_pairs adds them), so a step gives the same bits either way.  A wave whose part of
 // x or h is shorter than the others' runs its surplus macro steps on zeros.
 // Up to 64 sequences (half tiles), bf16, K split eight ways: each instruction does two of the eight parts (Halves), so four waves
 // split K and the two halves of the workgroup take half of the units each, in pairs of row tiles that hold eight units.  Against
@@ -692,7 +701,7 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
 #pragma unroll
     for (int i = 0; i < NXW; ++i) {
       const int s = kpart + KS * i;
-      if (((HALVES ? 2 * ks + 1 : ks) + KS * i + 1) * KSTEP > p.I) {   // over the end of the row, or a surplus step
+      if (((HALVES ? 2 * ks + 1 + KS * i : s) + 1) * KSTEP > p.I) {   // over the end of the row, or a surplus step
 #pragma unroll
         for (int t = 0; t < BTW; ++t) shift_tail<VEC>(xraw[i][t], s * KSTEP + VEC * lq, p.I);
       }
@@ -767,8 +776,17 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
 #pragma unroll
     for (int q = 0; q < IPT; ++q) {
       if (!mine[q]) continue;
-      float G[4];   // fixed order, as in forward_body; a sum of Halves is that of two parts
-      sum_forward_parts<T, KW>(G, [&](int w) { return cell[q][w * Sum::BLOCKS * 64]; });
+      float G[4] = {0.f, 0.f, 0.f, 0.f};   // fixed order, as in forward_body; a sum of Halves is that of two parts
+      if constexpr (parts_in_pairs<T, KW>) {
+        add_pairs<KW>(G, [&](int w) { return cell[q][w * Sum::BLOCKS * 64]; });
+      } else {
+#pragma unroll
+        for (int w = 0; w < KW; ++w) {
+          const f32x4 v = cell[q][w * Sum::BLOCKS * 64];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) G[r] += v[r];
+        }
+      }
       const float h = cell_forward<T, CELL>(G, bias[q], c_state[q], keep_second[q], keep_gate[q]);
       keep_h[q] = real[q] ? h : 0.0f;
       c_state[q] = CELL ? keep_h[q] : keep_second[q];

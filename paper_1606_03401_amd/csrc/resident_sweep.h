@@ -504,8 +504,17 @@ __global__ __launch_bounds__(512) void sweep_kernel(SweepParams p) {
       st_dy[q] = pf_dy[q];
       if constexpr (FWD) {
         if (!mine[q]) continue;
-        float G[4];
-        sum_forward_parts<T, KSF>(G, [&](int w) { return cellF[q][w * SumF::BLOCKS * 64]; });   // as in forward_body
+        float G[4] = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (parts_in_pairs<T, KSF>) {   // fixed order, as in forward_body
+          add_pairs<KSF>(G, [&](int w) { return cellF[q][w * SumF::BLOCKS * 64]; });
+        } else {
+#pragma unroll
+          for (int w = 0; w < KSF; ++w) {
+            const f32x4 v = cellF[q][w * SumF::BLOCKS * 64];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) G[r] += v[r];
+          }
+        }
         st_h[q] = cell_forward<T, CELL>(G, bias[q], st_cprev[q], st_c[q], st_gate[q]);
       } else {
 #pragma unroll
