@@ -472,24 +472,19 @@ __device__ __forceinline__ void chain_slowly(int b_lo, int b_hi, int u0, int u1,
 // split K and the two halves of the workgroup take half of the units each, in pairs of row tiles that hold eight units.  Against
 // eight waves with a part and all rows each: half the matrix instructions, half the partial sums through LDS (a 1 KiB block
 // costs a compute unit 30 cycles to write and 17 to read, and there were 32; the matrix unit was busy for 1024 of the h part's 1280 cycles):
-// H = 1024, B = 64 85.7 -> 79.4 us a launch of 41 steps on average.
+// H = 1024, B = 64 85.7 -> 79.4 us a launch of 41 steps on average.  Fetching the weights takes longer that way (a load takes 32
+// bytes of each line for 128), see halves_from.
 // NXW, NHW: macro steps of x and of h per wave (Halves: per part); the weights of the last NXL of x are parked in LDS (they are
 // read while the wave would wait anyway); NBT: batch tiles of the XCD's share (0: half a tile).
-// With an even number of pairs of row tiles: up to two tiles half of the waves would have none, and of five or six one half has twice
-// the other's, more than the registers hold with many columns of x (H = 640, I = 502, B = 5 2.4 % slower a gradient step, H = 576, B = 47
-// GRU 3 %, H = 650, I = 650 7 %; H = 641, I = 229, B = 64, t = 22 1.5 %).
-template <class T, int NRT, int KS, int NBT>
-constexpr bool chain_in_halves = sizeof(T) == 2 && KS == 8 && NBT == 0 && (NRT == 4 || NRT > 6);
-template <class T, int NRT, int KS, int NBT>   // row tiles of a wave
-constexpr int chain_row_tiles = chain_in_halves<T, NRT, KS, NBT> ? (NRT + 1) / 2 : (KS == 4 && NBT != 2 ? (NRT + 1) / 2 : NRT);
-template <class T, int NRT, int NXW, int NXL, int NHW, int KS, int NBT, int CELL>
+template <int NRT, int KS, int NBT, bool HALVES>   // row tiles of a wave
+constexpr int chain_row_tiles = HALVES || (KS == 4 && NBT != 2) ? (NRT + 1) / 2 : NRT;
+template <class T, int NRT, int NXW, int NXL, int NHW, int KS, int NBT, int CELL, bool HALVES>
 __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
   using M = Mma<T>;
   constexpr int VEC = M::VEC, KSTEP = 4 * VEC, FRAG = 64 * VEC;
-  constexpr bool HALVES = chain_in_halves<T, NRT, KS, NBT>;
   constexpr int KW = HALVES ? KS / 2 : KS;         // waves that split K
   constexpr int GROUPS = 8 / KW, FTB = (GROUPS == 2 && NBT == 2) ? 2 : 1, FTR = GROUPS / FTB;
-  constexpr int NRTW = chain_row_tiles<T, NRT, KS, NBT>, BTW = (NBT ? NBT : 1) / FTB;   // row and batch tiles of one wave
+  constexpr int NRTW = chain_row_tiles<NRT, KS, NBT, HALVES>, BTW = (NBT ? NBT : 1) / FTB;   // row and batch tiles of one wave
   using Weights = std::conditional_t<HALVES, bf16x16, typename M::Frag>;
   constexpr int NXR = NXW - NXL, COLS = NBT ? NBT * 16 : 8;
   constexpr int UW = NRT * 4;
@@ -521,7 +516,7 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
   const int nsx = p.KX / KSTEP, nsh = p.KH / KSTEP, nsteps = nsx + nsh;
   const size_t hhalf = (size_t)p.BP * p.KH;
   const int ks = wave % KW, grp = wave / KW;
-  const int rt0 = (FTR > 1 ? grp : 0) * NRTW, bt0 = (FTB > 1 ? grp : 0) * BTW;   // wave = group * KS + K part
+  const int rt0 = (FTR > 1 ? grp : 0) * NRTW, bt0 = (FTB > 1 ? grp : 0) * BTW;   // wave = group * KW + K part
   const int ngroups = p.HP / 4;                    // 16-row tiles of the packed weights
   // this wave's part of K (Halves: this lane's of the two); its h macro steps: mh0, mh0 + KS, ... (below nsh)
   const int kpart = HALVES ? 2 * ks + (lrow >> 3) : ks;
@@ -797,16 +792,32 @@ __global__ __launch_bounds__(512) void forward_chain_kernel(ResParams p) {
   store_kept(p.count - 1);
 }
 
+// Steps from which on a launch takes two macro steps per instruction (0: never); the bits are the same.  us a launch's start and a step,
+// one macro step and two: H = 1024, I = 256 20.1 + 1.40, 23.7 + 1.16; H = 1024, I = 64 18.7 + 1.41, 20.4 + 1.25; H = 896, I = 256
+// 17.4 + 1.51, 20.0 + 1.25: even at 9 to 15 steps.  Not with more columns of x than one macro step a part (H = 896, I = 512 19.6 + 1.60,
+// 25.1 + 1.43, launches of 8 to 12 steps 9 - 14 % slower), and not where a wave has two row tiles, whose sums are small either way (H = 500
+// I = 256 9.8 + 1.15, 9.7 + 1.42, I = 768 12.2 + 1.86, 11.4 + 2.38, I = 64 even).  Up to two tiles half of the waves would have none, and of five
+// or six one half has twice the other's (H = 640, I = 502, B = 5 2.4 % slower a gradient step, H = 650, I = 650 7 %).
+template <class T, int NRT, int NXW, int KS, int NBT>
+constexpr int halves_from = sizeof(T) == 2 && KS == 8 && NBT == 0 && NRT > 6 && NXW == 1 ? 16 : 0;
+template <class T, int NRT, int NXW, int NXL, int NHW, int KS, int NBT, int CELL, bool HALVES>
+hipError_t launch_chain_kernel(const ResParams& p, hipStream_t st) {
+  constexpr int FTB = (KS == 4 && NBT == 2) ? 2 : 1, NRTW = chain_row_tiles<NRT, KS, NBT, HALVES>;
+  constexpr int BLOCKS = Sums<NRTW, NBT == 0 ? 0 : NBT / FTB>::BLOCKS;
+  constexpr size_t lds = (size_t)8 * BLOCKS * 1024 + (size_t)8 * NRTW * NXL * (HALVES ? 2048 : 1024);
+  static_assert(lds <= 160 * 1024 - 64, "LDS of a compute unit");
+  hipError_t e = allow_dynamic_lds<forward_chain_kernel<T, NRT, NXW, NXL, NHW, KS, NBT, CELL, HALVES>>(lds);
+  if (e != hipSuccess) return e;
+  forward_chain_kernel<T, NRT, NXW, NXL, NHW, KS, NBT, CELL, HALVES><<<dim3(RES_WGS), dim3(512), lds, st>>>(p);
+  return hipGetLastError();
+}
 template <class T, int NRT, int NXW, int NXL, int NHW, int KS, int NBT, int CELL>
 hipError_t launch_chain_cell(const ResParams& p, hipStream_t st) {
-  constexpr int FTB = (KS == 4 && NBT == 2) ? 2 : 1, NRTW = chain_row_tiles<T, NRT, KS, NBT>;
-  constexpr int BLOCKS = Sums<NRTW, NBT == 0 ? 0 : NBT / FTB>::BLOCKS;
-  constexpr size_t lds = (size_t)8 * BLOCKS * 1024 + (size_t)8 * NRTW * NXL * (chain_in_halves<T, NRT, KS, NBT> ? 2048 : 1024);
-  static_assert(lds <= 160 * 1024 - 64, "LDS of a compute unit");
-  hipError_t e = allow_dynamic_lds<forward_chain_kernel<T, NRT, NXW, NXL, NHW, KS, NBT, CELL>>(lds);
-  if (e != hipSuccess) return e;
-  forward_chain_kernel<T, NRT, NXW, NXL, NHW, KS, NBT, CELL><<<dim3(RES_WGS), dim3(512), lds, st>>>(p);
-  return hipGetLastError();
+  constexpr int from = halves_from<T, NRT, NXW, KS, NBT>;
+  if constexpr (from > 0) {
+    if (p.count >= from) return launch_chain_kernel<T, NRT, NXW, NXL, NHW, KS, NBT, CELL, true>(p, st);
+  }
+  return launch_chain_kernel<T, NRT, NXW, NXL, NHW, KS, NBT, CELL, false>(p, st);
 }
 
 // An instantiation: what it covers (see the kernel) and its launchers by cell.  The tables are split over

@@ -614,14 +614,19 @@ def test_every_instantiation(dtype, B, I, H, cell):
             assert prof.batch_steps == 0 and prof.sweep_forward_steps > 0
 
 
-# Half tiles, where one matrix instruction takes two macro steps: a group of sequences that is full, has one or lacks one; row tiles in
-# pairs of four, six and eight, the last one short; parts of K of unequal length, and x that ends inside a macro step.
-@pytest.mark.parametrize("B,I,H,cell", [(1, 200, 500, 0), (9, 520, 512, 1), (8, 40, 705, 0), (63, 264, 769, 0), (57, 33, 1000, 1), (64, 1, 1024, 0),
-                                        (16, 130, 897, 0), (64, 256, 1024, 1)])
+# Half tiles, where one matrix instruction takes two macro steps, in sweeps (all of these) and in chains (seven and eight row tiles, see
+# test_gpu_routes): a group of sequences that is full, has one or lacks one; an odd and an even number of row tiles, the last one
+# short; parts of K of unequal length, and x that ends inside a macro step.
+HALVES = [(1, 200, 500, 0), (9, 520, 512, 1), (8, 40, 705, 0), (63, 264, 769, 0), (57, 33, 1000, 1), (64, 1, 1024, 0), (16, 130, 897, 0), (64, 256, 1024, 1),
+          (63, 250, 769, 0), (5, 8, 896, 1), (64, 256, 1024, 0)]
+HALVES_T = 40
+
+
+@pytest.mark.parametrize("B,I,H,cell", HALVES)
 def test_two_macro_steps_per_instruction(B, I, H, cell):
     from oracle import gru_bptt as og
     from test_gpu_parity import TOL
-    t = 12
+    t = HALVES_T
     w = wl.Workload("halves", B=B, I=I, H=H, t=t, kind=wl.KIND_ISM, m=t, gemm_dtype=wl.GEMM_BF16, loss=wl.LOSS_EXTERNAL_DY,
                     dy_first_step=1, seed=70 + B + I + H, cell=cell)
     inp = wl.make_inputs(w, nonzero_state=True, nonzero_bias=True)
@@ -633,8 +638,15 @@ def test_two_macro_steps_per_instruction(B, I, H, cell):
     for name in ("dW_ih", "dW_hh", "db", "dh0", "dx", "y") + (() if cell else ("dc0",)):
         got, want = getattr(base, name).astype(np.float64), getattr(ref, name)
         assert np.linalg.norm(got - want) <= TOL[w.gemm_dtype] * np.linalg.norm(want), name
+    from paper_1606_03401_amd.session import Session
     for kind, m in ((wl.KIND_HSM, 3), (wl.KIND_ISM, t)):
-        _same(_run(w, inp, kind, m, chain=True), base, (kind, m))
+        s = Session(w, inp, kind=kind, m=m)
+        mb.mebptt_profile_enable(1)
+        out = s.run_and_fetch()
+        prof = mb.mebptt_profile_collect()
+        mb.mebptt_profile_enable(0)
+        _same(out, base, (kind, m))
+        assert prof.sweep_steps > 0 and (prof.chain_steps > 0) == (I >= 8)
 
 
 def test_random_widths_types_and_budgets_bit_identical():
