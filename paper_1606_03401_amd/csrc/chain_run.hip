@@ -316,18 +316,27 @@ hipError_t launch_forward_tiles(Product& p, hipStream_t st) {
 // The largest output block per workgroup that still gives every compute unit one.  Vectors of four along
 // k (or along a row, for operands stored across k) need dimensions of at least four.
 // Operands pass through LDS (product_body) where all rows are whole 16-byte slots -- `slots`, which for a layer has to be the same wherever
-// its input sits, or a recomputed activation would not have the first one's bits -- and every wave has a step of 32.  us a launch, direct and staged:
-// batch 256, 1024 -> 1024 (2 x 2 tiles) 11.6 and 11.8, 1536 -> 1000 (1 x 2) 14.1 and 11.3, 900 -> 256 (1 x 1) 6.7 and 4.4.  On 2 x 4
-// tiles 11.6 and 15.7: there the stages leave a compute unit one workgroup.  Two stages a wave, two steps in flight: 13.3 on 2 x 2, 12.4 for
-// 10.1 on 1 x 2.  Gradient steps of twelve drawn chains take 0.94 - 1.00 of the time.
+// its input sits, or a recomputed activation would not have the first one's bits -- and every wave has a step of 32.  us a launch, direct and staged,
+// batch 256: 1024 -> 1024 (2 x 2 tiles) 11.0 and 10.2, 1024 -> 832 (1 x 2) 13.3 and 10.8, 1536 -> 512 (1 x 2) 10.6 and 8.7, 1024 -> 256 (1 x 1)
+// 6.3 and 4.7.  Where it does not pay:
+//   K % 32 != 0: what is left over is fetched by one wave alone when its steps are done.  1 x 1 tiles, batch 16, 284 -> 1024 3.3 and 3.8 us;
+//   even at about K = 700 (less than 16 left over: 600), 0.71 - 0.98 of the time from 1024 (896) on.  1 x 2 tiles 1.05 - 1.2 of the
+//   time up to K = 1000, 0.9 - 1.08 from there to 2040; 2 x 2 tiles up to 1.35 (batch 192, 2044 -> 2048 26.6 and 36.2);
+//   2 x 2 tiles that give some compute units a second workgroup: batch 461, 832 -> 832 15.0 and 16.5, batch 256, 1536 -> 1536 25.0 and 27.7.  With
+//   one each 0.84 - 1.04 of the time, 0.96 on average;
+//   2 x 4 tiles, 11.6 and 15.7: there the stages leave a compute unit one workgroup.
+// Two stages a wave, two steps in flight, were slower: 13.3 us on 2 x 2 tiles, 12.4 for 10.1 on 1 x 2.
 hipError_t launch_chain_forward(Product p, bool slots, hipStream_t st) {
   if (p.K < 4) return launch_forward_tiles<1, 1, true, false>(p, st);
   if (blocks_of(p.N, 4) * blocks_of(p.M, 4) >= FILL) return launch_forward_tiles<4, 4, false, false>(p, st);
   if (blocks_of(p.N, 4) * blocks_of(p.M, 2) >= FILL) return launch_forward_tiles<2, 4, false, false>(p, st);
-  const bool staged = slots && p.K >= KS * STEP;
-  if (blocks_of(p.N, 2) * blocks_of(p.M, 2) >= FILL) return staged ? launch_forward_tiles<2, 2, false, true>(p, st) : launch_forward_tiles<2, 2, false, false>(p, st);
+  const int rest = p.K % STEP;
+  const bool staged = slots && p.K >= KS * STEP && rest == 0;
+  const int wgs = blocks_of(p.N, 2) * blocks_of(p.M, 2);
+  if (wgs >= FILL) return staged && wgs == FILL ? launch_forward_tiles<2, 2, false, true>(p, st) : launch_forward_tiles<2, 2, false, false>(p, st);
   if (blocks_of(p.N, 2) * blocks_of(p.M, 1) >= FILL) return staged ? launch_forward_tiles<1, 2, false, true>(p, st) : launch_forward_tiles<1, 2, false, false>(p, st);
-  return staged ? launch_forward_tiles<1, 1, false, true>(p, st) : launch_forward_tiles<1, 1, false, false>(p, st);
+  const bool long_k = slots && p.K >= (rest < 16 ? 896 : 1024);
+  return staged || long_k ? launch_forward_tiles<1, 1, false, true>(p, st) : launch_forward_tiles<1, 1, false, false>(p, st);
 }
 
 template <int DTM, int DTN, int WTM, int WTN, bool NARROW>

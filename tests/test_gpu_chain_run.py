@@ -96,10 +96,15 @@ def test_chain_run_matches_oracle_at_every_budget(widths, B, unit_bytes):
     assert C(n, 0, 0) > C(n, sum(s), 0) or n == 1      # memory buys time
 
 
-# Forward products whose operands pass through LDS: steps of 32 that leave remainders of 0, 4, 8, 16, 28; more and fewer steps than waves;
-# rows that are no whole slots beside them; memorised states that lie on slots (4096) and that do not (1004).
+# Forward products whose operands pass through LDS, on 1 x 1, 1 x 2 and 2 x 2 tiles (test_gpu_routes: which): steps of 32 that leave remainders of 0,
+# 4, 8 and 28; as many steps as waves, one more and several times as many; rows and columns that end inside a tile; rows that are no whole
+# slots beside them; memorised states that lie on slots (4096) and that do not (1004).
+STAGED = [([256, 260, 1000, 300, 257, 528, 288, 2044], 70), ([284, 256, 512, 16], 16), ([1024, 300, 640, 272], 300),
+          ([288, 1000, 512, 1024, 500, 256], 250), ([1052, 130, 1000, 200, 1028, 60], 60)]
+
+
 @pytest.mark.parametrize("unit_bytes", [4096, 1004])
-@pytest.mark.parametrize("widths,B", [([256, 260, 1000, 300, 257, 528, 288, 2044], 70), ([284, 256, 512, 16], 16), ([1024, 300, 640, 272], 300)])
+@pytest.mark.parametrize("widths,B", STAGED)
 def test_forward_products_through_lds(widths, B, unit_bytes):
     test_chain_run_matches_oracle_at_every_budget(widths, B, unit_bytes)
 
