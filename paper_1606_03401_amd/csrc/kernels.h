@@ -148,6 +148,8 @@ hipError_t launch_forward_chain(const Dims& d, const void* Wp, const float* bp, 
 size_t forward_chain_x_bytes(const Dims& d);
 // Shapes whose resident launches are the wide ones: every step of a run goes out in them, single steps too.
 bool runs_wide(const Dims& d);
+// Whether the time-batched GEMMs of a run with resident launches go to a stream of their own.
+bool gemms_beside(const Dims& d);
 
 // A run of (forward operation keeping the internal state, backward operation) pairs for steps
 // s_hi, s_hi - 1, ..., in one weight-gradient chunk or two consecutive ones, in one launch with both weight

@@ -1757,11 +1757,10 @@ hipError_t launch_zero_operand_columns(const Dims& d, void* dGT, void* aT, int c
 // them; the fragments of aT every wave fetches straight into its MFMA registers.  Both are fetched PD macro steps
 // ahead.  (Both operands through LDS: 39.6 us per chunk on H = 1024, B = 64, so: 37.0; two macro steps per barrier: 37.8.)  gridDim.z workgroups may share one
 // output block, each with its own part of K and its own partial accumulator.
-// gridDim.z workgroups: see wgrad_splits.
-// EXTRA: aT has one row tile (the row of ones, whose product is the bias gradient) more than whole blocks, which would cost a column of
-// blocks that are nearly empty.  Its 2 * WT products per row block are dealt out over the waves of the first blocks instead: one more
-// MFMA per macro step; the fragment comes through a buffer that gives waves without a product zeros and moves nothing for them.
-// A chunk of H = 256, I = 256, B = 64 12.4 -> 10.5 us.
+// EXTRA (wgrad_plan says where, blocks of 128): aT has one row tile (the row of ones, whose product is the bias gradient) more than whole blocks,
+// which would cost a column of blocks that are nearly empty.  Its 2 * WT products per row block are dealt out over the waves of the first
+// blocks instead: one more MFMA per macro step; the fragment comes through a buffer that gives waves without a product zeros and moves
+// nothing for them.  A chunk of H = 256, I = 256, B = 64 12.4 -> 10.5 us.
 template <class T, int WT, bool EXTRA>
 __global__ __launch_bounds__(256) void wgrad_kernel(const T* __restrict__ dGT, const T* __restrict__ aT, int K, int KC,
                                                     int G4, int NTOT, int accumulate, float* __restrict__ dWacc) {
@@ -1857,13 +1856,16 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const T* __restrict__ dGT, c
   // read-modify-write of every chunk is fully coalesced; wgrad_finish_kernel converts it to the
   // caller's row-major dW once at the end of the run.
   // A part's accumulator: all blocks' tiles, then the extra tile's products, one after the other.
-  const size_t whole = (size_t)gridDim.x * gridDim.y * 4 * (WT * WT) * 64;
-  float4* part_acc = reinterpret_cast<float4*>(dWacc) + blockIdx.z * (whole + (EXTRA ? (size_t)gridDim.x * 2 * WT * 64 : 0));
-  float4* accp = part_acc + ((size_t)(blockIdx.x * gridDim.y + blockIdx.y) * 4 + wave) * (WT * WT) * 64 + lane;
-  if (EXTRA && extra_i < WT) {
-    float4* to = part_acc + whole + (size_t)(mt_wg + wm * WT + extra_i) * 64 + lane;
-    const float4 old = accumulate ? *to : float4{0.f, 0.f, 0.f, 0.f};
-    *to = float4{acc_extra[0] + old.x, acc_extra[1] + old.y, acc_extra[2] + old.z, acc_extra[3] + old.w};
+  float4* accp = reinterpret_cast<float4*>(dWacc) +
+                 (((size_t)blockIdx.z * gridDim.x * gridDim.y + blockIdx.x * gridDim.y + blockIdx.y) * 4 + wave) * (WT * WT) * 64 + lane;
+  if constexpr (EXTRA) {
+    const size_t whole = (size_t)gridDim.x * gridDim.y * 4 * (WT * WT) * 64, extra = (size_t)gridDim.x * 2 * WT * 64;
+    accp += blockIdx.z * extra;
+    if (extra_i < WT) {
+      float4* to = reinterpret_cast<float4*>(dWacc) + blockIdx.z * (whole + extra) + whole + (size_t)(mt_wg + wm * WT + extra_i) * 64 + lane;
+      const float4 old = accumulate ? *to : float4{0.f, 0.f, 0.f, 0.f};
+      *to = float4{acc_extra[0] + old.x, acc_extra[1] + old.y, acc_extra[2] + old.z, acc_extra[3] + old.w};
+    }
   }
   if (accumulate) {
     float4 old[WT * WT];
@@ -1960,43 +1962,56 @@ __global__ void wgrad_finish_kernel(const float* __restrict__ dWacc, int WT, int
   }
 }
 
-// Wave tile of the weight-gradient GEMM: 4 x 4 MFMA tiles, 128 x 128 per workgroup, whenever the
-// output has at least one such tile in each direction; else 2 x 2.
-static int wgrad_wave_tile(const Dims& d) {
-  const int MT = d.G4 / 16, NT = d.NA / 16;
-  return (MT >= 8 && NT >= 8) ? 4 : 2;
-}
-// Output blocks, and whether the operand of ones has no block of its own (EXTRA; its products need 2 * gy >= WT blocks a row).  Above one
-// block per compute unit, where K is not split, the blocks saved shorten no compute unit's work and the extra products cost: H = 1024,
-// I = 256, 352 -> 320 blocks 36.3 -> 39.3 us.
-struct WgradBlocks {
-  int gx, gy;
+// Blocks of the weight-gradient GEMM, and workgroups that share one along K.  Wave tiles of 4 x 4 MFMA tiles, 128 x 128 per workgroup,
+// whenever the output has at least one such block in each direction, else 2 x 2.
+// Where the blocks alone do not fill the chip, K is split for about 1.5 workgroups per compute unit.  bf16 GEMMs that run beside the
+// sweeps stay at that: with two, H = 512, B = 128 takes 21.5 us a chunk for 22.1 but a gradient step that stores everything 1192 us for 1185, and
+// without blocks for the row of ones B = 112, H = 499, t = 58 takes 578 us for 575.  Others have the chip to themselves, and fp32 products
+// take longer than what they hold up: they take two workgroups per compute unit, as many as it holds at a time, and leave out the blocks
+// of the row of ones (EXTRA), where that makes a chunk cheaper.  A chunk's cost is that of the compute unit with the most workgroups, in
+// macro steps of 4 x 4 products (EXTRA: 17 for 16), and of its partial accumulators, which a run also reads once more at its end: a workgroup's
+// 64 KiB take the time of 0.17 macro steps in bf16, 0.06 in fp32, all compute units at it; fewer workgroups than those write no faster.
+// us a chunk, and a gradient step, with the start's blocks / two workgroups / EXTRA:
+//   H = 512, I = 128, B = 256        37.6 / 33.5 / 31.8, t = 128 1432 / 1417 / 1414       fp32 H = 512, I = 256, B = 64  90 / 71 / 63, 2454 / 2462 / 2443
+//   H = 256, I = 256, B = 64         12.4 / 12.4 / 10.5, t = 128  669 /  669 /  662       fp32 H = 448, I = 64, B = 250  206 / 152 / 144, 5173 / 5102 / 5010
+//   H = 448, I = 29, B = 250         32.9 / 33.5 / -,    t = 128 1356 / 1360: not taken    fp32 H = 256, I = 128, B = 32  25.3 / 25.3 / 26.1, 1096 / 1096 / 1101: not
+//   H = 128, I = 128, B = 32          6.7 /  6.7 /  7.3, t = 128  540 /  540 /  544: not   fp32 H = 128, I = 128, B = 64  21.5 / 21.5 / 23.4, 828 / 828 / 839: not
+//   H = 512, I = 128, B = 16         12.5 / 13.9 / 12.5, t = 128  694 /   -  /  697: not
+// (Above one block per compute unit, where K is not split, EXTRA costs as well: H = 1024, I = 256, 352 -> 320 blocks 36.3 -> 39.3 us.)
+struct WgradPlan {
+  int wt, gx, gy, splits;
   bool extra;
+  int blocks() const { return gx * gy; }
 };
-static WgradBlocks wgrad_blocks(const Dims& d) {
-  const int WT = wgrad_wave_tile(d), NT = d.NA / 16;
-  WgradBlocks b{(d.G4 / 16 + 2 * WT - 1) / (2 * WT), (NT + 2 * WT - 1) / (2 * WT), false};
-  if (NT % (2 * WT) == 1 && 2 * (b.gy - 1) >= WT && b.gx * b.gy <= TARGET_WGS) {
-    --b.gy;
-    b.extra = true;
+static WgradPlan wgrad_plan(const Dims& d) {
+  const int MT = d.G4 / 16, NT = d.NA / 16, wt = MT >= 8 && NT >= 8 ? 4 : 2;
+  auto split = [](int blocks, int workgroups) { return std::max(1, std::min(workgroups / blocks, 8)); };
+  WgradPlan p{wt, (MT + 2 * wt - 1) / (2 * wt), (NT + 2 * wt - 1) / (2 * wt), 0, false};
+  p.splits = split(p.blocks(), 384 + p.blocks() / 2);
+  if (wt == 2 || p.blocks() > TARGET_WGS || (d.dtype && gemms_beside(d))) return p;
+  const double steps = d.KC / (d.dtype ? 32 : 16), accumulator = d.dtype ? 0.17 : 0.06;
+  auto cost = [&](const WgradPlan& q) {
+    const int workgroups = q.blocks() * q.splits;
+    return (workgroups + TARGET_WGS - 1) / TARGET_WGS * steps / q.splits * (q.extra ? 17.0 / 16 : 1) + accumulator * std::max(workgroups, TARGET_WGS);
+  };
+  WgradPlan two = p;
+  two.splits = split(p.blocks(), 2 * TARGET_WGS);
+  if (cost(two) < 0.99 * cost(p)) p = two;
+  if (NT % (2 * wt) == 1 && 2 * (p.gy - 1) >= wt) {   // 2 * gy >= wt: the extra products are dealt out over that many waves a row
+    WgradPlan best = p;
+    for (const int workgroups : {384 + (p.gx * (p.gy - 1)) / 2, 2 * TARGET_WGS}) {
+      WgradPlan q = p;
+      q.gy = p.gy - 1;
+      q.extra = true;
+      q.splits = split(q.blocks(), workgroups);
+      if (cost(q) < std::min(0.95 * cost(p), cost(best))) best = q;
+    }
+    p = best;
   }
-  return b;
+  return p;
 }
-// Workgroups that split K for one output block, where the blocks alone do not fill the chip.  bf16 up to 128 sequences, whose GEMMs run
-// beside the sweeps: about 1.5 workgroups per compute unit (with two, H = 512, B = 128 takes 21.5 us a chunk for 22.1 but a gradient step
-// that stores everything 1192 us for 1185).  More sequences have the chip to themselves, and fp32 products take longer than they wait:
-// two per compute unit, as many as it holds at a time.  us a chunk, 1.5 and two: H = 512, I = 128, B = 256 37.6 and 32.0 (a gradient
-// step of t = 10 000 104.8 and 103.3 ms), fp32 H = 512, I = 256, B = 64 90 and 61.
-static int wgrad_splits(const Dims& d) {
-  const WgradBlocks b = wgrad_blocks(d);
-  const int tiles = b.gx * b.gy;
-  if (!d.dtype || d.B > 128) return std::max(1, std::min(2 * TARGET_WGS / tiles, 8));
-  return std::max(1, std::min((384 + tiles / 2) / tiles, 8));
-}
-static size_t wgrad_partial_floats(const Dims& d) {   // one partial accumulator
-  const int WT = wgrad_wave_tile(d);
-  const WgradBlocks b = wgrad_blocks(d);
-  return ((size_t)b.gx * b.gy * 4 * WT * WT + (b.extra ? (size_t)b.gx * 2 * WT : 0)) * 64 * 4;
+static size_t wgrad_partial_floats(const WgradPlan& p) {   // one partial accumulator
+  return ((size_t)p.blocks() * 4 * p.wt * p.wt + (p.extra ? (size_t)p.gx * 2 * p.wt : 0)) * 64 * 4;
 }
 
 size_t wgrad_accumulator_bytes(const Dims& d) {
@@ -2006,19 +2021,20 @@ size_t wgrad_accumulator_bytes(const Dims& d) {
     tgemm_shares((int)(gx * gy), full, split);
     return (gx * gy + (gx * gy - full) * (split - 1)) * 256 * 256 * sizeof(float);
   }
-  return wgrad_partial_floats(d) * wgrad_splits(d) * sizeof(float);
+  const WgradPlan plan = wgrad_plan(d);
+  return wgrad_partial_floats(plan) * plan.splits * sizeof(float);
 }
 
 template <class T>
 static void launch_wgrad_t(const Dims& d, const void* dGT, const void* aT, int K, int accumulate, float* dWacc,
                            hipStream_t st) {
-  const WgradBlocks b = wgrad_blocks(d);
-  const dim3 grid(b.gx, b.gy, wgrad_splits(d)), block(256);
+  const WgradPlan plan = wgrad_plan(d);
+  const dim3 grid(plan.gx, plan.gy, plan.splits), block(256);
   auto launch = [&](auto kernel) { kernel<<<grid, block, 0, st>>>((const T*)dGT, (const T*)aT, K, d.KC, d.G4, d.NA, accumulate, dWacc); };
-  if (wgrad_wave_tile(d) == 4)
-    b.extra ? launch(wgrad_kernel<T, 4, true>) : launch(wgrad_kernel<T, 4, false>);
+  if (plan.wt == 2)
+    launch(wgrad_kernel<T, 2, false>);
   else
-    b.extra ? launch(wgrad_kernel<T, 2, true>) : launch(wgrad_kernel<T, 2, false>);
+    plan.extra ? launch(wgrad_kernel<T, 4, true>) : launch(wgrad_kernel<T, 4, false>);
 }
 
 hipError_t launch_wgrad(const Dims& d, const void* dGT, const void* aT, int nslots, int accumulate, float* dWacc,
@@ -2063,10 +2079,9 @@ hipError_t launch_wgrad_finish(const Dims& d, const float* dWacc, float* dW_ih, 
                                                           dW_ih, dW_hh, db, gx * gy, dc, dh0, dc0, plane, nw);
     return hipGetLastError();
   }
-  const int WT = wgrad_wave_tile(d);
-  const WgradBlocks b = wgrad_blocks(d);
-  wgrad_finish_kernel<<<grid, dim3(256), 0, st>>>(dWacc, WT, b.gy, wgrad_splits(d), wgrad_partial_floats(d), d.NX, d.HP,
-                                                        d.I, d.H, d.cell, dW_ih, dW_hh, db, b.gx * b.gy, dc, dh0, dc0, plane, nw);
+  const WgradPlan plan = wgrad_plan(d);
+  wgrad_finish_kernel<<<grid, dim3(256), 0, st>>>(dWacc, plan.wt, plan.gy, plan.splits, wgrad_partial_floats(plan), d.NX, d.HP,
+                                                        d.I, d.H, d.cell, dW_ih, dW_hh, db, plan.blocks(), dc, dh0, dc0, plane, nw);
   return hipGetLastError();
 }
 

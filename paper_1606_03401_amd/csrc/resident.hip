@@ -174,6 +174,28 @@ static const BackSweepConfig* back_sweep_config(const Dims& d) {
 
 bool can_run_sweep(const Dims& d) { return sweep_config(d) != nullptr; }
 bool can_run_backward_sweep(const Dims& d) { return back_sweep_config(d) != nullptr || runs_wide(d); }
+
+// Whether the time-batched GEMMs go to a stream of their own, beside the sequential work.  Launch-per-step
+// kernels fill the device, and the two only get in each other's way (H = 2048: 2.8 % slower beside,
+// H = 4096: 1.4 %).  A resident launch needs every compute unit at once: GEMMs beside it run in the gaps
+// between launches and hold the next one up, each chunk costs two events and their waits, and a sweep launch may not
+// run on into a chunk whose buffers are still being read.  That pays only where a chunk's GEMMs are long
+// against the launches and the launches short.  Own stream against beside, a gradient step:
+//   below 3 GFLOP a chunk: H = 32 (fp32) 163 / 206 us, H = 200, B = 37 1.04 / 1.13 ms, H = 256, B = 64 1.99 / 2.00;
+//   B <= 32 (chunks of 64 steps): H = 512, 768, 1024 0.4 - 3.1 % faster, hidden and internal states stored;
+//   B > 128: H = 384, 512 0.4 - 3.9 % faster;
+//   between, -2.3 - +4.4 % (the sign turns with what the plan stores, which the rule does not look at): H = 384, 512
+//   with internal states stored 1.6 - 2.3 % slower, with hidden states -0.4 - +1.8 %;
+//   H = 1024, B = 64 1.4 % slower (GRU 1.8 %), H = 768, B = 128 1.5 % slower;
+//   fp32, whose GEMMs take eight times as long, from 3 GFLOP on: H = 512, B = 32 0.9 % slower, H = 256, B = 256
+//   0.6 % slower with hidden states stored, 7.8 % faster with internal ones (beside all the same: a rule by sizes alone).
+//   wide launches: H = 2048, B = 128 0.4 % faster on the run's own stream, H = 4096, B = 32 even.
+bool gemms_beside(const Dims& d) {
+  if ((!can_run_forward_chain(d) && !can_run_backward_sweep(d)) || runs_wide(d)) return false;
+  const double chunk_flops = 8.0 * d.CH * d.B * d.H * ((double)d.I + d.H);
+  return chunk_flops >= 3e9 && (d.dtype == 0 || (d.B > 32 && d.B <= 128));
+}
+
 int sweep_max_steps() { return SWEEP_MAX_STEPS; }
 size_t sweep_ring_bytes(const Dims& d) {
   const size_t slot = (size_t)d.BP * d.G4 * d.op_bytes();

@@ -480,11 +480,17 @@ def test_paper_experiment_shape():
             assert np.array_equal(getattr(out, name), getattr(first, name)), (m, name)
 
 
-# Weight gradients whose row of ones has no block of its own: 64- and 128-wide blocks, a last row block that is half empty, fewer steps
-# of K than parts, a last chunk that is shorter; and K split over more parts (fp32, more than 128 sequences).
-@pytest.mark.parametrize("B,I,H,t,dtype,cell", [(37, 112, 144, 40, wl.GEMM_BF16, 0), (9, 112, 144, 40, wl.GEMM_FP32, 1), (130, 16, 48, 35, wl.GEMM_BF16, 0),
-                                                (1, 128, 128, 5, wl.GEMM_FP32, 0), (200, 128, 512, 34, wl.GEMM_BF16, 1), (3, 16, 48, 70, wl.GEMM_FP32, 0)])
-def test_weight_gradient_blocks(B, I, H, t, dtype, cell):
+# Weight gradients with and without blocks for the row of ones (last value; test_gpu_routes asks by name): 64- and 128-wide blocks, a last row
+# block that is half empty, fewer steps of K than parts, a last chunk that is shorter; and K split over more parts (fp32, more than
+# 128 sequences).
+WGRAD_BLOCKS = [(37, 112, 144, 40, wl.GEMM_BF16, 0, False), (9, 112, 144, 40, wl.GEMM_FP32, 1, False), (130, 16, 48, 35, wl.GEMM_BF16, 0, False),
+                (1, 128, 128, 5, wl.GEMM_FP32, 0, False), (200, 128, 512, 34, wl.GEMM_BF16, 1, True), (3, 16, 48, 70, wl.GEMM_FP32, 0, False),
+                (16, 220, 264, 70, wl.GEMM_BF16, 0, True), (9, 233, 270, 70, wl.GEMM_FP32, 1, True), (9, 233, 270, 3, wl.GEMM_FP32, 0, True),
+                (16, 250, 250, 5, wl.GEMM_BF16, 1, True)]
+
+
+@pytest.mark.parametrize("B,I,H,t,dtype,cell,ones_apart", WGRAD_BLOCKS)
+def test_weight_gradient_blocks(B, I, H, t, dtype, cell, ones_apart):
     w = wl.Workload("wgrad", B=B, I=I, H=H, t=t, kind=wl.KIND_HSM, m=6, gemm_dtype=dtype, loss=wl.LOSS_EXTERNAL_DY, dy_first_step=1,
                     seed=B + I + H, cell=cell)
     run_case(w, nonzero=True)

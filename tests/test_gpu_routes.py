@@ -11,6 +11,7 @@ import pytest
 
 import test_gpu_chain as chain
 import test_gpu_chain_run as chain_run
+import test_gpu_parity as parity
 
 pytestmark = pytest.mark.gpu
 
@@ -109,3 +110,13 @@ def test_dense_layers_whose_operands_pass_through_lds(what):
             for k, n in forward_tiles(names).items():
                 seen[k] = seen.get(k, 0) + n
         assert {(1, 1, True), (1, 2, True), (2, 2, True), (1, 1, False), (1, 2, False)} <= set(seen), seen
+
+
+def test_weight_gradients_without_blocks_for_the_row_of_ones():
+    """Of the shapes compared with the oracle, those that say so; and not where every workgroup has a compute unit of its own already (H = 128,
+    fp32: 1.3 % of a gradient step) or the GEMMs run beside the sweeps."""
+    shapes = [(B, I, H, dtype, cell, ones) for B, I, H, _, dtype, cell, ones in parity.WGRAD_BLOCKS]
+    shapes += [(64, 256, 256, 1, 0, True), (64, 256, 256, 0, 0, True), (64, 128, 128, 0, 0, False), (32, 128, 256, 0, 0, False), (32, 128, 128, 1, 0, False),
+               (128, 128, 512, 1, 0, False), (96, 1023, 512, 1, 0, False), (16, 128, 512, 1, 0, False), (64, 256, 1024, 1, 0, False)]
+    for (B, I, H, dtype, cell, ones), names in zip(shapes, launched([["rnn", B, I, H, 4, 0, 2, dtype, cell] for B, I, H, dtype, cell, _ in shapes])):
+        assert count(names, "wgrad_kernel", ones) == 1 and count(names, "wgrad_kernel", not ones) == 0, (B, I, H, dtype, names)
