@@ -1037,25 +1037,33 @@ static void launch_forward_batch_t(const Dims& d, const FwdParams& p, const FwdB
   // the K split of the shape's stand-alone forward kernel
   const bool small_k = cfg == FWD_TINY || cfg == FWD_SMALLK || wide_shape(d).groups;
   if constexpr (sizeof(T) == 2) {
-    // Larger tiles where they still make enough workgroups, see forward_batch_tiles_kernel.  us a launch of n operations, this
-    // kernel's 64 x 32 / 128 x 32 / 128 x 64 tiles:
-    //   H = 1024, I = 256, B = 64:  n = 4 10.6 / 14.2 / 18.8, n = 8 17.4 / 17.3 / 20.0, n = 16 29.6 / 28.9 / 25.0, n = 31 55.3 / 54.7 / 49.9
-    //   H = 768, I = 128, B = 128:  n = 4 11.4 / 12.9 / 15.2, n = 8 19.1 / 17.8 / 18.9, n = 16 33.8 / 31.3 / 32.5, n = 31 68.0 / 65.6 / 68.1
-    //   H = 2048, I = 512, B = 128: n = 4 31.4 / 25.5 / 29.2, n = 8 57.8 / 46.1 / 39.2
-    //   H = 4096, I = 1024, B = 32 (whose weights no L2 holds, and which 64 x 32 tiles fetch once per operation):
-    //                               n = 2 46.8 / 39.9 / 50.8, n = 4 89.9 / 45.9 / 50.6, n = 8 178 / 84.6 / 66.6
-    //   H = 650, I = 650, B = 20:   n = 4 11.6 / 13.2 / 17.8, n = 8 18.2 / 13.4 / 17.9, n = 31 45.9 / 22.4 / 23.7
-    // In the last, rows of x are no whole fragments, which the smaller tiles' loader fetches value by value.
+    // Larger tiles where they still make enough workgroups, see forward_batch_tiles_kernel: a compute unit holds two, and a launch of few takes as
+    // long as one of 256 (11 - 12 us per 1024 of K; the smaller tiles start at half of that).  us a launch, 64 x 32 / 128 x 32 / 128 x 64 tiles:
+    // * Rows of x that are no whole 16 bytes, which the smaller tiles' loader fetches value by value, from 192 columns on (before that the fetches
+    //   hide behind the rest, and a batch of a few sequences has few): H = 650, I = 650, B = 20, n = 8 18.2 / 13.4 / 17.9, n = 31 45.9 / 22.4 / 23.7.  Of 460 launches
+    //   of 192 and more narrow workgroups all faster, 0.58 - 0.70 of the time on average.  (H = 800, I = 69, B = 93 would lose 10 - 40 %.)
+    // * K > 2048: H = 4096, I = 1024, B = 32, whose weights no L2 holds and which small tiles fetch once per operation, n = 4 89.9 / 45.9 / 50.6,
+    //   n = 8 178 / 84.6 / 66.6; H = 2048, I = 512, B = 128 n = 8 57.8 / 46.1 / 39.2.  From 448 narrow workgroups on 0.80 of the time, 1.05 at worst.
+    // * Otherwise where no GEMMs run beside (with them a gradient step of H = 1024, B = 64 takes 10 539 us for 10 489) and the last round of
+    //   workgroups is well filled: H = 1280, I = 512, B = 128 n = 6 40.2 / 39.0 / 30.1, n = 3 23.0 / 20.3 / 23.4; H = 1056, I = 64, B = 100 n = 8 34.3 / 27.1 / 22.3.  Half-filled
+    //   rounds or a short K with narrow tiles: H = 1280, I = 64, B = 128 n = 5 22.8 / 29.4 / 22.7, n = 3 15.1 / 16.4 / 19.0.
     MacroStepOrder order;
     constexpr size_t LIMIT = (size_t)1 << 31;   // 32-bit byte offsets
     if (d.I >= 8 && (size_t)d.G4 * d.KP * 2 < LIMIT && (size_t)d.B * d.I * 4 < LIMIT && macro_step_order(d.KP / 32, small_k ? 4 : 8, order)) {
       const int rows = d.HP / 32, tiles = n * (d.BP / 16), wide = rows * ((tiles + 3) / 4), narrow = rows * ((tiles + 1) / 2);
-      const int least = d.I % 8 != 0 ? TARGET_WGS / 2 : (d.KP > 2048 ? TARGET_WGS : 2 * TARGET_WGS);
-      // (With the weight-gradient GEMMs beside it, which is where whole fragments and 33 - 128 sequences meet, a gradient step of H = 1024,
-      // B = 64 gains nothing: 10 489 us, 10 539 with the larger tiles.)
-      const bool alone = d.B <= 32 || d.B > 128 || d.KP > 2048;
-      if (wide >= 2 * TARGET_WGS && (alone || d.I % 8 != 0)) return launch_forward_batch_tiles<2, 4>(d, p, steps, order, n, st);
-      if (narrow >= least && (alone || d.I % 8 != 0)) return launch_forward_batch_tiles<2, 2>(d, p, steps, order, n, st);
+      auto fills = [](int workgroups, int eighths) { return 8 * workgroups >= (workgroups + 2 * TARGET_WGS - 1) / (2 * TARGET_WGS) * (2 * TARGET_WGS) * eighths; };
+      bool use_wide = wide >= 2 * TARGET_WGS, use_narrow = false;
+      if (d.I % 4 != 0 && d.KX >= 192 && d.B >= 16) {
+        use_narrow = narrow >= 192;
+      } else if (d.KP > 2048) {
+        use_narrow = narrow >= 448;
+      } else {
+        const bool alone = d.I % 4 == 0 && !gemms_beside(d);
+        use_wide = alone && wide >= 384 && fills(wide, 6);
+        use_narrow = alone && d.KP >= 1536 && narrow >= 448 && fills(narrow, 7);
+      }
+      if (use_wide) return launch_forward_batch_tiles<2, 4>(d, p, steps, order, n, st);
+      if (use_narrow) return launch_forward_batch_tiles<2, 2>(d, p, steps, order, n, st);
     }
   }
   if (small_k && d.cell)

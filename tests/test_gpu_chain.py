@@ -137,11 +137,16 @@ def test_batched_recomputation(B, I, H, t):
     check_against_oracle(w, inp, base, ref, TOL[w.gemm_dtype], label=f"batched recomputation {B}x{I}x{H}: ")
 
 
-# batches of n operations on 128 x 32 and 128 x 64 tiles: rows of x that are no whole fragments, and fewer than a macro step; operations of one, two
-# and three batch tiles whose tiles straddle workgroups, the last one partly empty; odd numbers of macro steps; K split 8 and 4 ways; padding units
-@pytest.mark.parametrize("B,I,H,t,cell", [(20, 650, 650, 33, 0), (37, 100, 600, 33, 0), (48, 9, 1024, 33, 0), (10, 33, 990, 33, 0), (32, 256, 1024, 33, 1),
-                                          (120, 94, 520, 33, 1), (16, 1000, 800, 20, 0), (33, 40, 1100, 20, 0), (20, 72, 2100, 12, 1)])
-def test_batches_on_large_tiles(B, I, H, t, cell):
+# Batches of operations on 128 x 32 and 128 x 64 tiles (last value: which, test_gpu_routes asks by name): rows of x that are no whole fragments;
+# operations of one, two, three and more batch tiles whose tiles straddle workgroups, the last one partly empty; odd numbers of macro steps;
+# K split 8 and 4 ways for both cores; padding units.
+TILED = [(20, 650, 650, 33, 0, 32), (37, 201, 600, 33, 0, 32), (48, 333, 1024, 33, 0, 64), (16, 250, 990, 33, 1, 32), (32, 256, 1024, 33, 1, 64),
+         (120, 194, 520, 33, 1, 64), (64, 203, 515, 20, 0, 32), (33, 40, 1100, 18, 0, 64), (33, 301, 1100, 20, 0, 64), (130, 203, 600, 14, 1, 64),
+         (20, 72, 2100, 12, 1, 32), (20, 72, 2100, 12, 0, 32), (17, 1300, 900, 33, 0, 32)]
+
+
+@pytest.mark.parametrize("B,I,H,t,cell,columns", TILED)
+def test_batches_on_large_tiles(B, I, H, t, cell, columns):
     w = wl.Workload("tiles", B=B, I=I, H=H, t=t, kind=wl.KIND_HSM, m=t, gemm_dtype=wl.GEMM_BF16, loss=wl.LOSS_EXTERNAL_DY, dy_first_step=2,
                     cell=cell, seed=B + I + H)
     inp = wl.make_inputs(w, nonzero_state=True, nonzero_bias=True)

@@ -120,3 +120,17 @@ def test_weight_gradients_without_blocks_for_the_row_of_ones():
                (128, 128, 512, 1, 0, False), (96, 1023, 512, 1, 0, False), (16, 128, 512, 1, 0, False), (64, 256, 1024, 1, 0, False)]
     for (B, I, H, dtype, cell, ones), names in zip(shapes, launched([["rnn", B, I, H, 4, 0, 2, dtype, cell] for B, I, H, dtype, cell, _ in shapes])):
         assert count(names, "wgrad_kernel", ones) == 1 and count(names, "wgrad_kernel", not ones) == 0, (B, I, H, dtype, names)
+
+
+def test_forward_batches_on_large_tiles():
+    """Of the shapes compared bit for bit, those tiles that they say; and the small ones where large tiles would be slower, up to twice the
+    time of a launch (H = 2048, I = 33, B = 33: 8.1 and 17.6 us for one operation; H = 800, I = 69, B = 93 14 % of a stretch)."""
+    from paper_1606_03401_amd import workloads as wl
+    small = [(93, 69, 800, 20, 0), (64, 36, 1024, 20, 0), (128, 69, 1024, 20, 0), (4, 650, 896, 20, 0), (64, 256, 1024, 33, 0), (33, 33, 2048, 4, 0)]
+    calls = [["rnn", B, I, H, t, wl.KIND_HSM, t, 1, cell] for B, I, H, t, cell in [s[:5] for s in chain.TILED] + small]
+    got = launched(calls)
+    for (B, I, H, t, cell, columns), names in zip(chain.TILED, got):
+        tiles = {int(m[1]) * 16: n for m, n in ((re.search(r"forward_batch_tiles_kernel<2, (\d), \d>", k), n) for k, n in names.items()) if m}
+        assert columns in tiles, (B, I, H, names)
+    for s, names in zip(small, got[len(chain.TILED):]):
+        assert count(names, "forward_batch_tiles_kernel") == 0 and (count(names, "forward_batch_kernel") > 0 or s[3] == 4), (s, names)
