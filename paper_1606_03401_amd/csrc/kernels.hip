@@ -17,6 +17,7 @@
 // result (the dh = dG W_hh product of step s+1 fused with the pointwise backward of step s).
 #include <algorithm>
 
+#include "common.h"
 #include "device.h"
 #include "dynamic_lds.h"
 
@@ -1986,10 +1987,13 @@ __global__ void wgrad_finish_kernel(const float* __restrict__ dWacc, int WT, int
 //   H = 128, I = 128, B = 32          6.7 /  6.7 /  7.3, t = 128  540 /  540 /  544: not   fp32 H = 128, I = 128, B = 64  21.5 / 21.5 / 23.4, 828 / 828 / 839: not
 //   H = 512, I = 128, B = 16         12.5 / 13.9 / 12.5, t = 128  694 /   -  /  697: not
 // (Above one block per compute unit, where K is not split, EXTRA costs as well: H = 1024, I = 256, 352 -> 320 blocks 36.3 -> 39.3 us.)
+// More accumulators than the first choice's are taken only by shapes that mebptt_run_static, whose workspace is of a fixed size, refuses anyway.
 struct WgradPlan {
   int wt, gx, gy, splits;
   bool extra;
   int blocks() const { return gx * gy; }
+  size_t partial_floats() const { return ((size_t)blocks() * 4 * wt * wt + (extra ? (size_t)gx * 2 * wt : 0)) * 64 * 4; }   // one partial accumulator
+  size_t accumulator_bytes() const { return partial_floats() * splits * sizeof(float); }
 };
 static WgradPlan wgrad_plan(const Dims& d) {
   const int MT = d.G4 / 16, NT = d.NA / 16, wt = MT >= 8 && NT >= 8 ? 4 : 2;
@@ -2002,9 +2006,11 @@ static WgradPlan wgrad_plan(const Dims& d) {
     const int workgroups = q.blocks() * q.splits;
     return (workgroups + TARGET_WGS - 1) / TARGET_WGS * steps / q.splits * (q.extra ? 17.0 / 16 : 1) + accumulator * std::max(workgroups, TARGET_WGS);
   };
+  const size_t chunk_buffers = 2 * ((size_t)d.CH * d.BP * d.G4 + (size_t)(d.G4 + d.NA) * d.KC) * d.op_bytes();
+  const size_t most = p.accumulator_bytes() + chunk_buffers > MEBPTT_STATIC_WORKSPACE_BYTES ? ~(size_t)0 : p.accumulator_bytes();
   WgradPlan two = p;
   two.splits = split(p.blocks(), 2 * TARGET_WGS);
-  if (cost(two) < 0.99 * cost(p)) p = two;
+  if (two.accumulator_bytes() <= most && cost(two) < 0.99 * cost(p)) p = two;
   if (NT % (2 * wt) == 1 && 2 * (p.gy - 1) >= wt) {   // 2 * gy >= wt: the extra products are dealt out over that many waves a row
     WgradPlan best = p;
     for (const int workgroups : {384 + (p.gx * (p.gy - 1)) / 2, 2 * TARGET_WGS}) {
@@ -2012,16 +2018,12 @@ static WgradPlan wgrad_plan(const Dims& d) {
       q.gy = p.gy - 1;
       q.extra = true;
       q.splits = split(q.blocks(), workgroups);
-      if (cost(q) < std::min(0.95 * cost(p), cost(best))) best = q;
+      if (q.accumulator_bytes() <= most && cost(q) < std::min(0.95 * cost(p), cost(best))) best = q;
     }
     p = best;
   }
   return p;
 }
-static size_t wgrad_partial_floats(const WgradPlan& p) {   // one partial accumulator
-  return ((size_t)p.blocks() * 4 * p.wt * p.wt + (p.extra ? (size_t)p.gx * 2 * p.wt : 0)) * 64 * 4;
-}
-
 size_t wgrad_accumulator_bytes(const Dims& d) {
   if (wgrad_uses_big_tiles(d)) {   // one padded 256 x 256 block per workgroup
     const size_t gx = (d.G4 / 16 + 15) / 16, gy = (d.NA / 16 + 15) / 16;
@@ -2029,8 +2031,7 @@ size_t wgrad_accumulator_bytes(const Dims& d) {
     tgemm_shares((int)(gx * gy), full, split);
     return (gx * gy + (gx * gy - full) * (split - 1)) * 256 * 256 * sizeof(float);
   }
-  const WgradPlan plan = wgrad_plan(d);
-  return wgrad_partial_floats(plan) * plan.splits * sizeof(float);
+  return wgrad_plan(d).accumulator_bytes();
 }
 
 template <class T>
@@ -2088,7 +2089,7 @@ hipError_t launch_wgrad_finish(const Dims& d, const float* dWacc, float* dW_ih, 
     return hipGetLastError();
   }
   const WgradPlan plan = wgrad_plan(d);
-  wgrad_finish_kernel<<<grid, dim3(256), 0, st>>>(dWacc, plan.wt, plan.gy, plan.splits, wgrad_partial_floats(plan), d.NX, d.HP,
+  wgrad_finish_kernel<<<grid, dim3(256), 0, st>>>(dWacc, plan.wt, plan.gy, plan.splits, plan.partial_floats(), d.NX, d.HP,
                                                         d.I, d.H, d.cell, dW_ih, dW_hh, db, plan.blocks(), dc, dh0, dc0, plane, nw);
   return hipGetLastError();
 }

@@ -4,6 +4,8 @@ import ctypes
 import os
 import re
 
+import pytest
+
 from paper_1606_03401_amd import binding as mb
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -147,3 +149,20 @@ def test_staged_input_of_a_launch_is_at_most_32_mib():
             staged = more - rings - 3 * mb.mebptt_unit_bytes(d) * mb.mebptt_stage_steps(d)
             step = B * _round_up(I, 32) * 2
             assert abs(staged - min(192, (32 << 20) // step) * step) < 8192 and staged < (32 << 20) + 8192, (B, I, H, staged)
+
+
+def test_static_workspace_takes_the_shapes_it_took():
+    """Shapes whose workspace fits the static array as long as the weight gradient has no more accumulators than 1.5 workgroups per
+    compute unit need: a plan that splits K further would have them refused.  (Without a device, and without arrays, what comes
+    back is another error.)"""
+    import torch
+    plan = mb.mebptt_plan(8, 3, mb.HSM)
+
+    def refused(B, I, H, dtype):
+        args = [mb.make_desc(B, I, H, 8, dtype, 1, 1, 0), plan] + [None] * 7 + [torch.zeros(0)] + [None] * 7
+        with pytest.raises(mb.MebpttError) as e:
+            mb.mebptt_run_static(*args, stream=0)
+        return e.value.code == mb.EWORKSPACE
+    for shape in ((2, 319, 317, 1), (2, 307, 291, 1), (1, 314, 311, 1), (1, 307, 307, 1), (4, 1494, 141, 1), (2, 1204, 170, 1)):
+        assert not refused(*shape), shape
+    assert refused(64, 256, 1024, 1)
