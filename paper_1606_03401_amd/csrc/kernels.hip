@@ -1024,6 +1024,35 @@ static void launch_forward_batch_tiles(const Dims& d, const FwdParams& p, const 
 
 int forward_batch_max_steps() { return FWD_BATCH_MAX_STEPS; }
 
+// What a launch of n operations takes (us, bf16) on 64 x 32, 128 x 32 and 128 x 64 tiles, from 17 000 launches timed on all three: B of 4 to 256, H of 200 to
+// 4096, I of 8 to 1024, LSTM and GRU.  Two thirds of the small tiles' estimates lie within 10 % of the time (whole 16-byte rows of x: 15 %), of the larger ones' within 7 %.
+// * Small tiles: rounds of workgroups, one on every compute unit, each with its K.  Rows of x that are no whole 16 bytes are fetched value by value, for as many sequences
+//   as a tile holds: H = I = 650, B = 20, 8 operations 17.7 us, on 128 x 32 tiles 13.8.  Workgroups go to the XCDs in turn; where their number per operation is no
+//   multiple of eight an XCD gets other rows of the weights each time, and what does not stay in its L2 (6 MB of a copy still do) is fetched anew
+//   for every operation: H = 1816, I = 416, B = 95, 7 operations 105 us (53 on 128 x 32), H = 1898, I = 20, B = 67, whose XCDs see an eighth each, 51 (46).
+// * Larger tiles: a compute unit holds two of them (128 x 32 with K split four ways: three), and up to there their number costs little.
+// With a workgroup each small tiles are up to 1.7 times as fast (H = 600, I = 193, B = 20, 5 operations 6.5 us for 10.1 and 13.9).  Of the launches timed, choosing larger
+// ones for 5 % takes 0.76 of the small ones' time in the mean (the best of the three 0.75), more than 1.05 of it for one in 150, 1.26 at worst.
+struct ForwardBatchTimes {
+  float small, narrow, wide;
+};
+static ForwardBatchTimes forward_batch_us(const Dims& d, int n, int ks) {
+  const float K = d.KP / 1024.f, X = d.KX / 1024.f, Hk = d.KH / 1024.f;
+  const int gx = (d.HP / 4 + 3) / 4, gy = (d.BP / 16 + 1) / 2, rows = d.HP / 32, tiles = n * (d.BP / 16);
+  const float rounds = (float)((gx * gy * n + TARGET_WGS - 1) / TARGET_WGS), filled = (float)d.B / (32 * gy);
+  int same = 8;   // an XCD sees one of this many neighbouring row groups of the weights
+  while ((gx * gy) % same != 0 || (gy > 1 && gx % same != 0)) same /= 2;
+  const float weights = (float)d.HP * 4 * d.KP * 2e-6f;   // MB
+  const bool ragged = d.I % 4 != 0;
+  ForwardBatchTimes t;
+  t.small = 3 + (ragged ? std::min(1.f, 4 * X) : 0) + rounds * (0.6f + 2.1f * Hk + (0.4f + (ragged ? 11.f : 4.f) * filled) * X) + (weights / same > 6 ? 0.045f * n * weights : 0);
+  const int narrow = rows * ((tiles + 1) / 2), wide = rows * ((tiles + 3) / 4);
+  t.narrow = narrow <= 256 ? 5 + 7 * K : narrow <= 512 ? 7 + 7.5f * K : narrow <= 768 ? (ks == 8 ? 6.5f + 13 * K : 8.5f + 10.3f * K) :
+             (ks == 8 ? 8.5f + 17 * K : 10.5f + 16.5f * K) * std::max(1.f, narrow / 1024.f);
+  t.wide = wide <= 256 ? 8 + 8.7f * K : wide <= 512 ? (ks == 8 ? 9 + 12.2f * K : 10.5f + 9.9f * K) : (14 + 19 * K) * std::max(1.f, wide / 768.f);
+  return t;
+}
+
 template <class T>
 static void launch_forward_batch_t(const Dims& d, const FwdParams& p, const FwdBatchSteps& steps, int n, hipStream_t st) {
   // 64 gate rows x 32 sequences per workgroup, two macro steps in flight per wave: two workgroups
@@ -1038,31 +1067,14 @@ static void launch_forward_batch_t(const Dims& d, const FwdParams& p, const FwdB
   // the K split of the shape's stand-alone forward kernel
   const bool small_k = cfg == FWD_TINY || cfg == FWD_SMALLK || wide_shape(d).groups;
   if constexpr (sizeof(T) == 2) {
-    // Larger tiles where they still make enough workgroups, see forward_batch_tiles_kernel: a compute unit holds two, and a launch of few takes as
-    // long as one of 256 (11 - 12 us per 1024 of K; the smaller tiles start at half of that).  us a launch, 64 x 32 / 128 x 32 / 128 x 64 tiles:
-    // * Rows of x that are no whole 16 bytes, which the smaller tiles' loader fetches value by value, from 192 columns on (before that the fetches
-    //   hide behind the rest, and a batch of a few sequences has few): H = 650, I = 650, B = 20, n = 8 18.2 / 13.4 / 17.9, n = 31 45.9 / 22.4 / 23.7.  Of 460 launches
-    //   of 192 and more narrow workgroups all faster, 0.58 - 0.70 of the time on average.  (H = 800, I = 69, B = 93 would lose 10 - 40 %.)
-    // * K > 2048: H = 4096, I = 1024, B = 32, whose weights no L2 holds and which small tiles fetch once per operation, n = 4 89.9 / 45.9 / 50.6,
-    //   n = 8 178 / 84.6 / 66.6; H = 2048, I = 512, B = 128 n = 8 57.8 / 46.1 / 39.2.  From 448 narrow workgroups on 0.80 of the time, 1.05 at worst.
-    // * Otherwise where no GEMMs run beside (with them a gradient step of H = 1024, B = 64 takes 10 539 us for 10 489) and the last round of
-    //   workgroups is well filled: H = 1280, I = 512, B = 128 n = 6 40.2 / 39.0 / 30.1, n = 3 23.0 / 20.3 / 23.4; H = 1056, I = 64, B = 100 n = 8 34.3 / 27.1 / 22.3.  Half-filled
-    //   rounds or a short K with narrow tiles: H = 1280, I = 64, B = 128 n = 5 22.8 / 29.4 / 22.7, n = 3 15.1 / 16.4 / 19.0.
+    // Larger tiles (forward_batch_tiles_kernel) where forward_batch_us expects 5 % of them.  Rows of x that are whole 16 bytes keep the small ones
+    // while GEMMs run beside: a gradient step of H = 1024, B = 64 takes 10 539 us with larger ones for 10 489.
     MacroStepOrder order;
     constexpr size_t LIMIT = (size_t)1 << 31;   // 32-bit byte offsets
     if (d.I >= 8 && (size_t)d.G4 * d.KP * 2 < LIMIT && (size_t)d.B * d.I * 4 < LIMIT && macro_step_order(d.KP / 32, small_k ? 4 : 8, order)) {
-      const int rows = d.HP / 32, tiles = n * (d.BP / 16), wide = rows * ((tiles + 3) / 4), narrow = rows * ((tiles + 1) / 2);
-      auto fills = [](int workgroups, int eighths) { return 8 * workgroups >= (workgroups + 2 * TARGET_WGS - 1) / (2 * TARGET_WGS) * (2 * TARGET_WGS) * eighths; };
-      bool use_wide = wide >= 2 * TARGET_WGS, use_narrow = false;
-      if (d.I % 4 != 0 && d.KX >= 192 && d.B >= 16) {
-        use_narrow = narrow >= 192;
-      } else if (d.KP > 2048) {
-        use_narrow = narrow >= 448;
-      } else {
-        const bool alone = d.I % 4 == 0 && !gemms_beside(d);
-        use_wide = alone && wide >= 384 && fills(wide, 6);
-        use_narrow = alone && d.KP >= 1536 && narrow >= 448 && fills(narrow, 7);
-      }
+      const ForwardBatchTimes us = forward_batch_us(d, n, small_k ? 4 : 8);
+      const bool larger = std::min(us.narrow, us.wide) < 0.95f * us.small && (d.I % 4 != 0 || !gemms_beside(d));
+      const bool use_wide = larger && us.wide < us.narrow, use_narrow = larger && !use_wide;
       if (use_wide) return launch_forward_batch_tiles<2, 4>(d, p, steps, order, n, st);
       if (use_narrow) return launch_forward_batch_tiles<2, 2>(d, p, steps, order, n, st);
     }

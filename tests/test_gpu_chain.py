@@ -140,9 +140,9 @@ def test_batched_recomputation(B, I, H, t):
 # Batches of operations on 128 x 32 and 128 x 64 tiles (last value: which, test_gpu_routes asks by name): rows of x that are no whole fragments;
 # operations of one, two, three and more batch tiles whose tiles straddle workgroups, the last one partly empty; odd numbers of macro steps;
 # K split 8 and 4 ways for both cores; padding units.
-TILED = [(20, 650, 650, 33, 0, 32), (37, 201, 600, 33, 0, 32), (48, 333, 1024, 33, 0, 64), (16, 250, 990, 33, 1, 32), (32, 256, 1024, 33, 1, 64),
-         (120, 194, 520, 33, 1, 64), (64, 203, 515, 20, 0, 32), (33, 40, 1100, 18, 0, 64), (33, 301, 1100, 20, 0, 64), (130, 203, 600, 14, 1, 64),
-         (20, 72, 2100, 12, 1, 32), (20, 72, 2100, 12, 0, 32), (17, 1300, 900, 33, 0, 32)]
+TILED = [(20, 650, 650, 33, 0, 32), (37, 201, 600, 33, 0, 64), (48, 333, 1024, 33, 0, 64), (16, 250, 990, 33, 1, 32), (32, 256, 1024, 33, 1, 64),
+         (120, 194, 520, 33, 1, 64), (64, 203, 515, 20, 0, 32), (33, 40, 1100, 18, 0, 64), (33, 301, 1100, 20, 0, 32), (130, 203, 600, 21, 1, 64),
+         (20, 72, 2100, 12, 1, 32), (20, 72, 2100, 12, 0, 32), (17, 1300, 900, 33, 0, 64)]
 
 
 @pytest.mark.parametrize("B,I,H,t,cell,columns", TILED)
