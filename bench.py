@@ -323,7 +323,7 @@ def measure(w, inp, *, kind=None, m=None, steps=3, warmup=1, graph=True, profile
             kernel = {"forward": "forward_kernel", "backward": "backward_kernel", "backward+forward": "pair_kernel",
                       "forward chain": "wide_chain_kernel" if wide else "forward_chain_kernel",
                       "sweep": "wide_sweep_kernel" if wide else "sweep_kernel",
-                      "forward batch": "forward_batch_kernel"}[dom]
+                      "forward batch": "forward_batch_kernel, or forward_batch_tiles_kernel where its tiles are faster"}[dom]
             if dom == "sweep":
                 # the weight operands stay on the chip; a step carries the dh GEMM and, in the launches
                 # that recompute the internal state themselves, the forward GEMM as well

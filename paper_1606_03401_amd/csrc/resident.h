@@ -463,7 +463,7 @@ __device__ __forceinline__ void chain_slowly(int b_lo, int b_hi, int u0, int u1,
 //      register), publish h_s.
 // What bounds a step is this chain of latencies, not bytes or flops: no weight moves.  Measured per step,
 // with counters and whole tiles before and so: H = 1024, B = 64 3.3 -> 2.27 us, H = 512, B = 256 3.6 -> 1.98 us.
-// Of the 2.27 us, in cycles of 2.2 GHz: x part 560, polls 620 - 820 (1.0 - 1.4 of them), h part with the
+// Of those 2.27 us (whole tiles' products and gate functions with divisions; now see halves_from), in cycles of 2.2 GHz: x part 560, polls 620 - 820 (1.0 - 1.4 of them), h part with the
 // stores and the next x 1280, barrier 250 - 520, pointwise step 1050, publishing 170.
 // Sums are formed exactly as forward_body forms them (KS partial sums over the macro steps
 // w, w+KS, ..., added in order, or as add_pairs adds them), so a step gives the same bits either way.  A wave whose part of
